@@ -1,15 +1,17 @@
 // Attention of group-wise parallel training (see include/ps_train.h; Section 4.1).
 //
-// Three kernels per call: the rotary table (cos, sin of position * base^(-2j/d) in double precision), the
+// Two kernels per call: the rotary table (cos, sin of position * base^(-2j/d) in double precision) with the
 // rotation of k (to the storage type, rounded as the inference path caches keys), and the attention itself,
-// which rotates its 16 query rows (in float32) while it stages them.
+// which rotates its query rows (in float32) while it brings them in.
 //
-// The attention kernels never touch a key the mask hides.  A query tile is a whole number of parallel groups
-// (as many as fit into 16 rows); what its rows may see are (a) real tokens of groups up to their own - these
-// are gathered with a stride of k + 1 rows, 16 per key tile - and (b) [MASK] tokens of their own group, which
-// all lie inside the query tile's own 16 rows: one more key tile.  Online softmax over the key tiles; scores are
-// MFMA tiles (the keys' rows are the 16-row operand, the 16 query rows the 16-column operand).  There is one kernel
-// per storage type (ga_attn_bf16_kernel, ga_attn_f32_kernel); each describes its own scheme.
+// The attention kernels walk (a) the real tokens of groups up to the queries' own and (b) the rows of the queries'
+// own groups, whose [MASK] tokens they see: no key tile that the mask hides entirely is touched.  Online softmax over
+// the key tiles; scores are MFMA tiles (the keys' rows are the row operand, the query rows the column operand).  bf16
+// values: ga_attn_wide_kernel (and, for the smallest calls, ga_attn_bf16_kernel); float32 values: ga_attn_f32_kernel.
+// Each describes its own scheme.
+//
+// In the two kernels of 16-row tiles a query tile is a whole number of parallel groups (as many as fit into 16 rows), so
+// the [MASK] tokens of its groups all lie inside its own rows: one more key tile.
 #include "ps_device.h"
 #include "ps_train.h"
 
@@ -20,46 +22,53 @@ constexpr float GA_LAZY = 8.f;
 
 struct GaParams {
     int seqs, T, k, nq, nkv, rows, gpt, ntiles;   // gpt: groups per query tile
+    unsigned k1_magic;    // ceil(2^32 / (k + 1)): a row's group is the upper half of the product (rows < 2^28; k > 0)
     float inv_sqrt_d;
     const void *q, *k_, *v;
     float* out;
     float2* table;      // [T + k][d / 2]
-    void* k_rot;        // [seqs][rows][nkv][d] storage type
+    void* k_rot;        // rotated keys, storage type: [seqs][rows][nkv][d], or real tokens only as [seqs][nkv][T][d]
     double log_base;
 };
 
-template <int D>
-__global__ void __launch_bounds__(256) ga_table_kernel(const GaParams P) {
-    const int n = (P.T + P.k) * (D / 2);
-    for (int x = blockIdx.x * 256 + threadIdx.x; x < n; x += gridDim.x * 256) {
-        const int pos = x / (D / 2), j = x - pos * (D / 2);
-        const double a = (double)pos * exp(-2.0 * j / D * P.log_base);
-        P.table[x] = make_float2((float)cos(a), (float)sin(a));
-    }
-}
-
-// rotary embedding of the keys: one thread per (row, kv head, pair of 4 + 4 elements j..j+3, j+d/2..)
-template <typename WT, int D>
+// Rotary table and keys in one launch.  A workgroup takes one position, works out its cosines and sines (double precision,
+// once for all heads, sequences and slots) and rotates the key rows that stand there, rounded as the inference path caches
+// keys; gridDim.y workgroups share a position's rows.  ALL: the rows of every slot, to k_rot in the layout of k (a row (group,
+// slot) stands at group + slot).  Otherwise the real tokens' rows only, to k_rot as [seq][kv head][token][D]: a [MASK] key is
+// seen by its own group only, and ga_attn_wide_kernel rotates those while it stages them.  (A table kernel and a kernel over
+// all rows that reads the table back: 29 us at T 2048, k 4, 32 heads x 128, of which all but 9 go with the [MASK] rows' bytes.)
+template <typename WT, int D, bool ALL>
 __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
-    constexpr int ESZ = Traits<WT>::ESZ, Q4 = D / 8;     // groups of 4 pairs per head
-    const long long n = (long long)P.seqs * P.rows * P.nkv * Q4;
-    for (long long x = (long long)blockIdx.x * 256 + threadIdx.x; x < n; x += (long long)gridDim.x * 256) {
+    constexpr int ESZ = Traits<WT>::ESZ, Q4 = D / 8;       // groups of 4 pairs per head
+    __shared__ float2 cs[D / 2];
+    const int pos = blockIdx.x, tid = threadIdx.x;
+    if (tid < D / 2) {
+        const double a = (double)pos * exp(-2.0 * tid / D * P.log_base);
+        const float2 t = make_float2((float)cos(a), (float)sin(a));
+        cs[tid] = t;
+        if (blockIdx.y == 0) P.table[(size_t)pos * (D / 2) + tid] = t;
+    }
+    __syncthreads();
+    const int s0 = max(0, pos - P.T + 1), slots = ALL ? min(pos, P.k) - s0 + 1 : pos < P.T;   // slots s0 .. at this position
+    const long long n = (long long)slots * P.seqs * P.nkv * Q4;
+    for (long long x = (long long)blockIdx.y * 256 + tid; x < n; x += (long long)gridDim.y * 256) {
         const int g4 = (int)(x % Q4);
-        const long long y = x / Q4;                        // (seq * rows + row) * nkv + head
-        const int row = (int)((y / P.nkv) % P.rows);
-        const int pos = row / (P.k + 1) + row % (P.k + 1);  // group + slot
-        const size_t base = (size_t)y * D;
-        const char* src = (const char*)P.k_;
-        const f32x4 a = load4<WT>(src + (base + 4 * g4) * ESZ), b = load4<WT>(src + (base + D / 2 + 4 * g4) * ESZ);
+        const unsigned y = (unsigned)(x / Q4), z = y / P.nkv, head = y - z * P.nkv;   // y = (slot * seqs + seq) * nkv + head
+        const unsigned slot = z / P.seqs, seq = z - slot * P.seqs;
+        const int sl = ALL ? s0 + (int)slot : 0;
+        const size_t row = (size_t)seq * P.rows + (size_t)(pos - sl) * (P.k + 1) + sl;
+        const size_t from = ((row * P.nkv + head) * D + 4 * g4) * ESZ;
+        const size_t to = ALL ? from : ((((size_t)seq * P.nkv + head) * P.T + pos) * D + 4 * g4) * ESZ;
+        const f32x4 a = load4<WT>((const char*)P.k_ + from), b = load4<WT>((const char*)P.k_ + from + D / 2 * ESZ);
         f32x4 ra, rb;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float2 t = P.table[(size_t)pos * (D / 2) + 4 * g4 + e];
+            const float2 t = cs[4 * g4 + e];
             ra[e] = a[e] * t.x - b[e] * t.y;
             rb[e] = b[e] * t.x + a[e] * t.y;
         }
-        store4<WT>((char*)P.k_rot + (base + 4 * g4) * ESZ, ra);
-        store4<WT>((char*)P.k_rot + (base + D / 2 + 4 * g4) * ESZ, rb);
+        store4<WT>((char*)P.k_rot + to, ra);
+        store4<WT>((char*)P.k_rot + to + D / 2 * ESZ, rb);
     }
 }
 
@@ -243,7 +252,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_f32_kernel(const GaPara
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 values.  A workgroup takes four adjacent query tiles, one per wavefront, and walks the key tiles of real
+// bf16 values, 16-row tiles (the smallest calls).  A workgroup takes four adjacent query tiles, one per wavefront, and walks the key tiles of real
 // tokens two at a time; the pair's K and V rows are brought in once for all four wavefronts.
 //
 // Loads are laid out for the texture unit, which handles a load in units of four lanes: four adjacent lanes read
@@ -300,37 +309,6 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
     const unsigned K1rs = (unsigned)K1 * rs32;              // ... between real tokens
     const char* kbase = (const char*)P.k_rot + ((size_t)seq * P.rows * P.nkv + hk) * D * 2;
     const char* vbase = (const char*)P.v + ((size_t)seq * P.rows * P.nkv + hk) * D * 2;
-
-    // ---- the query rows into registers, by way of LDS
-    {
-        const char* qsrc = (const char*)P.q + ((size_t)seq * P.rows * P.nq + h) * D * 2;
-        const float qscale = P.inv_sqrt_d * 1.4426950408889634f;
-        for (int t2 = lane; t2 < 16 * (D / 8); t2 += 64) {
-            const int r = min(t2 / (D / 8), nrows - 1), g4 = t2 % (D / 8);
-            const int row = r0 + r, pos = row / K1 + row % K1;                  // group + slot
-            const char* qrow = qsrc + (size_t)row * P.nq * D * 2;
-            const f32x4 a = load4<WT>(qrow + 4 * g4 * 2), b = load4<WT>(qrow + (D / 2 + 4 * g4) * 2);
-            u32x4 ra, rb;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float2 t = P.table[(size_t)pos * (D / 2) + 4 * g4 + e];
-                ra[e] = __float_as_uint((a[e] * t.x - b[e] * t.y) * qscale);
-                rb[e] = __float_as_uint((b[e] * t.x + a[e] * t.y) * qscale);
-            }
-            const int ts = (t2 / (D / 8)) * (D / 4) + g4;                       // (row, group of 4 elements) as attn_store_q counts
-            attn_store_q<WT, D>(sQ, ts, ra);
-            attn_store_q<WT, D>(sQ, ts + D / 8, rb);
-        }
-    }
-    lds_sync_wave();
-    __builtin_amdgcn_wave_barrier();
-    BRegs<WT, 1> bq[STEPS];
-#pragma unroll
-    for (int t = 0; t < STEPS; ++t) {
-        bq[t].h[0] = ld16(sQ + (2 * t * 64 + lane) * 16);
-        bq[t].l[0] = ld16(sQ + ((2 * t + 1) * 64 + lane) * 16);
-    }
-    __syncthreads();                                        // the buffers take K and V rows from here on
 
     // ---- staging: this lane's share of a pair
     // K: tile kg of the pair, requests t = kt0 .. kt0 + STEPS / 2 - 1 of (key kkey, piece kj)
@@ -398,6 +376,40 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
             *reinterpret_cast<uint4*>(buf + vw_rel + 16) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
         }
     };
+
+    Stage st;
+    stage_load(0, st);                                      // (on its way while the query rows are brought in)
+
+    // ---- the query rows into registers, by way of LDS
+    {
+        const char* qsrc = (const char*)P.q + ((size_t)seq * P.rows * P.nq + h) * D * 2;
+        const float qscale = P.inv_sqrt_d * 1.4426950408889634f;
+        for (int t2 = lane; t2 < 16 * (D / 8); t2 += 64) {
+            const int r = min(t2 / (D / 8), nrows - 1), g4 = t2 % (D / 8);
+            const int row = r0 + r, pos = row / K1 + row % K1;                  // group + slot
+            const char* qrow = qsrc + (size_t)row * P.nq * D * 2;
+            const f32x4 a = load4<WT>(qrow + 4 * g4 * 2), b = load4<WT>(qrow + (D / 2 + 4 * g4) * 2);
+            u32x4 ra, rb;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float2 t = P.table[(size_t)pos * (D / 2) + 4 * g4 + e];
+                ra[e] = __float_as_uint((a[e] * t.x - b[e] * t.y) * qscale);
+                rb[e] = __float_as_uint((b[e] * t.x + a[e] * t.y) * qscale);
+            }
+            const int ts = (t2 / (D / 8)) * (D / 4) + g4;                       // (row, group of 4 elements) as attn_store_q counts
+            attn_store_q<WT, D>(sQ, ts, ra);
+            attn_store_q<WT, D>(sQ, ts + D / 8, rb);
+        }
+    }
+    lds_sync_wave();
+    __builtin_amdgcn_wave_barrier();
+    BRegs<WT, 1> bq[STEPS];
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+        bq[t].h[0] = ld16(sQ + (2 * t * 64 + lane) * 16);
+        bq[t].l[0] = ld16(sQ + ((2 * t + 1) * 64 + lane) * 16);
+    }
+    __syncthreads();                                        // the buffers take K and V rows from here on
 
     // ---- this lane's query (column c of the score tile): group, slot, and which keys 4 kb + e of a tile it sees
     const int qr = min(c, nrows - 1), qg = g0 + qr / K1, qs = qr % K1;
@@ -492,8 +504,6 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
     };
 
     // ---- the pairs
-    Stage st;
-    stage_load(0, st);
     stage_store(smem, st);
     if (n_pairs > 1) stage_load(1, st);
     __syncthreads();
@@ -532,6 +542,404 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// bf16 values, the wide kernel.  A workgroup takes 128 consecutive layout rows, 32 per wavefront, whatever groups they
+// belong to (every row of every MFMA tile is a query: with 9 rows per group a tile of whole groups fills 9 of 16).  It
+// works on the rows of its own groups, whose [MASK] tokens its queries see, then on the real tokens' keys, 32 at a time.
+//
+// All products are v_mfma_f32_32x32x16_bf16 with the queries along the lanes (lane = query c + 32 * half): the scores
+// leave the matrix core as S^T, a lane holding 16 of 32 keys of its query, which is - the contraction may take the
+// keys in any order as long as both operands do - the operand layout of O^T = V^T P^T.  So a query's maximum, sum
+// and output belong to the lane pair (c, c + 32) from start to end: one exchange per 32 keys for the maximum, none for
+// the sum (each half adds up its own keys; the halves meet at the end), and rescaling is one multiplication per register.
+// Queries and probabilities are split into bf16 high and low parts (two MFMAs per product).
+//
+// K and V rows are staged once per workgroup, row by row, into two LDS buffers that take turns (registers requested a
+// tile ahead); V is transposed by the LDS unit on the way out (ds_read_b64_tr_b16: 16 lanes get 4 keys of one column each).
+// The scores of tile t + 1 are worked out beside the exponentials of tile t, so every wavefront has matrix and vector work
+// to offer at any time; two workgroups per compute unit (256 registers) are what the query and output registers allow.
+// Everything that a workgroup reads for the first time (table, query rows, own rows, first tiles) is requested at once.
+//
+// Bound by the matrix cores: 32 MFMAs of 32 cycles per tile and wavefront; the loop over the real tokens keeps them 80 %
+// busy (2560 cycles per tile with two wavefronts per SIMD), and the compute units run at 1.95 GHz meanwhile.  What is left is
+// a workgroup's start (its first rows come from memory: 16 k cycles at T 2048, k 4 of 121 k) and its own rows (14 k).
+// Against the 16-row kernel: T 2048, k 4, 32 heads x 128: 515 -> 347 us; 4 x T 1024, k 8, 32 / 8 heads: 1450 -> 735 us.
+// Tried: no scores ahead (other wavefront alone fills the gaps): 5 % slower; own rows as further tiles of the loop, rotated
+// between the barriers: 4 % (T 2048) and 12 % (4 x 1024, k 8) slower; raised wavefront priority in the matrix part, two
+// accumulators for the scores, four K operands requested ahead: no change.
+// ------------------------------------------------------------------------------------------
+constexpr int GW_ROWS = 32 * GA_WAVES;                     // query rows of a workgroup
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+__device__ __forceinline__ bf16x8 split_hi(const float (&v)[8], unsigned (&hi)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) hi[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
+    return __builtin_bit_cast(bf16x8, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+}
+__device__ __forceinline__ bf16x8 split_lo(const float (&v)[8], const unsigned (&hi)[4]) {
+    unsigned lo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        lo[i] = pack_bf16x2(v[2 * i] - __uint_as_float(hi[i] << 16), v[2 * i + 1] - __uint_as_float(hi[i] & 0xFFFF0000u));
+    return __builtin_bit_cast(bf16x8, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+}
+
+template <int D>
+__global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaParams P) {   // two workgroups per compute unit
+    constexpr int STEPS = D / 16;                           // MFMA steps of a score tile
+    constexpr int NJ = D / 32;                              // blocks of 32 output columns
+    constexpr int PAIRS = D / 16;                           // pairs (j, j + PAIRS) of 16-byte pieces of a row that are rotary partners
+    // the stages: two tiles of 32 K rows, two of V rows (paddings: no two of the lanes that are served together meet in a bank)
+    constexpr int NP = D / 64;                              // pieces of a row per thread, 8 threads per row
+    constexpr int KSTR = 2 * D + 16, VSTR = 2 * D + 64, KBUF = 32 * KSTR, VBUF = 32 * VSTR, OFF_V = 2 * KBUF;
+    // before them: the query rows on their way into registers (from 0), the rows' part of the rotary table
+    constexpr int OFF_T = GA_WAVES * 32 * KSTR, TROW = D / 2 * 8, TROWS = 66;   // positions of GW_ROWS rows: at most (GW_ROWS - 2) / K1 + 1 + K1, K1 = 2 .. 16
+    // ... then the own rows: layout rows R0 - 16 .. R0 + 127, K and V
+    constexpr int OROWS = GW_ROWS + 16, OFF_OV = OROWS * 2 * D;
+    constexpr int OCOLS = D == 128 ? 64 : 32;               // output columns that pass through LDS at a time
+    constexpr int SMEM = 2 * OFF_OV > OFF_T + TROWS * TROW ? 2 * OFF_OV : OFF_T + TROWS * TROW;
+    static_assert(OFF_V + 2 * VBUF <= SMEM && GA_WAVES * 32 * OCOLS * 4 <= SMEM && 2 * SMEM <= 160 * 1024, "");
+    __shared__ __attribute__((aligned(16))) char smem[SMEM];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, half = lane >> 5;
+    const int K1 = P.k + 1;
+    // Workgroups with the most keys start first; neighbours in the launch order, which go to different XCDs, take different
+    // heads, so that (kv heads x sequences a multiple of 8) a kv head's rows are read through one L2
+    const unsigned slots = (unsigned)P.nkv * P.seqs, heads = (unsigned)P.nq * P.seqs;
+    const int blk = (P.rows + GW_ROWS - 1) / GW_ROWS - 1 - (int)(blockIdx.x / heads);
+    const unsigned hs = blockIdx.x % heads, sl = hs % slots;
+    const int seq = sl / P.nkv, hk = sl % P.nkv, h = hk * (P.nq / P.nkv) + hs / slots;
+    const int R0 = GW_ROWS * blk, r0 = R0 + 32 * wave;
+    const bool active = r0 < P.rows;
+    auto group_of = [&](int row) __attribute__((always_inline)) { return P.k > 0 ? (int)__umulhi((unsigned)row, P.k1_magic) : row; };
+    const int r_last = min(R0 + GW_ROWS, P.rows) - 1;       // of the workgroup
+    const int g_last_wg = group_of(r_last), gB0 = group_of(R0);   // its last and first group
+    const int n_real = g_last_wg / 32 + 1;                  // tiles of 32 real tokens
+    const int w_first = min(r0, r_last), wg0 = group_of(w_first), wg1 = group_of(min(r0 + 31, r_last));   // this wavefront's first and last group
+    const int qrow = min(r0 + c, r_last), qg = group_of(qrow);   // this lane's query row (beyond the end: the last, repeated) and group
+    const size_t rs = (size_t)P.nkv * D * 2;                // bytes between layout rows
+    const char* kraw = (const char*)P.k_ + ((size_t)seq * P.rows * P.nkv + hk) * D * 2;
+    const char* vraw = (const char*)P.v + ((size_t)seq * P.rows * P.nkv + hk) * D * 2;
+
+    // ---- requests: the rows' part of the rotary table, the query rows, the own rows, the first tiles
+    constexpr int TU = (TROWS * TROW / 16 + GA_THREADS - 1) / GA_THREADS, TU1 = 4;   // 16-byte units per thread; the first 4 do for K1 >= 5
+    u32x4 tv[TU1];
+    const u32x4* const tab_src = reinterpret_cast<const u32x4*>(P.table + (size_t)gB0 * (D / 2));
+    const int tab_n = (g_last_wg - gB0 + K1) * (TROW / 16);   // positions of the rows of groups gB0 .. g_last_wg
+    if (P.k > 0) {
+#pragma unroll
+        for (int i = 0; i < TU1; ++i) tv[i] = tab_src[min(tid + GA_THREADS * i, tab_n - 1)];
+    }
+    constexpr int QPI = 64 / PAIRS, QI = 32 / QPI;          // query rows per request of a wavefront, requests
+    constexpr int OPI = GA_THREADS / PAIRS, OI = (OROWS + OPI - 1) / OPI;   // own rows per request of the workgroup, requests
+    const int pj = tid % PAIRS;                             // this thread's pair of pieces
+    uint4 qa[QI], qb[QI], ok[OI][2], ov[OI][2];
+    {
+        const char* src = (const char*)P.q + ((size_t)seq * P.rows * P.nq + h) * D * 2 + pj * 16;
+#pragma unroll
+        for (int i = 0; i < QI; ++i) {
+            const char* a = src + (size_t)min(r0 + QPI * i + lane / PAIRS, r_last) * P.nq * D * 2;
+            qa[i] = ld16(a);
+            qb[i] = ld16(a + D);
+        }
+    }
+    auto own_row = [&](int i) __attribute__((always_inline)) { return min(max(R0 - 16 + OPI * i + tid / PAIRS, 0), r_last); };
+    if (P.k > 0) {
+#pragma unroll
+        for (int i = 0; i < OI; ++i) {
+            const size_t off = (size_t)own_row(i) * rs + pj * 16;
+            ok[i][0] = ld16(kraw + off);
+            ok[i][1] = ld16(kraw + off + D);
+            ov[i][0] = ld16(vraw + off);
+            ov[i][1] = ld16(vraw + off + D);
+        }
+    }
+    // staging of the real tokens' tiles: 8 threads per key
+    const int skey = tid / 8, sj = tid % 8;
+    const char* krot = (const char*)P.k_rot + (size_t)(seq * (size_t)P.nkv + hk) * P.T * D * 2;
+    auto load_k = [&](int t, uint4 (&x)[NP]) __attribute__((always_inline)) {
+        const char* kp = krot + (size_t)(unsigned)min(32 * t + skey, g_last_wg) * (2 * D) + sj * 16;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) x[i] = ld16(kp + i * 128);
+    };
+    const unsigned K1rs = (unsigned)K1 * (unsigned)rs;
+    auto load_v = [&](int t, uint4 (&x)[NP]) __attribute__((always_inline)) {
+        const char* vp = vraw + (size_t)(unsigned)min(32 * t + skey, g_last_wg) * K1rs + sj * 16;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) x[i] = ld16(vp + i * 128);
+    };
+    auto store_k = [&](int t, const uint4 (&x)[NP]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) *reinterpret_cast<uint4*>(smem + (t & 1) * KBUF + skey * KSTR + sj * 16 + i * 128) = x[i];
+    };
+    auto store_v = [&](int t, const uint4 (&x)[NP]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) *reinterpret_cast<uint4*>(smem + OFF_V + (t & 1) * VBUF + skey * VSTR + sj * 16 + i * 128) = x[i];
+    };
+    uint4 k0[NP], k1[NP], v0[NP], kst[NP], vst[NP];
+    load_k(0, k0);
+    load_k(1, k1);
+    load_k(2, kst);
+    load_v(0, v0);
+    load_v(1, vst);
+    if (P.k > 0) {
+#pragma unroll
+        for (int i = 0; i < TU1; ++i) reinterpret_cast<u32x4*>(smem + OFF_T)[min(tid + GA_THREADS * i, tab_n - 1)] = tv[i];
+        if (tab_n > TU1 * GA_THREADS) {                     // (two or three rows per group: more positions)
+            u32x4 tw[TU - TU1];
+#pragma unroll
+            for (int i = TU1; i < TU; ++i) tw[i - TU1] = tab_src[min(tid + GA_THREADS * i, tab_n - 1)];
+#pragma unroll
+            for (int i = TU1; i < TU; ++i) reinterpret_cast<u32x4*>(smem + OFF_T)[min(tid + GA_THREADS * i, tab_n - 1)] = tw[i - TU1];
+        }
+        __syncthreads();
+    }
+
+    // (a row R0 - 16 .. R0 - 1 of an earlier group is seen by nobody here and takes any entry of the table)
+    // a pair of pieces of a row, rotated: cosines and sines of pairs 8 pj .. 8 pj + 7 at the row's position
+    auto rotate = [&](uint4 xa, uint4 xb, const float4* tab, float scale, float (&ra)[8], float (&rb)[8]) __attribute__((always_inline)) {
+        float a[8], b[8];
+        unpack_group<bf16_t>(xa, a);
+        unpack_group<bf16_t>(xb, b);
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const float4 cs = tab[e / 2];
+            ra[e] = (a[e] * cs.x - b[e] * cs.y) * scale;
+            rb[e] = (b[e] * cs.x + a[e] * cs.y) * scale;
+            ra[e + 1] = (a[e + 1] * cs.z - b[e + 1] * cs.w) * scale;
+            rb[e + 1] = (b[e + 1] * cs.z + a[e + 1] * cs.w) * scale;
+        }
+    };
+    auto position = [&](int row) __attribute__((always_inline)) { return row - group_of(row) * P.k; };   // group + slot
+    auto table_lds = [&](int pos) __attribute__((always_inline)) {
+        return reinterpret_cast<const float4*>(smem + OFF_T + max(pos - gB0, 0) * TROW) + pj * 4;
+    };
+
+    // ---- the query rows, rotated in float32, scaled by log2(e) / sqrt(d), split: high parts, then low parts by way of LDS
+    // into registers (lane (c, half): bytes [32 t + 16 half, +16) of row c at step t)
+    bf16x8 qh[STEPS], ql[STEPS];
+    {
+        char* const sQ = smem + wave * (32 * KSTR);
+        const float qscale = P.inv_sqrt_d * 1.4426950408889634f;
+        uint4 la[QI], lb[QI];
+#pragma unroll
+        for (int i = 0; i < QI; ++i) {
+            const int rr = QPI * i + lane / PAIRS, pos = position(min(r0 + rr, r_last));
+            float ra[8], rb[8];
+            if (P.k > 0) rotate(qa[i], qb[i], table_lds(pos), qscale, ra, rb);
+            else rotate(qa[i], qb[i], reinterpret_cast<const float4*>(P.table + (size_t)pos * (D / 2)) + pj * 4, qscale, ra, rb);
+            unsigned hi[4];
+            *reinterpret_cast<bf16x8*>(sQ + rr * KSTR + pj * 16) = split_hi(ra, hi);
+            la[i] = __builtin_bit_cast(uint4, split_lo(ra, hi));
+            *reinterpret_cast<bf16x8*>(sQ + rr * KSTR + (pj + PAIRS) * 16) = split_hi(rb, hi);
+            lb[i] = __builtin_bit_cast(uint4, split_lo(rb, hi));
+        }
+        lds_sync_wave();
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) qh[t] = __builtin_bit_cast(bf16x8, ld16(sQ + c * KSTR + 32 * t + 16 * half));
+        lds_sync_wave();
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < QI; ++i) {
+            const int rr = QPI * i + lane / PAIRS;
+            *reinterpret_cast<uint4*>(sQ + rr * KSTR + pj * 16) = la[i];
+            *reinterpret_cast<uint4*>(sQ + rr * KSTR + (pj + PAIRS) * 16) = lb[i];
+        }
+        lds_sync_wave();
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) ql[t] = __builtin_bit_cast(bf16x8, ld16(sQ + c * KSTR + 32 * t + 16 * half));
+    }
+
+    float m_run = -INFINITY, l_run = 0.f;                   // of this lane's query: the reference of the exponentials (both halves agree), the half's sum
+    f32x16 o[NJ];                                           // O^T: column 32 j + 8 (i / 4) + 4 half + i % 4 of this lane's query
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[j][i] = 0.f;
+    // The parts of a tile's work.  Scores: kf(step) = the 32 K rows as MFMA operand (key c, bytes [32 step + 16 half, +16));
+    // the lane's i-th score is that of key 8 (i / 4) + i % 4 + 4 half
+    auto scores = [&](auto kf) __attribute__((always_inline)) {
+        f32x16 x;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = 0.f;
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const bf16x8 f = kf(st);
+            x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qh[st], x, 0, 0, 0);
+            x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, ql[st], x, 0, 0, 0);
+        }
+        return x;
+    };
+    auto mask = [&](f32x16& x, int lo, int hi) __attribute__((always_inline)) {   // keys lo .. hi (counted from 4 half) are visible
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int key = 8 * (i / 4) + i % 4;
+            x[i] = (key >= lo && key <= hi) ? x[i] : -INFINITY;
+        }
+    };
+    // the reference follows the maximum only when that has moved up by more than GA_LAZY (in units of ln 2): sums and outputs
+    // are relative to the same reference, so the quotient is the same, and most tiles need no rescaling
+    auto follow = [&](const f32x16& x) __attribute__((always_inline)) {
+        float mt = x[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mt = fmaxf(mt, x[i]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
+        mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+        const bool moved = mt > m_run + GA_LAZY;            // (also the first keys a row sees: m_run = -inf)
+        if (__any(moved)) {
+            const float m_new = moved ? mt : m_run;
+            const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
+            l_run *= alpha;
+            m_run = m_new;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) o[j] *= alpha;
+        }
+    };
+    // exponentials against m, P.V: vf(j, m) = V^T as operand, columns 32 j + c, keys 16 m + 4 half + 0..3 and 16 m + 8 + 4 half + 0..3
+    auto accumulate = [&](const f32x16& x, float m, auto vf) __attribute__((always_inline)) {
+        float pr[2][8];
+        float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float e = __builtin_amdgcn_exp2f(x[i] - m);
+            pr[i / 8][i % 8] = e;
+            if (i & 1) l1 += e; else l0 += e;
+        }
+        l_run += l0 + l1;
+        bf16x8 ph[2], pl[2];
+#pragma unroll
+        for (int m2 = 0; m2 < 2; ++m2) {
+            unsigned hi8[4];
+            ph[m2] = split_hi(pr[m2], hi8);
+            pl[m2] = split_lo(pr[m2], hi8);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; j += 2)
+#pragma unroll
+            for (int m2 = 0; m2 < 2; ++m2) {
+                const bf16x8 va = vf(j, m2), vb = vf(j + 1, m2);
+                o[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, ph[m2], o[j], 0, 0, 0);
+                o[j + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb, ph[m2], o[j + 1], 0, 0, 0);
+                o[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[m2], o[j], 0, 0, 0);
+                o[j + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb, pl[m2], o[j + 1], 0, 0, 0);
+            }
+    };
+    const int vkey = (lane & 15) >> 2, vhi = (lane >> 4) & 1;   // V^T from rows in LDS: 16 lanes read 4 keys x 32 bytes and get 4 keys of a column each
+    auto transposed = [&](const char* a, int rows8) __attribute__((always_inline)) {
+        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)a);
+        const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(a + rows8));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+
+    // ---- the [MASK] keys of the own groups: rows in LDS, K rotated (and rounded as cached keys are); 16-byte K pieces stand at
+    // piece ^ key, 32-byte V chunks at chunk ^ f(key).  A wavefront's queries see rows among their own 32 and, where its
+    // first row is not the first of its group, among the 16 before
+    if (P.k > 0) {
+        uint4 rk[OI][2];
+#pragma unroll
+        for (int i = 0; i < OI; ++i) {
+            float ra[8], rb[8];
+            rotate(ok[i][0], ok[i][1], table_lds(position(own_row(i))), 1.f, ra, rb);
+            unsigned hi[4];
+            rk[i][0] = __builtin_bit_cast(uint4, split_hi(ra, hi));
+            rk[i][1] = __builtin_bit_cast(uint4, split_hi(rb, hi));
+        }
+        __syncthreads();                                    // table and query areas have been read
+#pragma unroll
+        for (int i = 0; i < OI; ++i) {
+            const int orow = OPI * i + tid / PAIRS;
+            const int ksw = D == 128 ? orow & 15 : (orow >> 1) & 7, vsw = D == 128 ? (orow & 3) << 1 : orow & 2;
+            char* const kd = smem + orow * (2 * D) + ((pj ^ ksw) << 4);
+            char* const vd = smem + OFF_OV + orow * (2 * D) + (((pj >> 1) ^ vsw) << 5) + ((pj & 1) << 4);
+            if (OPI * i + OPI <= OROWS || orow < OROWS) {
+                *reinterpret_cast<uint4*>(kd) = rk[i][0];
+                *reinterpret_cast<uint4*>(smem + ((kd - smem) ^ (PAIRS * 16))) = rk[i][1];
+                *reinterpret_cast<uint4*>(vd) = ov[i][0];
+                *reinterpret_cast<uint4*>(smem + OFF_OV + ((vd - smem - OFF_OV) ^ (PAIRS * 16))) = ov[i][1];
+            }
+        }
+        __syncthreads();
+        const int kro = c * (2 * D) + ((half ^ (D == 128 ? c & 15 : (c >> 1) & 7)) << 4);
+        const int vro = (4 * half + vkey) * (2 * D) + ((vhi ^ (D == 128 ? vkey << 1 : vkey & 2)) << 5) + (lane & 3) * 8;
+#pragma unroll 1
+        for (int before = 0; before < 2; ++before) {
+            if (!active || (before && wg0 * K1 == r0)) continue;
+            const int first = before ? r0 - 16 : r0;        // layout row of the tile's first key
+            const char* kt = smem + (first - R0 + 16) * (2 * D);
+            f32x16 x = scores([&](int st) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, ld16(kt + (kro ^ (st << 5)))); });
+            mask(x, qg * K1 + 1 - first - 4 * half, (before ? min(qrow, r0 - 1) : qrow) - first - 4 * half);
+            follow(x);
+            accumulate(x, m_run > -INFINITY ? m_run : 0.f, [&](int j, int m2) __attribute__((always_inline)) {   // (a real token's row sees none)
+                return transposed(kt + OFF_OV + m2 * 16 * 2 * D + (vro ^ (j << 6)), 8 * 2 * D);
+            });
+        }
+    }
+    __syncthreads();                                        // the stages' buffers are free
+
+    // ---- the real tokens.  K is staged one tile further than V: a tile's scores are worked out while the tile before is
+    // exponentiated and multiplied with its values
+    store_k(0, k0);
+    store_k(1, k1);
+    store_v(0, v0);
+    const int kr = c * KSTR + half * 16, vr = OFF_V + (4 * half + vkey) * VSTR + vhi * 32 + (lane & 3) * 8;
+    auto stage_scores = [&](int t) __attribute__((always_inline)) {
+        const char* a = smem + (t & 1) * KBUF + kr;
+        return scores([&](int st) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, ld16(a + 32 * st)); });
+    };
+    __syncthreads();
+    f32x16 s = stage_scores(0);
+    __syncthreads();
+    const int real_end = active ? wg1 / 32 + 1 : 0, whole_end = (wg0 + 1) / 32;   // tiles this wavefront's queries see some of, all of
+    for (int t = 0; t < n_real; ++t) {
+        store_k(t, kst);                                    // (tile t + 2's, into the buffer of tile t, whose scores are known)
+        store_v(t + 1, vst);
+        load_k(t + 3, kst);
+        load_v(t + 2, vst);
+        if (t < real_end) {
+            if (t >= whole_end) mask(s, 0, qg - 32 * t - 4 * half);
+            follow(s);
+            const f32x16 sn = stage_scores(t + 1);
+            // (every query sees the first tile's first key: m_run is finite)
+            accumulate(s, m_run, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
+            s = sn;
+        }
+        __syncthreads();
+    }
+
+    // ---- output: OCOLS columns at a time by way of the wavefront's LDS area, divided by the rows' sums
+    const auto lw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+    const float inv = 1.f / (__uint_as_float(lw[0]) + __uint_as_float(lw[1]));   // (every row sees at least its own real token)
+    constexpr int PCS = OCOLS / 4;                          // 16-byte pieces of a row
+    char* const sO = smem + wave * (32 * OCOLS * 4);
+    float* obase = P.out + ((size_t)seq * P.rows * P.nq + h) * D;
+#pragma unroll
+    for (int j0 = 0; j0 < NJ; j0 += OCOLS / 32) {
+#pragma unroll
+        for (int j = 0; j < OCOLS / 32; ++j)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                f32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = o[j0 + j][4 * i4 + e] * inv;
+                *reinterpret_cast<f32x4*>(sO + (c * PCS + ((8 * j + 2 * i4 + half) ^ (c & (PCS - 1)))) * 16) = w;
+            }
+        lds_sync_wave();
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < PCS / 2; ++u) {
+            const int rr = (64 / PCS) * u + lane / PCS, pc = lane % PCS;
+            const f32x4 w = *reinterpret_cast<const f32x4*>(sO + (rr * PCS + (pc ^ (rr & (PCS - 1)))) * 16);
+            if (r0 + rr < P.rows) *reinterpret_cast<f32x4*>(obase + (size_t)(r0 + rr) * P.nq * D + 32 * j0 + 4 * pc) = w;
+        }
+        lds_sync_wave();
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 int check(const ps_group_attn_args* a) {
@@ -556,15 +964,33 @@ GaLayout layout(const ps_group_attn_args* a) {
     return L;
 }
 
+template <typename WT, int D, bool ALL>
+void launch_rope(const GaParams& P, hipStream_t s) {
+    // a workgroup per position; where positions are few, several (of at most one item per thread each) share one's rows
+    const long long items = (long long)P.seqs * P.nkv * (D / 8) * (ALL ? P.k + 1 : 1);
+    const int gy = (int)max(1LL, min((items + 255) / 256, 2048LL / (P.T + P.k)));
+    hipLaunchKernelGGL((ga_rope_kernel<WT, D, ALL>), dim3(P.T + P.k, gy), dim3(256), 0, s, P);
+}
+
 template <typename WT, int D>
 int launch(const GaParams& P, hipStream_t s) {
-    const long long nrope = (long long)P.seqs * P.rows * P.nkv * (D / 8);
-    hipLaunchKernelGGL((ga_table_kernel<D>), dim3(min(1024, ((P.T + P.k) * (D / 2) + 255) / 256)), dim3(256), 0, s, P);
-    hipLaunchKernelGGL((ga_rope_kernel<WT, D>), dim3((unsigned)min(65535LL, (nrope + 255) / 256)), dim3(256), 0, s, P);
-    if constexpr (Traits<WT>::BF)
-        hipLaunchKernelGGL((ga_attn_bf16_kernel<D>), dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs), dim3(GA_THREADS), 0, s, P);
-    else
+    if constexpr (Traits<WT>::BF) {
+        // The wide kernel, except where the real tokens' keys are a single stage and the groups' own rows are most of the work:
+        // there the 16-row kernel, whose workgroups are half as long, is the faster one (us, both kernels and the keys'
+        // rotation: T 30, k 4, 8 heads x 128: 13.4 against 13.7; T 16, k 10, 32 heads: 13.7 against 14.0; but T 30, k 1:
+        // 9.8 against 9.0; T 64, k 4, 40 heads: 17.7 against 15.6; T 2048, k 4, 32 heads: 515 against 347)
+        const long long blocks = (long long)((P.rows + GW_ROWS - 1) / GW_ROWS) * P.nq * P.seqs;
+        if (blocks > 0x7FFFFFFF || (P.T <= 32 && P.k >= 4)) {
+            launch_rope<WT, D, true>(P, s);
+            hipLaunchKernelGGL((ga_attn_bf16_kernel<D>), dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs), dim3(GA_THREADS), 0, s, P);
+        } else {
+            launch_rope<WT, D, false>(P, s);
+            hipLaunchKernelGGL((ga_attn_wide_kernel<D>), dim3((unsigned)blocks), dim3(GA_THREADS), 0, s, P);
+        }
+    } else {
+        launch_rope<WT, D, true>(P, s);
         hipLaunchKernelGGL((ga_attn_f32_kernel<D>), dim3(P.ntiles, P.nq, P.seqs), dim3(GA_THREADS), 0, s, P);
+    }
     return hipGetLastError() == hipSuccess ? PS_OK : PS_ERR_DEVICE;
 }
 
@@ -584,6 +1010,7 @@ extern "C" int ps_group_attention(const ps_group_attn_args* a, void* stream) {
     P.seqs = a->seqs; P.T = a->tokens; P.k = a->k; P.nq = a->n_heads; P.nkv = a->n_kv_heads;
     P.rows = a->tokens * (a->k + 1);
     P.gpt = 16 / (a->k + 1);
+    P.k1_magic = (unsigned)((0x100000000ull + a->k) / (unsigned)(a->k + 1));
     P.ntiles = (a->tokens + P.gpt - 1) / P.gpt;
     P.inv_sqrt_d = (float)(1.0 / sqrt((double)a->head_dim));
     P.q = a->q; P.k_ = a->k_; P.v = a->v; P.out = a->out;

@@ -66,6 +66,17 @@ def test_longer_sequences_with_other_group_sizes():
     _case(1, 120, 3, 4, 4, 128, "f32", 11)
 
 
+@pytest.mark.parametrize("seqs,T,k,nq,nkv,d", [
+    (1, 33, 0, 2, 2, 128), (1, 128, 0, 2, 1, 64), (1, 129, 0, 1, 1, 128),     # k = 0 (no own rows): 1, exactly 1 and 2 blocks of 128 rows
+    (1, 64, 1, 2, 2, 128), (2, 65, 1, 3, 1, 64),                              # two rows per group: the most positions in a block; 1 and 2 blocks
+    (1, 43, 2, 2, 2, 64), (1, 96, 2, 3, 3, 128),                              # blocks that start inside a group; rows = 129, 288
+    (1, 33, 4, 2, 1, 128), (2, 51, 4, 2, 2, 64), (1, 33, 8, 4, 2, 128),       # T just above the 16-row kernel's range
+    (1, 33, 15, 2, 2, 128), (1, 40, 10, 3, 3, 64), (3, 16, 3, 5, 1, 128),     # 16 rows per group; a wavefront without rows; 15 heads x sequences
+    (1, 32, 4, 2, 2, 128), (1, 32, 15, 2, 1, 64)])                            # the 16-row kernel's largest
+def test_blocks_of_128_rows_at_their_edges(seqs, T, k, nq, nkv, d):
+    _case(seqs, T, k, nq, nkv, d, "bf16", 100 + T + k)
+
+
 def test_the_error_is_the_rounding_of_the_rotated_keys():
     """The tolerance above is spent on keys that round the other way after a float32 rotation (the kernel's) than
     after a float64 rotation (the oracle's).  With the keys rotated in float32 on the CPU, as the kernel's key
