@@ -9,9 +9,6 @@
 // the key tiles; scores are MFMA tiles (the keys' rows are the row operand, the query rows the column operand).  bf16
 // values: ga_attn_wide_kernel (and, for the smallest calls, ga_attn_bf16_kernel); float32 values: ga_attn_f32_kernel.
 // Each describes its own scheme.
-//
-// In the two kernels of 16-row tiles a query tile is a whole number of parallel groups (as many as fit into 16 rows), so
-// the [MASK] tokens of its groups all lie inside its own rows: one more key tile.
 #include "ps_device.h"
 #include "ps_train.h"
 
@@ -73,186 +70,183 @@ __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
 }
 
 // ------------------------------------------------------------------------------------------
-// float32 values.  A workgroup takes one query tile; its four wavefronts take the key tiles in turn, each with
-// its own running maximum, sum and output, and their results meet in LDS at the end.  Scores are MFMA tiles (the K
-// rows, lane (c, kb): bytes [64 t + 16 kb, +16) of key c, straight from memory as the 16-row operand; the query
-// rows, rotated while they are staged, the 16-column operand in registers); P.V is plain FMA work: a lane owns
-// head_dim / 64 output columns of all 16 rows and reads the probabilities as LDS broadcasts.
+// float32 values.  A workgroup takes 64 consecutive layout rows, 16 per wavefront, with two wavefronts to every 16 rows
+// that share their keys; it walks the real tokens' keys 32 at a time, then the rows R0 - 16 .. R0 + 63, among which the
+// queries see their own groups' [MASK] rows, and of every 32 keys a wavefront takes 16.
+//
+// All products are v_mfma_f32_16x16x4_f32 with the queries along the lanes (lane = query c + 16 kb): scores as S^T, a lane
+// holding keys 4 kb .. 4 kb + 3 of its query, register i of which is the column operand of O^T = V^T P^T for the four keys
+// 4 kb + i; the row operand, column 4 m + e of those keys' values (m = the lane's c, e = 0 .. 3), are the four elements of one 16-byte
+// LDS read.  Maximum, sum and output stay with the four lanes of a query; the two wavefronts of 16 rows meet in LDS at the
+// end.  K and V rows are staged for all eight wavefronts, into two buffers that take turns.
+//
+// Bound by the float32 matrix rate (32 MFMAs of 32 cycles per 16 x 16 tile at head_dim 64).  Before, P.V was FMA work against
+// probabilities broadcast from LDS, a workgroup took one tile of whole groups and every wavefront fetched its own operands:
+// 2 x T 300, k 3, 8 heads x 64: 43 -> 29 us; 4 x T 512, k 10, 16 / 4 heads x 64: 724 -> 300 us (float32 matrix rate: 185); T 1024,
+// k 4, 32 heads x 128: 1047 -> 470 us.
 // ------------------------------------------------------------------------------------------
+constexpr int GF_THREADS = 512, GF_ROWS = 64;
+
 template <int D>
-__global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_f32_kernel(const GaParams P) {   // workgroups per compute unit
-    typedef float WT;
-    constexpr int ESZ = 4, STEPS = D / Traits<WT>::KSTEP, DPL = D / 64;
-    constexpr int OFF_Q = 0;                                // 16 query rows as MFMA operands: 16 * D * 4 bytes
-    constexpr int OFF_P = OFF_Q + 16 * D * 4;               // [waves][16 rows][16 keys] probabilities
-    constexpr int OFF_A = OFF_P + GA_WAVES * 16 * 16 * 4;   // [waves][16] rescale factors of the running output
-    constexpr int OFF_ML = OFF_A + GA_WAVES * 16 * 4;       // [waves][16][2] final (max, sum)
-    constexpr int OFF_O = OFF_ML + GA_WAVES * 16 * 2 * 4;   // [waves][16][D] outputs
-    __shared__ __attribute__((aligned(16))) char smem[OFF_O + GA_WAVES * 16 * D * 4];
-    typedef typename VRaw<WT, DPL>::type raw_t;
+__global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaParams P) {   // four wavefronts per SIMD: two workgroups
+    constexpr int STEPS = D / 16, NV = D / 64;              // 64-byte steps of a row; 16-byte pieces of a row per thread and lane
+    constexpr int KSTR = 4 * D + 16, VSTR = 4 * D, KBUF = 32 * KSTR, BUF = KBUF + 32 * VSTR;
+    constexpr int QAREA = 16 * D * 4;                       // 16 query rows as MFMA operands; later one wavefront's output on its way to the other
+    constexpr int OFF_ML = 4 * QAREA;                       // [4][64 lanes] (maximum, sum)
+    static_assert(OFF_ML + 4 * 64 * 8 <= 2 * BUF, "query and merge areas fit the buffers");
+    __shared__ __attribute__((aligned(16))) char smem[2 * BUF];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 15, kb = lane >> 4;
-    const int tile = P.ntiles - 1 - (int)blockIdx.x;        // the tiles with the most keys start first
-    const int h = blockIdx.y, seq = blockIdx.z, hk = h / (P.nq / P.nkv);
+    const int c = lane & 15, kb = lane >> 4, qt = wave & 3, kh = wave >> 2;   // query tile, half of the keys
     const int K1 = P.k + 1;
-    const int g0 = tile * P.gpt, ng = min(P.gpt, P.T - g0), nrows = ng * K1, r0 = g0 * K1;
-    const int g_last = g0 + ng - 1;
-    char* sQ = smem + OFF_Q;
-    float* sP = reinterpret_cast<float*>(smem + OFF_P) + wave * 256;
-    float* sA = reinterpret_cast<float*>(smem + OFF_A) + wave * 16;
-    float* sML = reinterpret_cast<float*>(smem + OFF_ML);
-    float* sO = reinterpret_cast<float*>(smem + OFF_O);
+    auto group_of = [&](int row) __attribute__((always_inline)) { return P.k > 0 ? (int)__umulhi((unsigned)row, P.k1_magic) : row; };
+    const int blk = (P.rows + GF_ROWS - 1) / GF_ROWS - 1 - (int)(blockIdx.x / (unsigned)P.nq);   // the rows with the most keys start first
+    const int h = blockIdx.x % (unsigned)P.nq, seq = blockIdx.z, hk = h / (P.nq / P.nkv);
+    const int R0 = GF_ROWS * blk, r0 = R0 + 16 * qt;
+    const bool active = r0 < P.rows;
+    const int r_last = min(R0 + GF_ROWS, P.rows) - 1, g_last_wg = group_of(r_last);
+    const int n_real = g_last_wg / 32 + 1, n_stages = n_real + (P.k > 0 ? (r_last - R0 + 16) / 32 + 1 : 0);
+    const int wg0 = group_of(min(r0, r_last)), wg1 = group_of(min(r0 + 15, r_last));   // the tile's first and last group
+    const int qrow = min(r0 + c, r_last), qg = group_of(qrow);   // this lane's query (beyond the end: the last, repeated)
 
-    // ---- the query rows, rotated, into LDS as the 16-column MFMA operand; rows beyond the tile repeat the last
-    const char* qsrc = (const char*)P.q + ((size_t)seq * P.rows * P.nq + h) * D * ESZ;
-    for (int t2 = tid; t2 < 16 * (D / 8); t2 += GA_THREADS) {
-        const int r = min(t2 / (D / 8), nrows - 1), g4 = t2 % (D / 8);
-        const int row = r0 + r, pos = row / K1 + row % K1;                      // group + slot
-        const char* qrow = qsrc + (size_t)row * P.nq * D * ESZ;
-        const f32x4 a = load4<WT>(qrow + 4 * g4 * ESZ), b = load4<WT>(qrow + (D / 2 + 4 * g4) * ESZ);
-        u32x4 ra, rb;
+    // ---- staging: 16 threads per row
+    const int skey = tid >> 4, sp = tid & 15;
+    const size_t rs = (size_t)P.nkv * D * 4, head_off = (((size_t)seq * P.rows) * P.nkv + hk) * D * 4 + sp * 16;
+    const char* kbase = (const char*)P.k_rot + head_off;
+    const char* vbase = (const char*)P.v + head_off;
+    struct Stage { uint4 k[NV], v[NV]; };
+    auto stage_load = [&](int t, Stage& x) __attribute__((always_inline)) {
+        const int row = t < n_real ? min(32 * t + skey, g_last_wg) * K1 : min(max(R0 - 16 + 32 * (t - n_real) + skey, 0), r_last);
+        const size_t off = (size_t)(unsigned)row * rs;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float2 t = P.table[(size_t)pos * (D / 2) + 4 * g4 + e];
-            ra[e] = __float_as_uint(a[e] * t.x - b[e] * t.y);
-            rb[e] = __float_as_uint(b[e] * t.x + a[e] * t.y);
-        }
-        const int ts = (t2 / (D / 8)) * (D / 4) + g4;                           // (row, group of 4 elements) as attn_store_q counts
-        attn_store_q<WT, D>(sQ, ts, ra);
-        attn_store_q<WT, D>(sQ, ts + D / 8, rb);
-    }
-    __syncthreads();
-    BRegs<WT, 1> bq[STEPS];
-#pragma unroll
-    for (int t = 0; t < STEPS; ++t) bq[t].h[0] = ld16(sQ + (t * 64 + lane) * 16);
-    // this lane's query (column c of the score tile): group and slot
-    const int qr = min(c, nrows - 1), qg = g0 + qr / K1, qs = qr % K1;
-    const bool qlive = c < nrows;
-
-    const char* kbase = (const char*)P.k_rot + ((size_t)seq * P.rows * P.nkv + hk) * D * ESZ;
-    const char* vbase = (const char*)P.v + ((size_t)seq * P.rows * P.nkv + hk) * D * ESZ;
-    const size_t rstride = (size_t)P.nkv * D * ESZ;        // bytes between layout rows
-    const int n_real = (g_last >> 4) + 1;                   // key tiles of real tokens; one more tile: the tile's own [MASK] rows
-    const int n_tiles = n_real + (P.k > 0 ? 1 : 0);
-    float m_run = -INFINITY, l_run = 0.f;                   // of query c (the same in the four lanes that share it)
-    float o[16][DPL];                                       // this lane's columns of all 16 rows
-#pragma unroll
-    for (int rr = 0; rr < 16; ++rr)
-#pragma unroll
-        for (int e = 0; e < DPL; ++e) o[rr][e] = 0.f;
-    // layout row of key j of key tile t (clamped to a row that exists); tile n_real holds the [MASK] rows of the
-    // query tile's own groups
-    auto key_row = [&](int t, int j) __attribute__((always_inline)) {
-        return t >= n_real ? r0 + min(j, nrows - 1) : min(16 * t + j, g_last) * K1;
+        for (int i = 0; i < NV; ++i) { x.k[i] = ld16(kbase + off + 256 * i); x.v[i] = ld16(vbase + off + 256 * i); }
     };
+    auto stage_store = [&](int t, const Stage& x) __attribute__((always_inline)) {
+        char* b = smem + (t & 1) * BUF;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            *reinterpret_cast<uint4*>(b + skey * KSTR + sp * 16 + 256 * i) = x.k[i];
+            *reinterpret_cast<uint4*>(b + KBUF + skey * VSTR + sp * 16 + 256 * i) = x.v[i];
+        }
+    };
+    Stage st, st1;
+    stage_load(0, st);
+    stage_load(min(1, n_stages - 1), st1);
+
+    // ---- the query rows, rotated, into LDS as MFMA operands, and from there into both of their wavefronts' registers
     {
-    // a key tile at a time; its K rows and value rows are requested one tile ahead
-    auto load_tile = [&](int t, uint4 (&kreg)[STEPS], raw_t (&vraw)[16]) __attribute__((always_inline)) {
-        const char* krow = kbase + (size_t)key_row(t, c) * rstride + kb * 16;
+        const char* qsrc = (const char*)P.q + ((size_t)seq * P.rows * P.nq + h) * D * 4;
 #pragma unroll
-        for (int st = 0; st < STEPS; ++st) kreg[st] = ld16(krow + st * 64);
+        for (int i = 0; i < GF_ROWS * (D / 8) / GF_THREADS; ++i) {
+            const int x = tid + GF_THREADS * i, r = x / (D / 8), g4 = x % (D / 8);
+            const int row = min(R0 + r, r_last), pos = row - group_of(row) * P.k;                // group + slot
+            const char* qr = qsrc + (size_t)row * P.nq * D * 4 + 16 * g4;
+            const f32x4 a = load4<float>(qr), b = load4<float>(qr + 2 * D);
+            const float4* tab = reinterpret_cast<const float4*>(P.table + (size_t)pos * (D / 2) + 4 * g4);
+            const float4 t0 = tab[0], t1 = tab[1];
+            const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+            u32x4 ra, rb;
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            vraw[j] = *reinterpret_cast<const raw_t*>(vbase + (size_t)key_row(t, j) * rstride + (size_t)DPL * lane * ESZ);
-    };
-    uint4 kreg[STEPS], kreg_n[STEPS];
-    raw_t vraw[16], vraw_n[16];
-    load_tile(min(wave, n_tiles - 1), kreg, vraw);
-    for (int kt = wave; kt < n_tiles; kt += GA_WAVES) {
-        const bool own = kt == n_real;                      // the [MASK] tokens of the tile's own groups
-        load_tile(min(kt + GA_WAVES, n_tiles - 1), kreg_n, vraw_n);   // (beyond the last: a repeat nobody uses)
-        f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int t = 0; t < STEPS; ++t) mma_step<WT, 1>(kreg[t], bq[t], acc);
-        // scores of keys 4 kb .. 4 kb + 3 for query c, masked
-        float sc[4], mt = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = 4 * kb + r;
-            bool vis;
-            if (own) {
-                const int kg = g0 + j / K1, ks = j % K1;
-                vis = j < nrows && ks > 0 && kg == qg && ks <= qs;       // a [MASK] token of the query's own group, not after it
-            } else {
-                vis = 16 * kt + j <= qg;                                  // the real token of a group up to the query's own
+            for (int e = 0; e < 4; ++e) {
+                ra[e] = __float_as_uint(a[e] * cs[e] - b[e] * sn[e]);
+                rb[e] = __float_as_uint(b[e] * cs[e] + a[e] * sn[e]);
             }
-            sc[r] = (vis && qlive) ? acc[0][r] * P.inv_sqrt_d : -INFINITY;
-            mt = fmaxf(mt, sc[r]);
+            const int ts = (r & 15) * (D / 4) + g4;                                             // (row, group of 4 elements) as attn_store_q counts
+            attn_store_q<float, D>(smem + (r >> 4) * QAREA, ts, ra);
+            attn_store_q<float, D>(smem + (r >> 4) * QAREA, ts + D / 8, rb);
         }
-        mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
-        mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-        const float m_new = fmaxf(m_run, mt);
-        const float alpha = m_new > -INFINITY ? expf(m_run - m_new) : 1.f;   // exp(-inf) = 0 when nothing was seen before
-        f32x4 pr;
-        float ls = 0.f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            pr[r] = sc[r] > -INFINITY ? expf(sc[r] - m_new) : 0.f;
-            ls += pr[r];
-        }
-        ls += __shfl_xor(ls, 16, 64);
-        ls += __shfl_xor(ls, 32, 64);
-        l_run = l_run * alpha + ls;
-        m_run = m_new;
-        *reinterpret_cast<f32x4*>(sP + c * 16 + 4 * kb) = pr;
-        if (kb == 0) sA[c] = alpha;
-        lds_sync_wave();                                    // written and read by this wavefront only
-        __builtin_amdgcn_wave_barrier();
-        float v[16][DPL];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) widen_v(vraw[j], v[j]);
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            if (rr < nrows) {                               // wavefront-uniform
-                const float a = sA[rr];
-                const f32x4* prow = reinterpret_cast<const f32x4*>(sP + rr * 16);
-#pragma unroll
-                for (int e = 0; e < DPL; ++e) o[rr][e] *= a;
-#pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    const f32x4 p4 = prow[k4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int e = 0; e < DPL; ++e) o[rr][e] += p4[r] * v[4 * k4 + r][e];
-                }
-            }
-        }
-        lds_sync_wave();
-        __builtin_amdgcn_wave_barrier();                    // the next tile overwrites the probabilities
-#pragma unroll
-        for (int st = 0; st < STEPS; ++st) kreg[st] = kreg_n[st];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) vraw[j] = vraw_n[j];
     }
-    }
-    // ---- the wavefronts' results meet in LDS
-    if (kb == 0) { sML[(wave * 16 + c) * 2] = m_run; sML[(wave * 16 + c) * 2 + 1] = l_run; }
-#pragma unroll
-    for (int rr = 0; rr < 16; ++rr)
-#pragma unroll
-        for (int e = 0; e < DPL; ++e) sO[(wave * 16 + rr) * D + DPL * lane + e] = o[rr][e];
     __syncthreads();
-    float* obase = P.out + ((size_t)seq * P.rows * P.nq + h) * D;
-    for (int x = tid; x < nrows * D; x += GA_THREADS) {
-        const int rr = x / D, dd = x - rr * D;
-        float M = -INFINITY;
+    BRegs<float, 1> bq[STEPS];
 #pragma unroll
-        for (int w = 0; w < GA_WAVES; ++w) M = fmaxf(M, sML[(w * 16 + rr) * 2]);
-        float num = 0.f, den = 0.f;
+    for (int t = 0; t < STEPS; ++t) bq[t].h[0] = ld16(smem + qt * QAREA + (t * 64 + lane) * 16);
+    __syncthreads();
+
+    const float scale = P.inv_sqrt_d * 1.4426950408889634f;   // scores in units of ln 2
+    float m_run = -INFINITY, l_run = 0.f;                   // of this lane's query: the reference (the same in its four lanes), the lane's own sum
+    f32x4 o[D / 16];                                        // O^T: o[4 v + e][i] is column 64 v + 16 kb + 4 i + e of this lane's query
 #pragma unroll
-        for (int w = 0; w < GA_WAVES; ++w) {
-            const float mw = sML[(w * 16 + rr) * 2];
-            const float f = mw > -INFINITY ? expf(mw - M) : 0.f;
-            num += sO[(w * 16 + rr) * D + dd] * f;
-            den += sML[(w * 16 + rr) * 2 + 1] * f;
+    for (int j = 0; j < D / 16; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    stage_store(0, st);
+    st = st1;
+    __syncthreads();
+    for (int t = 0; t < n_stages; ++t) {
+        if (t + 1 < n_stages) stage_store(t + 1, st);
+        if (t + 2 < n_stages) stage_load(t + 2, st);
+        // this wavefront's 16 keys: first token / layout row; of the own rows the 16 of the tile itself and, where its first
+        // row is not the first of its group, the 16 before
+        const bool real = t < n_real;
+        const int unit = 2 * (real ? t : t - n_real) + kh, first = 16 * unit + (real ? 0 : R0 - 16);
+        const bool busy = active & (real ? first <= wg1 : (unit == qt + 1) | ((unit == qt) & (wg0 * K1 != r0)));
+        if (busy) {
+            const char* kt = smem + (t & 1) * BUF + 16 * kh * KSTR + c * KSTR + kb * 16;
+            const char* vt = smem + (t & 1) * BUF + KBUF + (16 * kh + 4 * kb) * VSTR + c * 16;
+            f32x4 acc[2][1] = {{f32x4{0.f, 0.f, 0.f, 0.f}}, {f32x4{0.f, 0.f, 0.f, 0.f}}};   // (two shorter sums: less rounding, no MFMA waits for the one before)
+#pragma unroll
+            for (int s = 0; s < STEPS; s += 2) {
+                mma_step<float, 1>(ld16(kt + 64 * s), bq[s], acc[0]);
+                mma_step<float, 1>(ld16(kt + 64 * s + 64), bq[s + 1], acc[1]);
+            }
+            f32x4 sc = (acc[0][0] + acc[1][0]) * scale;
+            if (!real | (first + 15 > wg0)) {
+                const int lo = real ? 0 : qg * K1 + 1 - first - 4 * kb, hi = (real ? qg : qrow) - first - 4 * kb;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sc[e] = (e >= lo && e <= hi) ? sc[e] : -INFINITY;
+            }
+            const float mt = quad_rows_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+            const bool moved = mt > m_run + GA_LAZY;        // (the reference follows the maximum in steps of at least GA_LAZY)
+            if (__any(moved)) {
+                const float m_new = moved ? mt : m_run;
+                const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
+                l_run *= alpha;
+                m_run = m_new;
+#pragma unroll
+                for (int j = 0; j < D / 16; ++j) o[j] *= alpha;
+            }
+            const float m_use = m_run > -INFINITY ? m_run : 0.f;   // (no visible key yet: every exponent is -inf)
+            f32x4 pr;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) pr[e] = __builtin_amdgcn_exp2f(sc[e] - m_use);
+            l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const f32x4 vv = *reinterpret_cast<const f32x4*>(vt + i * VSTR + 256 * v);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[4 * v + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], pr[i], o[4 * v + e], 0, 0, 0);
+                }
         }
-        obase[(size_t)(r0 + rr) * P.nq * D + dd] = num / den;   // (every row sees at least its own real token: den > 0)
+        __syncthreads();
+    }
+
+    // ---- the two wavefronts of a tile meet; the first writes the rows
+    l_run = quad_rows_sum(l_run);
+    if (kh == 1) {
+        *reinterpret_cast<float2*>(smem + OFF_ML + (qt * 64 + lane) * 8) = make_float2(m_run, l_run);
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) *reinterpret_cast<f32x4*>(smem + qt * QAREA + (j * 64 + lane) * 16) = o[j];
+    }
+    __syncthreads();
+    if (kh == 0 && active) {
+        const float2 ml = *reinterpret_cast<const float2*>(smem + OFF_ML + (qt * 64 + lane) * 8);
+        const float M = fmaxf(m_run, ml.x);                 // (this wavefront had the first token: finite)
+        const float f0 = __builtin_amdgcn_exp2f(m_run - M), f1 = __builtin_amdgcn_exp2f(ml.x - M), den = l_run * f0 + ml.y * f1;
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) o[j] = (o[j] * f0 + *reinterpret_cast<const f32x4*>(smem + qt * QAREA + (j * 64 + lane) * 16) * f1) / den;
+        if (r0 + c < P.rows) {
+            float* orow = P.out + (((size_t)seq * P.rows + r0 + c) * P.nq + h) * D + 16 * kb;
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(orow + 64 * v + 4 * i) = f32x4{o[4 * v][i], o[4 * v + 1][i], o[4 * v + 2][i], o[4 * v + 3][i]};
+        }
     }
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 values, 16-row tiles (the smallest calls).  A workgroup takes four adjacent query tiles, one per wavefront, and walks the key tiles of real
+// bf16 values, 16-row tiles (the smallest calls).  A query tile is a whole number of parallel groups (as many as fit into
+// 16 rows), so the [MASK] tokens of its groups all lie inside its own rows.  A workgroup takes four adjacent query tiles, one per wavefront, and walks the key tiles of real
 // tokens two at a time; the pair's K and V rows are brought in once for all four wavefronts.
 //
 // Loads are laid out for the texture unit, which handles a load in units of four lanes: four adjacent lanes read
@@ -989,7 +983,7 @@ int launch(const GaParams& P, hipStream_t s) {
         }
     } else {
         launch_rope<WT, D, true>(P, s);
-        hipLaunchKernelGGL((ga_attn_f32_kernel<D>), dim3(P.ntiles, P.nq, P.seqs), dim3(GA_THREADS), 0, s, P);
+        hipLaunchKernelGGL((ga_attn_f32_kernel<D>), dim3((unsigned)((P.rows + GF_ROWS - 1) / GF_ROWS) * P.nq, 1, P.seqs), dim3(GF_THREADS), 0, s, P);
     }
     return hipGetLastError() == hipSuccess ? PS_OK : PS_ERR_DEVICE;
 }

@@ -77,6 +77,14 @@ def test_blocks_of_128_rows_at_their_edges(seqs, T, k, nq, nkv, d):
     _case(seqs, T, k, nq, nkv, d, "bf16", 100 + T + k)
 
 
+@pytest.mark.parametrize("seqs,T,k,nq,nkv,d", [
+    (1, 64, 0, 2, 1, 64), (1, 65, 0, 1, 1, 128),                  # k = 0: exactly 1 and 2 blocks of 64 rows; 2 and 3 stages of 32 keys
+    (1, 33, 1, 2, 2, 64), (2, 43, 2, 3, 1, 64),                   # blocks that start inside a group; a query tile without rows
+    (1, 13, 4, 2, 2, 128), (1, 40, 10, 2, 1, 64), (3, 17, 15, 2, 2, 64)])
+def test_float32_blocks_of_64_rows_at_their_edges(seqs, T, k, nq, nkv, d):
+    _case(seqs, T, k, nq, nkv, d, "f32", 200 + T + k)
+
+
 def test_the_error_is_the_rounding_of_the_rotated_keys():
     """The tolerance above is spent on keys that round the other way after a float32 rotation (the kernel's) than
     after a float64 rotation (the oracle's).  With the keys rotated in float32 on the CPU, as the kernel's key
