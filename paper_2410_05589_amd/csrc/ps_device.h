@@ -366,6 +366,7 @@ __device__ __forceinline__ u64 row_max_u64(u64 v) {
 // over LPR = 64 (the wavefront) or 16 (a row) lanes
 template <int LPR> __device__ __forceinline__ float grp_sum(float v) { if constexpr (LPR == 64) return wave_sum(v); else return row_sum(v); }
 template <int LPR> __device__ __forceinline__ float grp_max(float v) { if constexpr (LPR == 64) return wave_max(v); else return row_max(v); }
+template <int LPR> __device__ __forceinline__ unsigned grp_max_u32(unsigned v) { if constexpr (LPR == 64) return wave_max_u32(v); else return row_max_u32(v); }
 template <int LPR> __device__ __forceinline__ u64 grp_max_u64(u64 v) { if constexpr (LPR == 64) return wave_max_u64(v); else return row_max_u64(v); }
 
 // ---- top-k keys: (logit, id) packed so that unsigned comparison orders by larger logit first,
@@ -380,6 +381,56 @@ __device__ __forceinline__ float key_value(u64 k) {
     return __uint_as_float(ord ^ ((ord >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
 __device__ __forceinline__ int key_id(u64 k) { return 0x7FFFFFFF - (int)(unsigned)k; }
+
+// Merging sorted lists, one per lane of a group of LPR: is this lane's head the largest of the group?  One lane says yes, or
+// none if all heads are 0 ("none"; top = 0 then).  One reduction of the high words (the logits); only where several lanes
+// hold the largest logit a second one, of the low words (the ids), decides.  The winner stores its head and moves its
+// list up, so a round has no broadcast of the winner and no search: with two reductions of 64-bit keys and a search for
+// the largest key below the previous winner in every lane a round was 0.3 us.
+template <int LPR>
+__device__ __forceinline__ bool grp_head(u64 key, unsigned& top) {
+    const unsigned hi = (unsigned)(key >> 32);
+    top = grp_max_u32<LPR>(hi);
+    bool win = hi == top && top != 0u;
+    const u64 b = __ballot(win);
+    bool several;
+    if constexpr (LPR == 64) {
+        several = (b & (b - 1)) != 0;
+    } else {
+        const unsigned row = (unsigned)(b >> (threadIdx.x & 48)) & 0xFFFFu;
+        several = __any((row & (row - 1)) != 0u);
+    }
+    if (several) {
+        const unsigned lo = grp_max_u32<LPR>(win ? (unsigned)key : 0u);
+        win = win && (unsigned)key == lo;
+    }
+    return win;
+}
+// the head leaves the list; "none" comes in at the end
+template <int N>
+__device__ __forceinline__ void list_up(u64 (&keys)[N]) {
+#pragma unroll
+    for (int i = 0; i + 1 < N; ++i) keys[i] = keys[i + 1];
+    keys[N - 1] = 0;
+}
+// largest first (Batcher's odd-even merge sort; N a power of two)
+template <int N>
+__device__ __forceinline__ void list_sort(u64 (&keys)[N]) {
+#pragma unroll
+    for (int p = 1; p < N; p *= 2)
+#pragma unroll
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int j = k % p; j + k < N; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+                        const u64 a = keys[i + j], b = keys[i + j + k];
+                        const bool swap = a < b;
+                        keys[i + j] = swap ? b : a;
+                        keys[i + j + k] = swap ? a : b;
+                    }
+}
 
 // The draw of the sampling epilogue (Algorithm 1's draft line samples from the draft distributions): the
 // Gumbel-max construction, token = argmax_i (z_i + g_i) with g_i = -log(-log(u_i)), which is an exact sample of
@@ -907,13 +958,12 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
 
 // Softmax statistics and top-k of the logits a workgroup holds in LDS (s_lm[local tile][row][16]) for its
 // vocabulary tiles: per output row the maximum, the sum of exponentials against it and the topk largest keys
-// in order go to lm_part as tagged data.  LPR lanes share a row; the keys are unique, so "the largest key below
-// the previous winner" enumerates them in order.
-template <int LPR>
+// in order go to lm_part as tagged data.  LPR lanes share a row, a lane sorts its EPL keys (LPR * EPL >= the
+// workgroup's entries of a row), and the lanes' lists are merged head by head.
+template <int LPR, int EPL>
 __device__ __forceinline__ void lm_local_stats(const StepParams& P, const PhaseDesc& D, int j, int rows, const float* s_lm,
                                                int wave, int lane, int sl_log, int SL) {
     constexpr int GPW = 64 / LPR;               // rows a wavefront works on at a time
-    constexpr int EPL = LPR == 64 ? 8 : 16;     // elements per lane kept in registers (more: re-read from LDS)
     const int n_el = D.rounds * SL * 16;
     const int li = lane & (LPR - 1), grp = lane / LPR;
     const int topk = P.topk;
@@ -924,6 +974,62 @@ __device__ __forceinline__ void lm_local_stats(const StepParams& P, const PhaseD
         const int mm = m0 + grp * PS_WAVES;
         const bool live = mm < rows;
         const int m = live ? mm : m0;           // lanes without a row of their own repeat the wavefront's first (and store nothing)
+        u64 keys[EPL];
+        float v[EPL], mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+            const int x = li + LPR * i, lt = x >> 4;
+            v[i] = x < n_el ? s_lm[(lt * rows + m) * 16 + (x & 15)] : -INFINITY;
+            keys[i] = 0;
+            if (v[i] > -INFINITY) {
+                keys[i] = make_key(v[i], 16 * tile_index(D, lt >> sl_log, lt & (SL - 1), j) + (x & 15));
+                mx = fmaxf(mx, v[i]);
+            }
+        }
+        mx = grp_max<LPR>(mx);
+        float se = 0.f;
+        if (mx > -INFINITY) {
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) se += expf(v[i] - mx);
+        }
+        se = grp_sum<LPR>(se);
+        const unsigned obase = (unsigned)((j * rows + m) * stride);
+        if (live && li < 2) ll_st1(rl, obase + li, li ? se : mx, seq);
+        if (P.sample_ids) {   // the workgroup's best perturbed logit (see gumbel_of)
+            u64 gbest = 0;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i)
+                if (keys[i]) {
+                    const int id = key_id(keys[i]);
+                    const u64 kx = make_key(v[i] + gumbel_of(P, m, id), id);
+                    gbest = kx > gbest ? kx : gbest;
+                }
+            gbest = grp_max_u64<LPR>(gbest);
+            if (live && li < 2)
+                ll_st1(rl, obase + 2 + 2 * topk + li, __uint_as_float(li ? (unsigned)(gbest >> 32) : (unsigned)gbest), seq);
+        }
+        list_sort(keys);
+        for (int t = 0; t < topk; ++t) {
+            unsigned top;
+            const bool win = grp_head<LPR>(keys[0], top);
+            if (live && (win || (top == 0u && li == 0)))   // (all lists exhausted: this and every later entry is "none")
+                coh_st16(rl, (obase + 2 + 2 * t) * 8, u32x4{(unsigned)keys[0], seq, (unsigned)(keys[0] >> 32), seq});
+            if (win) list_up(keys);
+        }
+    }
+}
+// The same for a workgroup with more entries per row than 64 lanes hold in lists: the keys are unique, so "the largest
+// key below the previous winner" enumerates them in order.
+__device__ __forceinline__ void lm_local_stats_long(const StepParams& P, const PhaseDesc& D, int j, int rows, const float* s_lm,
+                                               int wave, int lane, int sl_log, int SL) {
+    constexpr int LPR = 64, EPL = 8;            // elements per lane kept in registers (the others are re-read from LDS)
+    const int n_el = D.rounds * SL * 16;
+    const int li = lane;
+    const int topk = P.topk;
+    const rsrc_t rl = make_rsrc(P.lm_part);
+    const unsigned stride = 4 + 2 * topk;       // tagged elements: max, sum exp, topk keys (low, high word), the draw's key
+    const unsigned seq = ps_seq();
+    for (int m = wave; m < rows; m += PS_WAVES) {
         u64 keys[EPL];
         float mx = -INFINITY;
 #pragma unroll
@@ -944,7 +1050,7 @@ __device__ __forceinline__ void lm_local_stats(const StepParams& P, const PhaseD
             for (int x = li; x < n_el; x += LPR) se += expf(s_lm[((x >> 4) * rows + m) * 16 + (x & 15)] - mx);
         se = grp_sum<LPR>(se);
         const unsigned obase = (unsigned)((j * rows + m) * stride);
-        if (live && li < 2) ll_st1(rl, obase + li, li ? se : mx, seq);
+        if (li < 2) ll_st1(rl, obase + li, li ? se : mx, seq);
         const int nepl = min(EPL, (n_el + LPR - 1) / LPR);   // registers per lane that hold elements
         u64 prev = ~0ull;
         for (int t = 0; t < topk; ++t) {
@@ -960,7 +1066,7 @@ __device__ __forceinline__ void lm_local_stats(const StepParams& P, const PhaseD
                 if (kx < prev && kx > best) best = kx;
             }
             best = grp_max_u64<LPR>(best);
-            if (live && li < 2)
+            if (li < 2)
                 ll_st1(rl, obase + 2 + 2 * t + li, __uint_as_float(li ? (unsigned)(best >> 32) : (unsigned)best), seq);
             prev = best ? best : 0;   // 0: list exhausted, every later entry is "none"
         }
@@ -981,7 +1087,7 @@ __device__ __forceinline__ void lm_local_stats(const StepParams& P, const PhaseD
                 gbest = kx > gbest ? kx : gbest;
             }
             gbest = grp_max_u64<LPR>(gbest);
-            if (live && li < 2)
+            if (li < 2)
                 ll_st1(rl, obase + 2 + 2 * topk + li, __uint_as_float(li ? (unsigned)(gbest >> 32) : (unsigned)gbest), seq);
         }
     }
@@ -1203,10 +1309,15 @@ __device__ __forceinline__ void gemm_phase(const StepParams& P, int wg, int wave
     if (ph == PH_LMHEAD) {
         // per-workgroup softmax statistics and top-k over the logits held in LDS: a whole wavefront takes a
         // row; with more rows than wavefronts 16 lanes do (four rows per wavefront at a time) as long as a
-        // lane's share of the row's logits fits its registers
+        // lane's share of the row's logits fits its registers.  Lists as short as the share allows: what is
+        // sorted and moved up in vain costs as much as the rest
         __syncthreads();
-        if (rows > PS_WAVES && D.rounds * SL * 16 <= 16 * 16) lm_local_stats<16>(P, D, j, rows, s_lm, wave, lane, sl_log, SL);
-        else lm_local_stats<64>(P, D, j, rows, s_lm, wave, lane, sl_log, SL);
+        const int n_el = D.rounds * SL * 16;
+        if (rows > PS_WAVES && n_el <= 16 * 8) lm_local_stats<16, 8>(P, D, j, rows, s_lm, wave, lane, sl_log, SL);
+        else if (rows > PS_WAVES && n_el <= 16 * 16) lm_local_stats<16, 16>(P, D, j, rows, s_lm, wave, lane, sl_log, SL);
+        else if (n_el <= 64 * 2) lm_local_stats<64, 2>(P, D, j, rows, s_lm, wave, lane, sl_log, SL);
+        else if (n_el <= 64 * 8) lm_local_stats<64, 8>(P, D, j, rows, s_lm, wave, lane, sl_log, SL);
+        else lm_local_stats_long(P, D, j, rows, s_lm, wave, lane, sl_log, SL);
     }
     stamp(P, wg, SB + 5);
 }
@@ -2296,7 +2407,6 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
 // LM-head merge of one output row by one workgroup.  Thread p fetches workgroup p's statistics
 // of the row (max, sum of exponentials, its sorted top-k keys) in one round of loads; every
 // wavefront merges the lists of its 64 threads into a sorted top-k, wavefront 0 merges those.
-// Keys are unique, so "the largest key below the previous winner" enumerates them in order.
 // sk: LDS scratch of PS_MERGE_BYTES.
 // ------------------------------------------------------------------------------------------
 #define PS_MAX_TOPK 32
@@ -2356,20 +2466,19 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
         const u64 wg_best = wave_max_u64(gkey);
         if (lane == 0) sg[wave] = wg_best;
     }
-    u64 prev = ~0ull;
     for (int t = 0; t < topk; ++t) {
-        u64 best = 0;
+        unsigned top;
+        const bool win = grp_head<64>(keys[0], top);
+        if (win || (top == 0u && lane == 0)) sk[wave * PS_MAX_TOPK + t] = keys[0];   // ("none": all lists are exhausted)
+        if (win) {
 #pragma unroll
-        for (int i0 = 0; i0 < PS_MAX_TOPK; i0 += KB) {
-            if (i0 < topk) {   // entries beyond topk are "none"
+            for (int i0 = 0; i0 < PS_MAX_TOPK; i0 += KB) {
+                if (i0 < topk) {                           // (entries beyond topk are "none")
 #pragma unroll
-                for (int i = i0; i < i0 + KB; ++i)
-                    if (keys[i] < prev && keys[i] > best) best = keys[i];
+                    for (int i = i0; i < i0 + KB; ++i) keys[i] = i + 1 < PS_MAX_TOPK ? keys[i + 1] : 0;
+                }
             }
         }
-        best = wave_max_u64(best);
-        if (lane == 0) sk[wave * PS_MAX_TOPK + t] = best;
-        prev = best;                                       // 0: exhausted, every later entry is "none"
     }
     stamp(P, blockIdx.x, 43);
     __syncthreads();
@@ -2396,26 +2505,22 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
             P.sample_ids[m] = (gave_up || !best) ? -1 : id;
             if (P.sample_p) P.sample_p[m] = (gave_up || !best) ? 0.f : expf(key_value(best) - gumbel_of(P, m, id) - lse);
         }
-        // PS_WAVES sorted lists of topk keys: 4 candidates per lane
-        constexpr int CPL = PS_WAVES * PS_MAX_TOPK / 64;
+        // PS_WAVES sorted lists of topk keys: four consecutive entries of a list per lane
+        constexpr int CPL = PS_WAVES * PS_MAX_TOPK / 64, LPL = PS_MAX_TOPK / CPL;
         u64 cand[CPL];
 #pragma unroll
         for (int i = 0; i < CPL; ++i) {
-            const int x = lane + 64 * i, w = x / PS_MAX_TOPK, t = x - w * PS_MAX_TOPK;
-            cand[i] = t < topk ? sk[x] : 0;
+            const int t = CPL * (lane % LPL) + i;
+            cand[i] = t < topk ? sk[(lane / LPL) * PS_MAX_TOPK + t] : 0;
         }
-        u64 prev2 = ~0ull;
         for (int t = 0; t < topk; ++t) {
-            u64 best = 0;
-#pragma unroll
-            for (int i = 0; i < CPL; ++i)
-                if (cand[i] < prev2 && cand[i] > best) best = cand[i];
-            best = wave_max_u64(best);
-            if (lane == 0) {
-                P.top_ids[(size_t)m * topk + t] = gave_up ? -1 : (best ? key_id(best) : 0x7FFFFFFF);
-                P.top_p[(size_t)m * topk + t] = (best && !gave_up) ? expf(key_value(best) - lse) : 0.f;
+            unsigned top;
+            const bool win = grp_head<64>(cand[0], top);
+            if (win || (top == 0u && lane == 0)) {
+                P.top_ids[(size_t)m * topk + t] = gave_up ? -1 : (win ? key_id(cand[0]) : 0x7FFFFFFF);
+                P.top_p[(size_t)m * topk + t] = (win && !gave_up) ? expf(key_value(cand[0]) - lse) : 0.f;
             }
-            prev2 = best;
+            if (win) list_up(cand);
         }
         stamp(P, blockIdx.x, 56);
     }
