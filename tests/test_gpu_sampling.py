@@ -1,5 +1,7 @@
 """GPU parity of the sampling epilogue (temperature, the in-kernel draw, lengths kept on the device) through
 the C ABI against the CPU oracle."""
+import dataclasses
+
 import numpy as np
 import pytest
 from scipy import stats
@@ -9,7 +11,7 @@ from oracle import sampling as smp
 from paper_2410_05589_amd import binding as B
 from paper_2410_05589_amd import inputs
 from paper_2410_05589_amd.configs import WORKLOADS, Workload, small_shape
-from tests.gpu_util import compare_with_oracle
+from tests.gpu_util import compare_with_oracle, run_gpu_step
 
 pytestmark = pytest.mark.gpu
 
@@ -177,3 +179,26 @@ def test_lengths_on_the_device_let_a_replayed_graph_advance():
         cur += n_new
     assert d.last_status() == B.PS_OK
     d.close()
+
+
+@pytest.mark.parametrize("vocab,batch,topk", [
+    (2064, 3, 20), (2064, 1, 32),       # 16 lanes per row with lists of 8; 64 lanes with lists of 2
+    (50003, 3, 9), (50003, 1, 16),      # lists of 16; 64 lanes with lists of 8
+    (140000, 1, 4)])                    # more entries per workgroup than the lists hold
+def test_equal_logits_are_listed_in_order_of_their_ids(vocab, batch, topk):
+    """Rows of the LM head repeat (37 different ones), so every logit stands in many lanes, wavefronts and workgroups
+    with exactly the same value: the top-k must be the stable order of the step's own logits."""
+    print("vocab", vocab, "batch", batch, "topk", topk, flush=True)
+    shape = dataclasses.replace(WORKLOADS["c0"].shape, vocab=vocab)
+    wl = Workload("ties", shape, batch=batch, kv_len=(20,) * batch, n_new=1, k=4, topk=topk, seed=5)
+    w = inputs.make_weights(shape, wl.seed)
+    w["w_lm"] = np.ascontiguousarray(w["w_lm"][np.arange(vocab) % 37])
+    d = B.Drafter(shape, w, max_batch=batch, max_new=1, max_positions=20 + wl.m, max_topk=topk, k_max=4)
+    res = run_gpu_step(d, inputs.make_step_inputs(wl), 1, 4, topk)
+    d.close()
+    for b in range(batch):
+        for r in range(5):
+            order = np.argsort(-res["logits"][b, r], kind="stable")[:topk]
+            assert res["logits"][b, r][order[0]] == res["logits"][b, r][order[1]]
+            np.testing.assert_array_equal(res["top_ids"][b, r], order)
+            np.testing.assert_allclose(res["top_p"][b, r], res["probs"][b, r][order], rtol=1e-5)
