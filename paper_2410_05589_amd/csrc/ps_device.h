@@ -902,6 +902,17 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
 #pragma unroll
                     for (int h = 0; h < NL; ++h) ok = ok && sx_ok(raw[i][h]);
                 if (__all(ok) || !spin_again(P, spins)) break;   // produced earlier in this step: wait for it
+                // Not all there yet: until this thread's columns of one row are, only those are asked for (a tile's rows
+                // are stored together).  Everybody asking for whole panels again and again is traffic that the
+                // producers' own accesses queue behind: 1 .. 2.5 % of a step of the small shapes (H 256 and 512, where most
+                // workgroups only wait), nothing of the large ones'
+                if (!from_x) {
+                    const int r0 = min(rb, rows - 1), srow = PH == PH_LMHEAD ? lm_src_row(P, r0) : r0;
+                    for (;;) {
+                        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, kkc * 4, srow * ld * 4, PS_SC1);
+                        if (__all(sx_ok(x)) || !spin_again(P, spins)) break;
+                    }
+                }
             }
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
