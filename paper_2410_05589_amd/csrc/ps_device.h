@@ -2547,7 +2547,7 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
 // is only looked at when the kernel ends, so its round trip costs nothing.  step_read only
 // requests (thread 0 returns the number, the others 0); the persistent kernel hands the number to
 // its first phase, which stores it to LDS just before its first barrier: the first phase reads
-// only the step's inputs, so the counter's round trip hides behind the first activation loads.
+// only the step's inputs (but see PS_IN_FUSED there), so the counter's round trip hides behind the first activation loads.
 __device__ __forceinline__ unsigned step_read(const StepParams& P, bool count, unsigned& ticket) {
     unsigned seq = 0;
     ticket = 0xFFFFFFFFu;
@@ -2635,6 +2635,13 @@ __global__ void __launch_bounds__(PS_WG_THREADS, 1) fused_kernel(const StepParam
     const unsigned my_seq = step_read(P, false, ticket);
     kv_fill(P);                                  // (read after the first phase's barriers at the earliest)
     preload_weights(wb, first_stream(P, PH_QKV, wg, wave), lane * 16);
+    // With the input projection the first phase does read an exchange buffer, the projection's output, and needs the step's
+    // number to know which copy.  (Without this it took what the projection's kernel, which runs just before, had left at
+    // that place of the compute unit's LDS: right only as long as that kernel runs on every compute unit this one uses.)
+    if (P.in_mode == PS_IN_FUSED) {
+        if (threadIdx.x == 0) *(lds_u32*)(unsigned)PS_LDS_SEQ = my_seq;
+        __syncthreads();
+    }
     // (bf16 storage: the attention needs the registers; the output projection's first weight loads are
     // requested after it - a workgroup without attention work gets there at once)
     gemm_phase<WT, MT, PH_QKV>(P, wg, wave, smem, wb, Traits<WT>::BF ? P.ph[PH_OPROJ].wpack : first_stream(P, PH_OPROJ, wg, wave), my_seq);
