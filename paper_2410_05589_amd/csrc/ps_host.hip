@@ -465,6 +465,20 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
     return false;
 }
 
+// Workgroups of a step: one per compute unit, but five for every eight where the weights are so few that a compute unit's
+// share is below 48 KB and the rows fill at most two column tiles.  Such a step is a chain of hand-offs in which most
+// workgroups wait most of the time, and what they ask for while they wait is in the way of the others.  Measured on 256
+// compute units, us with 256 / 192 / 160 / 128 workgroups: H 512 bf16, 5 rows 48.6 / 46.6 / 42.1 / 43.5, 24 rows
+// 61.6 / 59.1 / 58.5 / 59.7, 48 rows 70.9 / 70.5 / 73.5 / 73.0, 64 rows 99.9 / 101.4 / 103.1 / 103.0; H 256 float32, 5 rows
+// 39.1 / 37.8 / 37.2 / 36.8; H 512 float32 (66 KB per compute unit), batch of 8: 95 / 106 / - / 116.
+static int step_workgroups(const ps_draft_config* c, int n_cu, bool fused, int rows) {
+    int T[PH_COUNT], Kt[PH_COUNT];
+    phase_dims(c, T, Kt);
+    size_t bytes = 0;
+    for (int ph = 0; ph <= PH_LMHEAD; ++ph) bytes += (size_t)T[ph] * Kt[ph] * 1024;
+    return fused && rows <= 32 && bytes < (size_t)n_cu * (48 * 1024) && n_cu >= 8 ? n_cu * 5 / 8 : n_cu;
+}
+
 // see ps_draft_debug.h
 extern "C" int ps_draft_debug_plan(const ps_draft_config* c, int batch, int n_new, int k, int all_rows, int n_cu, int lds_limit,
                                    int* out) {
@@ -627,6 +641,32 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
         P.kv_len[b] = a->kv_len[b];
         P.skip[b] = a->n_new_seq ? a->n_new - a->n_new_seq[b] : 0;
     }
+    // the GEMM phases' plans
+    const bool bf = c.dtype == PS_BF16;
+    P.r_magic = 0xFFFFFFFFu / (unsigned)P.R + 1u;
+    int T[PH_COUNT], Kt[PH_COUNT], K[PH_COUNT];
+    phase_dims(&c, T, Kt, K);
+    auto plan_phases = [&](int n) {
+        for (int ph = 0; ph < PH_COUNT; ++ph) {
+            if (T[ph] == 0) continue;                        // (no input projection in this configuration)
+            const int rows = ph == PH_LMHEAD ? P.Rtot : ph == PH_FC ? a->batch * a->n_new : P.Mtot;
+            // the persistent kernel runs every phase with the column tiles of the widest one
+            const int mt = ((ctx->fused && ph != PH_FC) ? P.Mtot + 15 : rows + 15) / 16;
+            if (!make_desc(&P.ph[ph], ph, T[ph], Kt[ph], K[ph], rows, mt, bf, n, ctx->plan_override[ph], ctx->lds_limit)) return false;
+        }
+        return true;
+    };
+    int nwg = step_workgroups(&c, ctx->n_cu, ctx->fused != 0, P.Mtot);
+    if (!plan_phases(nwg)) {
+        nwg = ctx->n_cu;
+        if (!plan_phases(nwg)) return PS_ERR_UNSUPPORTED;
+    }
+    for (int ph = 0; ph < PH_COUNT; ++ph) {
+        if (T[ph] == 0) continue;
+        P.ph[ph].wpack = ctx->wpack[ph];
+        P.ph[ph].frag = (float*)(ctx->act_base + ctx->off_frag[ph]);
+        P.ph[ph].ssq_frag = (float*)(ctx->act_base + ctx->off_ssqf[ph]);
+    }
     // attention work items: (sequence, kv head, block of ch keys)
     const int ra = (c.n_heads / c.n_kv_heads) * M;
     int ch = PS_ATTN_KEYS;
@@ -638,17 +678,17 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
         items += c.n_kv_heads * ((a->kv_len[b] + M + ch - 1) / ch);
         items_wo += c.n_kv_heads * ((a->kv_len[b] + ch - 1) / ch);
     }
-    bool sep = M <= 16 && (items_wo + ctx->n_cu - 1) / ctx->n_cu < (items + ctx->n_cu - 1) / ctx->n_cu;
+    bool sep = M <= 16 && (items_wo + nwg - 1) / nwg < (items + nwg - 1) / nwg;
     if (ctx->attn_sep_override >= 0 && M <= 16) sep = ctx->attn_sep_override != 0;
     if (sep) items = items_wo;
     const int tail = sep ? 0 : M;
     // Key blocks of twice the size (two groups of 16 keys per wavefront) when the workgroups still face
     // more than one round of work items and that way every one of them gets at most a single item
     int nk = 1;
-    if (items > ctx->n_cu && ra <= 16 && ps_attn_lds_bytes(c.head_dim, 2) <= ctx->lds_limit) {
+    if (items > nwg && ra <= 16 && ps_attn_lds_bytes(c.head_dim, 2) <= ctx->lds_limit) {
         int items2 = 0;
         for (int b = 0; b < a->batch; ++b) items2 += c.n_kv_heads * ((a->kv_len[b] + tail + 2 * ch - 1) / (2 * ch));
-        if (items2 <= ctx->n_cu) { nk = 2; ch *= 2; items = items2; }
+        if (items2 <= nwg) { nk = 2; ch *= 2; items = items2; }
     }
     P.attn_items = items; P.attn_single = ra <= 16; P.attn_sep = sep ? 1 : 0; P.attn_tail = tail; P.attn_nk = nk;
     const bool attn2 = c.dtype == PS_BF16;   // bf16 storage: attn_phase2 (ps_device.h)
@@ -659,33 +699,17 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
             if (sep || (a->kv_len[b] + tail + ch - 1) / ch > 1) mi += c.n_kv_heads * rt;
         P.attn_merge_items = mi;
         const int want = items > mi ? items : mi;
-        P.attn_nwg = want < ctx->n_cu ? want : ctx->n_cu;
+        P.attn_nwg = want < nwg ? want : nwg;
     }
     if (attn2) {
-        const Attn2Plan ap = plan_attn2(a->kv_len, a->batch, c.n_kv_heads, ra, M, ctx->n_cu, ctx->attn_nk_override);
+        const Attn2Plan ap = plan_attn2(a->kv_len, a->batch, c.n_kv_heads, ra, M, nwg, ctx->attn_nk_override);
         P.attn_ch_log = ap.ch_log; P.attn_npass = ap.npass; P.pass_magic = 0xFFFFFFFFu / (unsigned)ap.npass + 1u;
         P.attn_items = ap.items; P.attn_units = ap.items * ap.npass; P.attn_merge_items = ap.merge_items;
         P.attn_sep = 0; P.attn_tail = 0; P.attn_nk = 1;
         const int want = P.attn_units > ap.merge_items ? P.attn_units : ap.merge_items;
-        P.attn_nwg = want < ctx->n_cu ? want : ctx->n_cu;
+        P.attn_nwg = want < nwg ? want : nwg;
     }
 
-    const bool bf = c.dtype == PS_BF16;
-    const int nwg = ctx->n_cu;
-    P.r_magic = 0xFFFFFFFFu / (unsigned)P.R + 1u;
-    int T[PH_COUNT], Kt[PH_COUNT], K[PH_COUNT];
-    phase_dims(&c, T, Kt, K);
-    for (int ph = 0; ph < PH_COUNT; ++ph) {
-        if (T[ph] == 0) continue;                            // (no input projection in this configuration)
-        const int rows = ph == PH_LMHEAD ? P.Rtot : ph == PH_FC ? a->batch * a->n_new : P.Mtot;
-        // the persistent kernel runs every phase with the column tiles of the widest one
-        const int mt = ((ctx->fused && ph != PH_FC) ? P.Mtot + 15 : rows + 15) / 16;
-        if (!make_desc(&P.ph[ph], ph, T[ph], Kt[ph], K[ph], rows, mt, bf, nwg, ctx->plan_override[ph], ctx->lds_limit))
-            return PS_ERR_UNSUPPORTED;
-        P.ph[ph].wpack = ctx->wpack[ph];
-        P.ph[ph].frag = (float*)(ctx->act_base + ctx->off_frag[ph]);
-        P.ph[ph].ssq_frag = (float*)(ctx->act_base + ctx->off_ssqf[ph]);
-    }
     P.ph[PH_QKV].norm = 1; P.ph[PH_QKV].gain = P.g_in; P.ph[PH_QKV].src = nullptr; P.ph[PH_QKV].src_ld = P.H;
     P.ph[PH_OPROJ].src = P.o_buf; P.ph[PH_OPROJ].src_ld = P.QD;
     P.ph[PH_GATEUP].norm = 1; P.ph[PH_GATEUP].gain = P.g_post; P.ph[PH_GATEUP].src = P.y_buf; P.ph[PH_GATEUP].src_ld = P.H;

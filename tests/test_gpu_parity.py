@@ -160,6 +160,23 @@ def test_changing_shapes_on_one_context():
     d.close()
 
 
+@pytest.mark.parametrize("dtype,hidden,ffn", [("f32", 256, 704), ("bf16", 512, 1376)])
+def test_steps_with_fewer_and_with_all_workgroups_take_turns(dtype, hidden, ffn):
+    """Shapes with few weights: a step of up to 32 rows runs with fewer workgroups than one of more rows; both on one
+    context, at the line between them and in every order."""
+    shape = small_shape(dtype, hidden=hidden, n_heads=hidden // 64, n_kv_heads=hidden // 64, head_dim=64, ffn=ffn, vocab=2064)
+    w = inputs.make_weights(shape, 37)
+    d = _drafter(shape, w, max_batch=8, max_new=4, max_positions=400, k_max=4)
+    seq = [(1, 1, 4), (8, 4, 4), (1, 1, 4), (4, 4, 4), (4, 4, 4), (3, 4, 4), (8, 1, 4), (4, 4, 4), (8, 4, 4), (8, 4, 4), (1, 1, 0), (4, 4, 4)]   # rows 5, 64, 5, 32, 32, 24, 40, 32, 64, 64, 1, 32
+    for step, (batch, n_new, k) in enumerate(seq):
+        kv = tuple((37 * (b + 1) + 11 * step) % 300 for b in range(batch))
+        wl = Workload("turns", shape, batch=batch, kv_len=kv, n_new=n_new, k=k, topk=4, seed=200 + step)
+        inp = inputs.make_step_inputs(wl, kv_len=kv, n_new=n_new, k=k)
+        res = run_gpu_step(d, inp, n_new, k, 4)
+        print("step", step, (batch, n_new, k), compare_with_oracle(shape, res, oracle_step(shape, w, inp, n_new, k, 4), inp, n_new, k, 4), flush=True)
+    d.close()
+
+
 def test_maximum_rows_and_topk():
     # 8 sequences x 8 rows = 64 activation rows (the most the library takes), top-32, all rows decoded
     shape = small_shape("bf16", hidden=512, n_heads=8, n_kv_heads=4, head_dim=64, ffn=1376, vocab=3000)
