@@ -33,7 +33,7 @@ struct GaParams {
 // keys; gridDim.y workgroups share a position's rows.  ALL: the rows of every slot, to k_rot in the layout of k (a row (group,
 // slot) stands at group + slot).  Otherwise the real tokens' rows only, to k_rot as [seq][kv head][token][D]: a [MASK] key is
 // seen by its own group only, and ga_attn_wide_kernel rotates those while it stages them.  (A table kernel and a kernel over
-// all rows that reads the table back: 29 us at T 2048, k 4, 32 heads x 128, of which all but 9 go with the [MASK] rows' bytes.)
+// all rows that reads the table back: about 30 us at T 2048, k 4, 32 heads x 128; the real tokens only, as here: 9.8 us.)
 template <typename WT, int D, bool ALL>
 __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
     constexpr int ESZ = Traits<WT>::ESZ, Q4 = D / 8;       // groups of 4 pairs per head
@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
 //
 // Bound by the float32 matrix rate (32 MFMAs of 32 cycles per 16 x 16 tile at head_dim 64).  Before, P.V was FMA work against
 // probabilities broadcast from LDS, a workgroup took one tile of whole groups and every wavefront fetched its own operands:
-// 2 x T 300, k 3, 8 heads x 64: 43 -> 29 us; 4 x T 512, k 10, 16 / 4 heads x 64: 724 -> 300 us (float32 matrix rate: 185); T 1024,
+// whole calls, 2 x T 300, k 3, 8 heads x 64: 40.5 -> 26.8 us; 4 x T 512, k 10, 16 / 4 heads x 64: 724 -> 300 us (float32 matrix rate: 185); T 1024,
 // k 4, 32 heads x 128: 1047 -> 470 us.
 // ------------------------------------------------------------------------------------------
 constexpr int GF_THREADS = 512, GF_ROWS = 64;
@@ -239,7 +239,7 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
 #pragma unroll
             for (int v = 0; v < NV; ++v)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(orow + 64 * v + 4 * i) = f32x4{o[4 * v][i], o[4 * v + 1][i], o[4 * v + 2][i], o[4 * v + 3][i]};
+                for (int i = 0; i < 4; ++i) __builtin_nontemporal_store(f32x4{o[4 * v][i], o[4 * v + 1][i], o[4 * v + 2][i], o[4 * v + 3][i]}, reinterpret_cast<f32x4*>(orow + 64 * v + 4 * i));
         }
     }
 }
@@ -552,12 +552,16 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
 // tile ahead); V is transposed by the LDS unit on the way out (ds_read_b64_tr_b16: 16 lanes get 4 keys of one column each).
 // The scores of tile t + 1 are worked out beside the exponentials of tile t, so every wavefront has matrix and vector work
 // to offer at any time; two workgroups per compute unit (256 registers) are what the query and output registers allow.
-// Everything that a workgroup reads for the first time (table, query rows, own rows, first tiles) is requested at once.
+// Everything that a workgroup reads for the first time (table, query rows, own rows, first tiles) is requested at once.  The query
+// rows are read and the output rows are written once, past the caches (non-temporal): the L2 is left to the heads' keys and
+// values (T 2048, k 4: 349 -> 336 us; 4 x T 1024, k 8: 740 -> 707; T 203: 30.0 -> 27.3; the own rows read that way, too: 1 % slower,
+// the next workgroup reads 16 of them again).
 //
 // Bound by the matrix cores: 32 MFMAs of 32 cycles per tile and wavefront; the loop over the real tokens keeps them 80 %
 // busy (2560 cycles per tile with two wavefronts per SIMD), and the compute units run at 1.95 GHz meanwhile.  What is left is
 // a workgroup's start (its first rows come from memory: 16 k cycles at T 2048, k 4 of 121 k) and its own rows (14 k).
-// Against the 16-row kernel: T 2048, k 4, 32 heads x 128: 515 -> 347 us; 4 x T 1024, k 8, 32 / 8 heads: 1450 -> 735 us.
+// Whole calls, against the 16-row kernel and its three launches: T 2048, k 4, 32 heads x 128: 503 -> 365 us (472 TFLOP/s of
+// visible pairs, every product twice); 4 x T 1024, k 8, 32 / 8 heads: 1501 -> 752 us; T 203, k 5, 40 heads: 40.9 -> 26.0 us.
 // Tried: no scores ahead (other wavefront alone fills the gaps): 5 % slower; own rows as further tiles of the loop, rotated
 // between the barriers: 4 % (T 2048) and 12 % (4 x 1024, k 8) slower; raised wavefront priority in the matrix part, two
 // accumulators for the scores, four K operands requested ahead: no change.
@@ -635,8 +639,8 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
 #pragma unroll
         for (int i = 0; i < QI; ++i) {
             const char* a = src + (size_t)min(r0 + QPI * i + lane / PAIRS, r_last) * P.nq * D * 2;
-            qa[i] = ld16(a);
-            qb[i] = ld16(a + D);
+            qa[i] = ldg_stream16(a);
+            qb[i] = ldg_stream16(a + D);
         }
     }
     auto own_row = [&](int i) __attribute__((always_inline)) { return min(max(R0 - 16 + OPI * i + tid / PAIRS, 0), r_last); };
@@ -927,7 +931,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         for (int u = 0; u < PCS / 2; ++u) {
             const int rr = (64 / PCS) * u + lane / PCS, pc = lane % PCS;
             const f32x4 w = *reinterpret_cast<const f32x4*>(sO + (rr * PCS + (pc ^ (rr & (PCS - 1)))) * 16);
-            if (r0 + rr < P.rows) *reinterpret_cast<f32x4*>(obase + (size_t)(r0 + rr) * P.nq * D + 32 * j0 + 4 * pc) = w;
+            if (r0 + rr < P.rows) __builtin_nontemporal_store(w, reinterpret_cast<f32x4*>(obase + (size_t)(r0 + rr) * P.nq * D + 32 * j0 + 4 * pc));
         }
         lds_sync_wave();
         __builtin_amdgcn_wave_barrier();
@@ -972,7 +976,7 @@ int launch(const GaParams& P, hipStream_t s) {
         // The wide kernel, except where the real tokens' keys are a single stage and the groups' own rows are most of the work:
         // there the 16-row kernel, whose workgroups are half as long, is the faster one (us, both kernels and the keys'
         // rotation: T 30, k 4, 8 heads x 128: 13.4 against 13.7; T 16, k 10, 32 heads: 13.7 against 14.0; but T 30, k 1:
-        // 9.8 against 9.0; T 64, k 4, 40 heads: 17.7 against 15.6; T 2048, k 4, 32 heads: 515 against 347)
+        // 9.8 against 9.0; T 64, k 4, 40 heads: 17.7 against 15.6)
         const long long blocks = (long long)((P.rows + GW_ROWS - 1) / GW_ROWS) * P.nq * P.seqs;
         if (blocks > 0x7FFFFFFF || (P.T <= 32 && P.k >= 4)) {
             launch_rope<WT, D, true>(P, s);
