@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
     __syncthreads();
     if (kh == 0 && active) {
         const float2 ml = *reinterpret_cast<const float2*>(smem + OFF_ML + (qt * 64 + lane) * 8);
-        const float M = fmaxf(m_run, ml.x);                 // (this wavefront had the first token: finite)
+        const float M = fmaxf(m_run, ml.x);                 // (-inf only if no visible score is finite)
         const float f0 = __builtin_amdgcn_exp2f(m_run - M), f1 = __builtin_amdgcn_exp2f(ml.x - M), den = l_run * f0 + ml.y * f1;
 #pragma unroll
         for (int j = 0; j < D / 16; ++j) o[j] = (o[j] * f0 + *reinterpret_cast<const f32x4*>(smem + qt * QAREA + (j * 64 + lane) * 16) * f1) / den;
@@ -901,8 +901,8 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
             if (t >= whole_end) mask(s, 0, qg - 32 * t - 4 * half);
             follow(s);
             const f32x16 sn = stage_scores(t + 1);
-            // (every query sees the first tile's first key: m_run is finite)
-            accumulate(s, m_run, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
+            // (visible is not finite: the scores so far may all have overflowed to -inf)
+            accumulate(s, m_run > -INFINITY ? m_run : 0.f, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
             s = sn;
         }
         __syncthreads();

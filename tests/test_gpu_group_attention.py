@@ -85,6 +85,31 @@ def test_float32_blocks_of_64_rows_at_their_edges(seqs, T, k, nq, nkv, d):
     _case(seqs, T, k, nq, nkv, d, "f32", 200 + T + k)
 
 
+@pytest.mark.parametrize("dtype,k,d", [("bf16", 0, 128), ("bf16", 0, 64), ("bf16", 3, 128), ("f32", 0, 64)])
+def test_scores_that_overflow_before_a_row_sees_a_finite_one(dtype, k, d):
+    """The first 32 real tokens' keys lie opposite to every query and so far out that their scores are -inf in float32
+    (q.k = -1e40; in the pair of dimensions that the rotation turns least); from token 32 on all keys are ordinary.  Rows
+    that see an ordinary real token have a finite result, the oracle's (float64: the first 32 weigh exp(-1e39) = 0)."""
+    T, nq = 70, 2
+    print("case overflowing scores", dtype, "k", k, "d", d, flush=True)
+    inp = inputs.make_group_attention_inputs(31 + k, 1, T, k, nq, nq, d, dtype)
+    from oracle.ps_oracle import round_to_storage, widen
+    q, kk = widen(inp["q"], dtype), widen(inp["k"], dtype)
+    j = d // 2 - 1
+    q[...] = 0.0
+    q[..., j] = 1e20
+    kk[:, :32 * (k + 1)] = 0.0
+    kk[:, :32 * (k + 1), :, j] = -1e20
+    kk[:, 32 * (k + 1):, :, j] *= 1e-20
+    kk[:, 32 * (k + 1):, :, d - 1] *= 1e-20
+    inp["q"], inp["k"] = round_to_storage(q, dtype), round_to_storage(kk, dtype)
+    got = run_gpu(inp, 1, T, k, nq, nq, d, dtype)[0]
+    want = ga.group_attention(inp["q"][0], inp["k"][0], inp["v"][0], T, k, 10000.0, dtype)
+    rows = slice(32 * (k + 1), None)
+    assert np.isfinite(got[rows]).all()
+    assert np.abs(got[rows] - want[rows]).max() <= (2e-3 if dtype == "bf16" else 2e-5) * np.abs(want[rows]).max()
+
+
 def test_the_error_is_the_rounding_of_the_rotated_keys():
     """The tolerance above is spent on keys that round the other way after a float32 rotation (the kernel's) than
     after a float64 rotation (the oracle's).  With the keys rotated in float32 on the CPU, as the kernel's key
