@@ -752,7 +752,10 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         for (int t = 0; t < STEPS; ++t) ql[t] = __builtin_bit_cast(bf16x8, ld16(sQ + c * KSTR + 32 * t + 16 * half));
     }
 
-    float m_run = -INFINITY, l_run = 0.f;                   // of this lane's query: the reference of the exponentials (both halves agree), the half's sum
+    // of this lane's query: the reference of the exponentials (both halves agree) and the half's sum.  The reference starts at
+    // the lowest finite number, not at -inf: as long as a row has seen no key, or only keys whose scores overflowed to -inf,
+    // their exponentials against it are exp2(-inf) = 0, not exp2(-inf + inf)
+    float m_run = -3.402823466e38f, l_run = 0.f;
     f32x16 o[NJ];                                           // O^T: column 32 j + 8 (i / 4) + 4 half + i % 4 of this lane's query
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
@@ -787,7 +790,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         for (int i = 1; i < 16; ++i) mt = fmaxf(mt, x[i]);
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
         mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        const bool moved = mt > m_run + GA_LAZY;            // (also the first keys a row sees: m_run = -inf)
+        const bool moved = mt > m_run + GA_LAZY;            // (also the first finite scores of a row)
         if (__any(moved)) {
             const float m_new = moved ? mt : m_run;
             const float alpha = moved ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
@@ -871,7 +874,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
             f32x16 x = scores([&](int st) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, ld16(kt + (kro ^ (st << 5)))); });
             mask(x, qg * K1 + 1 - first - 4 * half, (before ? min(qrow, r0 - 1) : qrow) - first - 4 * half);
             follow(x);
-            accumulate(x, m_run > -INFINITY ? m_run : 0.f, [&](int j, int m2) __attribute__((always_inline)) {   // (a real token's row sees none)
+            accumulate(x, m_run, [&](int j, int m2) __attribute__((always_inline)) {
                 return transposed(kt + OFF_OV + m2 * 16 * 2 * D + (vro ^ (j << 6)), 8 * 2 * D);
             });
         }
@@ -901,8 +904,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
             if (t >= whole_end) mask(s, 0, qg - 32 * t - 4 * half);
             follow(s);
             const f32x16 sn = stage_scores(t + 1);
-            // (visible is not finite: the scores so far may all have overflowed to -inf)
-            accumulate(s, m_run > -INFINITY ? m_run : 0.f, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
+            accumulate(s, m_run, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
             s = sn;
         }
         __syncthreads();
