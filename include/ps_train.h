@@ -27,6 +27,8 @@ extern "C" {
  *   k, v       DEVICE [seqs, rows, n_kv_heads, head_dim], dtype (k before the rotary embedding)
  *   out        DEVICE [seqs, rows, n_heads, head_dim] float32, written: softmax(q k^T / sqrt(head_dim)) v per head
  *              under the mask above; query head h uses kv head h / (n_heads / n_kv_heads)
+ *              (a key or value row that the mask hides from a row does not enter that row's result, whatever it
+ *              holds: Inf and NaN in it stay with the rows that see it)
  *   workspace  DEVICE, at least ps_group_attention_workspace_bytes(args) bytes, 256-byte aligned, owned by the
  *              caller: the rotary table and the rotated k (dtype: keys are rounded to the storage type after
  *              the rotary embedding, as the inference path caches them; queries are rotated in float32 on chip)

@@ -69,6 +69,110 @@ __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
     }
 }
 
+// the largest of z, |a|, |b|, or NaN if there is one
+__device__ __forceinline__ float abs_max3(float z, float a, float b) {
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(z, __builtin_fabsf(a)), __builtin_fabsf(b));
+}
+
+// One output row by itself, from the keys and values that it sees and no others.  The kernels below multiply whole tiles: a
+// key that the mask hides has probability 0, and 0 times a value row that holds Inf or NaN would reach rows that may not see
+// it.  Nothing finite comes of a non-finite sum, so a row whose sum of exponentials is a number but whose output is not
+// finite is looked at here by its wavefront: if a column that is not finite has no visible value to blame, the row is worked
+// out again.  No call with finite values gets here: what it costs them is the look at the output registers.
+template <typename WT, int D>
+__device__ __forceinline__ void ga_row_alone(const GaParams& P, int seq, int h, int row, int lane) {
+    constexpr int ESZ = Traits<WT>::ESZ, CPL = D / 64;
+    const int K1 = P.k + 1, g = row / K1, n = g + 1 + (row - g * K1), hk = h / (P.nq / P.nkv);   // n visible keys, key i at position i
+    const size_t rs = (size_t)P.nkv * D * ESZ, head = ((size_t)seq * P.rows * P.nkv + hk) * D * ESZ;
+    const char* q = (const char*)P.q + (((size_t)seq * P.rows + row) * P.nq + h) * D * ESZ;
+    const float2* tq = P.table + (size_t)(row - g * P.k) * (D / 2);
+    auto key_off = [&](int i) __attribute__((always_inline)) { return (size_t)(unsigned)(i <= g ? i * K1 : g * K1 + i - g) * rs + head; };
+    auto value = [&](int i, int e) __attribute__((always_inline)) {   // column lane + 64 e of key i's value
+        const char* vp = (const char*)P.v + key_off(i) + (size_t)(lane + 64 * e) * ESZ;
+        if constexpr (Traits<WT>::BF) return bf16_to_f32(*(const uint16_t*)vp);
+        else return *(const float*)vp;
+    };
+    float* out = P.out + (((size_t)seq * P.rows + row) * P.nq + h) * D + lane;
+    bool open = false, bad[CPL];                            // columns of this lane that no visible value explains so far
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) {
+        bad[e] = !(fabsf(__hip_atomic_load(out + 64 * e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < INFINITY);
+        open |= bad[e];
+    }
+    for (int i0 = 0; i0 < n && __any(open); i0 += 8) {
+        open = false;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) {
+            float z = 0.f;
+#pragma unroll
+            for (int x = 0; x < 8; x += 2) z = abs_max3(z, value(min(i0 + x, n - 1), e), value(min(i0 + x + 1, n - 1), e));
+            bad[e] = bad[e] && z < INFINITY;
+            open |= bad[e];
+        }
+    }
+    if (!__any(open)) return;
+    float m = -INFINITY, l = 0.f, o[CPL];
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) o[e] = 0.f;
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const int i = min(i0 + lane, n - 1);
+        const char* kp = (const char*)P.k_ + key_off(i);
+        const float2* tk = P.table + (size_t)i * (D / 2);
+        float sc = 0.f;
+#pragma unroll 1
+        for (int j = 0; j < D / 2; j += 4) {
+            const f32x4 qa = load4<WT>(q + j * ESZ), qb = load4<WT>(q + (D / 2 + j) * ESZ);
+            const f32x4 ka = load4<WT>(kp + j * ESZ), kb = load4<WT>(kp + (D / 2 + j) * ESZ);
+            f32x4 ra, rb;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ra[e] = ka[e] * tk[j + e].x - kb[e] * tk[j + e].y;
+                rb[e] = kb[e] * tk[j + e].x + ka[e] * tk[j + e].y;
+            }
+            ra = store4<WT>(nullptr, ra, false);            // (rounded as cached keys are)
+            rb = store4<WT>(nullptr, rb, false);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float c = tq[j + e].x, s = tq[j + e].y;
+                sc += (qa[e] * c - qb[e] * s) * ra[e] + (qb[e] * c + qa[e] * s) * rb[e];
+            }
+        }
+        sc = i0 + lane < n ? sc * (P.inv_sqrt_d * 1.4426950408889634f) : -INFINITY;
+        const float m_new = fmaxf(m, wave_max(sc)), ref = m_new > -INFINITY ? m_new : 0.f;
+        const float alpha = __builtin_amdgcn_exp2f(m - ref), p = __builtin_amdgcn_exp2f(sc - ref);
+        l = l * alpha + wave_sum(p);
+        m = m_new;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) o[e] *= alpha;
+        for (int x = 0; x < min(64, n - i0); ++x) {
+            const float px = __shfl(p, x, 64);
+#pragma unroll
+            for (int e = 0; e < CPL; ++e) o[e] += px * value(i0 + x, e);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) out[64 * e] = o[e] / l;
+}
+// Rows r0 + (the bits of rows), which the wavefront has just stored as they came out.  A call, not inlined, that reads the
+// kernel's arguments again: what it needs would otherwise be kept in registers from the start (wide kernel at head_dim 128:
+// 16 spilled instead of none, whole calls 2 .. 14 % slower).  With finite scores and every value NaN a call takes two to four times
+// as long.
+typedef const __attribute__((address_space(4))) GaParams* ga_args_t;
+__device__ __forceinline__ ga_args_t ga_args() { return (ga_args_t)__builtin_amdgcn_kernarg_segment_ptr(); }
+template <typename WT, int D>
+__device__ __attribute__((noinline)) void ga_rows_alone(ga_args_t args, int seq, int h, int r0, unsigned rows, int lane) {
+    const u64 a = (u64)args;
+    const ga_args_t ua = (ga_args_t)((u64)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)(a >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((unsigned)a));
+    GaParams P;
+    __builtin_memcpy(&P, (const void*)ua, sizeof(P));
+    seq = __builtin_amdgcn_readfirstlane(seq);
+    h = __builtin_amdgcn_readfirstlane(h);
+    r0 = __builtin_amdgcn_readfirstlane(r0);
+    rows = __builtin_amdgcn_readfirstlane(rows);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");      // (those stores have arrived before other lanes write the same rows)
+    for (; rows; rows &= rows - 1) ga_row_alone<WT, D>(P, seq, h, r0 + __builtin_ctz(rows), lane);
+}
+
 // ------------------------------------------------------------------------------------------
 // float32 values.  A workgroup takes 64 consecutive layout rows, 16 per wavefront, with two wavefronts to every 16 rows
 // that share their keys; it walks the real tokens' keys 32 at a time, then the rows R0 - 16 .. R0 + 63, among which the
@@ -234,6 +338,10 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
         const float f0 = __builtin_amdgcn_exp2f(m_run - M), f1 = __builtin_amdgcn_exp2f(ml.x - M), den = l_run * f0 + ml.y * f1;
 #pragma unroll
         for (int j = 0; j < D / 16; ++j) o[j] = (o[j] * f0 + *reinterpret_cast<const f32x4*>(smem + qt * QAREA + (j * 64 + lane) * 16) * f1) / den;
+        float z = 0.f;
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) z = abs_max3(abs_max3(z, o[j][0], o[j][1]), o[j][2], o[j][3]);
+        const u64 b = __ballot(den == den && !(z < INFINITY) && r0 + c < P.rows);
         if (r0 + c < P.rows) {
             float* orow = P.out + (((size_t)seq * P.rows + r0 + c) * P.nq + h) * D + 16 * kb;
 #pragma unroll
@@ -241,6 +349,8 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
 #pragma unroll
                 for (int i = 0; i < 4; ++i) __builtin_nontemporal_store(f32x4{o[4 * v][i], o[4 * v + 1][i], o[4 * v + 2][i], o[4 * v + 3][i]}, reinterpret_cast<f32x4*>(orow + 64 * v + 4 * i));
         }
+        const unsigned alone = (unsigned)(b | b >> 16 | b >> 32 | b >> 48) & 0xFFFFu;
+        if (alone) ga_rows_alone<float, D>(ga_args(), seq, h, r0, alone, lane);
     }
 }
 
@@ -525,6 +635,17 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
     for (int j = 0; j < D / 16; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) sO[(4 * kb + r) * D + 16 * j + c] = oacc[j][r];
+    unsigned alone = 0;                                     // rows whose output is not finite
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float z = 0.f;
+#pragma unroll
+        for (int j = 0; j < D / 16; j += 2) z = abs_max3(z, oacc[j][r], oacc[j + 1][r]);
+        const u64 b = __ballot(!(z < INFINITY));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) alone |= (b >> (16 * i) & 0xFFFFu) ? 1u << (4 * i + r) : 0u;
+    }
+    alone &= (unsigned)__ballot(l_run == l_run) & ((1u << nrows) - 1u);
     lds_sync_wave();
     __builtin_amdgcn_wave_barrier();
     if (active) {
@@ -533,6 +654,7 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
             const int rr = x / D, dd = x - rr * D;
             obase[(size_t)(r0 + rr) * P.nq * D + dd] = sO[x] / sA[rr];   // (every row sees at least its own real token: the sum is > 0)
         }
+        if (alone) ga_rows_alone<WT, D>(ga_args(), seq, h, r0, alone, lane);
     }
 }
 
@@ -912,7 +1034,13 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
 
     // ---- output: OCOLS columns at a time by way of the wavefront's LDS area, divided by the rows' sums
     const auto lw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-    const float inv = 1.f / (__uint_as_float(lw[0]) + __uint_as_float(lw[1]));   // (every row sees at least its own real token)
+    const float den = __uint_as_float(lw[0]) + __uint_as_float(lw[1]), inv = 1.f / den;   // (every row sees at least its own real token)
+    float z[2] = {0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) z[i / 2 & 1] = abs_max3(z[i / 2 & 1], o[j][i], o[j][i + 1]);
+    const u64 zb = __ballot(den == den && !(z[0] < INFINITY && z[1] < INFINITY) && r0 + c < P.rows);
     constexpr int PCS = OCOLS / 4;                          // 16-byte pieces of a row
     char* const sO = smem + wave * (32 * OCOLS * 4);
     float* obase = P.out + ((size_t)seq * P.rows * P.nq + h) * D;
@@ -938,6 +1066,8 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         lds_sync_wave();
         __builtin_amdgcn_wave_barrier();
     }
+    const unsigned alone = (unsigned)(zb | zb >> 32);
+    if (alone) ga_rows_alone<bf16_t, D>(ga_args(), seq, h, r0, alone, lane);
 }
 
 size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }

@@ -110,6 +110,35 @@ def test_scores_that_overflow_before_a_row_sees_a_finite_one(dtype, k, d):
     assert np.abs(got[rows] - want[rows]).max() <= (2e-3 if dtype == "bf16" else 2e-5) * np.abs(want[rows]).max()
 
 
+@pytest.mark.parametrize("dtype,T,k,nq,nkv,d", [
+    ("bf16", 70, 4, 2, 1, 128), ("bf16", 70, 4, 2, 2, 64), ("bf16", 150, 0, 2, 2, 128), ("bf16", 40, 15, 2, 2, 64),
+    ("f32", 70, 4, 2, 1, 64), ("f32", 90, 0, 2, 2, 128), ("f32", 20, 15, 2, 2, 64),
+    ("bf16", 20, 5, 2, 2, 128), ("bf16", 32, 15, 2, 2, 64)])                    # (16-row tiles)
+def test_values_that_a_row_may_not_see_do_not_reach_it(dtype, T, k, nq, nkv, d):
+    """Value rows that hold Inf and NaN: two [MASK] tokens' and one real token's.  Rows that see none of them have the
+    oracle's result (their own keys and values only), the others are not finite."""
+    from oracle.ps_oracle import widen
+    print("case non-finite values", dtype, "T", T, "k", k, "d", d, flush=True)
+    inp = inputs.make_group_attention_inputs(61 + T + k, 1, T, k, nq, nkv, d, dtype)
+    want = ga.group_attention(inp["q"][0], inp["k"][0], inp["v"][0], T, k, 10000.0, dtype)
+    K1 = k + 1
+    poison = [((T // 4) * K1 + k // 2, np.inf), ((T // 2 + 1) * K1 + k, np.nan), ((2 * T // 3) * K1, -np.inf)]
+    v = widen(inp["v"], dtype)
+    for row, x in poison:
+        v[0, row] = x
+    if dtype == "bf16":
+        bits = v.astype(np.float32).view(np.uint32) >> np.uint32(16)
+        inp["v"] = bits.astype(np.uint16)
+    else:
+        inp["v"] = v.astype(np.float32)
+    got = run_gpu(inp, 1, T, k, nq, nkv, d, dtype)[0]
+    vis = ga.group_mask(T, k)
+    sees = vis[:, [row for row, _ in poison]].any(axis=1)
+    assert sees.any() and not sees.all()
+    assert not np.isfinite(got[sees]).any()
+    assert np.abs(got[~sees] - want[~sees]).max() <= (2e-3 if dtype == "bf16" else 2e-5) * np.abs(want).max()
+
+
 def test_the_error_is_the_rounding_of_the_rotated_keys():
     """The tolerance above is spent on keys that round the other way after a float32 rotation (the kernel's) than
     after a float64 rotation (the oracle's).  With the keys rotated in float32 on the CPU, as the kernel's key
