@@ -36,6 +36,14 @@ PS_API int ps_draft_debug_attn_plan(const ps_draft_config* config, int batch, co
                              int n_cu, int* out);
 
 /*
+ * Host only.  How ps_group_attention would launch a call (pointers are not looked at; its errors otherwise): out[8] =
+ * {kernel (0: float32, 1: bf16 with 16-row tiles, 2: bf16 with blocks of 128 rows), workgroups of the attention in x, y
+ * and z, threads of one, workgroups of the keys' rotation in x and y, threads of one}.
+ */
+struct ps_group_attn_args;
+PS_API int ps_train_debug_launch(const struct ps_group_attn_args* args, unsigned* out);
+
+/*
  * The following steps of ctx give up a wait for data of another workgroup after `spins` polls
  * (<= 0: the default, about a second).  With 1 every wait whose data is not there at the first
  * look is given up at once: the kernel still ends normally, the step's outputs are marked

@@ -11,11 +11,14 @@
 // Each describes its own scheme.
 #include "ps_device.h"
 #include "ps_train.h"
+#include "ps_draft_debug.h"
 
 namespace {
 
 constexpr int GA_THREADS = 256, GA_WAVES = GA_THREADS / 64;
 constexpr float GA_LAZY = 8.f;
+// A launch may have 2^32 - 1 work items in x at most: workgroups beyond GA_GRID_X go on in y (blockIdx.y is 0 but in huge calls)
+constexpr unsigned GA_GRID_X = 1u << 22;
 
 struct GaParams {
     int seqs, T, k, nq, nkv, rows, gpt, ntiles;   // gpt: groups per query tile
@@ -203,8 +206,10 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
     const int c = lane & 15, kb = lane >> 4, qt = wave & 3, kh = wave >> 2;   // query tile, half of the keys
     const int K1 = P.k + 1;
     auto group_of = [&](int row) __attribute__((always_inline)) { return P.k > 0 ? (int)__umulhi((unsigned)row, P.k1_magic) : row; };
-    const int blk = (P.rows + GF_ROWS - 1) / GF_ROWS - 1 - (int)(blockIdx.x / (unsigned)P.nq);   // the rows with the most keys start first
-    const int h = blockIdx.x % (unsigned)P.nq, seq = blockIdx.z, hk = h / (P.nq / P.nkv);
+    const unsigned wg = blockIdx.y * GA_GRID_X + blockIdx.x;
+    const int blk = (P.rows + GF_ROWS - 1) / GF_ROWS - 1 - (int)(wg / (unsigned)P.nq);   // the rows with the most keys start first
+    if (blk < 0) return;                                    // (beyond the last, in a launch of several rows of workgroups)
+    const int h = wg % (unsigned)P.nq, seq = blockIdx.z, hk = h / (P.nq / P.nkv);
     const int R0 = GF_ROWS * blk, r0 = R0 + 16 * qt;
     const bool active = r0 < P.rows;
     const int r_last = min(R0 + GF_ROWS, P.rows) - 1, g_last_wg = group_of(r_last);
@@ -728,8 +733,10 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     // Workgroups with the most keys start first; neighbours in the launch order, which go to different XCDs, take different
     // heads, so that (kv heads x sequences a multiple of 8) a kv head's rows are read through one L2
     const unsigned slots = (unsigned)P.nkv * P.seqs, heads = (unsigned)P.nq * P.seqs;
-    const int blk = (P.rows + GW_ROWS - 1) / GW_ROWS - 1 - (int)(blockIdx.x / heads);
-    const unsigned hs = blockIdx.x % heads, sl = hs % slots;
+    const unsigned wg = blockIdx.y * GA_GRID_X + blockIdx.x;
+    const int blk = (P.rows + GW_ROWS - 1) / GW_ROWS - 1 - (int)(wg / heads);
+    if (blk < 0) return;                                    // (beyond the last, in a launch of several rows of workgroups)
+    const unsigned hs = wg % heads, sl = hs % slots;
     const int seq = sl / P.nkv, hk = sl % P.nkv, h = hk * (P.nq / P.nkv) + hs / slots;
     const int R0 = GW_ROWS * blk, r0 = R0 + 32 * wave;
     const bool active = r0 < P.rows;
@@ -1094,34 +1101,66 @@ GaLayout layout(const ps_group_attn_args* a) {
     return L;
 }
 
-template <typename WT, int D, bool ALL>
-void launch_rope(const GaParams& P, hipStream_t s) {
-    // a workgroup per position; where positions are few, several (of at most one item per thread each) share one's rows
-    const long long items = (long long)P.seqs * P.nkv * (D / 8) * (ALL ? P.k + 1 : 1);
-    const int gy = (int)max(1LL, min((items + 255) / 256, 2048LL / (P.T + P.k)));
-    hipLaunchKernelGGL((ga_rope_kernel<WT, D, ALL>), dim3(P.T + P.k, gy), dim3(256), 0, s, P);
+// How a call is launched: the attention's kernel with its grid, and the rotation's
+enum { GA_F32 = 0, GA_TILES = 1, GA_WIDE = 2 };
+struct GaLaunch {
+    int kernel;
+    dim3 rope, attn;      // (256 threads each; GA_F32's attention: GF_THREADS)
+};
+dim3 grid_xy(long long workgroups, int z) {
+    const unsigned x = (unsigned)min(workgroups, (long long)GA_GRID_X);
+    return dim3(x, (unsigned)((workgroups + x - 1) / x), z);
 }
-
-template <typename WT, int D>
-int launch(const GaParams& P, hipStream_t s) {
-    if constexpr (Traits<WT>::BF) {
+int plan(const GaParams& P, int dtype, int head_dim, GaLaunch* L) {
+    const long long max_wg = 0x7FFFFFFF;                    // (the kernels number their workgroups in 31 bits)
+    if (dtype == PS_BF16) {
         // The wide kernel, except where the real tokens' keys are a single stage and the groups' own rows are most of the work:
         // there the 16-row kernel, whose workgroups are half as long, is the faster one (us, both kernels and the keys'
         // rotation: T 30, k 4, 8 heads x 128: 13.4 against 13.7; T 16, k 10, 32 heads: 13.7 against 14.0; but T 30, k 1:
         // 9.8 against 9.0; T 64, k 4, 40 heads: 17.7 against 15.6)
         const long long blocks = (long long)((P.rows + GW_ROWS - 1) / GW_ROWS) * P.nq * P.seqs;
-        if (blocks > 0x7FFFFFFF || (P.T <= 32 && P.k >= 4)) {
-            launch_rope<WT, D, true>(P, s);
-            hipLaunchKernelGGL((ga_attn_bf16_kernel<D>), dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs), dim3(GA_THREADS), 0, s, P);
+        L->kernel = blocks > max_wg || (P.T <= 32 && P.k >= 4) ? GA_TILES : GA_WIDE;
+        L->attn = L->kernel == GA_WIDE ? grid_xy(blocks, 1) : dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs);
+    } else {
+        const long long blocks = (long long)((P.rows + GF_ROWS - 1) / GF_ROWS) * P.nq;
+        if (blocks > max_wg) return PS_ERR_UNSUPPORTED;     // (its rows would be terabytes)
+        L->kernel = GA_F32;
+        L->attn = grid_xy(blocks, P.seqs);
+    }
+    // the rotation: a workgroup per position; where positions are few, several (of at most one item per thread each) share one's rows
+    const long long items = (long long)P.seqs * P.nkv * (head_dim / 8) * (L->kernel == GA_WIDE ? 1 : P.k + 1);
+    L->rope = dim3(P.T + P.k, (unsigned)max(1LL, min((items + 255) / 256, 2048LL / (P.T + P.k))));
+    return PS_OK;
+}
+
+template <typename WT, int D>
+int launch(const GaParams& P, const GaLaunch& L, hipStream_t s) {
+    if constexpr (Traits<WT>::BF) {
+        if (L.kernel == GA_WIDE) {
+            hipLaunchKernelGGL((ga_rope_kernel<WT, D, false>), L.rope, dim3(256), 0, s, P);
+            hipLaunchKernelGGL((ga_attn_wide_kernel<D>), L.attn, dim3(GA_THREADS), 0, s, P);
         } else {
-            launch_rope<WT, D, false>(P, s);
-            hipLaunchKernelGGL((ga_attn_wide_kernel<D>), dim3((unsigned)blocks), dim3(GA_THREADS), 0, s, P);
+            hipLaunchKernelGGL((ga_rope_kernel<WT, D, true>), L.rope, dim3(256), 0, s, P);
+            hipLaunchKernelGGL((ga_attn_bf16_kernel<D>), L.attn, dim3(GA_THREADS), 0, s, P);
         }
     } else {
-        launch_rope<WT, D, true>(P, s);
-        hipLaunchKernelGGL((ga_attn_f32_kernel<D>), dim3((unsigned)((P.rows + GF_ROWS - 1) / GF_ROWS) * P.nq, 1, P.seqs), dim3(GF_THREADS), 0, s, P);
+        hipLaunchKernelGGL((ga_rope_kernel<WT, D, true>), L.rope, dim3(256), 0, s, P);
+        hipLaunchKernelGGL((ga_attn_f32_kernel<D>), L.attn, dim3(GF_THREADS), 0, s, P);
     }
     return hipGetLastError() == hipSuccess ? PS_OK : PS_ERR_DEVICE;
+}
+
+// everything but the pointers
+GaParams shape(const ps_group_attn_args* a) {
+    GaParams P = {};
+    P.seqs = a->seqs; P.T = a->tokens; P.k = a->k; P.nq = a->n_heads; P.nkv = a->n_kv_heads;
+    P.rows = a->tokens * (a->k + 1);
+    P.gpt = 16 / (a->k + 1);
+    P.k1_magic = (unsigned)((0x100000000ull + a->k) / (unsigned)(a->k + 1));
+    P.ntiles = (a->tokens + P.gpt - 1) / P.gpt;
+    P.inv_sqrt_d = (float)(1.0 / sqrt((double)a->head_dim));
+    P.log_base = log((double)a->rope_base);
+    return P;
 }
 
 }   // namespace
@@ -1136,18 +1175,25 @@ extern "C" int ps_group_attention(const ps_group_attn_args* a, void* stream) {
     if (!a->q || !a->k_ || !a->v || !a->out || !a->workspace) return PS_ERR_NULL;
     const GaLayout L = layout(a);
     if (a->workspace_bytes < L.total || ((uintptr_t)a->workspace & 255)) return PS_ERR_WORKSPACE;
-    GaParams P;
-    P.seqs = a->seqs; P.T = a->tokens; P.k = a->k; P.nq = a->n_heads; P.nkv = a->n_kv_heads;
-    P.rows = a->tokens * (a->k + 1);
-    P.gpt = 16 / (a->k + 1);
-    P.k1_magic = (unsigned)((0x100000000ull + a->k) / (unsigned)(a->k + 1));
-    P.ntiles = (a->tokens + P.gpt - 1) / P.gpt;
-    P.inv_sqrt_d = (float)(1.0 / sqrt((double)a->head_dim));
+    GaParams P = shape(a);
+    GaLaunch G;
+    if (const int pl = plan(P, a->dtype, a->head_dim, &G)) return pl;
     P.q = a->q; P.k_ = a->k_; P.v = a->v; P.out = a->out;
     char* ws = (char*)a->workspace;
     P.table = (float2*)(ws + L.table); P.k_rot = ws + L.k_rot;
-    P.log_base = log((double)a->rope_base);
     hipStream_t s = (hipStream_t)stream;
-    if (a->dtype == PS_BF16) return a->head_dim == 128 ? launch<bf16_t, 128>(P, s) : launch<bf16_t, 64>(P, s);
-    return a->head_dim == 128 ? launch<float, 128>(P, s) : launch<float, 64>(P, s);
+    if (a->dtype == PS_BF16) return a->head_dim == 128 ? launch<bf16_t, 128>(P, G, s) : launch<bf16_t, 64>(P, G, s);
+    return a->head_dim == 128 ? launch<float, 128>(P, G, s) : launch<float, 64>(P, G, s);
+}
+
+// see ps_draft_debug.h
+extern "C" int ps_train_debug_launch(const ps_group_attn_args* a, unsigned* out) {
+    const int st = check(a);
+    if (st != PS_OK) return st;
+    if (!out) return PS_ERR_NULL;
+    GaLaunch G;
+    if (const int pl = plan(shape(a), a->dtype, a->head_dim, &G)) return pl;
+    const unsigned v[8] = {(unsigned)G.kernel, G.attn.x, G.attn.y, G.attn.z, (unsigned)(G.kernel == GA_F32 ? GF_THREADS : GA_THREADS), G.rope.x, G.rope.y, 256u};
+    for (int i = 0; i < 8; ++i) out[i] = v[i];
+    return PS_OK;
 }

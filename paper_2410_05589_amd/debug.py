@@ -8,7 +8,7 @@ PS_PLAN_FIELDS = 12
 PLAN_FIELD_NAMES = ("T", "Kt", "K", "rows", "kw_log", "s_log", "Gs", "per_round", "rounds", "piece_groups",
                     "npieces", "lds_bytes")
 EXPORTED_SYMBOLS = ("ps_draft_debug_plan", "ps_draft_debug_attn_plan", "ps_draft_debug_spin_limit", "ps_draft_debug_timeline",
-                    "ps_verify_debug_exchange", "ps_measure_stream_read", "ps_measure_copy")
+                    "ps_train_debug_launch", "ps_verify_debug_exchange", "ps_measure_stream_read", "ps_measure_copy")
 
 _ready = False
 
@@ -26,6 +26,8 @@ def _lib():
         lib.ps_draft_debug_spin_limit.argtypes = [ctypes.c_void_p, ctypes.c_int]
         lib.ps_draft_debug_timeline.restype = ctypes.c_int
         lib.ps_draft_debug_timeline.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+        lib.ps_train_debug_launch.restype = ctypes.c_int
+        lib.ps_train_debug_launch.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_uint)]
         lib.ps_verify_debug_exchange.restype = None
         lib.ps_verify_debug_exchange.argtypes = [ctypes.c_int, ctypes.c_int]
         lib.ps_measure_stream_read.restype = ctypes.c_int
@@ -50,6 +52,13 @@ def ps_draft_debug_attn_plan(config, kv_len, n_new, k, n_cu):
     out = (ctypes.c_int * 4)()
     st = _lib().ps_draft_debug_attn_plan(ctypes.byref(config), len(kv_len), ln, n_new, k, n_cu, out)
     return st, dict(zip(("nk", "units", "blocks", "merge_items"), out[:4]))
+
+
+def ps_train_debug_launch(args):
+    """Returns (status, {"kernel", "grid" (x, y, z), "threads", "rope_grid" (x, y), "rope_threads"})."""
+    out = (ctypes.c_uint * 8)()
+    st = _lib().ps_train_debug_launch(ctypes.byref(args), out)
+    return st, {"kernel": out[0], "grid": tuple(out[1:4]), "threads": out[4], "rope_grid": tuple(out[5:7]), "rope_threads": out[7]}
 
 
 def ps_draft_debug_spin_limit(ctx, spins):

@@ -139,6 +139,26 @@ def test_values_that_a_row_may_not_see_do_not_reach_it(dtype, T, k, nq, nkv, d):
     assert np.abs(got[~sees] - want[~sees]).max() <= (2e-3 if dtype == "bf16" else 2e-5) * np.abs(want).max()
 
 
+def test_more_workgroups_than_one_dimension_of_a_launch_holds():
+    """4097 one-token sequences of 4096 heads: 2^24 + 4096 workgroups of 256 work items.  Each row sees itself only, so
+    every head's output is the sequence's value row, exactly."""
+    import torch
+    seqs, nq, d = 4097, 4096, 64
+    print("case seqs", seqs, "heads", nq, flush=True)
+    a = TR.make_args(seqs, 1, 0, nq, 1, d, "bf16", 10000.0)
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    q = torch.randn((seqs, 1, nq, d), generator=g, device="cuda:0", dtype=torch.bfloat16)
+    kk, v = (torch.randn((seqs, 1, 1, d), generator=g, device="cuda:0", dtype=torch.bfloat16) for _ in range(2))
+    out = torch.full((seqs, 1, nq, d), -12345.0, dtype=torch.float32, device="cuda:0")
+    ws = torch.empty(TR.ps_group_attention_workspace_bytes(a) + 256, dtype=torch.uint8, device="cuda:0")
+    a.q, a.k_, a.v, a.out = q.data_ptr(), kk.data_ptr(), v.data_ptr(), out.data_ptr()
+    a.workspace, a.workspace_bytes = (ws.data_ptr() + 255) & ~255, ws.numel() - 256
+    st = TR.ps_group_attention(a, torch.cuda.current_stream().cuda_stream)
+    assert st == B.PS_OK, B.ps_draft_strerror(st)
+    torch.cuda.synchronize()
+    assert bool((out == v.float()).all())
+
+
 def test_the_error_is_the_rounding_of_the_rotated_keys():
     """The tolerance above is spent on keys that round the other way after a float32 rotation (the kernel's) than
     after a float64 rotation (the oracle's).  With the keys rotated in float32 on the CPU, as the kernel's key

@@ -55,3 +55,28 @@ def test_validation_on_the_host(lib):
     need = TR.ps_group_attention_workspace_bytes(args())
     assert TR.ps_group_attention(args(workspace_bytes=need - 1), None) == B.PS_ERR_WORKSPACE
     assert TR.ps_group_attention(args(workspace=0x100010), None) == B.PS_ERR_WORKSPACE
+
+
+def test_launches_stay_within_the_limits_of_a_launch(lib):
+    """Work items of a launch in x are at most 2^32 - 1 and workgroups in y and z at most 65535 each, whatever the
+    sizes that the entry point takes; and the attention's workgroups cover all rows of all heads and sequences."""
+    from paper_2410_05589_amd import debug as DBG
+    rows_of = {0: 64, 2: 128}
+    for dtype, seqs, T, k, nq, nkv, d in [
+            ("bf16", 1, 2048, 4, 32, 32, 128), ("bf16", 4096, 1, 0, 4096, 1, 64), ("bf16", 4097, 1, 0, 4096, 1, 64),
+            ("bf16", 65535, 1, 0, 8192, 1, 64), ("bf16", 1, (1 << 20) - 15, 15, 128, 8, 128), ("bf16", 65535, 4, 3, 640, 1, 128),
+            ("f32", 2, 300, 3, 8, 8, 64), ("f32", 1, 1024, 15, 32768, 1, 64), ("f32", 1, (1 << 20) - 15, 15, 32, 8, 128),
+            ("f32", 65535, 1, 0, 65535, 1, 64), ("f32", 3, 1 << 19, 0, 1024, 1, 64)]:
+        a = TR.make_args(seqs, T, k, nq, nkv, d, dtype, 10000.0)
+        st, g = DBG.ps_train_debug_launch(a)
+        tag = (dtype, seqs, T, k, nq, g)
+        assert st == B.PS_OK, tag
+        for (x, y, z), threads in ((g["grid"], g["threads"]), (g["rope_grid"] + (1,), g["rope_threads"])):
+            assert x * threads < 1 << 32 and 1 <= y <= 65535 and 1 <= z <= 65535, tag
+        assert g["rope_grid"][0] == T + k, tag
+        if g["kernel"] in rows_of:
+            blocks = -(-T * (k + 1) // rows_of[g["kernel"]]) * nq * (1 if g["kernel"] == 0 else seqs)
+            x, y, z = g["grid"]
+            assert blocks <= x * y < blocks + x and z == (seqs if g["kernel"] == 0 else 1), tag
+    assert DBG.ps_train_debug_launch(TR.make_args(1, 64, 16, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_UNSUPPORTED
+    assert DBG.ps_train_debug_launch(TR.make_args(0, 64, 4, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_SHAPE
