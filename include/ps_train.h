@@ -29,6 +29,7 @@ extern "C" {
  *              under the mask above; query head h uses kv head h / (n_heads / n_kv_heads)
  *              (a key or value row that the mask hides from a row does not enter that row's result, whatever it
  *              holds: Inf and NaN in it stay with the rows that see it)
+ *              (q, k, v and out need to be aligned to 4 bytes only)
  *   workspace  DEVICE, at least ps_group_attention_workspace_bytes(args) bytes, 256-byte aligned, owned by the
  *              caller: the rotary table and the rotated k (dtype: keys are rounded to the storage type after
  *              the rotary embedding, as the inference path caches them; queries are rotated in float32 on chip)

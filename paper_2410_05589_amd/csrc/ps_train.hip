@@ -20,6 +20,25 @@ constexpr float GA_LAZY = 8.f;
 // A launch may have 2^32 - 1 work items in x at most: workgroups beyond GA_GRID_X go on in y (blockIdx.y is 0 but in huge calls)
 constexpr unsigned GA_GRID_X = 1u << 22;
 
+// Wide accesses to the caller's q, k, v and out, which are only promised to be aligned to 4 bytes: the types say so, and the
+// compiler emits the same 16-byte instructions (global memory takes them at any multiple of 4).
+typedef unsigned u32x4_q __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x2_q __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f32x4_q __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ uint4 ld16_q(const void* p) { return __builtin_bit_cast(uint4, (u32x4)*reinterpret_cast<const u32x4_q*>(p)); }
+__device__ __forceinline__ uint4 ldg_stream16_q(const void* p) {
+    return __builtin_bit_cast(uint4, (u32x4)__builtin_nontemporal_load(reinterpret_cast<const u32x4_q*>(p)));
+}
+template <typename WT> __device__ __forceinline__ f32x4 load4_q(const void* p) {
+    if constexpr (Traits<WT>::BF) {
+        const u32x2 v = *reinterpret_cast<const u32x2_q*>(p);
+        return f32x4{bf16_to_f32(v[0] & 0xFFFFu), bf16_to_f32(v[0] >> 16), bf16_to_f32(v[1] & 0xFFFFu), bf16_to_f32(v[1] >> 16)};
+    } else {
+        return *reinterpret_cast<const f32x4_q*>(p);
+    }
+}
+__device__ __forceinline__ void stg_stream16_q(float* p, f32x4 v) { __builtin_nontemporal_store((f32x4_q)v, reinterpret_cast<f32x4_q*>(p)); }
+
 struct GaParams {
     int seqs, T, k, nq, nkv, rows, gpt, ntiles;   // gpt: groups per query tile
     unsigned k1_magic;    // ceil(2^32 / (k + 1)): a row's group is the upper half of the product (rows < 2^28; k > 0)
@@ -59,7 +78,7 @@ __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
         const size_t row = (size_t)seq * P.rows + (size_t)(pos - sl) * (P.k + 1) + sl;
         const size_t from = ((row * P.nkv + head) * D + 4 * g4) * ESZ;
         const size_t to = ALL ? from : ((((size_t)seq * P.nkv + head) * P.T + pos) * D + 4 * g4) * ESZ;
-        const f32x4 a = load4<WT>((const char*)P.k_ + from), b = load4<WT>((const char*)P.k_ + from + D / 2 * ESZ);
+        const f32x4 a = load4_q<WT>((const char*)P.k_ + from), b = load4_q<WT>((const char*)P.k_ + from + D / 2 * ESZ);
         f32x4 ra, rb;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -124,8 +143,8 @@ __device__ __forceinline__ void ga_row_alone(const GaParams& P, int seq, int h, 
         float sc = 0.f;
 #pragma unroll 1
         for (int j = 0; j < D / 2; j += 4) {
-            const f32x4 qa = load4<WT>(q + j * ESZ), qb = load4<WT>(q + (D / 2 + j) * ESZ);
-            const f32x4 ka = load4<WT>(kp + j * ESZ), kb = load4<WT>(kp + (D / 2 + j) * ESZ);
+            const f32x4 qa = load4_q<WT>(q + j * ESZ), qb = load4_q<WT>(q + (D / 2 + j) * ESZ);
+            const f32x4 ka = load4_q<WT>(kp + j * ESZ), kb = load4_q<WT>(kp + (D / 2 + j) * ESZ);
             f32x4 ra, rb;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -227,7 +246,7 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
         const int row = t < n_real ? min(32 * t + skey, g_last_wg) * K1 : min(max(R0 - 16 + 32 * (t - n_real) + skey, 0), r_last);
         const size_t off = (size_t)(unsigned)row * rs;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) { x.k[i] = ld16(kbase + off + 256 * i); x.v[i] = ld16(vbase + off + 256 * i); }
+        for (int i = 0; i < NV; ++i) { x.k[i] = ld16(kbase + off + 256 * i); x.v[i] = ld16_q(vbase + off + 256 * i); }
     };
     auto stage_store = [&](int t, const Stage& x) __attribute__((always_inline)) {
         char* b = smem + (t & 1) * BUF;
@@ -249,7 +268,7 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
             const int x = tid + GF_THREADS * i, r = x / (D / 8), g4 = x % (D / 8);
             const int row = min(R0 + r, r_last), pos = row - group_of(row) * P.k;                // group + slot
             const char* qr = qsrc + (size_t)row * P.nq * D * 4 + 16 * g4;
-            const f32x4 a = load4<float>(qr), b = load4<float>(qr + 2 * D);
+            const f32x4 a = load4_q<float>(qr), b = load4_q<float>(qr + 2 * D);
             const float4* tab = reinterpret_cast<const float4*>(P.table + (size_t)pos * (D / 2) + 4 * g4);
             const float4 t0 = tab[0], t1 = tab[1];
             const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
@@ -352,7 +371,7 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
 #pragma unroll
             for (int v = 0; v < NV; ++v)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) __builtin_nontemporal_store(f32x4{o[4 * v][i], o[4 * v + 1][i], o[4 * v + 2][i], o[4 * v + 3][i]}, reinterpret_cast<f32x4*>(orow + 64 * v + 4 * i));
+                for (int i = 0; i < 4; ++i) stg_stream16_q(orow + 64 * v + 4 * i, f32x4{o[4 * v][i], o[4 * v + 1][i], o[4 * v + 2][i], o[4 * v + 3][i]});
         }
         const unsigned alone = (unsigned)(b | b >> 16 | b >> 32 | b >> 48) & 0xFFFFu;
         if (alone) ga_rows_alone<float, D>(ga_args(), seq, h, r0, alone, lane);
@@ -497,7 +516,7 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
             const int r = min(t2 / (D / 8), nrows - 1), g4 = t2 % (D / 8);
             const int row = r0 + r, pos = row / K1 + row % K1;                  // group + slot
             const char* qrow = qsrc + (size_t)row * P.nq * D * 2;
-            const f32x4 a = load4<WT>(qrow + 4 * g4 * 2), b = load4<WT>(qrow + (D / 2 + 4 * g4) * 2);
+            const f32x4 a = load4_q<WT>(qrow + 4 * g4 * 2), b = load4_q<WT>(qrow + (D / 2 + 4 * g4) * 2);
             u32x4 ra, rb;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -768,8 +787,8 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
 #pragma unroll
         for (int i = 0; i < QI; ++i) {
             const char* a = src + (size_t)min(r0 + QPI * i + lane / PAIRS, r_last) * P.nq * D * 2;
-            qa[i] = ldg_stream16(a);
-            qb[i] = ldg_stream16(a + D);
+            qa[i] = ldg_stream16_q(a);
+            qb[i] = ldg_stream16_q(a + D);
         }
     }
     auto own_row = [&](int i) __attribute__((always_inline)) { return min(max(R0 - 16 + OPI * i + tid / PAIRS, 0), r_last); };
@@ -777,10 +796,10 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
 #pragma unroll
         for (int i = 0; i < OI; ++i) {
             const size_t off = (size_t)own_row(i) * rs + pj * 16;
-            ok[i][0] = ld16(kraw + off);
-            ok[i][1] = ld16(kraw + off + D);
-            ov[i][0] = ld16(vraw + off);
-            ov[i][1] = ld16(vraw + off + D);
+            ok[i][0] = ld16_q(kraw + off);
+            ok[i][1] = ld16_q(kraw + off + D);
+            ov[i][0] = ld16_q(vraw + off);
+            ov[i][1] = ld16_q(vraw + off + D);
         }
     }
     // staging of the real tokens' tiles: 8 threads per key
@@ -795,7 +814,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     auto load_v = [&](int t, uint4 (&x)[NP]) __attribute__((always_inline)) {
         const char* vp = vraw + (size_t)(unsigned)min(32 * t + skey, g_last_wg) * K1rs + sj * 16;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) x[i] = ld16(vp + i * 128);
+        for (int i = 0; i < NP; ++i) x[i] = ld16_q(vp + i * 128);
     };
     auto store_k = [&](int t, const uint4 (&x)[NP]) __attribute__((always_inline)) {
 #pragma unroll
@@ -1068,7 +1087,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         for (int u = 0; u < PCS / 2; ++u) {
             const int rr = (64 / PCS) * u + lane / PCS, pc = lane % PCS;
             const f32x4 w = *reinterpret_cast<const f32x4*>(sO + (rr * PCS + (pc ^ (rr & (PCS - 1)))) * 16);
-            if (r0 + rr < P.rows) __builtin_nontemporal_store(w, reinterpret_cast<f32x4*>(obase + (size_t)(r0 + rr) * P.nq * D + 32 * j0 + 4 * pc));
+            if (r0 + rr < P.rows) stg_stream16_q(obase + (size_t)(r0 + rr) * P.nq * D + 32 * j0 + 4 * pc, w);
         }
         lds_sync_wave();
         __builtin_amdgcn_wave_barrier();

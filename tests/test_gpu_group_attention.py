@@ -139,6 +139,34 @@ def test_values_that_a_row_may_not_see_do_not_reach_it(dtype, T, k, nq, nkv, d):
     assert np.abs(got[~sees] - want[~sees]).max() <= (2e-3 if dtype == "bf16" else 2e-5) * np.abs(want).max()
 
 
+@pytest.mark.parametrize("dtype,T,k,nq,nkv,d", [("bf16", 90, 4, 4, 2, 128), ("bf16", 70, 0, 2, 2, 64), ("bf16", 20, 5, 2, 2, 128), ("f32", 50, 3, 4, 2, 64)])
+def test_tensors_that_are_aligned_to_four_bytes_only(dtype, T, k, nq, nkv, d):
+    """q, k, v and out at 4, 8 and 12 bytes from a 16-byte boundary: the outputs of the same call with aligned ones."""
+    import torch
+    print("case alignment", dtype, "T", T, "k", k, "d", d, flush=True)
+    inp = inputs.make_group_attention_inputs(91, 1, T, k, nq, nkv, d, dtype)
+    want = run_gpu(inp, 1, T, k, nq, nkv, d, dtype)
+    esz = 2 if dtype == "bf16" else 4
+    for shift in (4, 8, 12):
+        a = TR.make_args(1, T, k, nq, nkv, d, dtype, 10000.0)
+        t = {}
+        for n in ("q", "k", "v"):
+            x = B.to_device(inp[n], dtype).reshape(-1)
+            t[n] = torch.empty(x.numel() + 16 // esz, dtype=x.dtype, device="cuda:0")[shift // esz:shift // esz + x.numel()]
+            t[n].copy_(x)
+        out = torch.full((want.size + 4,), -12345.0, dtype=torch.float32, device="cuda:0")
+        o = out[shift // 4:shift // 4 + want.size]
+        assert all(x.data_ptr() % 16 == shift for x in (t["q"], t["k"], t["v"], o))
+        ws = torch.empty(TR.ps_group_attention_workspace_bytes(a) + 256, dtype=torch.uint8, device="cuda:0")
+        a.q, a.k_, a.v, a.out = t["q"].data_ptr(), t["k"].data_ptr(), t["v"].data_ptr(), o.data_ptr()
+        a.workspace, a.workspace_bytes = (ws.data_ptr() + 255) & ~255, ws.numel() - 256
+        assert TR.ps_group_attention(a, torch.cuda.current_stream().cuda_stream) == B.PS_OK
+        torch.cuda.synchronize()
+        assert np.array_equal(o.cpu().numpy().reshape(want.shape), want), shift
+        rest = torch.cat([out[:shift // 4], out[shift // 4 + want.size:]])
+        assert bool((rest == -12345.0).all()), shift
+
+
 def test_more_workgroups_than_one_dimension_of_a_launch_holds():
     """4097 one-token sequences of 4096 heads: 2^24 + 4096 workgroups of 256 work items.  Each row sees itself only, so
     every head's output is the sequence's value row, exactly."""
