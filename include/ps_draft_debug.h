@@ -18,8 +18,9 @@ extern "C" {
 
 /*
  * Host only.  For a configuration and the shape of a step, how ps_draft_step would cut up the
- * five GEMM phases on a device with n_cu compute units and lds_limit bytes of LDS per workgroup
- * (persistent-kernel mode): per phase PS_PLAN_FIELDS ints {T, Kt, K, rows, kw_log, s_log, Gs,
+ * five GEMM phases over n_cu workgroups with lds_limit bytes of LDS each
+ * (persistent-kernel mode; a step may take fewer workgroups than there are compute units, see
+ * ps_draft_debug_step_plan): per phase PS_PLAN_FIELDS ints {T, Kt, K, rows, kw_log, s_log, Gs,
  * per_round, rounds, piece_groups, npieces, lds_bytes} into out[5 * PS_PLAN_FIELDS].
  */
 #define PS_PLAN_FIELDS 12
@@ -28,12 +29,22 @@ PS_API int ps_draft_debug_plan(const ps_draft_config* config, int batch, int n_n
 
 /*
  * Host only.  How ps_draft_step would cut up the attention of a step over bf16 caches (PS_ERR_UNSUPPORTED for
- * float32) for sequences of kv_len[0 .. batch) valid positions on a device with n_cu compute units: out[4] =
+ * float32) for sequences of kv_len[0 .. batch) valid positions over n_cu workgroups: out[4] =
  * {NK: groups of 16 keys per wavefront and block (blocks of 128 NK cache keys), work units (blocks x passes of 16
  * query rows), blocks, merge items (0: every sequence is a single block and hands its rows on directly)}.
  */
 PS_API int ps_draft_debug_attn_plan(const ps_draft_config* config, int batch, const int32_t* kv_len, int n_new, int k,
                              int n_cu, int* out);
+
+/*
+ * Host only.  The whole plan of a step of sequences of kv_len[0 .. batch) valid positions on a device with n_cu compute
+ * units (at most 512) and lds_limit bytes of LDS per workgroup, as ps_draft_step makes it: out[PS_STEP_PLAN_INTS] = {workgroups;
+ * per GEMM phase the PS_PLAN_FIELDS ints of ps_draft_debug_plan; the attention's {keys of a block, work units, blocks, merge
+ * items, workgroups, 1 if the step's own rows are left to the merge items}}.
+ */
+#define PS_STEP_PLAN_INTS (1 + 5 * PS_PLAN_FIELDS + 6)
+PS_API int ps_draft_debug_step_plan(const ps_draft_config* config, int batch, const int32_t* kv_len, int n_new, int k, int all_rows,
+                             int n_cu, int lds_limit, int* out);
 
 /*
  * Host only.  How ps_group_attention would launch a call (pointers are not looked at; its errors otherwise): out[8] =

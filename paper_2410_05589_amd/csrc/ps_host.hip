@@ -377,6 +377,13 @@ extern "C" int ps_draft_set_profile_events(ps_draft_ctx* ctx, void* const* event
 // ------------------------------------------------------------------------------------------
 // launch plan
 // ------------------------------------------------------------------------------------------
+// what a step's plan depends on besides the configuration and the call: the device and the tuning aids
+struct PlanLimits {
+    int n_cu, lds;
+    bool fused;
+    const int (*phase)[2];            // see parse_plan_override
+    int attn_sep, attn_nk;            // attn_sep_override, attn_nk_override of a context
+};
 int panel_row_stride_host(int panel_steps) {
     const int len = panel_steps * 64;
     return len + ((64 - (len & 255)) + 256) % 256;
@@ -465,18 +472,10 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
     return false;
 }
 
-// Workgroups of a step: one per compute unit, but five for every eight where the weights are so few that a compute unit's
-// share is below 48 KB and the rows fill at most two column tiles.  Such a step is a chain of hand-offs in which most
-// workgroups wait most of the time, and what they ask for while they wait is in the way of the others.  Measured on 256
-// compute units, us with 256 / 192 / 160 / 128 workgroups: H 512 bf16, 5 rows 48.6 / 46.6 / 42.1 / 43.5, 24 rows
-// 61.6 / 59.1 / 58.5 / 59.7, 48 rows 70.9 / 70.5 / 73.5 / 73.0, 64 rows 99.9 / 101.4 / 103.1 / 103.0; H 256 float32, 5 rows
-// 39.1 / 37.8 / 37.2 / 36.8; H 512 float32 (66 KB per compute unit), batch of 8: 95 / 106 / - / 116.
-static int step_workgroups(const ps_draft_config* c, int n_cu, bool fused, int rows) {
-    int T[PH_COUNT], Kt[PH_COUNT];
-    phase_dims(c, T, Kt);
-    size_t bytes = 0;
-    for (int ph = 0; ph <= PH_LMHEAD; ++ph) bytes += (size_t)T[ph] * Kt[ph] * 1024;
-    return fused && rows <= 32 && bytes < (size_t)n_cu * (48 * 1024) && n_cu >= 8 ? n_cu * 5 / 8 : n_cu;
+static void plan_fields(const PhaseDesc& d, int* out) {
+    const int v[PS_PLAN_FIELDS] = {d.T, d.Kt, d.K, d.rows, d.kw_log, d.s_log, d.Gs, d.per_round, d.rounds,
+                                   d.piece_groups, d.npieces, d.lds_bytes};
+    for (int i = 0; i < PS_PLAN_FIELDS; ++i) out[i] = v[i];
 }
 
 // see ps_draft_debug.h
@@ -496,9 +495,7 @@ extern "C" int ps_draft_debug_plan(const ps_draft_config* c, int batch, int n_ne
         const int rows = ph == PH_LMHEAD ? Rtot : Mtot;
         if (!make_desc(&d, ph, T[ph], Kt[ph], K[ph], rows, (Mtot + 15) / 16, c->dtype == PS_BF16, n_cu, none, lds_limit))
             return PS_ERR_UNSUPPORTED;
-        const int v[PS_PLAN_FIELDS] = {d.T, d.Kt, d.K, d.rows, d.kw_log, d.s_log, d.Gs, d.per_round, d.rounds,
-                                       d.piece_groups, d.npieces, d.lds_bytes};
-        for (int i = 0; i < PS_PLAN_FIELDS; ++i) out[ph * PS_PLAN_FIELDS + i] = v[i];
+        plan_fields(d, out + ph * PS_PLAN_FIELDS);
     }
     return PS_OK;
 }
@@ -508,10 +505,10 @@ extern "C" int ps_draft_debug_plan(const ps_draft_config* c, int batch, int n_ne
 // by a small cost model in microseconds, measured on the benchmark's workloads: a unit costs about 2 + 1 per group of
 // 16 keys a wavefront takes in turn (two at a time), the workgroups take ceil(units / compute units) rounds of them,
 // and a sequence of several blocks costs one more exchange through memory (the merge items).
-struct Attn2Plan { int ch_log, npass, items, merge_items; };
+struct Attn2Plan { int ch_log, npass, items, merge_items, rounds; double cost; };
 static Attn2Plan plan_attn2(const int32_t* kv_len, int batch, int n_kv_heads, int ra, int M, int n_cu, int nk_override) {
     const int npass = (ra + 15) / 16, rt = (ra + PS_WAVES - 1) / PS_WAVES;
-    int best_log = 0;
+    int best_log = 0, best_rounds = 0;
     double best = 1e30;
     for (int lg = 0; lg <= PS_ATTN2_NK_LOG_MAX; ++lg) {
         if (nk_override > 0 && (1 << lg) != nk_override) continue;
@@ -530,9 +527,10 @@ static Attn2Plan plan_attn2(const int32_t* kv_len, int batch, int n_kv_heads, in
         }
         const long long rounds = (units + n_cu - 1) / n_cu;
         const double cost = (double)rounds * (2.0 + 1.0 * ((groups + PS_WAVES - 1) / PS_WAVES)) + (merge ? 5.0 : 0.0);
-        if (cost < best - 1e-9) { best = cost; best_log = lg; }
+        if (cost < best - 1e-9) { best = cost; best_log = lg; best_rounds = (int)rounds; }
     }
     Attn2Plan ap;
+    ap.cost = best; ap.rounds = best_rounds;
     ap.ch_log = PS_ATTN_KEYS_LOG + best_log; ap.npass = npass; ap.items = 0; ap.merge_items = 0;
     for (int b = 0; b < batch; ++b) {
         int nch = (int)(((long long)kv_len[b] + (1 << ap.ch_log) - 1) >> ap.ch_log);
@@ -557,6 +555,135 @@ extern "C" int ps_draft_debug_attn_plan(const ps_draft_config* c, int batch, con
     const int M = n_new + k;
     const Attn2Plan ap = plan_attn2(kv_len, batch, c->n_kv_heads, (c->n_heads / c->n_kv_heads) * M, M, n_cu, 0);
     out[0] = 1 << (ap.ch_log - PS_ATTN_KEYS_LOG); out[1] = ap.items * ap.npass; out[2] = ap.items; out[3] = ap.merge_items;
+    return PS_OK;
+}
+
+// The attention's part of a step's plan, on nwg workgroups: attn_phase (float32 caches) or attn_phase2 (bf16) in ps_device.h
+struct AttnPlan {
+    int items, units, merge_items, nwg, nk;   // work items = key blocks; units: passes over them (float32: items)
+    int single, sep, tail;                    // float32
+    int ch_log, npass;                        // bf16
+    int rounds;                               // of units that the busiest workgroup takes
+    double cost;                              // of the longest workgroup: blocks of the smaller size in turn (float32), modelled microseconds (bf16)
+};
+static AttnPlan plan_attn(const ps_draft_config* c, const int32_t* kv_len, int batch, int M, int nwg, const PlanLimits& lim) {
+    AttnPlan A;
+    memset(&A, 0, sizeof(A));
+    const int nkv = c->n_kv_heads, ra = (c->n_heads / nkv) * M;
+    A.single = ra <= 16;
+    A.nk = 1;
+    if (c->dtype == PS_BF16) {
+        const Attn2Plan ap = plan_attn2(kv_len, batch, nkv, ra, M, nwg, lim.attn_nk);
+        A.ch_log = ap.ch_log; A.npass = ap.npass; A.items = ap.items; A.units = ap.items * ap.npass; A.merge_items = ap.merge_items;
+        A.rounds = ap.rounds; A.cost = ap.cost;
+    } else {
+        int ch = PS_ATTN_KEYS;
+        // The M rows of this step normally belong to the last key block of their sequence.  When they alone
+        // make up that block (or spill into one more) and leaving them out spares the workgroups a whole
+        // round of work items, the merge items take them instead (at most 16 rows: they are kept in registers).
+        int items = 0, items_wo = 0;
+        for (int b = 0; b < batch; ++b) {
+            items += nkv * ((kv_len[b] + M + ch - 1) / ch);
+            items_wo += nkv * ((kv_len[b] + ch - 1) / ch);
+        }
+        bool sep = M <= 16 && (items_wo + nwg - 1) / nwg < (items + nwg - 1) / nwg;
+        if (lim.attn_sep >= 0 && M <= 16) sep = lim.attn_sep != 0;
+        if (sep) items = items_wo;
+        const int tail = sep ? 0 : M;
+        // Key blocks of twice the size (two groups of 16 keys per wavefront) when the workgroups still face
+        // more than one round of work items and that way every one of them gets at most a single item
+        if (items > nwg && ra <= 16 && ps_attn_lds_bytes(c->head_dim, 2) <= lim.lds) {
+            int items2 = 0;
+            for (int b = 0; b < batch; ++b) items2 += nkv * ((kv_len[b] + tail + 2 * ch - 1) / (2 * ch));
+            if (items2 <= nwg) { A.nk = 2; ch *= 2; items = items2; }
+        }
+        A.items = A.units = items; A.sep = sep ? 1 : 0; A.tail = tail;
+        // sequences that span several key blocks are put together by (sequence, kv head, 8 rows) work items
+        const int rt = (ra + PS_WAVES - 1) / PS_WAVES;
+        for (int b = 0; b < batch; ++b)
+            if (sep || (kv_len[b] + tail + ch - 1) / ch > 1) A.merge_items += nkv * rt;
+        A.rounds = (items + nwg - 1) / nwg;
+        A.cost = (double)A.rounds * A.nk;
+    }
+    const int want = A.units > A.merge_items ? A.units : A.merge_items;
+    A.nwg = want < nwg ? want : nwg;
+    return A;
+}
+
+// How ps_draft_step cuts up a step: the number of workgroups, the GEMM phases and the attention
+struct StepPlan { int nwg; PhaseDesc ph[PH_COUNT]; AttnPlan attn; };
+
+// Workgroups of a step: one per compute unit, but five for every eight where the weights are so few that a compute unit's
+// share is below 48 KB, the rows fill at most two column tiles, and the attention does not need the others.  Such a step is
+// a chain of hand-offs in which most workgroups wait most of the time, and what they ask for while they wait is in the way of
+// the others.  us with 256 / 160 workgroups on 256 compute units:
+//   weights per compute unit (batch 1, cache 100, 5 rows; batch 4, cache 100, 24 rows): bf16 32 KB 48.7 / 42.2, 55.0 / 54.0;
+//     40 KB 47.3 / 44.8, 60.4 / 56.8; 48 KB 47.2 / 44.8, 60.3 / 56.9; 56 KB 47.4 / 44.9, 60.2 / 57.2; float32 32 KB 42.5 / 40.9,
+//     52.0 / 51.7; 40 KB 43.4 / 41.8, 53.1 / 53.1; 48 KB 40.8 / 40.4, 53.1 / 53.3; 56 KB 41.4 / 41.2, 54.0 / 54.1; 64 KB 42.0 /
+//     41.8, 54.3 / 54.9: float32 gains nothing from 48 KB on (bf16 still would)
+//   rows (H 512 bf16): 48 rows 70.9 / 73.5, 64 rows 99.9 / 103.1
+//   attention, float32 (H 256, 4 heads; batch x cache): 4 x 1024 56.7 / 56.3, but where fewer workgroups mean more rounds or blocks
+//     of twice the size 1 x 8000 47.4 / 49.8, 4 x 2048 57.1 / 60.2, 6 x 1024 59.0 / 60.9, 6 x 2048 63.9 / 71.9, 16 x 600 67.3 / 69.8,
+//     32 x 300 71.1 / 78.1: all workgroups there
+//   attention, bf16 (H 512, 8 heads), by its cost model: the same blocks or up to a third more time are won back (1 x 4096
+//     47.9 / 46.3, 4 x 1024 61.6 / 57.5, 6 x 2048 67.5 / 65.7, 16 x 2048 79.4 / 72.6; 2 kv heads: 5 x 3000 64.6 / 61.7, 32 x 1024
+//     69.6 / 66.5, but 16 x 1024 62.5 / 63.3 and 8 x 4096 64.1 / 65.3), another round is not (32 x 1024 70.9 / 78.8, 32 x 2048 81.6 / 91.9),
+//     nor half as much again (6 x 4096 70.1 / 72.6, 4 x 8000 70.5 / 71.1)
+static int step_workgroups(const ps_draft_config* c, const int32_t* kv_len, int batch, int M, const PlanLimits& lim) {
+    int T[PH_COUNT], Kt[PH_COUNT];
+    phase_dims(c, T, Kt);
+    size_t bytes = 0;
+    for (int ph = 0; ph <= PH_LMHEAD; ++ph) bytes += (size_t)T[ph] * Kt[ph] * 1024;
+    if (!lim.fused || lim.n_cu < 8 || batch * M > 32 || bytes >= (size_t)lim.n_cu * (48 * 1024)) return lim.n_cu;
+    const int fewer = lim.n_cu * 5 / 8;
+    const AttnPlan all = plan_attn(c, kv_len, batch, M, lim.n_cu, lim), few = plan_attn(c, kv_len, batch, M, fewer, lim);
+    return few.rounds <= all.rounds && few.cost <= all.cost * (c->dtype == PS_BF16 ? 4.0 / 3.0 : 1.0) + 1e-9 ? fewer : lim.n_cu;
+}
+
+static bool plan_step(const ps_draft_config* c, const int32_t* kv_len, int batch, int n_new, int k, int all_rows, const PlanLimits& lim,
+                      StepPlan* sp) {
+    const int M = n_new + k, Mtot = batch * M, Rtot = batch * (all_rows ? M : k + 1);
+    int T[PH_COUNT], Kt[PH_COUNT], K[PH_COUNT];
+    phase_dims(c, T, Kt, K);
+    auto phases = [&](int nwg) {
+        memset(sp->ph, 0, sizeof(sp->ph));
+        for (int ph = 0; ph < PH_COUNT; ++ph) {
+            if (T[ph] == 0) continue;                        // (no input projection in this configuration)
+            const int rows = ph == PH_LMHEAD ? Rtot : ph == PH_FC ? batch * n_new : Mtot;
+            // the persistent kernel runs every phase with the column tiles of the widest one
+            const int mt = ((lim.fused && ph != PH_FC) ? Mtot + 15 : rows + 15) / 16;
+            if (!make_desc(&sp->ph[ph], ph, T[ph], Kt[ph], K[ph], rows, mt, c->dtype == PS_BF16, nwg, lim.phase[ph], lim.lds)) return false;
+        }
+        return true;
+    };
+    sp->nwg = step_workgroups(c, kv_len, batch, M, lim);
+    if (!phases(sp->nwg)) {
+        sp->nwg = lim.n_cu;
+        if (!phases(sp->nwg)) return false;
+    }
+    sp->attn = plan_attn(c, kv_len, batch, M, sp->nwg, lim);
+    return true;
+}
+
+// see ps_draft_debug.h
+extern "C" int ps_draft_debug_step_plan(const ps_draft_config* c, int batch, const int32_t* kv_len, int n_new, int k, int all_rows,
+                                        int n_cu, int lds_limit, int* out) {
+    if (!c || !kv_len || !out) return PS_ERR_NULL;
+    const int st = check_config(c);
+    if (st != PS_OK) return st;
+    if (batch < 1 || batch > c->max_batch || n_new < 1 || n_new > c->max_new || k < 0 || k > c->k_max) return PS_ERR_SHAPE;
+    if (n_cu < 1 || n_cu > PS_MAX_WG || lds_limit < 64 * 1024 || lds_limit > PS_LDS_BYTES) return PS_ERR_SHAPE;
+    for (int b = 0; b < batch; ++b)
+        if (kv_len[b] < 0 || (long long)kv_len[b] + n_new + k > c->max_positions) return PS_ERR_KV_CAPACITY;
+    static const int none[PH_COUNT][2] = {};
+    const PlanLimits lim = {n_cu, lds_limit, true, none, -1, 0};
+    StepPlan sp;
+    if (!plan_step(c, kv_len, batch, n_new, k, all_rows, lim, &sp)) return PS_ERR_UNSUPPORTED;
+    *out++ = sp.nwg;
+    for (int ph = 0; ph <= PH_LMHEAD; ++ph, out += PS_PLAN_FIELDS) plan_fields(sp.ph[ph], out);
+    const int keys = c->dtype == PS_BF16 ? 1 << sp.attn.ch_log : PS_ATTN_KEYS * sp.attn.nk;
+    const int v[PS_STEP_PLAN_INTS - 1 - 5 * PS_PLAN_FIELDS] = {keys, sp.attn.units, sp.attn.items, sp.attn.merge_items, sp.attn.nwg, sp.attn.sep};
+    for (int x : v) *out++ = x;
     return PS_OK;
 }
 
@@ -641,75 +768,26 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
         P.kv_len[b] = a->kv_len[b];
         P.skip[b] = a->n_new_seq ? a->n_new - a->n_new_seq[b] : 0;
     }
-    // the GEMM phases' plans
-    const bool bf = c.dtype == PS_BF16;
+    // how the step is cut up
+    const bool attn2 = c.dtype == PS_BF16;                   // bf16 storage: attn_phase2 (ps_device.h)
     P.r_magic = 0xFFFFFFFFu / (unsigned)P.R + 1u;
-    int T[PH_COUNT], Kt[PH_COUNT], K[PH_COUNT];
-    phase_dims(&c, T, Kt, K);
-    auto plan_phases = [&](int n) {
-        for (int ph = 0; ph < PH_COUNT; ++ph) {
-            if (T[ph] == 0) continue;                        // (no input projection in this configuration)
-            const int rows = ph == PH_LMHEAD ? P.Rtot : ph == PH_FC ? a->batch * a->n_new : P.Mtot;
-            // the persistent kernel runs every phase with the column tiles of the widest one
-            const int mt = ((ctx->fused && ph != PH_FC) ? P.Mtot + 15 : rows + 15) / 16;
-            if (!make_desc(&P.ph[ph], ph, T[ph], Kt[ph], K[ph], rows, mt, bf, n, ctx->plan_override[ph], ctx->lds_limit)) return false;
-        }
-        return true;
-    };
-    int nwg = step_workgroups(&c, ctx->n_cu, ctx->fused != 0, P.Mtot);
-    if (!plan_phases(nwg)) {
-        nwg = ctx->n_cu;
-        if (!plan_phases(nwg)) return PS_ERR_UNSUPPORTED;
-    }
+    StepPlan sp;
+    const PlanLimits lim = {ctx->n_cu, ctx->lds_limit, ctx->fused != 0, ctx->plan_override, ctx->attn_sep_override, ctx->attn_nk_override};
+    if (!plan_step(&c, a->kv_len, a->batch, a->n_new, a->k, a->out_rows, lim, &sp)) return PS_ERR_UNSUPPORTED;
+    const int nwg = sp.nwg;
     for (int ph = 0; ph < PH_COUNT; ++ph) {
-        if (T[ph] == 0) continue;
+        P.ph[ph] = sp.ph[ph];
+        if (P.ph[ph].T == 0) continue;                       // (no input projection in this configuration)
         P.ph[ph].wpack = ctx->wpack[ph];
         P.ph[ph].frag = (float*)(ctx->act_base + ctx->off_frag[ph]);
         P.ph[ph].ssq_frag = (float*)(ctx->act_base + ctx->off_ssqf[ph]);
     }
-    // attention work items: (sequence, kv head, block of ch keys)
-    const int ra = (c.n_heads / c.n_kv_heads) * M;
-    int ch = PS_ATTN_KEYS;
-    // The M rows of this step normally belong to the last key block of their sequence.  When they alone
-    // make up that block (or spill into one more) and leaving them out spares the workgroups a whole
-    // round of work items, the merge items take them instead (at most 16 rows: they are kept in registers).
-    int items = 0, items_wo = 0;
-    for (int b = 0; b < a->batch; ++b) {
-        items += c.n_kv_heads * ((a->kv_len[b] + M + ch - 1) / ch);
-        items_wo += c.n_kv_heads * ((a->kv_len[b] + ch - 1) / ch);
-    }
-    bool sep = M <= 16 && (items_wo + nwg - 1) / nwg < (items + nwg - 1) / nwg;
-    if (ctx->attn_sep_override >= 0 && M <= 16) sep = ctx->attn_sep_override != 0;
-    if (sep) items = items_wo;
-    const int tail = sep ? 0 : M;
-    // Key blocks of twice the size (two groups of 16 keys per wavefront) when the workgroups still face
-    // more than one round of work items and that way every one of them gets at most a single item
-    int nk = 1;
-    if (items > nwg && ra <= 16 && ps_attn_lds_bytes(c.head_dim, 2) <= ctx->lds_limit) {
-        int items2 = 0;
-        for (int b = 0; b < a->batch; ++b) items2 += c.n_kv_heads * ((a->kv_len[b] + tail + 2 * ch - 1) / (2 * ch));
-        if (items2 <= nwg) { nk = 2; ch *= 2; items = items2; }
-    }
-    P.attn_items = items; P.attn_single = ra <= 16; P.attn_sep = sep ? 1 : 0; P.attn_tail = tail; P.attn_nk = nk;
-    const bool attn2 = c.dtype == PS_BF16;   // bf16 storage: attn_phase2 (ps_device.h)
-    {   // sequences that span several key blocks are put together by (sequence, kv head, 8 rows) work items
-        const int rt = (ra + PS_WAVES - 1) / PS_WAVES;
-        int mi = 0;
-        for (int b = 0; b < a->batch; ++b)
-            if (sep || (a->kv_len[b] + tail + ch - 1) / ch > 1) mi += c.n_kv_heads * rt;
-        P.attn_merge_items = mi;
-        const int want = items > mi ? items : mi;
-        P.attn_nwg = want < nwg ? want : nwg;
-    }
+    P.attn_items = sp.attn.items; P.attn_single = sp.attn.single; P.attn_sep = sp.attn.sep; P.attn_tail = sp.attn.tail; P.attn_nk = sp.attn.nk;
+    P.attn_merge_items = sp.attn.merge_items; P.attn_nwg = sp.attn.nwg;
     if (attn2) {
-        const Attn2Plan ap = plan_attn2(a->kv_len, a->batch, c.n_kv_heads, ra, M, nwg, ctx->attn_nk_override);
-        P.attn_ch_log = ap.ch_log; P.attn_npass = ap.npass; P.pass_magic = 0xFFFFFFFFu / (unsigned)ap.npass + 1u;
-        P.attn_items = ap.items; P.attn_units = ap.items * ap.npass; P.attn_merge_items = ap.merge_items;
-        P.attn_sep = 0; P.attn_tail = 0; P.attn_nk = 1;
-        const int want = P.attn_units > ap.merge_items ? P.attn_units : ap.merge_items;
-        P.attn_nwg = want < nwg ? want : nwg;
+        P.attn_ch_log = sp.attn.ch_log; P.attn_npass = sp.attn.npass; P.pass_magic = 0xFFFFFFFFu / (unsigned)sp.attn.npass + 1u;
+        P.attn_units = sp.attn.units;
     }
-
     P.ph[PH_QKV].norm = 1; P.ph[PH_QKV].gain = P.g_in; P.ph[PH_QKV].src = nullptr; P.ph[PH_QKV].src_ld = P.H;
     P.ph[PH_OPROJ].src = P.o_buf; P.ph[PH_OPROJ].src_ld = P.QD;
     P.ph[PH_GATEUP].norm = 1; P.ph[PH_GATEUP].gain = P.g_post; P.ph[PH_GATEUP].src = P.y_buf; P.ph[PH_GATEUP].src_ld = P.H;
@@ -727,7 +805,7 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
     }
 
     // the persistent kernel needs the largest LDS footprint of its phases and one workgroup per CU
-    int lds = attn2 ? ps_attn2_lds_bytes(c.head_dim) : ps_attn_lds_bytes(c.head_dim, nk);
+    int lds = attn2 ? ps_attn2_lds_bytes(c.head_dim) : ps_attn_lds_bytes(c.head_dim, sp.attn.nk);
     for (int ph = 0; ph < PH_COUNT; ++ph) {
         if (P.ph[ph].lds_bytes > lds) lds = P.ph[ph].lds_bytes;
     }

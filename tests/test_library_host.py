@@ -286,3 +286,77 @@ def test_phase_plans_over_a_sweep_of_shapes_and_devices(lib):
                 _check_plan(cfg, plans, batch, n_new, k, n_cu, lds)
                 checked += 1
     assert checked > 500
+
+
+def _weight_bytes(cfg):
+    qd, esz = cfg.n_heads * cfg.head_dim, 2 if cfg.dtype == B.PS_BF16 else 4
+    kv = cfg.n_kv_heads * cfg.head_dim
+    return esz * cfg.hidden * (qd + 2 * kv + qd + 3 * cfg.ffn + 16 * -(-cfg.vocab // 16))
+
+
+def test_step_plans_choose_the_workgroups_of_small_steps(lib):
+    """The whole plan of a step as ps_draft_step makes it: five workgroups for every eight compute units below 48 KB of
+    weights per compute unit, up to 32 rows and as long as the attention does not need the others; on both sides of each limit."""
+    def nwg(shape, kv, n_new, k, n_cu=256, lds=160 * 1024):
+        cfg = B.make_config(shape, max_batch=len(kv), max_new=n_new, max_positions=1 << 16, max_topk=8, k_max=max(k, 1))
+        st, n, plans, attn = DBG.ps_draft_debug_step_plan(cfg, kv, n_new, k, 0, n_cu, lds)
+        assert st == B.PS_OK
+        _check_plan(cfg, plans, len(kv), n_new, k, n, lds)
+        return n
+    bf, tiny = small_shape("bf16"), WORKLOADS["c0"].shape
+    assert nwg(bf, [100], 1, 4) == 160 and nwg(bf, [100], 1, 4, n_cu=304) == 190 and nwg(bf, [100], 1, 4, n_cu=7) == 7
+    assert nwg(bf, [100] * 8, 1, 3) == 160 and nwg(bf, [100] * 11, 1, 2) == 256                   # 32 and 33 rows
+    for vocab, n in ((5136, 160), (6160, 256)):                                                   # 44 and 48.2 KB of weights per compute unit
+        assert nwg(small_shape("bf16", vocab=vocab), [100], 1, 4) == n, vocab
+    assert nwg(small_shape("f32"), [100], 1, 4) == 256
+    for kv, n_new, k, n in (([4000], 1, 4, 160), ([8000], 1, 4, 256),                             # float32: one round of blocks of 128 keys, ...
+                            ([1024] * 4, 1, 4, 160), ([2048] * 4, 1, 4, 256),                     # ... or the step's rows left to the merge items for it
+                            ([512] * 6, 1, 4, 160), ([1024] * 6, 1, 4, 256), ([2048] * 6, 1, 4, 256),
+                            ([256] * 16, 1, 1, 160), ([600] * 16, 1, 1, 256), ([300] * 32, 1, 0, 256)):
+        assert nwg(tiny, kv, n_new, k) == n, (kv, n_new, k)
+    for kv, n_new, k, n in (([4096], 1, 4, 160), ([1024] * 4, 1, 4, 160), ([2048] * 6, 1, 4, 160),     # bf16: the same or up to a third more
+                            ([4096] * 6, 1, 4, 256), ([1024] * 32, 1, 0, 256), ([2048] * 32, 1, 0, 256)):   # half as much more; another round
+        assert nwg(bf, kv, n_new, k) == n, (kv, n_new, k)
+    cfg = B.make_config(tiny, max_batch=1, max_new=1, max_positions=128, max_topk=4, k_max=4)
+    for kw, want in ((dict(n_cu=0), B.PS_ERR_SHAPE), (dict(n_cu=513), B.PS_ERR_SHAPE), (dict(kv=(124,)), B.PS_ERR_KV_CAPACITY), (dict(k=5), B.PS_ERR_SHAPE)):
+        a = dict(dict(kv=(64,), k=4, n_cu=256), **kw)
+        assert DBG.ps_draft_debug_step_plan(cfg, a["kv"], 1, a["k"], 0, a["n_cu"], 160 * 1024)[0] == want, kw
+
+
+def test_step_plans_over_a_sweep_of_small_shapes(lib):
+    """Random small shapes, batches, lengths and devices: the phase plans hold for the number of workgroups that was chosen
+    (what the device code relies on), that number is one of the two, and the attention's work covers every sequence."""
+    import random
+    rnd = random.Random(19)
+    chosen = {"all": 0, "fewer": 0}
+    for _ in range(600):
+        dtype = rnd.choice(["bf16", "f32"])
+        head_dim, n_kv, grp = rnd.choice([64, 128]), rnd.choice([1, 2, 4]), rnd.choice([1, 2, 4])
+        mul = 32 if dtype == "bf16" else 16
+        shape = small_shape(dtype, hidden=n_kv * grp * head_dim, n_heads=n_kv * grp, n_kv_heads=n_kv, head_dim=head_dim,
+                            ffn=mul * rnd.randint(1, 60), vocab=rnd.randint(16, 9000))
+        k, n_new = rnd.randint(0, 8), rnd.randint(1, 6)
+        M = n_new + k
+        if grp * M > 64:
+            continue
+        batch = rnd.randint(1, max(1, min(32, 64 // M)))
+        kv = [rnd.choice([0, 1, 127, 128, 129, rnd.randint(0, 3000)]) for _ in range(batch)]
+        cfg = B.make_config(shape, max_batch=batch, max_new=n_new, max_positions=4096, max_topk=8, k_max=max(k, 1))
+        for n_cu, lds in ((256, 160 * 1024), (304, 160 * 1024), (80, 64 * 1024), (8, 96 * 1024), (7, 96 * 1024)):
+            st, n, plans, attn = DBG.ps_draft_debug_step_plan(cfg, kv, n_new, k, rnd.randint(0, 1), n_cu, lds)
+            assert st in (B.PS_OK, B.PS_ERR_UNSUPPORTED), (st, kv)
+            if st != B.PS_OK:
+                continue
+            tag = (dtype, kv, n_new, k, n_cu, n, attn)
+            assert n in (n_cu, n_cu * 5 // 8 if n_cu >= 8 else n_cu), tag
+            small = batch * M <= 32 and _weight_bytes(cfg) <= n_cu * 48 * 1024     # (the packed bytes are these, rounded up)
+            assert n == n_cu or small, tag
+            chosen["all" if n == n_cu else "fewer"] += 1
+            _check_plan(cfg, plans, batch, n_new, k, n, lds)
+            blocks = n_kv * sum(max(1, -(-l // attn["keys"])) if dtype == "bf16" else -(-(l + (0 if attn["sep"] else M)) // attn["keys"]) for l in kv)
+            passes = -(-grp * M // 16) if dtype == "bf16" else 1
+            assert attn["blocks"] == blocks and attn["units"] == blocks * passes, tag
+            assert attn["workgroups"] == min(n, max(attn["units"], attn["merge_items"])), tag
+            if dtype == "f32" and n < n_cu:
+                assert attn["units"] <= n or -(-attn["units"] // n) <= -(-attn["units"] // n_cu), tag
+    assert min(chosen.values()) > 100, chosen
