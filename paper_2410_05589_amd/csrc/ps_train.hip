@@ -1134,11 +1134,18 @@ int plan(const GaParams& P, int dtype, int head_dim, GaLaunch* L) {
     const long long max_wg = 0x7FFFFFFF;                    // (the kernels number their workgroups in 31 bits)
     if (dtype == PS_BF16) {
         // The wide kernel, except where the real tokens' keys are a single stage and the groups' own rows are most of the work:
-        // there the 16-row kernel, whose workgroups are half as long, is the faster one (us, both kernels and the keys'
-        // rotation: T 30, k 4, 8 heads x 128: 13.4 against 13.7; T 16, k 10, 32 heads: 13.7 against 14.0; but T 30, k 1:
-        // 9.8 against 9.0; T 64, k 4, 40 heads: 17.7 against 15.6)
+        // there the 16-row kernel, whose workgroups are half as long, is the faster one as long as
+        // - groups straddle the wide kernel's 32-row tiles, which then looks at the 16 rows before a tile, too;
+        // - its workgroups, which are up to three times as many, find a compute unit each;
+        // - rotating all key rows for it, not only the real tokens', costs no time: up to 8192 rows.
+        // us, 16-row / wide kernel, whole calls at head_dim 128: T 16, k 8, 8 heads 12.9 / 13.9; T 32, k 8, 32 / 8 heads (256 workgroups)
+        // 13.5 / 14.8; T 32, k 4, 8 heads 13.7 / 13.9; T 8, k 10, 8 heads 13.0 / 13.7; T 1, k 4 11.0 / 12.2; but k 3 (T 24) 13.8 / 13.0,
+        // k 7 (T 24) 14.0 / 13.1, k 15 (T 24) 14.7 / 13.3; 4 x T 16, k 8, 32 / 8 heads (512 workgroups) 16.8 / 14.9; T 32, k 10,
+        // 32 heads (11264 key rows) 15.5 / 14.6, 4 x T 16, k 4, 32 heads (10240) 16.0 / 14.4; 8 x T 32, k 8, 40 heads 50 / 35
         const long long blocks = (long long)((P.rows + GW_ROWS - 1) / GW_ROWS) * P.nq * P.seqs;
-        L->kernel = blocks > max_wg || (P.T <= 32 && P.k >= 4) ? GA_TILES : GA_WIDE;
+        const long long tile_wg = (long long)((P.ntiles + GA_WAVES - 1) / GA_WAVES) * P.nq * P.seqs, key_rows = (long long)P.seqs * P.rows * P.nkv;
+        const bool tiles = P.T <= 32 && P.k >= 4 && (P.T == 1 || 32 % (P.k + 1) != 0) && tile_wg <= 256 && key_rows <= 8192;
+        L->kernel = blocks > max_wg || tiles ? GA_TILES : GA_WIDE;
         L->attn = L->kernel == GA_WIDE ? grid_xy(blocks, 1) : dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs);
     } else {
         const long long blocks = (long long)((P.rows + GF_ROWS - 1) / GF_ROWS) * P.nq;

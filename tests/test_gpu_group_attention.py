@@ -70,11 +70,19 @@ def test_longer_sequences_with_other_group_sizes():
     (1, 33, 0, 2, 2, 128), (1, 128, 0, 2, 1, 64), (1, 129, 0, 1, 1, 128),     # k = 0 (no own rows): 1, exactly 1 and 2 blocks of 128 rows
     (1, 64, 1, 2, 2, 128), (2, 65, 1, 3, 1, 64),                              # two rows per group: the most positions in a block; 1 and 2 blocks
     (1, 43, 2, 2, 2, 64), (1, 96, 2, 3, 3, 128),                              # blocks that start inside a group; rows = 129, 288
-    (1, 33, 4, 2, 1, 128), (2, 51, 4, 2, 2, 64), (1, 33, 8, 4, 2, 128),       # T just above the 16-row kernel's range
+    (1, 33, 4, 2, 1, 128), (2, 51, 4, 2, 2, 64), (1, 33, 8, 4, 2, 128),       # just above 32 tokens
     (1, 33, 15, 2, 2, 128), (1, 40, 10, 3, 3, 64), (3, 16, 3, 5, 1, 128),     # 16 rows per group; a wavefront without rows; 15 heads x sequences
-    (1, 32, 4, 2, 2, 128), (1, 32, 15, 2, 1, 64)])                            # the 16-row kernel's largest
+    (1, 32, 4, 2, 2, 128), (1, 32, 15, 2, 1, 64)])                            # 32 tokens, on either side of the 16-row kernel's range
 def test_blocks_of_128_rows_at_their_edges(seqs, T, k, nq, nkv, d):
     _case(seqs, T, k, nq, nkv, d, "bf16", 100 + T + k)
+
+
+@pytest.mark.parametrize("seqs,T,k,nq,nkv,d", [
+    (1, 1, 4, 2, 1, 128), (2, 1, 15, 2, 2, 64), (1, 31, 4, 4, 2, 128), (2, 32, 5, 2, 1, 64),   # 3 and 2 groups per tile, a ragged last tile
+    (1, 32, 14, 2, 2, 128), (3, 17, 10, 4, 4, 64),                                             # one group per tile
+    (1, 32, 8, 32, 8, 64), (1, 32, 7, 2, 2, 128), (1, 26, 8, 36, 36, 64)])                     # 256 workgroups; two calls of the wide kernel
+def test_tiles_of_16_rows_at_their_edges(seqs, T, k, nq, nkv, d):
+    _case(seqs, T, k, nq, nkv, d, "bf16", 300 + T + k)
 
 
 @pytest.mark.parametrize("seqs,T,k,nq,nkv,d", [
@@ -113,7 +121,8 @@ def test_scores_that_overflow_before_a_row_sees_a_finite_one(dtype, k, d):
 @pytest.mark.parametrize("dtype,T,k,nq,nkv,d", [
     ("bf16", 70, 4, 2, 1, 128), ("bf16", 70, 4, 2, 2, 64), ("bf16", 150, 0, 2, 2, 128), ("bf16", 40, 15, 2, 2, 64),
     ("f32", 70, 4, 2, 1, 64), ("f32", 90, 0, 2, 2, 128), ("f32", 20, 15, 2, 2, 64),
-    ("bf16", 20, 5, 2, 2, 128), ("bf16", 32, 15, 2, 2, 64)])                    # (16-row tiles)
+    ("bf16", 20, 5, 2, 2, 128), ("bf16", 32, 14, 2, 2, 64),                      # (16-row tiles)
+    ("bf16", 32, 15, 2, 2, 64)])
 def test_values_that_a_row_may_not_see_do_not_reach_it(dtype, T, k, nq, nkv, d):
     """Value rows that hold Inf and NaN: two [MASK] tokens' and one real token's.  Rows that see none of them have the
     oracle's result (their own keys and values only), the others are not finite."""

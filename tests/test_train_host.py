@@ -80,3 +80,15 @@ def test_launches_stay_within_the_limits_of_a_launch(lib):
             assert blocks <= x * y < blocks + x and z == (seqs if g["kernel"] == 0 else 1), tag
     assert DBG.ps_train_debug_launch(TR.make_args(1, 64, 16, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_UNSUPPORTED
     assert DBG.ps_train_debug_launch(TR.make_args(0, 64, 4, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_SHAPE
+
+
+def test_which_calls_take_the_16_row_kernel(lib):
+    """Both sides of every limit of the rule: T 32, k 4, group sizes that divide 32, 256 workgroups, 8192 key rows."""
+    from paper_2410_05589_amd import debug as DBG
+    for want, calls in ((1, [(1, 32, 4, 8, 8), (1, 32, 8, 32, 8), (1, 1, 7, 8, 8), (1, 1, 15, 8, 8), (1, 16, 14, 8, 8), (1, 25, 8, 36, 36)]),
+                        (2, [(1, 33, 4, 8, 8), (1, 32, 3, 8, 8), (1, 32, 7, 8, 8), (1, 32, 15, 8, 8), (1, 32, 8, 33, 11), (1, 26, 8, 36, 36),
+                             (1, 16, 10, 48, 48), (8, 32, 8, 40, 40)])):
+        for seqs, T, k, nq, nkv in calls:
+            for d in (64, 128):
+                st, g = DBG.ps_train_debug_launch(TR.make_args(seqs, T, k, nq, nkv, d, "bf16", 10000.0))
+                assert st == B.PS_OK and g["kernel"] == want, (seqs, T, k, nq, nkv, g)
