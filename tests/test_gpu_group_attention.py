@@ -45,10 +45,10 @@ def _case(seqs, T, k, nq, nkv, d, dtype, seed, base=10000.0):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_small_shapes_ragged_tiles(dtype):
-    _case(2, 37, 4, 4, 2, 64, dtype, 1)          # 3 groups per query tile, a ragged last tile, GQA
-    _case(1, 50, 2, 2, 2, 128, dtype, 2)         # 5 groups per tile
-    _case(1, 21, 7, 2, 1, 64, dtype, 3)          # 2 groups per tile: 16 rows exactly
-    _case(1, 9, 15, 2, 2, 64, dtype, 4)          # one group per tile
+    _case(2, 37, 4, 4, 2, 64, dtype, 1)          # blocks that end inside a group, a ragged last block, GQA
+    _case(1, 50, 2, 2, 2, 128, dtype, 2)
+    _case(1, 21, 7, 2, 1, 64, dtype, 3)          # groups that divide the blocks' rows
+    _case(1, 9, 15, 2, 2, 64, dtype, 4)          # the longest groups
     _case(1, 70, 0, 4, 4, 64, dtype, 5)          # k = 0: ordinary causal attention
     _case(1, 1, 4, 2, 2, 64, dtype, 6)           # a single token
 
@@ -58,8 +58,8 @@ def test_longer_sequence_and_other_rope_base_bf16():
 
 
 def test_longer_sequences_with_other_group_sizes():
-    """Several pairs of key tiles per wavefront (tiles every query sees entirely, the clamped last tile, the tile of
-    the own [MASK] rows) with 2, 1 and 8 groups per query tile."""
+    """Several tiles of keys per wavefront (tiles every query sees entirely, the masked last ones, the own [MASK] rows), several
+    blocks of rows, with 8, 16 and 2 rows per group in the wide bf16 kernel and 4 in the float32 one."""
     _case(1, 200, 7, 4, 4, 128, "bf16", 8)
     _case(1, 130, 15, 2, 1, 128, "bf16", 9)
     _case(2, 150, 1, 4, 2, 64, "bf16", 10)

@@ -105,11 +105,9 @@ def test_attention_loop_keeps_the_next_key_groups_in_flight(asm):
     assert found[0][1] and min(found[0][1]) >= 8, found
 
 
-def test_training_attention_kernel_fits_four_workgroups_per_compute_unit(tmp_path):
-    """The bf16 training attention runs four workgroups (16 wavefronts) per compute unit: at most 128 vector
-    registers per lane and 40 KiB of LDS per workgroup, no flat loads (LDS addresses stay LDS addresses), and
-    only a handful of spilled registers (loop-invariant values)."""
-    out = str(tmp_path / "ps_train.s")
+@pytest.fixture(scope="module")
+def train_asm(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("asm") / "ps_train.s")
     cmd = [build.hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fno-gpu-rdc", "-fvisibility=hidden",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "-mllvm", "-instcombine-max-copied-from-constant-users=10000",
@@ -117,12 +115,56 @@ def test_training_attention_kernel_fits_four_workgroups_per_compute_unit(tmp_pat
            "--cuda-device-only", "-S", "-o", out, os.path.join(build.CSRC, "ps_train.hip")]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert res.returncode == 0, res.stdout[-2000:]
-    text = open(out).read()
-    assert "flat_load" not in text
-    seen = 0
-    for m in re.finditer(r"\.group_segment_fixed_size:\s+(\d+)\n(?:.*\n)*?\s+\.name:\s+(\S+)\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)\n\s+\.vgpr_spill_count:\s+(\d+)", text):
-        lds, name, vgpr, spill = int(m.group(1)), m.group(2), int(m.group(3)), int(m.group(4))
-        if "ga_attn_bf16_kernel" in name:
-            seen += 1
-            assert vgpr <= 128 and lds <= 40 * 1024 and spill <= 4, (name, vgpr, lds, spill)
-    assert seen == 2        # head_dim 64 and 128
+    return open(out).read()
+
+
+def _resources(text, kernel):
+    """(bytes of LDS, bytes of scratch, vector registers, spilled ones) of the kernel's instances."""
+    found = re.findall(r"\.group_segment_fixed_size:\s+(\d+)\n(?:.*\n)*?\s+\.name:\s+(\S+)\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)\n"
+                       r"(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)\n\s+\.vgpr_spill_count:\s+(\d+)", text)
+    return [tuple(int(x) for x in (m[0], m[2], m[3], m[4])) for m in found if kernel in m[1]]
+
+
+def test_training_attention_kernel_fits_four_workgroups_per_compute_unit(train_asm):
+    """The 16-row bf16 kernel of the training attention runs four workgroups (16 wavefronts) per compute unit: at most
+    128 vector registers per lane and 40 KiB of LDS per workgroup, no flat loads (LDS addresses stay LDS addresses), and
+    only a handful of spilled registers (loop-invariant values)."""
+    assert "flat_load" not in train_asm
+    found = _resources(train_asm, "ga_attn_bf16_kernel")
+    assert len(found) == 2        # head_dim 64 and 128
+    for lds, scratch, vgpr, spill in found:
+        assert vgpr <= 128 and lds <= 40 * 1024 and spill <= 4, found
+
+
+def test_training_attention_wide_and_float32_kernels_fit_two_workgroups_per_compute_unit(train_asm):
+    """The wide bf16 kernel runs two workgroups of four wavefronts per compute unit (256 vector registers per lane), the
+    float32 kernel two of eight (128): in half of a compute unit's 160 KiB of LDS each, with nothing spilled.  (Eight spilled
+    registers cost the wide kernel 3 % of a short call.  The scratch memory is that of the call that looks at rows
+    which are not finite.)"""
+    for kernel, regs in (("ga_attn_wide_kernel", 256), ("ga_attn_f32_kernel", 128)):
+        found = _resources(train_asm, kernel)
+        assert len(found) == 2, (kernel, found)
+        for lds, scratch, vgpr, spill in found:
+            assert lds <= 80 * 1024 and vgpr <= regs and spill == 0 and scratch <= 32, (kernel, found)
+
+
+def test_training_attention_main_loops(train_asm):
+    """The loops over the real tokens' keys hold the MFMAs of one tile and no scratch accesses: 2 products x 2 parts of the
+    bf16 split x head_dim / 16 steps (wide kernel), 2 x head_dim / 4 (float32)."""
+    for kernel, mfma, counts in (("ga_attn_wide_kernel", "v_mfma_f32_32x32x16_bf16", {64: 16, 128: 32}),
+                                 ("ga_attn_f32_kernel", "v_mfma_f32_16x16x4_f32", {64: 32, 128: 64})):
+        for d, n in counts.items():
+            text = train_asm[re.search(r"^_Z\w*%sILi%d\w*:" % (kernel, d), train_asm, flags=re.M).end():]
+            text = text[:text.index(".Lfunc_end")]
+            loops, label = {}, None
+            for line in text.splitlines():
+                m = re.match(r"^\.L(BB\d+_\d+):\s*(;.*)?$", line)
+                if m:
+                    note = m.group(2) or ""
+                    h = re.search(r"in Loop: Header=(BB\d+_\d+) Depth=1", note)
+                    label = h.group(1) if h else (m.group(1) if "Loop Header: Depth=1" in note else None)
+                    continue
+                if label:
+                    loops.setdefault(label, []).append(line)
+            found = [(sum(mfma in l for l in body), sum("scratch_" in l for l in body)) for body in loops.values()]
+            assert (n, 0) in found, (kernel, d, found)
