@@ -905,7 +905,7 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
                 // Not all there yet: until this thread's columns of one row are, only those are asked for (a tile's rows
                 // are stored together).  Everybody asking for whole panels again and again is traffic that the
                 // producers' own accesses queue behind: 1 .. 2.5 % of a step of the small shapes (H 256 and 512, where most
-                // workgroups only wait), nothing of the large ones'
+                // workgroups only wait), nothing of the large ones'.  These polls count towards the same limit as the panel's
                 if (!from_x) {
                     const int r0 = min(rb, rows - 1), srow = PH == PH_LMHEAD ? lm_src_row(P, r0) : r0;
                     for (;;) {

@@ -61,6 +61,8 @@ enum { PS_IN_HIDDEN = 0, PS_IN_TOKENS = 1, PS_IN_FUSED = 2 };   // where the rea
 #define PS_CTR_DONE 2
 #define PS_CTR_FOOT 4
 #define PS_CTR_WORDS (PS_CTR_FOOT + 2 * PS_FOOT_INTS)
+// Polls before a wait is given up.  A poll is a load past the L2 and a short pause, about 1 us, so that is about a second (several
+// for a wait that asks for whole panels each time: stage_piece's waits do that only once one row of the panel is there)
 #define PS_SPIN_LIMIT (1 << 20)
 
 // How one weight-streaming GEMM phase is cut up.  A "tile" is 16 weight rows; a "step" is the

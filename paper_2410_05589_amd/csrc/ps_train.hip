@@ -206,10 +206,11 @@ __device__ __attribute__((noinline)) void ga_rows_alone(ga_args_t args, int seq,
 // LDS read.  Maximum, sum and output stay with the four lanes of a query; the two wavefronts of 16 rows meet in LDS at the
 // end.  K and V rows are staged for all eight wavefronts, into two buffers that take turns.
 //
-// Bound by the float32 matrix rate (32 MFMAs of 32 cycles per 16 x 16 tile at head_dim 64).  Before, P.V was FMA work against
-// probabilities broadcast from LDS, a workgroup took one tile of whole groups and every wavefront fetched its own operands:
-// whole calls, 2 x T 300, k 3, 8 heads x 64: 40.5 -> 26.8 us; 4 x T 512, k 10, 16 / 4 heads x 64: 724 -> 300 us (float32 matrix rate: 185); T 1024,
-// k 4, 32 heads x 128: 1047 -> 470 us.
+// Large calls are bound by the float32 matrix rate (32 MFMAs of 32 cycles per 16 x 16 tile at head_dim 64): 4 x T 512, k 10, 16 / 4 heads
+// x 64 takes 300 us, 185 at that rate.  A small one is bound by the chain of its longest rows' stages: 2 x T 300, k 3, 8 heads x 64 has
+// 304 workgroups for 512 places and the matrix cores 17 % busy.  Before, P.V was FMA work against probabilities broadcast from
+// LDS, a workgroup took one tile of whole groups and every wavefront fetched its own operands: whole calls, the two above:
+// 724 -> 300 and 40.5 -> 27.0 us; T 1024, k 4, 32 heads x 128: 1047 -> 470 us.
 // ------------------------------------------------------------------------------------------
 constexpr int GF_THREADS = 512, GF_ROWS = 64;
 
@@ -700,14 +701,15 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
 // to offer at any time; two workgroups per compute unit (256 registers) are what the query and output registers allow.
 // Everything that a workgroup reads for the first time (table, query rows, own rows, first tiles) is requested at once.  The query
 // rows are read and the output rows are written once, past the caches (non-temporal): the L2 is left to the heads' keys and
-// values (T 2048, k 4: 349 -> 336 us; 4 x T 1024, k 8: 740 -> 707; T 203: 30.0 -> 27.3; the own rows read that way, too: 1 % slower,
-// the next workgroup reads 16 of them again).
+// values (3.7 % of a T 2048, k 4 call, 4.5 % of 4 x T 1024, k 8, 9 % of T 203; the own rows read that way, too: 1 % slower, the next
+// workgroup reads 16 of them again).
 //
-// Bound by the matrix cores: 32 MFMAs of 32 cycles per tile and wavefront; the loop over the real tokens keeps them 80 %
-// busy (2560 cycles per tile with two wavefronts per SIMD), and the compute units run at 1.95 GHz meanwhile.  What is left is
-// a workgroup's start (its first rows come from memory: 16 k cycles at T 2048, k 4 of 121 k) and its own rows (14 k).
-// Whole calls, against the 16-row kernel and its three launches: T 2048, k 4, 32 heads x 128: 503 -> 365 us (472 TFLOP/s of
-// visible pairs, every product twice); 4 x T 1024, k 8, 32 / 8 heads: 1501 -> 752 us; T 203, k 5, 40 heads: 40.9 -> 26.0 us.
+// A tile is 32 MFMAs of 32 cycles per wavefront and about as much vector work: at T 2048, k 4 the matrix cores are busy 52 % of the
+// kernel's time and the vector ALU 47 % (4 x T 1024, k 8: 48 and 50 %), at 1.9 GHz; the two wavefronts of a SIMD cover each other's
+// waits only in part, and a workgroup's start (its rows come from memory) and its own rows have few MFMAs to show.  At T 203 that is
+// most of the time (matrix cores 12 %).  All 256 registers are in use and none is spilled: eight spilled ones cost 1 .. 4 %.
+// Whole calls among others of their kind, against the 16-row kernel and its three launches: T 2048, k 4, 32 heads x 128: 503 -> 347 us
+// (496 TFLOP/s of visible pairs, every product twice); 4 x T 1024, k 8, 32 / 8 heads: 1501 -> 717 us; T 203, k 5, 40 heads: 40.9 -> 25.0 us.
 // Tried: no scores ahead (other wavefront alone fills the gaps): 5 % slower; own rows as further tiles of the loop, rotated
 // between the barriers: 4 % (T 2048) and 12 % (4 x 1024, k 8) slower; raised wavefront priority in the matrix part, two
 // accumulators for the scores, four K operands requested ahead: no change.
