@@ -19,6 +19,7 @@ constexpr int GA_THREADS = 256, GA_WAVES = GA_THREADS / 64;
 constexpr float GA_LAZY = 8.f;
 // A launch may have 2^32 - 1 work items in x at most: workgroups beyond GA_GRID_X go on in y (blockIdx.y is 0 but in huge calls)
 constexpr unsigned GA_GRID_X = 1u << 22;
+constexpr long long GA_MAX_WG = 0x7FFFFFFF;                // the kernels number their workgroups in 31 bits
 
 // Wide accesses to the caller's q, k, v and out, which are only promised to be aligned to 4 bytes: the types say so, and the
 // compiler emits the same 16-byte instructions (global memory takes them at any multiple of 4).
@@ -1109,6 +1110,7 @@ int check(const ps_group_attn_args* a) {
     if (a->k > 15 || (long long)a->tokens + a->k > (1 << 20)) return PS_ERR_UNSUPPORTED;
     if (a->n_heads > 65535 || a->seqs > 65535) return PS_ERR_UNSUPPORTED;
     if ((long long)(a->k + 1) * a->n_kv_heads * a->head_dim * 4 > (1LL << 27)) return PS_ERR_UNSUPPORTED;   // 32-bit offsets inside a key tile
+    if (a->dtype == PS_F32 && ((long long)a->tokens * (a->k + 1) + GF_ROWS - 1) / GF_ROWS * a->n_heads > GA_MAX_WG) return PS_ERR_UNSUPPORTED;   // (its rows would be terabytes)
     return PS_OK;
 }
 
@@ -1132,8 +1134,8 @@ dim3 grid_xy(long long workgroups, int z) {
     const unsigned x = (unsigned)min(workgroups, (long long)GA_GRID_X);
     return dim3(x, (unsigned)((workgroups + x - 1) / x), z);
 }
-int plan(const GaParams& P, int dtype, int head_dim, GaLaunch* L) {
-    const long long max_wg = 0x7FFFFFFF;                    // (the kernels number their workgroups in 31 bits)
+GaLaunch plan(const GaParams& P, int dtype, int head_dim) {
+    GaLaunch L;
     if (dtype == PS_BF16) {
         // The wide kernel, except where the real tokens' keys are a single stage and the groups' own rows are most of the work:
         // there the 16-row kernel, whose workgroups are half as long, is the faster one as long as
@@ -1147,18 +1149,17 @@ int plan(const GaParams& P, int dtype, int head_dim, GaLaunch* L) {
         const long long blocks = (long long)((P.rows + GW_ROWS - 1) / GW_ROWS) * P.nq * P.seqs;
         const long long tile_wg = (long long)((P.ntiles + GA_WAVES - 1) / GA_WAVES) * P.nq * P.seqs, key_rows = (long long)P.seqs * P.rows * P.nkv;
         const bool tiles = P.T <= 32 && P.k >= 4 && (P.T == 1 || 32 % (P.k + 1) != 0) && tile_wg <= 256 && key_rows <= 8192;
-        L->kernel = blocks > max_wg || tiles ? GA_TILES : GA_WIDE;
-        L->attn = L->kernel == GA_WIDE ? grid_xy(blocks, 1) : dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs);
+        L.kernel = blocks > GA_MAX_WG || tiles ? GA_TILES : GA_WIDE;
+        L.attn = L.kernel == GA_WIDE ? grid_xy(blocks, 1) : dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs);
     } else {
         const long long blocks = (long long)((P.rows + GF_ROWS - 1) / GF_ROWS) * P.nq;
-        if (blocks > max_wg) return PS_ERR_UNSUPPORTED;     // (its rows would be terabytes)
-        L->kernel = GA_F32;
-        L->attn = grid_xy(blocks, P.seqs);
+        L.kernel = GA_F32;
+        L.attn = grid_xy(blocks, P.seqs);
     }
     // the rotation: a workgroup per position; where positions are few, several (of at most one item per thread each) share one's rows
-    const long long items = (long long)P.seqs * P.nkv * (head_dim / 8) * (L->kernel == GA_WIDE ? 1 : P.k + 1);
-    L->rope = dim3(P.T + P.k, (unsigned)max(1LL, min((items + 255) / 256, 2048LL / (P.T + P.k))));
-    return PS_OK;
+    const long long items = (long long)P.seqs * P.nkv * (head_dim / 8) * (L.kernel == GA_WIDE ? 1 : P.k + 1);
+    L.rope = dim3(P.T + P.k, (unsigned)max(1LL, min((items + 255) / 256, 2048LL / (P.T + P.k))));
+    return L;
 }
 
 template <typename WT, int D>
@@ -1204,8 +1205,7 @@ extern "C" int ps_group_attention(const ps_group_attn_args* a, void* stream) {
     const GaLayout L = layout(a);
     if (a->workspace_bytes < L.total || ((uintptr_t)a->workspace & 255)) return PS_ERR_WORKSPACE;
     GaParams P = shape(a);
-    GaLaunch G;
-    if (const int pl = plan(P, a->dtype, a->head_dim, &G)) return pl;
+    const GaLaunch G = plan(P, a->dtype, a->head_dim);
     P.q = a->q; P.k_ = a->k_; P.v = a->v; P.out = a->out;
     char* ws = (char*)a->workspace;
     P.table = (float2*)(ws + L.table); P.k_rot = ws + L.k_rot;
@@ -1219,8 +1219,7 @@ extern "C" int ps_train_debug_launch(const ps_group_attn_args* a, unsigned* out)
     const int st = check(a);
     if (st != PS_OK) return st;
     if (!out) return PS_ERR_NULL;
-    GaLaunch G;
-    if (const int pl = plan(shape(a), a->dtype, a->head_dim, &G)) return pl;
+    const GaLaunch G = plan(shape(a), a->dtype, a->head_dim);
     const unsigned v[8] = {(unsigned)G.kernel, G.attn.x, G.attn.y, G.attn.z, (unsigned)(G.kernel == GA_F32 ? GF_THREADS : GA_THREADS), G.rope.x, G.rope.y, 256u};
     for (int i = 0; i < 8; ++i) out[i] = v[i];
     return PS_OK;

@@ -78,6 +78,8 @@ def test_launches_stay_within_the_limits_of_a_launch(lib):
             blocks = -(-T * (k + 1) // rows_of[g["kernel"]]) * nq * (1 if g["kernel"] == 0 else seqs)
             x, y, z = g["grid"]
             assert blocks <= x * y < blocks + x and z == (seqs if g["kernel"] == 0 else 1), tag
+    huge = TR.make_args(1, 1 << 19, 15, 32768, 1, 64, "f32", 10000.0)           # 2^32 blocks of 64 rows
+    assert DBG.ps_train_debug_launch(huge)[0] == B.PS_ERR_UNSUPPORTED and TR.ps_group_attention_workspace_bytes(huge) == 0
     assert DBG.ps_train_debug_launch(TR.make_args(1, 64, 16, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_UNSUPPORTED
     assert DBG.ps_train_debug_launch(TR.make_args(0, 64, 4, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_SHAPE
 
