@@ -8,8 +8,8 @@
 // per call, and no scratch memory is used.  All arithmetic is float64; P is kept unscaled with 1 / its sum
 // beside it.  What a test needs while P is still the target's own row (the token, r, P(x), q(x)) is fetched
 // for all nodes at once when the kernel starts, so a walk without rejections reads the vocabulary only for
-// the final draw.  Two kernels: P in registers for vocabularies up to 32768 entries, P recomputed from the
-// target's and the drafter's rows for larger ones.
+// the final draw.  Two kernels: the residual in registers (vocabularies up to 32768 entries, or up to 262144 where several
+// workgroups share a sequence), and the residual recomputed from the target's and the drafter's rows (all others).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -111,12 +111,17 @@ __device__ __forceinline__ double block_exclusive_scan(double v, double* s_red, 
 
 // What the walk needs per node, fetched by one thread per node in one round of loads and left in LDS: the
 // node's links (read one after the other from the kernel arguments they would cost a scalar-cache miss
-// each), its token (-1 if outside the vocabulary), its uniform number, and what a test of the node reads
-// while P is still the target's own row at its parent: P(x) and q(x).
+// each), its token (-1 if outside the vocabulary), its uniform number, what a test of the node reads while P is
+// still the target's own row at its parent, P(x) and q(x), and how that test ends.
 struct NodeLds {
-    int tok[PS_TREE_MAX_NODES], first[PS_TREE_MAX_NODES], next[PS_TREE_MAX_NODES], depth[PS_TREE_MAX_NODES];
+    int4 link[PS_TREE_MAX_NODES];          // first child, next sibling, token, depth | NODE_ACCEPT
     float r[PS_TREE_MAX_NODES], px[PS_TREE_MAX_NODES], qx[PS_TREE_MAX_NODES];
 };
+constexpr int NODE_ACCEPT = 1 << 16;
+// Algorithm 1's test of a proposal: r < min(1, P(x) / q(x))
+__device__ __forceinline__ bool accepts(float r, double Px, double qx) {
+    return (double)r < (qx > 0.0 ? fmin(1.0, Px / qx) : 1.0);
+}
 __device__ __forceinline__ void load_nodes(const WalkParams& Wp, int b, const float* q, const float* p, NodeLds& L) {
     const int tid = threadIdx.x, V = Wp.vocab, N = Wp.t.n_nodes;
     if (tid < N) {
@@ -124,15 +129,24 @@ __device__ __forceinline__ void load_nodes(const WalkParams& Wp, int b, const fl
         if (Wp.tokens) x = Wp.tokens[(size_t)b * N + tid];
         else if (tid > 0) x = Wp.top_ids[((size_t)b * Wp.rows + (Wp.t.depth[tid] - 1)) * Wp.topk + Wp.t.rank[tid]];
         const bool ok = tid > 0 && (unsigned)x < (unsigned)V;
-        L.tok[tid] = ok ? x : -1;
-        L.first[tid] = Wp.t.first_child[tid];
-        L.next[tid] = Wp.t.next_sibling[tid];
-        L.depth[tid] = Wp.t.depth[tid];
-        L.r[tid] = Wp.r[(size_t)b * N + tid];
-        L.px[tid] = ok ? p[(size_t)Wp.t.parent[tid] * V + x] : 0.f;
-        L.qx[tid] = ok ? q[(size_t)(Wp.t.depth[tid] - 1) * V + x] : 0.f;
+        const float r = Wp.r[(size_t)b * N + tid];
+        const float px = ok ? p[(size_t)Wp.t.parent[tid] * V + x] : 0.f;
+        const float qx = ok ? q[(size_t)(Wp.t.depth[tid] - 1) * V + x] : 0.f;
+        L.r[tid] = r;
+        L.px[tid] = px;
+        L.qx[tid] = qx;
+        L.link[tid] = make_int4(Wp.t.first_child[tid], Wp.t.next_sibling[tid], ok ? x : -1,
+                                Wp.t.depth[tid] | (ok && accepts(r, (double)px, (double)qx) ? NODE_ACCEPT : 0));
     }
     __syncthreads();
+}
+// a node's links, the same in every thread
+struct NodeLink { int first, next, tok, depth; bool accept; };
+__device__ __forceinline__ NodeLink node_link(const NodeLds& L, int s) {
+    const int4 v = L.link[s];
+    const int w = __builtin_amdgcn_readfirstlane(v.w);
+    return {__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y), __builtin_amdgcn_readfirstlane(v.z),
+            w & (NODE_ACCEPT - 1), (w & NODE_ACCEPT) != 0};
 }
 
 // W consecutive vocabulary entries as one load (W = 4 needs vocab % 4 == 0 and 16-byte aligned rows)
@@ -154,7 +168,7 @@ template <> __device__ __forceinline__ void widen<4>(const float4& v, double (&o
 // draw cuts the vocabulary into slabs of W * WALK_THREADS entries: totals per slab first, then the cumulative
 // sum inside the slab in which it passes the target.
 //
-// MULTI: gridDim.x workgroups share a sequence (blockIdx.y); workgroup g takes slabs [g S, (g + 1) S) of the
+// MULTI (vocabularies beyond 262144 entries): gridDim.x workgroups share a sequence (blockIdx.y); workgroup g takes slabs [g S, (g + 1) S) of the
 // vocabulary for every sum and all of them take every decision.  A sum over the vocabulary is then the sum, in
 // workgroup order, of the workgroups' parts, which they leave for each other in exchange memory (Wp.xch: one
 // slot per sequence, round and workgroup; a slot is two 8-byte units {half of the double, tag}, written and
@@ -260,20 +274,19 @@ __global__ void __launch_bounds__(WALK_THREADS) verify_walk_kernel(const WalkPar
     const int n_slabs = MULTI ? min(Wp.slabs_per_wg, n_slabs_all - slab0) : n_slabs_all;
     const int jlo = slab0 * WALK_THREADS, nvec = min(nvec_all, jlo + n_slabs * WALK_THREADS);
     constexpr int UN = 4;                 // vectors of each row on their way at once (8: measured slower)
-    int u = 0, n_acc = 0;
-    int s = L.first[0];
+    int u = 0, u_depth = 0, n_acc = 0;
+    int s = node_link(L, 0).first;
     while (s >= 0) {   // the children of u in ascending index
-        const int x = L.tok[s];
+        const NodeLink node = node_link(L, s);
+        const int x = node.tok;
         bool accept = false;
         if (x >= 0) {
             const double qx = (double)L.qx[s];
-            const double Px = residual((double)L.px[s], qx) * s_c[J];
-            const double ratio = qx > 0.0 ? fmin(1.0, Px / qx) : 1.0;
-            accept = (double)L.r[s] < ratio;
+            accept = J > 0 ? accepts(L.r[s], residual((double)L.px[s], qx) * s_c[J], qx) : node.accept;
             if (!accept) {
                 ++J;
                 const VF* pu = reinterpret_cast<const VF*>(p + (size_t)u * V);
-                const VF* qt = reinterpret_cast<const VF*>(q + (size_t)(L.depth[s] - 1) * V);
+                const VF* qt = reinterpret_cast<const VF*>(q + (size_t)u_depth * V);
                 double local = 0.0;
                 for (int j0 = jlo + tid; j0 < nvec; j0 += WALK_THREADS * UN) {
                     VF pv[UN], qv[UN];
@@ -308,16 +321,17 @@ __global__ void __launch_bounds__(WALK_THREADS) verify_walk_kernel(const WalkPar
             }
             ++n_acc;
             u = s;
+            u_depth = node.depth;
             J = 0;
-            s = L.first[u];
+            s = node.first;
         } else {
-            s = L.next[s];
+            s = node.next;
         }
     }
 
     // The last token.  P = R_J c_J at node u; its children's draft row is row depth(u) of q (unused if J = 0).
     const VF* pu = reinterpret_cast<const VF*>(p + (size_t)u * V);
-    const VF* qt = reinterpret_cast<const VF*>(q + (size_t)(J > 0 ? L.depth[u] : 0) * V);
+    const VF* qt = reinterpret_cast<const VF*>(q + (size_t)(J > 0 ? u_depth : 0) * V);
     const double cJ = s_c[J];
     auto P_of = [&](int j, double (&o)[W]) {   // entries of vector j (j < nvec)
         double a[W], c[W];
@@ -411,169 +425,185 @@ __global__ void __launch_bounds__(WALK_THREADS) verify_walk_kernel(const WalkPar
     }
 }
 
-// The same walk for vocabularies of at most REG_EPT * REG_THREADS entries (a multiple of 4, rows 16-byte
-// aligned): P lives in registers, so a rejection only reads its row of q (and, the first time at a node, the
-// target's row) and the scratch buffer is not touched.  The vocabulary is cut into slabs of 4 * REG_THREADS
-// entries; thread t holds entries [4t, 4t + 4) of every slab, so all loads are contiguous across a wavefront.
-// P(x) of a residual goes from the thread that holds it to the others through LDS.  The final draw finds
-// the slab in which the cumulative sum passes the target from the slabs' totals, then scans that slab.
-constexpr int REG_EPT = 32, REG_THREADS = 1024, REG_WAVES = REG_THREADS / 64, REG_SLABS = REG_EPT / 4;
-__global__ void __launch_bounds__(REG_THREADS) verify_walk_reg_kernel(const WalkParams Wp) {
-    __shared__ double s_red[REG_WAVES];
-    __shared__ double s_part[REG_SLABS][REG_WAVES];
-    __shared__ double s_bc;
+// The same walk with the two rows of a node in registers (vocab a multiple of 4, rows 16-byte aligned): the residual as
+// doubles, the drafter's row as it is.  All children of a node are proposals of the same draft row, so its first rejection
+// reads the target's and the drafter's row and every further one reads nothing.  A wavefront holds a contiguous part of
+// the vocabulary (SLABS loads of 256 entries at most, as many as the vocabulary needs of every wavefront), so the parts of
+// the last sum tell which wavefront the final draw falls to, and that wavefront finishes it by itself: the draw of a
+// residual costs no further pass.  A test against a residual is the recurrence R_j = (R_{j-1} c_{j-1} - q)+ on the node's two
+// numbers, as in verify_walk_kernel, with no exchange between threads.
+//
+// One compute unit holds 32768 entries (SLABS = 8).  MULTI: gridDim.x workgroups share a sequence and exchange their
+// sums as in verify_walk_kernel; four slabs each, so 16 of them hold 262144 entries.
+//
+// What bounds a walk is its chain: two launches (of tree tokens and walk), the nodes' numbers (two dependent loads), the
+// rows of every node where a child was rejected (one compute unit takes 2 us for 256 KB), a sum over the workgroup per
+// rejection.  Trees of 61 nodes, tokens and walk, among others of their kind: one sequence of V 32000 27.9 -> 13.5 us, eight of
+// V 128256 37.3 -> 18.3 us, against this kernel with the drafter's row read again for every sibling, P(x) through LDS
+// and a pass over all slabs for the draw (and, V 128256, both rows read again for every rejection and the draw).
+constexpr int REG_SLABS = 8, REG_SLABS_MULTI = 4, REG_SLAB = 4 * WALK_THREADS;   // (entries a workgroup holds per slab of all its wavefronts)
+template <int SLABS, bool MULTI>
+__global__ void __launch_bounds__(WALK_THREADS) verify_walk_reg_kernel(const WalkParams Wp) {
+    __shared__ double s_red[2][WALK_WAVES];                // the wavefronts' parts of a sum; two that take turns: one barrier per sum
+    __shared__ double s_x[XCH_WGS + 1];
+    __shared__ double s_c[PS_TREE_MAX_NODES + 1];
+    __shared__ unsigned s_tag;
     __shared__ NodeLds L;
-    const int b = blockIdx.x, tid = threadIdx.x, V = Wp.vocab, N = Wp.t.n_nodes;
+    const int b = MULTI ? blockIdx.y : blockIdx.x, g = MULTI ? blockIdx.x : 0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int V = Wp.vocab, N = Wp.t.n_nodes;
     const float* q = Wp.q + (size_t)b * Wp.rows * V;
     const float* p = Wp.p + (size_t)b * N * V;
+    if (MULTI && tid == 0) {                               // (read after the barrier in load_nodes; see verify_walk_kernel)
+        s_x[XCH_WGS] = 0.0;
+        const unsigned t = __hip_atomic_load(xch_epoch(Wp, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        s_tag = t ? t : 1u;
+    }
     load_nodes(Wp, b, q, p, L);
+    const unsigned tag = MULTI ? s_tag : 0u;
 
-    const int nvec = V / 4;                      // float4 units; this thread's: tid + REG_THREADS * k
-    double Pr[REG_EPT];                          // P (to be scaled by inv_tot) once it is no longer a row of p:
-                                                 // Pr[4k + e] = entry 4 (tid + REG_THREADS k) + e, 0 beyond V
-    int u = 0, n_acc = 0;
-    bool fresh = true;
-    double inv_tot = 1.0;
-    // Pr <- the target's row at u (P = that row: inv_tot = 1)
-    auto load_row = [&]() {
-        const float4* pu4 = reinterpret_cast<const float4*>(p + (size_t)u * V);
-        float4 pv[REG_SLABS];
+    // this workgroup's vectors of four entries [jlo, jhi), this wavefront's from j0 on, 64 per slab
+    const int jlo = MULTI ? g * SLABS * WALK_THREADS : 0, jhi = MULTI ? min(V / 4, jlo + SLABS * WALK_THREADS) : V / 4;
+    const int slabs = (jhi - jlo + WALK_THREADS - 1) / WALK_THREADS;   // <= SLABS (host)
+    const int j0 = jlo + wave * 64 * slabs;
+    double R[4 * SLABS];                                   // the residual (times a constant), 0 beyond the vocabulary
+    float Q[4 * SLABS];                                    // the drafter's row, once a child of u has been rejected
+    auto load_row = [&](const float* __restrict__ row, float (&x)[4 * SLABS]) __attribute__((always_inline)) {
+        const float4* r4 = reinterpret_cast<const float4*>(row);
 #pragma unroll
-        for (int k = 0; k < REG_SLABS; ++k) {
-            const int j = tid + REG_THREADS * k;
-            pv[k] = j < nvec ? pu4[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int k = 0; k < REG_SLABS; ++k) {
-            Pr[4 * k] = (double)pv[k].x; Pr[4 * k + 1] = (double)pv[k].y;
-            Pr[4 * k + 2] = (double)pv[k].z; Pr[4 * k + 3] = (double)pv[k].w;
+        for (int k = 0; k < SLABS; ++k) {
+            const int j = j0 + 64 * k + lane;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k < slabs && j < jhi) v = r4[j];
+            x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
         }
     };
-    // Pr <- (Pr * inv_tot - qt)+; returns this thread's part of the sum
-    auto subtract = [&](const float* __restrict__ qt) -> double {
-        const float4* q4 = reinterpret_cast<const float4*>(qt);
-        float4 qv[REG_SLABS];
+    // the sum of the threads' parts over the workgroup (and, MULTI, over the workgroups); false if a wait ran out.  The
+    // wavefronts' parts stay in s_red[par] (the workgroups' in s_x) until the next sum
+    int par = 0, rnd = 0;
+    double total = 0.0;
+    auto sum = [&](double local) __attribute__((always_inline)) {
+        par ^= 1;
+        const double w = wave_sum_f64(local);
+        if (lane == 0) s_red[par][wave] = w;
+        __syncthreads();
+        total = 0.0;
 #pragma unroll
-        for (int k = 0; k < REG_SLABS; ++k) {
-            const int j = tid + REG_THREADS * k;
-            qv[k] = j < nvec ? q4[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        double local = 0.0;
-#pragma unroll
-        for (int k = 0; k < REG_SLABS; ++k) {
-            const float qe[4] = {qv[k].x, qv[k].y, qv[k].z, qv[k].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double v = fmax(Pr[4 * k + e] * inv_tot - (double)qe[e], 0.0);
-                Pr[4 * k + e] = v;
-                local += v;
-            }
-        }
-        return local;
-    };
-
-    int s = L.first[0];
-    while (s >= 0) {   // the children of u in ascending index
-        const int x = L.tok[s];
-        bool accept = false;
-        if (x >= 0) {
-            double Px;
-            if (fresh) {
-                Px = (double)L.px[s];
-            } else {
-                const int j = x >> 2;   // unit j is slab j / REG_THREADS of thread j % REG_THREADS
-                if (tid == (j & (REG_THREADS - 1))) {
-                    const int idx = 4 * (j / REG_THREADS) + (x & 3);
-                    double v = 0.0;
-#pragma unroll
-                    for (int e = 0; e < REG_EPT; ++e)
-                        if (e == idx) v = Pr[e];
-                    s_bc = v * inv_tot;
+        for (int i = 0; i < WALK_WAVES; ++i) total += s_red[par][i];
+        if constexpr (MULTI) {
+            if (!xch_sum(Wp, total, b, rnd++, tag, s_x, total)) {
+                if (tid == 0) {                            // the sequence is marked, its tag is used up
+                    Wp.n_accepted[b] = -2;
+                    __hip_atomic_store(xch_epoch(Wp, b), tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                __syncthreads();   // (the next write of s_bc lies behind the barriers of a block_sum)
-                Px = s_bc;
+                return false;
             }
-            const double qx = (double)L.qx[s];
-            const double ratio = qx > 0.0 ? fmin(1.0, Px / qx) : 1.0;
-            accept = (double)L.r[s] < ratio;
+        }
+        return true;
+    };
+
+    int u = 0, u_depth = 0, n_acc = 0, J = 0;              // J children of u have been rejected
+    double c = 1.0;                                        // P = R c
+    int s = node_link(L, 0).first;
+    while (s >= 0) {   // the children of u in ascending index
+        const NodeLink node = node_link(L, s);
+        bool accept = false;
+        if (node.tok >= 0) {
+            accept = node.accept;
+            if (J > 0) {
+                const double qx = (double)L.qx[s];
+                double v = fmax((double)L.px[s] - qx, 0.0);
+                for (int t = 1; t < J; ++t) v = fmax(v * s_c[t] - qx, 0.0);
+                accept = accepts(L.r[s], v * c, qx);
+            }
             if (!accept) {
-                if (fresh) load_row();
-                fresh = false;
-                const double t = block_sum<REG_WAVES>(subtract(q + (size_t)(L.depth[s] - 1) * V), s_red);
-                inv_tot = t > 0.0 ? 1.0 / t : 1.0;
+                double local = 0.0;
+                if (J == 0) {
+                    float x[4 * SLABS];
+                    load_row(p + (size_t)u * V, x);
+                    load_row(q + (size_t)u_depth * V, Q);
+#pragma unroll
+                    for (int i = 0; i < 4 * SLABS; ++i) R[i] = (double)x[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 4 * SLABS; ++i) {
+                    R[i] = fmax(R[i] * c - (double)Q[i], 0.0);
+                    local += R[i];
+                }
+                if (!sum(local)) return;
+                c = total > 0.0 ? 1.0 / total : 1.0;
+                s_c[++J] = c;                              // (every thread writes the same value and reads it back itself)
             }
         }
         if (accept) {
-            if (tid == 0) {
+            if (tid == 0 && g == 0) {
                 Wp.path[(size_t)b * Wp.rows + n_acc] = s;
-                Wp.out_tokens[(size_t)b * (Wp.rows + 1) + n_acc] = x;
+                Wp.out_tokens[(size_t)b * (Wp.rows + 1) + n_acc] = node.tok;
             }
             ++n_acc;
             u = s;
-            fresh = true;
-            inv_tot = 1.0;
-            s = L.first[u];
+            u_depth = node.depth;
+            J = 0;
+            c = 1.0;
+            s = node.first;
         } else {
-            s = L.next[s];
+            s = node.next;
         }
     }
 
-    // The last token.  Totals of the slabs (each wavefront adds up its part of every slab, the wavefronts'
-    // parts meet in LDS), the slab ks in which the cumulative sum first exceeds the target, then the
-    // cumulative sum inside that slab in id order.
-    if (fresh) load_row();
-    const int lane = tid & 63, wave = tid >> 6;
+    // The last token: the number of ids whose cumulative sum of P does not exceed r[0] times the sum of P.  The constant
+    // in R does not matter; where the last sum was that of R, its parts are still there
+    if (J == 0) {
+        float x[4 * SLABS];
+        load_row(p + (size_t)u * V, x);
+        double local = 0.0;
 #pragma unroll
-    for (int k = 0; k < REG_SLABS; ++k) {
-        double v = 0.0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            Pr[4 * k + e] *= inv_tot;   // (1 for a row of p: exact)
-            v += Pr[4 * k + e];
+        for (int i = 0; i < 4 * SLABS; ++i) {
+            R[i] = (double)x[i];
+            local += R[i];
         }
-        v = wave_sum_f64(v);
-        if (lane == 0) s_part[k][wave] = v;
-    }
-    __syncthreads();
-    double slab_tot[REG_SLABS], total = 0.0;
-#pragma unroll
-    for (int k = 0; k < REG_SLABS; ++k) {
-        double t = 0.0;
-        for (int w = 0; w < REG_WAVES; ++w) t += s_part[k][w];
-        slab_tot[k] = t;
-        total += t;
+        if (!sum(local)) return;
     }
     const double target = (double)L.r[0] * total;
-    const int n_slabs = (nvec + REG_THREADS - 1) / REG_THREADS;
-    int ks = n_slabs - 1;
-    double base = 0.0, cum = 0.0;
+    double cum = 0.0;                                      // the cumulative sum in front of what is looked at
+    if constexpr (MULTI) {                                 // the first workgroup whose cumulative sum exceeds the target (the last if none does)
+        int owner = 0;
+        while (owner + 1 < (int)gridDim.x && !(cum + s_x[owner] > target)) cum += s_x[owner++];
+        if (g != owner) return;
+    }
+    int wo = 0;                                            // ... the first wavefront
+    while (wo + 1 < WALK_WAVES && !(cum + s_red[par][wo] > target)) cum += s_red[par][wo++];
+    if (wave != wo) return;
+    double part[SLABS], mine[4] = {R[0], R[1], R[2], R[3]};
+#pragma unroll
+    for (int k = 0; k < SLABS; ++k) part[k] = wave_sum_f64((R[4 * k] + R[4 * k + 1]) + (R[4 * k + 2] + R[4 * k + 3]));
+    int ks = 0;                                            // ... the first slab
     bool found = false;
 #pragma unroll
-    for (int k = 0; k < REG_SLABS; ++k) {
-        if (k < n_slabs && !found) {
-            if (cum + slab_tot[k] > target || k == n_slabs - 1) { ks = k; base = cum; found = true; }
-            cum += slab_tot[k];
+    for (int k = 0; k + 1 < SLABS; ++k) {
+        found = found || cum + part[k] > target || k + 1 >= slabs;
+        if (!found) {
+            cum += part[k];
+            ks = k + 1;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mine[e] = R[4 * (k + 1) + e];
         }
     }
-    double mine[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < REG_SLABS; ++k)
-        if (k == ks) { mine[0] = Pr[4 * k]; mine[1] = Pr[4 * k + 1]; mine[2] = Pr[4 * k + 2]; mine[3] = Pr[4 * k + 3]; }
-    double dummy;
-    double run = base + block_exclusive_scan<REG_WAVES>(mine[0] + mine[1] + mine[2] + mine[3], s_red, dummy);
-    const int id0 = 4 * (tid + REG_THREADS * ks);
-    double cnt = 0.0;
+    const double own = (mine[0] + mine[1]) + (mine[2] + mine[3]);
+    double run = cum + wave_inclusive_scan_f64(own) - own;
+    const int first = 4 * (j0 + 64 * ks);
+    int n = first;                                         // every id before counts
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         run += mine[e];
-        if (id0 + e < V && run <= target) cnt += 1.0;
+        n += __popcll(__ballot(first + 4 * lane + e < V && run <= target));
     }
-    const int n = 4 * REG_THREADS * ks + (int)block_sum<REG_WAVES>(cnt, s_red);   // every id of the slabs before ks counts
-    if (tid == 0) {
+    if (lane == 0) {
         Wp.out_tokens[(size_t)b * (Wp.rows + 1) + n_acc] = n < V - 1 ? n : V - 1;
         for (int i = n_acc + 1; i <= Wp.rows; ++i) Wp.out_tokens[(size_t)b * (Wp.rows + 1) + i] = -1;
         for (int i = n_acc; i < Wp.rows; ++i) Wp.path[(size_t)b * Wp.rows + i] = -1;
         Wp.n_accepted[b] = n_acc;
+        if (MULTI) __hip_atomic_store(xch_epoch(Wp, b), tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -673,9 +703,9 @@ int scratch_ptr(unsigned char** out) {
 // vocabularies that take the exchange between workgroups: whole vectors of four entries, more than the
 // register kernel holds; slabs of the vocabulary per workgroup and workgroups per sequence
 bool wants_exchange(int vocab, bool aligned, int* per, int* G) {
-    if (vocab % 4 != 0 || !aligned || vocab <= REG_EPT * REG_THREADS) return false;
+    if (vocab % 4 != 0 || !aligned || vocab <= REG_SLABS * REG_SLAB) return false;
     const long long slabs = ((long long)vocab / 4 + WALK_THREADS - 1) / WALK_THREADS;
-    int p = 4;
+    int p = REG_SLABS_MULTI;
     while ((slabs + p - 1) / p > XCH_WGS) ++p;
     *per = p;
     *G = (int)((slabs + p - 1) / p);
@@ -709,8 +739,8 @@ int walk_impl(const ps_tree_shape* tree, const ps_verify_args* a, void* stream, 
         // this entry point never falls back silently: beyond what the library's own memory holds it says so
         if (exchange && (a->batch > XCH_SEQS || (long long)a->batch * G > compute_units())) return PS_ERR_UNSUPPORTED;
     }
-    if (vec && a->vocab <= REG_EPT * REG_THREADS) {
-        hipLaunchKernelGGL(verify_walk_reg_kernel, dim3(a->batch), dim3(REG_THREADS), 0, (hipStream_t)stream, W);
+    if (vec && a->vocab <= REG_SLABS * REG_SLAB) {
+        hipLaunchKernelGGL((verify_walk_reg_kernel<REG_SLABS, false>), dim3(a->batch), dim3(WALK_THREADS), 0, (hipStream_t)stream, W);
     } else if (vec) {
         // several workgroups per sequence (4 slabs each, at most XCH_WGS) when all of them get a compute unit
         // and there is exchange memory: the caller's workspace, else the library's own for up to XCH_SEQS sequences
@@ -727,7 +757,9 @@ int walk_impl(const ps_tree_shape* tree, const ps_verify_args* a, void* stream, 
             W.xch = reinterpret_cast<unsigned long long*>(mem);
             W.slabs_per_wg = per;
             W.ghosts = G < XCH_WGS ? (int)g_ghosts : 0;
-            hipLaunchKernelGGL((verify_walk_kernel<4, true>), dim3(G, a->batch), dim3(WALK_THREADS), 0, (hipStream_t)stream, W);
+            if (per == REG_SLABS_MULTI)
+                hipLaunchKernelGGL((verify_walk_reg_kernel<REG_SLABS_MULTI, true>), dim3(G, a->batch), dim3(WALK_THREADS), 0, (hipStream_t)stream, W);
+            else hipLaunchKernelGGL((verify_walk_kernel<4, true>), dim3(G, a->batch), dim3(WALK_THREADS), 0, (hipStream_t)stream, W);
         } else {
             hipLaunchKernelGGL((verify_walk_kernel<4, false>), dim3(a->batch), dim3(WALK_THREADS), 0, (hipStream_t)stream, W);
         }

@@ -106,6 +106,19 @@ def test_walk_at_the_largest_sizes():
     _check(parent, rank, inp, 9, 8, "largest")
 
 
+@pytest.mark.parametrize("vocab", [4, 252, 4096, 4100, 28676, 32768, 32772, 65540, 262144, 262148])
+def test_walks_at_the_edges_of_what_registers_hold(vocab):
+    """One vector of four ids, parts of a slab, one id quadruple more than a slab, the largest vocabularies of one and of sixteen
+    workgroups and the next ones; sums of float64 in another order: decisions are exact (see _check)."""
+    parent, rank = inputs.draft_tree([3, 2])
+    batch = 8 if vocab < 65536 else 3
+    topk = min(8, vocab)
+    for agreement in (0.2, 0.9):
+        inp = inputs.verify_inputs(900 + vocab % 89, batch, parent, rank, 3, topk, vocab, agreement=agreement)
+        inp["r"][:, 0] = np.linspace(0.0, 1.0 - 2.0 ** -24, batch).astype(np.float32)   # draws all over the vocabulary
+        _check(parent, rank, inp, 3, topk, "edge V%d agreement %.1f" % (vocab, agreement))
+
+
 def test_root_only_tree_just_draws_a_token():
     parent, rank = np.array([-1], dtype=np.int32), np.array([0], dtype=np.int32)
     inp = inputs.verify_inputs(5, 4, parent, rank, 1, 4, 777)
