@@ -552,14 +552,31 @@ __device__ __forceinline__ uint4 ld16_lds(lds_cptr p) {
     const u32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(p);
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
+// Two layouts of the panel (D.units, the host's choice).  Row by row, rows D.rs bytes apart (panel_row_stride); or in
+// units of 16 bytes, first the unit's place along the contraction (g = 4 step + kb), then the row, exchanged within its
+// 16 rows: unit (g, m) stands at g * D.rs + 16 (m ^ (g & 15)), D.rs = 16 bytes times the rows in whole sixteens.  The 64 lanes of a
+// read then hit every bank equally often, and so do 16 lanes that write consecutive units of a row; row by row a read
+// of 16 rows hits a quarter of the banks.
+template <int MT> struct PanelAddr {
+    static constexpr bool WIDE = MT >= PS_UNITS_MT;
+    lds_cptr pa[MT];                       // column c of column tile mt: its 16 bytes of step 0
+    int inc[WIDE ? 1 : MT], lo[WIDE ? 1 : MT];   // bytes between steps, from a high part to its low part
+    unsigned xm;                           // (WIDE) what of 64 (t & 3) is exchanged into the address of step t: units 0xC0, rows 0
+    __device__ __forceinline__ void advance(int steps) {   // (by a multiple of 4)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) pa[mt] += steps * inc[WIDE ? 0 : mt];
+    }
+};
 template <typename WT, int MT>
-__device__ __forceinline__ void load_b(BRegs<WT, MT>& b, const lds_cptr (&pa)[MT], const int (&pinc)[MT],
-                                       const int (&plo)[MT], int t) {
+__device__ __forceinline__ void load_b(BRegs<WT, MT>& b, const PanelAddr<MT>& A, int t) {
+    constexpr bool WIDE = PanelAddr<MT>::WIDE;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const lds_cptr p = pa[mt] + t * pinc[mt];
+        lds_cptr p = A.pa[mt];
+        if constexpr (WIDE) p = (lds_cptr)((unsigned)(size_t)p ^ (((t & 3) << 6) & A.xm));
+        p += t * A.inc[WIDE ? 0 : mt];
         b.h[mt] = ld16_lds(p);
-        if constexpr (Traits<WT>::BF) b.l[mt] = ld16_lds(p + plo[mt]);
+        if constexpr (Traits<WT>::BF) b.l[mt] = ld16_lds(p + A.lo[WIDE ? 0 : mt]);
     }
 }
 
@@ -599,25 +616,32 @@ __device__ __forceinline__ void preload_weights(uint4 (&wb)[PS_U], const char* b
 // then refills its register with step t + PS_U and reads the B operands of step t + 1.  The
 // loads of the last group start the wavefront's next stream, so when this returns wb holds the
 // head of that stream.  Every load is unconditional and only the oldest is waited for.
+// (consume_group: PS_U of the steps, A at the first of them; `last`: no step follows)
+template <typename WT, int MT>
+__device__ __forceinline__ void consume_group(uint4 (&wb)[PS_U], const char* refill, bool last, int lane16, const PanelAddr<MT>& A,
+                                              BRegs<WT, MT>& bc, f32x4 (&acc)[MT]) {
+    BRegs<WT, MT> bn;
+#pragma unroll
+    for (int u = 0; u < PS_U; ++u) {
+        mma_step<WT, MT>(wb[u], bc, acc);
+        wb[u] = ldg_stream16(refill + u * PS_WS + lane16);   // reuses the register just consumed
+        int tb = u + 1;
+        if (u == PS_U - 1 && last) tb = u;
+        load_b<WT, MT>(bn, A, tb);
+        bc = bn;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
 template <typename WT, int MT>
 __device__ __forceinline__ void consume_weights(uint4 (&wb)[PS_U], const char* wp, int n, const char* next_wp, int lane16,
-                                                const lds_cptr (&pa)[MT], const int (&pinc)[MT],
-                                                const int (&plo)[MT], f32x4 (&acc)[MT]) {
+                                                PanelAddr<MT>& A, f32x4 (&acc)[MT]) {
     constexpr int U = PS_U;
-    BRegs<WT, MT> bc, bn;
-    load_b<WT, MT>(bc, pa, pinc, plo, 0);
+    BRegs<WT, MT> bc;
+    load_b<WT, MT>(bc, A, 0);
     for (int t0 = 0; t0 < n; t0 += U) {
         const char* src = (t0 + U < n) ? wp + (size_t)(t0 + U) * PS_WS : next_wp;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            mma_step<WT, MT>(wb[u], bc, acc);
-            wb[u] = ldg_stream16(src + u * PS_WS + lane16);   // reuses the register just consumed
-            int tb = t0 + u + 1;
-            if (u == U - 1 && tb >= n) tb = n - 1;            // nothing follows the last step
-            load_b<WT, MT>(bn, pa, pinc, plo, tb);
-            bc = bn;
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        consume_group<WT, MT>(wb, src, t0 + U >= n, lane16, A, bc, acc);
+        A.advance(U);
     }
 }
 
@@ -803,8 +827,7 @@ __host__ __device__ inline int panel_row_stride(int panel_steps) {
 // LDS layout of a GEMM phase (bytes from the start of dynamic LDS)
 #define PS_LDS_SSQ PS_LDS_BASE   // [64 rows][8] partial sums of squares (RMSNorm); bytes below: see PS_LDS_BASE
 #define PS_LDS_ZERO (PS_LDS_BASE + 2048)    // 64 zero bytes: B operand of unused MFMA columns
-#define PS_LDS_RED (PS_LDS_BASE + 2304)     // [wavefronts][MT][64 lanes] f32x4: partial sums of wavefronts sharing a tile
-__host__ __device__ inline int panel_offset(int mt) { return PS_LDS_RED + PS_WAVES * mt * 1024; }
+#define PS_LDS_RED (PS_LDS_BASE + 2304)     // [wavefronts][MT][64 lanes] f32x4: partial sums of wavefronts sharing a tile (if any do)
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -814,30 +837,142 @@ __device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2_t));
 }
 
+// Sums over the wavefront of eight registers: two rounds of swaps that halve the registers (every lane keeps the half it
+// goes on with), then row sums.  Lane l gets the sums of v[2 (l / 16)] and v[2 (l / 16) + 1].
+__device__ __forceinline__ float2 wave_sum8(const float (&v)[8]) {
+    float w[4], x[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]), false, false);
+        w[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);   // lanes 0 .. 31: v[i], 32 .. 63: v[i + 4]
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(w[i]), __float_as_uint(w[i + 2]), false, false);
+        x[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);   // rows of 16 lanes: v[i], v[i + 2], v[i + 4], v[i + 6]
+    }
+    return make_float2(row_sum(x[0]), row_sum(x[1]));
+}
+
+// A thread's 16-byte groups gi of rows rb, rb + nrt, ... of the panel, as they came from memory, into LDS (see stage_piece;
+// whole: the piece lies inside K).  With many rows this is what a workgroup does longest between two streams, so the
+// checks, the zeros beyond K and the reductions of the sums of squares are kept off the elements: 48 rows, eight pieces of
+// the LM head's panel: a reduction per row took 9 us of a 270 us step.
+constexpr int PS_RB = 8;                             // rows per thread requested before any is used
+template <typename WT, int MT, int PH>
+__device__ __forceinline__ void place_rows(const StepParams& P, const PhaseDesc& D, int wave, char* smem, char* s_pa, char* s_pb, int gi,
+                                           bool gvalid, bool live, bool whole, int rb, const u32x4 (&raw)[PS_RB][Traits<WT>::GE / 4],
+                                           const float (&gn)[Traits<WT>::GE], bool fresh_ssq, bool want_ssq) {
+    constexpr bool BF = Traits<WT>::BF;
+    constexpr int GE = Traits<WT>::GE, NL = GE / 4;
+    constexpr bool from_x = PH == PH_QKV || PH == PH_FC;
+    const int lane = threadIdx.x & 63;
+    float* s_ssq = reinterpret_cast<float*>(smem + PS_LDS_SSQ);
+    const int nrt = PS_WG_THREADS >> D.g2_log, wsub = wave & (((1 << D.g2_log) >> 6) - 1), rows = D.rows, RS = D.rs;
+    const bool norm = PH == PH_QKV || PH == PH_GATEUP || (PH == PH_LMHEAD && D.norm != 0);
+    // is row r of the QKV panel an fp32 row (the input projection's output)?
+    auto fused_row = [&](int r) __attribute__((always_inline)) {
+        return PH == PH_QKV && P.in_mode == PS_IN_FUSED && r - row_seq(P, r) * P.M < P.n_new;
+    };
+    float ss[PS_RB];
+#pragma unroll
+    for (int i = 0; i < PS_RB; ++i) {
+        const int r = rb + nrt * i;
+        ss[i] = 0.f;
+        if (r >= rows) continue;
+        float v[GE];
+        if (from_x && !fused_row(r)) {
+            unpack_group<WT>(make_uint4(raw[i][0][0], raw[i][0][1], raw[i][0][2], raw[i][0][3]), v);
+        } else {
+#pragma unroll
+            for (int h = 0; h < NL; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[4 * h + j] = __uint_as_float(raw[i][h][j]);
+        }
+        if (!whole) {
+#pragma unroll
+            for (int e = 0; e < GE; ++e) v[e] = live ? v[e] : 0.f;
+        }
+        if (PH == PH_QKV) {
+            // (the step's input rows of slots a sequence does not use are zero rows; the host array is read: this
+            // runs before the workgroup's first barrier)
+            const int b = row_seq(P, r), ii = r - b * P.M;
+            if (ii < P.skip[b]) {
+#pragma unroll
+                for (int e = 0; e < GE; ++e) v[e] = 0.f;
+            }
+        }
+        if (norm) {
+#pragma unroll
+            for (int e = 0; e < GE; ++e) { ss[i] += v[e] * v[e]; v[e] *= gn[e]; }
+            ss[i] = gvalid ? ss[i] : 0.f;            // (a thread without a group of its own repeats another's)
+        }
+        if (gvalid) {
+            const int at = MT >= PS_UNITS_MT && D.units ? gi * RS + ((r ^ (gi & 15)) << 4) : r * RS + gi * 16;
+            if constexpr (BF) {
+                uint4 ph4, pl4;
+                unsigned* hp = &ph4.x;
+                unsigned* lp = &pl4.x;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned hi = pack_bf16x2(v[2 * j], v[2 * j + 1]);
+                    hp[j] = hi;
+                    lp[j] = pack_bf16x2(v[2 * j] - __uint_as_float(hi << 16), v[2 * j + 1] - __uint_as_float(hi & 0xFFFF0000u));
+                }
+                *reinterpret_cast<uint4*>(s_pa + at) = ph4;
+                *reinterpret_cast<uint4*>(s_pb + at) = pl4;
+            } else {
+                *reinterpret_cast<uint4*>(s_pa + at) =
+                    make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);           // (rows side by side cost registers)
+    }
+    if (norm && want_ssq) {
+        const float2 t = wave_sum8(ss);
+        if ((lane & 15) < 2) {                       // two lanes of every sixteen
+            const int rr = rb + nrt * (2 * (lane >> 4) + (lane & 1));
+            if (rr < rows) {
+                float* s = s_ssq + rr * 8 + wsub;
+                const float x = lane & 1 ? t.y : t.x;
+                *s = fresh_ssq ? x : *s + x;
+            }
+        }
+    }
+}
+
+// has everything that was requested been written? ("not written yet" is the largest 32-bit word)
+template <int NL>
+__device__ __forceinline__ bool sx_ok_rows(const u32x4 (&raw)[PS_RB][NL]) {
+    unsigned top = 0;
+#pragma unroll
+    for (int i = 0; i < PS_RB; ++i)
+#pragma unroll
+        for (int h = 0; h < NL; ++h) top = max(max(top, max(raw[i][h][0], raw[i][h][1])), max(raw[i][h][2], raw[i][h][3]));
+    return top != PS_SENT;
+}
+
 // Stages steps [a_step, a_step + nsteps) of the activation panel.  The 16-byte groups of a row
 // lie along 2^g2_log threads, the remaining threads take different rows; every thread requests
 // its group of RB rows before it uses any of them (one memory round trip per RB rows), and
 // re-requests them until none holds the "not written" pattern.  The panel holds x (.) gain
 // (RMSNorm's 1/rms is applied in the epilogue); the sum of x^2 of row r over the groups a
 // wavefront saw goes to s_ssq[8 r + w] (w = the wavefront's index along the row).
-template <typename WT, int PH>
+template <typename WT, int MT, int PH>
 __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc& D, int wave, char* smem,
                                             char* s_pa, char* s_pb, int a_step, int nsteps, bool first_piece,
                                             bool want_ssq) {
-    constexpr bool BF = Traits<WT>::BF;
     constexpr int KSTEP = Traits<WT>::KSTEP, GE = Traits<WT>::GE, ESZ = Traits<WT>::ESZ;
     constexpr int NL = GE / 4;                       // 16-byte loads per group of exchanged fp32
-    constexpr int RB = 8;                            // rows per thread requested before any is used
+    constexpr int RB = PS_RB;
     constexpr bool from_x = PH == PH_QKV || PH == PH_FC;   // the step's inputs, complete at launch
-    const int tid = threadIdx.x, lane = tid & 63;
-    float* s_ssq = reinterpret_cast<float*>(smem + PS_LDS_SSQ);
+    const int tid = threadIdx.x;
     const int G = nsteps * 4;
     const int g2_log = D.g2_log, G2 = 1 << g2_log;
     // rows are wavefront-uniform (2^g2_log >= 64 threads lie along a row): everything that
     // depends only on the row is scalar arithmetic
     const int gi0 = tid & (G2 - 1), rsub = (wave << 6) >> g2_log, nrt = PS_WG_THREADS >> g2_log;
-    const int wsub = wave & ((G2 >> 6) - 1);
-    const int rows = D.rows, K = D.K, RS = D.rs, ld = D.src_ld;
+    const int rows = D.rows, K = D.K, ld = D.src_ld;
     const bool norm = PH == PH_QKV || PH == PH_GATEUP || (PH == PH_LMHEAD && D.norm != 0);
     const int in_mode = P.in_mode;
     // where the rows come from.  QKV: the real rows of Z by input mode (see StepParams), the [MASK] rows from
@@ -846,10 +981,6 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
                                 : PH != PH_QKV ? (const void*)act_ptr(P, D.src)
                                 : in_mode == PS_IN_HIDDEN ? P.x : in_mode == PS_IN_TOKENS ? P.embed : (const void*)act_ptr(P, P.x_buf));
     const rsrc_t rmask = make_rsrc(PH == PH_FC ? P.embed : P.mask_emb);
-    // is row r of the QKV panel an fp32 row (the input projection's output)?
-    auto fused_row = [&](int r) __attribute__((always_inline)) {
-        return PH == PH_QKV && in_mode == PS_IN_FUSED && r - row_seq(P, r) * P.M < P.n_new;
-    };
     for (int gc = 0; gc < G; gc += G2) {
         const int gi = gc + gi0;
         const bool gvalid = gi < G;
@@ -896,12 +1027,7 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
                     }
                 }
                 if (from_x) break;
-                bool ok = true;
-#pragma unroll
-                for (int i = 0; i < RB; ++i)
-#pragma unroll
-                    for (int h = 0; h < NL; ++h) ok = ok && sx_ok(raw[i][h]);
-                if (__all(ok) || !spin_again(P, spins)) break;   // produced earlier in this step: wait for it
+                if (__all(sx_ok_rows<NL>(raw)) || !spin_again(P, spins)) break;   // produced earlier in this step: wait for it
                 // Not all there yet: until this thread's columns of one row are, only those are asked for (a tile's rows
                 // are stored together).  Everybody asking for whole panels again and again is traffic that the
                 // producers' own accesses queue behind: 1 .. 2.5 % of a step of the small shapes (H 256 and 512, where most
@@ -914,57 +1040,72 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
                     }
                 }
             }
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const int r = rb + nrt * i;
-                if (r >= rows) continue;
-                float v[GE];
-                if (from_x && !fused_row(r)) {
-                    unpack_group<WT>(make_uint4(raw[i][0][0], raw[i][0][1], raw[i][0][2], raw[i][0][3]), v);
-                } else {
-#pragma unroll
-                    for (int h = 0; h < NL; ++h)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) v[4 * h + j] = __uint_as_float(raw[i][h][j]);
-                }
-                // (the step's input rows of slots a sequence does not use are zero rows; the host array is read: this
-                // runs before the workgroup's first barrier)
-                bool zero_row = !live;
-                if (PH == PH_QKV) {
-                    const int b = row_seq(P, r), ii = r - b * P.M;
-                    zero_row = zero_row || ii < P.skip[b];
-                }
-                float ss = 0.f;
-#pragma unroll
-                for (int e = 0; e < GE; ++e) {
-                    if (zero_row) v[e] = 0.f;
-                    if (norm) { ss += v[e] * v[e]; v[e] *= gn[e]; }
-                }
-                if (gvalid) {
-                    if constexpr (BF) {
-                        uint4 ph4, pl4;
-                        unsigned* hp = &ph4.x;
-                        unsigned* lp = &pl4.x;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const unsigned hi = pack_bf16x2(v[2 * j], v[2 * j + 1]);
-                            hp[j] = hi;
-                            lp[j] = pack_bf16x2(v[2 * j] - __uint_as_float(hi << 16), v[2 * j + 1] - __uint_as_float(hi & 0xFFFF0000u));
-                        }
-                        *reinterpret_cast<uint4*>(s_pa + r * RS + gi * 16) = ph4;
-                        *reinterpret_cast<uint4*>(s_pb + r * RS + gi * 16) = pl4;
-                    } else {
-                        *reinterpret_cast<uint4*>(s_pa + r * RS + gi * 16) =
-                            make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
-                    }
-                }
-                if (norm && want_ssq) {
-                    ss = wave_sum(ss);
-                    if (lane == 0) s_ssq[r * 8 + wsub] = (first_piece && gc == 0) ? ss : s_ssq[r * 8 + wsub] + ss;
-                }
-            }
+            place_rows<WT, MT, PH>(P, D, wave, smem, s_pa, s_pb, gi, gvalid, live, (a_step + nsteps) * KSTEP <= K, rb, raw, gn, first_piece && gc == 0, want_ssq);
         }
     }
+}
+
+// A later piece of a panel that does not fit in LDS as a whole, requested while the piece before it is streamed (D.ahead:
+// a thread's share is one group of up to PS_RB rows).  These reads go through the L2: the 32 workgroups of an XCD read the same
+// piece, and past the L2 that is as many bytes again as the weights are.  A plain load of this kernel returns what the
+// kernel before left in memory - "not written yet" - or something newer, so the check for that pattern, when the
+// piece is placed, still tells; what was read too early is read again past the L2.
+template <typename WT> struct PieceAhead {
+    u32x4 raw[PS_RB][Traits<WT>::GE / 4];
+    uint4 gain;
+    // no instruction: what the registers held is not needed any more (the compiler cannot see that a piece is placed only
+    // where one was requested, and would keep the last one's registers through the streaming loop)
+    __device__ __forceinline__ void forget() {
+        u32x4 g;
+        asm volatile("" : "=v"(g));
+        gain = make_uint4(g[0], g[1], g[2], g[3]);
+#pragma unroll
+        for (int i = 0; i < PS_RB; ++i)
+#pragma unroll
+            for (int h = 0; h < Traits<WT>::GE / 4; ++h) asm volatile("" : "=v"(raw[i][h]));
+    }
+};
+template <typename WT>
+__device__ __forceinline__ void request_piece(const StepParams& P, const PhaseDesc& D, int wave, int a_step, int nsteps, PieceAhead<WT>& x) {
+    constexpr int KSTEP = Traits<WT>::KSTEP, GE = Traits<WT>::GE, ESZ = Traits<WT>::ESZ, NL = GE / 4;
+    const int rsub = (wave << 6) >> D.g2_log, nrt = PS_WG_THREADS >> D.g2_log;
+    const int gi = min((int)threadIdx.x & ((1 << D.g2_log) - 1), nsteps * 4 - 1);
+    const int kk = a_step * KSTEP + gi * GE, kkc = kk < D.K ? kk : 0;
+    const rsrc_t rs = make_rsrc(act_ptr(P, D.src));
+    x.gain = ld16(D.norm ? (const char*)D.gain + (size_t)kkc * ESZ : (const char*)P.ph[PH_LMHEAD].wpack);
+#pragma unroll
+    for (int i = 0; i < PS_RB; ++i) {
+        const int srow = lm_src_row(P, min(rsub + nrt * i, D.rows - 1));   // clamped: every load is unconditional
+#pragma unroll
+        for (int h = 0; h < NL; ++h) x.raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kkc + 4 * h) * 4, srow * D.src_ld * 4, 0);
+    }
+}
+template <typename WT, int MT>
+__device__ __forceinline__ void place_piece(const StepParams& P, const PhaseDesc& D, int wave, char* smem, char* s_pa, char* s_pb, int a_step,
+                                            int nsteps, PieceAhead<WT>& x, bool want_ssq) {
+    constexpr int KSTEP = Traits<WT>::KSTEP, GE = Traits<WT>::GE, NL = GE / 4;
+    const int rsub = (wave << 6) >> D.g2_log, nrt = PS_WG_THREADS >> D.g2_log;
+    const int gi = (int)threadIdx.x & ((1 << D.g2_log) - 1);
+    const bool gvalid = gi < nsteps * 4;
+    const int kk = a_step * KSTEP + (gvalid ? gi : nsteps * 4 - 1) * GE, kkc = kk < D.K ? kk : 0;
+    float gn[GE];
+    unpack_group<WT>(x.gain, gn);
+    auto all_there = [&]() __attribute__((always_inline)) {
+        return __all(sx_ok_rows<NL>(x.raw));
+    };
+    if (!all_there()) {
+        const rsrc_t rs = make_rsrc(act_ptr(P, D.src));
+        int spins = 0;
+        do {
+#pragma unroll
+            for (int i = 0; i < PS_RB; ++i) {
+                const int srow = lm_src_row(P, min(rsub + nrt * i, D.rows - 1));
+#pragma unroll
+                for (int h = 0; h < NL; ++h) x.raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kkc + 4 * h) * 4, srow * D.src_ld * 4, PS_SC1);
+            }
+        } while (!all_there() && spin_again(P, spins));
+    }
+    place_rows<WT, MT, PH_LMHEAD>(P, D, wave, smem, s_pa, s_pb, gi, gvalid, gvalid && kk < D.K, (a_step + nsteps) * KSTEP <= D.K, rsub, x.raw, gn, false, want_ssq);
 }
 
 // Softmax statistics and top-k of the logits a workgroup holds in LDS (s_lm[local tile][row][16]) for its
@@ -1125,9 +1266,11 @@ __device__ __forceinline__ void gemm_phase(const StepParams& P, int wg, int wave
 
     char* s_zero = smem + PS_LDS_ZERO;
     char* s_red = smem + PS_LDS_RED;
-    char* s_pa = smem + panel_offset(MT);                        // high parts (or f32 values)
-    char* s_pb = s_pa + rows * RS;                               // low parts (bf16 only)
-    float* s_lm = reinterpret_cast<float*>(s_pb + (BF ? rows * RS : 0));
+    char* s_pa = smem + D.panel_off;                             // high parts (or f32 values)
+    const bool units = MT >= PS_UNITS_MT && D.units;
+    const int part = units ? D.piece_groups * PS_U * 4 * RS : rows * RS;
+    char* s_pb = s_pa + part;                                    // low parts (bf16 only)
+    float* s_lm = reinterpret_cast<float*>(s_pb + (BF ? part : 0));
     const float* s_ssq = reinterpret_cast<const float*>(smem + PS_LDS_SSQ);
     const int nsub = (1 << D.g2_log) >> 6;                       // entries of s_ssq per row
     const bool norm = PH == PH_QKV || PH == PH_GATEUP || (PH == PH_LMHEAD && D.norm != 0);
@@ -1139,20 +1282,30 @@ __device__ __forceinline__ void gemm_phase(const StepParams& P, int wg, int wave
         if (publish_seq) *(lds_u32*)(unsigned)PS_LDS_SEQ = publish_seq;
         return;
     }
-    if (tid < 16) reinterpret_cast<uint32_t*>(s_zero)[tid] = 0u;
+    if (!PanelAddr<MT>::WIDE && tid < 16) reinterpret_cast<uint32_t*>(s_zero)[tid] = 0u;
     if (ph == PH_LMHEAD) {
         const int n_lm = D.rounds * SL * rows * 16;
         for (int x = tid; x < n_lm; x += PS_WG_THREADS) s_lm[x] = -INFINITY;
     }
 
     // per-lane panel addressing: column c of column tile mt is activation row 16 mt + c
-    lds_cptr pa[MT];
-    int pinc[MT], plo[MT];
+    PanelAddr<MT> pa;
+    if constexpr (PanelAddr<MT>::WIDE) {         // (columns without a row repeat the last row: nobody uses their results)
+        pa.xm = units ? 0xC0u : 0u;
+        pa.inc[0] = units ? 4 * RS : 64;
+        pa.lo[0] = part;
+    }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int m = 16 * mt + c;
-        if (m < rows) { pa[mt] = (lds_cptr)(s_pa + m * RS + kb * 16); pinc[mt] = 64; plo[mt] = (int)(s_pb - s_pa); }
-        else { pa[mt] = (lds_cptr)(s_zero + kb * 16); pinc[mt] = 0; plo[mt] = 0; }
+        if constexpr (PanelAddr<MT>::WIDE) {
+            const int mm = min(m, rows - 1);
+            pa.pa[mt] = (lds_cptr)(s_pa + (units ? kb * RS + ((mm ^ kb) << 4) : mm * RS + kb * 16));
+        } else if (m < rows) {
+            pa.pa[mt] = (lds_cptr)(s_pa + m * RS + kb * 16); pa.inc[mt] = 64; pa.lo[mt] = part;
+        } else {
+            pa.pa[mt] = (lds_cptr)(s_zero + kb * 16); pa.inc[mt] = 0; pa.lo[mt] = 0;
+        }
     }
     int sg_lo, sg_hi;
     slice_groups(D, s, sg_lo, sg_hi);
@@ -1174,43 +1327,97 @@ __device__ __forceinline__ void gemm_phase(const StepParams& P, int wg, int wave
         }
     }
 
+    // The parts of the work, one stream of a piece's steps each: tile by tile, all pieces of the panel for each; or (LM head with
+    // several rounds and pieces) piece by piece, so that the panel is staged once and not once per round, the
+    // tiles' sums waiting where their logits will stand
     bool streamed = false;
-    for (int rd = 0; rd < D.rounds; ++rd) {
+    constexpr bool may_ahead = PH == PH_LMHEAD;
+    const bool by_piece = may_ahead && D.by_piece;
+    PieceAhead<WT> next_piece;                                   // (may_ahead, D.ahead: the piece to be placed next)
+    f32x4 acc[MT];
+    int rd2 = 0, pc2 = 0;
+    for (bool more = true; more;) {
+        const int rd = rd2, pc = pc2;
+        if (by_piece) {
+            if (++rd2 == D.rounds) { rd2 = 0; ++pc2; }
+            more = pc2 < D.npieces;
+        } else {
+            if (++pc2 == D.npieces) { pc2 = 0; ++rd2; }
+            more = rd2 < D.rounds;
+        }
         const int tau = tile_index(D, rd, slot, j);
         const bool valid = tau < D.T;
-        f32x4 acc[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int pc = 0; pc < D.npieces; ++pc) {
-            const int g_lo = sg_lo + pc * D.piece_groups;
-            const int ng = min(D.piece_groups, sg_hi - g_lo);
-            if (rd == 0 || D.npieces > 1) {   // a panel that fits as a whole is staged once
-                if (rd > 0 || pc > 0) __syncthreads();   // everyone is done with the previous piece
-                stage_piece<WT, PH>(P, D, wave, smem, s_pa, s_pb, g_lo * PS_U, ng * PS_U, pc == 0, rd == 0);
-                if (publish_seq && rd == 0 && pc == 0) *(lds_u32*)(unsigned)PS_LDS_SEQ = publish_seq;   // see step_read
-                __syncthreads();
-                if (rd == 0 && pc == 0) {
-#pragma unroll
-                    for (int i = 0; i < (PS_PF > 0 ? PS_PF : 0); ++i) asm volatile("" ::"v"(pf[i]));
-                    stamp(P, wg, SB + 1);
+        const int g_lo = sg_lo + pc * D.piece_groups;
+        const int ng = min(D.piece_groups, sg_hi - g_lo);
+        const bool first = rd == 0 && pc == 0;
+        if (rd == 0 || (D.npieces > 1 && !by_piece)) {   // a panel that fits as a whole is staged once
+            if (!first) __syncthreads();             // everyone is done with the previous piece
+            bool placed = false;
+            if constexpr (may_ahead) {
+                if (D.ahead && !first) {
+                    place_piece<WT, MT>(P, D, wave, smem, s_pa, s_pb, g_lo * PS_U, ng * PS_U, next_piece, rd == 0);
+                    placed = true;
                 }
             }
-            if (valid) {
-                int a0, n, na, nn;
-                const char* wp = stream_ptr(D, tau, g_lo, ng, kw, a0, n);
-                const char* next_wp = after_wp;
-                if (pc + 1 < D.npieces) {
-                    const int g2 = g_lo + D.piece_groups;
-                    next_wp = stream_ptr(D, tau, g2, min(D.piece_groups, sg_hi - g2), kw, na, nn);
-                } else if (rd + 1 < D.rounds && tile_index(D, rd + 1, slot, j) < D.T) {
-                    next_wp = stream_ptr(D, tile_index(D, rd + 1, slot, j), sg_lo, min(D.piece_groups, sg_hi - sg_lo), kw, na, nn);
-                }
-                lds_cptr pa_t[MT];
+            if (!placed) stage_piece<WT, MT, PH>(P, D, wave, smem, s_pa, s_pb, g_lo * PS_U, ng * PS_U, pc == 0, rd == 0);
+            if (publish_seq && first) *(lds_u32*)(unsigned)PS_LDS_SEQ = publish_seq;   // see step_read
+            __syncthreads();
+            if (first) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) pa_t[mt] = pa[mt] + a0 * pinc[mt];
-                consume_weights<WT, MT>(wb, wp, n, next_wp, lane16, pa_t, pinc, plo, acc);
-                streamed = true;
+                for (int i = 0; i < (PS_PF > 0 ? PS_PF : 0); ++i) asm volatile("" ::"v"(pf[i]));
+                stamp(P, wg, SB + 1);
             }
+        }
+        if constexpr (may_ahead) next_piece.forget();
+        // the tile's sum so far: lane (c, kb) has rows 16 mt + c, tile rows 4 kb .. 4 kb + 3
+        auto waiting_sum = [&](int mt) __attribute__((always_inline)) {
+            return reinterpret_cast<f32x4*>(s_lm + ((size_t)(rd * SL + slot) * rows + min(16 * mt + c, rows - 1)) * 16 + 4 * kb);
+        };
+        if (pc == 0 || !valid) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        } else if (by_piece) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = *waiting_sum(mt);
+        }
+        // another piece comes next (the panel's first again, for the next round's tiles): requested before this one is done
+        const bool ahead = may_ahead && D.ahead && more && (!by_piece || rd2 == 0);
+        const int g_next = sg_lo + pc2 * D.piece_groups;
+        if (valid) {
+            int a0, n, na, nn;
+            const char* wp = stream_ptr(D, tau, g_lo, ng, kw, a0, n);
+            const char* next_wp = after_wp;
+            // (the tiles of a wavefront come to an end before its rounds do, if at all)
+            const int tau2 = tile_index(D, rd2, slot, j);
+            const int tau_n = tau2 < D.T ? tau2 : tile_index(D, 0, slot, j), pc_n = tau2 < D.T ? pc2 : pc2 + 1;
+            if (more && (by_piece ? pc_n < D.npieces : tau2 < D.T)) {
+                const int g2 = sg_lo + pc_n * D.piece_groups;
+                next_wp = stream_ptr(D, tau_n, g2, min(D.piece_groups, sg_hi - g2), kw, na, nn);
+            }
+            PanelAddr<MT> pa_t = pa;
+            pa_t.advance(a0);
+            // (the last PS_U steps run straight on: there the compiler can count the weight loads in front of the piece's)
+            const int n_loop = ahead ? n - PS_U : n;
+            consume_weights<WT, MT>(wb, wp, n_loop, ahead ? wp + (size_t)n_loop * PS_WS : next_wp, lane16, pa_t, acc);
+            if constexpr (may_ahead) {
+                if (ahead) {
+                    request_piece<WT>(P, D, wave, g_next * PS_U, min(D.piece_groups, sg_hi - g_next) * PS_U, next_piece);
+                    BRegs<WT, MT> bc;
+                    load_b<WT, MT>(bc, pa_t, 0);
+                    consume_group<WT, MT>(wb, next_wp, true, lane16, pa_t, bc, acc);
+                }
+            }
+            streamed = true;
+        } else if constexpr (may_ahead) {
+            if (ahead) request_piece<WT>(P, D, wave, g_next * PS_U, min(D.piece_groups, sg_hi - g_next) * PS_U, next_piece);
+        }
+        if (pc + 1 < D.npieces) {                    // the tile goes on with another piece
+            if (by_piece && valid) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    if (16 * mt + c < rows) *waiting_sum(mt) = acc[mt];
+            }
+            continue;
         }
         if (rd == D.rounds - 1) stamp(P, wg, SB + 2);
 

@@ -388,7 +388,12 @@ int panel_row_stride_host(int panel_steps) {
     const int len = panel_steps * 64;
     return len + ((64 - (len & 255)) + 256) % 256;
 }
-static int panel_offset_host(int mt) { return PS_LDS_BASE + 2304 + PS_WAVES * mt * 1024; }   // see PS_LDS_RED in ps_device.h
+// bytes of one part (float32 values, or the high or low parts) of a panel: see PanelAddr
+static long long panel_part_host(int rows, bool units, int panel_steps) {
+    return units ? (long long)panel_steps * 4 * ((rows + 15) / 16 * 256) : (long long)rows * panel_row_stride_host(panel_steps);
+}
+// where a panel starts in LDS: see PS_LDS_RED in ps_device.h (shared: several wavefronts share a tile)
+static int panel_offset_host(int mt, bool shared) { return PS_LDS_BASE + 2304 + (shared ? PS_WAVES * mt * 1024 : 0); }
 
 // Cuts one GEMM phase: T tiles x Kt steps (K elements) over nwg workgroups of PS_WAVES wavefronts.
 //
@@ -412,7 +417,7 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
     // the LM head whose activation panel does not fit in LDS as a whole (many rows): a workgroup
     // that needs only 1/S of the panel stages it in far fewer pieces.
     int s_log = 0;
-    const bool whole_fits = (long long)rows * arrays * panel_row_stride_host(ktp) <= lds_limit - panel_offset_host(mt) - 256;
+    const bool whole_fits = arrays * panel_part_host(rows, false, ktp) <= lds_limit - panel_offset_host(mt, true) - 256;
     if (ph == PH_OPROJ || ph == PH_DOWN || ph == PH_FC || (ph != PH_LMHEAD && !whole_fits))
         while (s_log < 3 && (2 << s_log) <= NG && (2 << s_log) <= nwg) ++s_log;
     if (override_[0] > 0 && ph != PH_LMHEAD) {
@@ -441,26 +446,53 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
             const int kw = 1 << best_log, SL = PS_WAVES >> best_log;
             const int per_round = Gs * SL;
             const int rounds = (T + per_round - 1) / per_round;
-            const int fixed = panel_offset_host(mt) + (ph == PH_LMHEAD ? rounds * SL * rows * 64 : 0);
+            const int panel_off = panel_offset_host(mt, kw > 1);
+            const int fixed = panel_off + (ph == PH_LMHEAD ? rounds * SL * rows * 64 : 0);
             const int budget = lds_limit - fixed - 256;
             if (budget <= 0) continue;
-            // fewest pieces whose panel fits; every slice must have the same number of pieces, each of
-            // at least kw groups (the streaming loop relies on it)
-            int np = 1;
-            while (np <= max_slice && (long long)rows * arrays * panel_row_stride_host((max_slice + np - 1) / np * PS_U) > budget) ++np;
-            if (np > max_slice) continue;
-            const int pg = (max_slice + np - 1) / np;
-            const int npieces = (max_slice + pg - 1) / pg;
-            if ((min_slice + pg - 1) / pg != npieces) continue;
-            const int last = min_slice - (npieces - 1) * pg;   // smallest last piece over the slices
-            if (pg < kw || last < kw) continue;
+            // Fewest pieces whose panel fits; every slice must have the same number of pieces, each of
+            // at least kw groups (the streaming loop relies on it).  The LM head's pieces after the first are requested
+            // ahead if a thread's share of one is a single group of at most 8 rows (see request_piece): rather more
+            // pieces than none requested ahead
+            struct Cut { int pg, npieces, g2_log; bool ahead; };
+            auto cut = [&](bool units, Cut* x) {
+                int np = 1;
+                while (np <= max_slice && arrays * panel_part_host(rows, units, (max_slice + np - 1) / np * PS_U) > budget) ++np;
+                if (np > max_slice) return false;
+                auto make = [&](int pg) {
+                    x->pg = pg;
+                    x->npieces = (max_slice + pg - 1) / pg;
+                    x->g2_log = 6;
+                    while ((1 << x->g2_log) < pg * PS_U * 4 && (1 << x->g2_log) < PS_WG_THREADS) ++x->g2_log;
+                    x->ahead = ph == PH_LMHEAD && x->npieces > 1 && pg * PS_U * 4 <= (1 << x->g2_log) && rows <= (PS_WG_THREADS >> x->g2_log) * 8;
+                    const int last = min_slice - (x->npieces - 1) * pg;   // smallest last piece over the slices
+                    return (min_slice + pg - 1) / pg == x->npieces && pg >= kw && last >= kw;
+                };
+                const int pg = (max_slice + np - 1) / np;
+                if (ph == PH_LMHEAD && np > 1)
+                    for (int n = np; n <= max_slice; ++n)
+                        if (make((max_slice + n - 1) / n) && x->ahead) return true;
+                return make(pg);
+            };
+            // Panel layout: in units from 17 rows on (see PanelAddr), unless the whole sixteens of rows that this takes make
+            // more pieces.  us, units / rows, 7B shape: 48 rows 253 / 262, 27 rows 203.6 / 204.0, 42 rows 226.5 / 229.1; 8B shape with
+            // V 128256: 42 rows (as many pieces) 380 / 385, 18 rows (more pieces) 310 / 304, 36 rows 369 / 349
+            Cut by_rows, by_units;
+            const bool rows_fit = cut(false, &by_rows), units_fit = rows > 16 && cut(true, &by_units);
+            if (!rows_fit && !units_fit) continue;
+            const bool units = units_fit && (!rows_fit || by_units.npieces <= by_rows.npieces);
+            const Cut x = units ? by_units : by_rows;
             d->T = T; d->Kt = ktp; d->K = K; d->rows = rows; d->kw_log = best_log; d->s_log = s_log; d->Gs = Gs;
-            d->nwg = nwg; d->per_round = per_round; d->rounds = rounds; d->piece_groups = pg; d->npieces = npieces;
-            d->rs = panel_row_stride_host(pg * PS_U);
-            int g2 = 6;
-            while ((1 << g2) < pg * PS_U * 4 && (1 << g2) < PS_WG_THREADS) ++g2;
-            d->g2_log = g2;
-            d->lds_bytes = fixed + rows * arrays * d->rs + 256;
+            d->nwg = nwg; d->per_round = per_round; d->rounds = rounds; d->piece_groups = x.pg; d->npieces = x.npieces;
+            d->panel_off = panel_off;
+            d->units = units;
+            d->rs = units ? (rows + 15) / 16 * 256 : panel_row_stride_host(x.pg * PS_U);
+            d->g2_log = x.g2_log;
+            d->lds_bytes = fixed + arrays * (int)panel_part_host(rows, units, x.pg * PS_U) + 256;
+            d->ahead = x.ahead;
+            // The tiles' sums can wait in the place of their logits, so the panel of an LM head of several rounds is staged
+            // once, not once per round (8B shape, V 128256, 24 rows: 346 -> 309 us, 42 rows: 494 -> 385)
+            d->by_piece = ph == PH_LMHEAD && x.npieces > 1 && rounds > 1 && kw == 1;
             // The longer the wait for the activations (the more of them the previous phase has to
             // produce), the more weights fit into it: one 8-KiB piece per wavefront for up to ~110 KB of
             // fp32 activations, two beyond, unless there are several column tiles of rows (then the

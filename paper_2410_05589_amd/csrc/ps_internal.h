@@ -22,6 +22,8 @@
 #ifndef PS_PF
 #define PS_PF 2            // at most this many 8-KiB pieces of its first weight stream a wavefront pulls into the L2 while it waits
 #endif
+// column tiles of rows (of 16) from which on the kernels know the panel layout in units (see PanelAddr)
+#define PS_UNITS_MT 2
 #define PS_U_MAX 32        // packed weight buffers are padded by this many KiB (streaming reads ahead)
 #define PS_LDS_BYTES (160 * 1024)
 // The first PS_LDS_BASE bytes of dynamic LDS are the same in every phase's layout: what a workgroup reads once
@@ -84,9 +86,13 @@ struct PhaseDesc {
     int rounds;
     int piece_groups;  // groups of the activation panel held in LDS at a time
     int npieces;
-    int rs;            // bytes between panel rows in LDS
+    int by_piece;      // LM head: piece by piece, all rounds of tiles for each (else tile by tile, all pieces for each)
+    int panel_off;     // where the panel starts in LDS
+    int units;         // layout of the panel in LDS (see PanelAddr)
+    int rs;            // bytes between panel rows (units: between the units of consecutive places along the contraction)
     int g2_log;        // staging: log2 of the threads laid along the contraction dimension
     int src_ld;        // elements between rows of src
+    int ahead;         // LM head: pieces of the panel after the first are requested while the piece before is streamed
     int lds_bytes;     // dynamic LDS the phase needs
     int pf;            // 8-KiB pieces of the first stream to pull into the L2 during the wait for the panel (<= PS_PF)
     const void* gain;  // RMSNorm gain (config dtype)

@@ -185,6 +185,24 @@ def test_maximum_rows_and_topk():
     _run_case(wl, all_rows=True, topk=1, label="64 rows, all decoded, top-1")
 
 
+@pytest.mark.parametrize("dtype,hidden,steps", [("bf16", 2048, ((17, 0), (11, 2), (8, 5), (8, 7), (9, 1))), ("f32", 1024, ((11, 2), (8, 7)))])
+def test_lm_head_panels_of_several_pieces_and_rounds(dtype, hidden, steps):
+    """A vocabulary of two rounds of tiles (the last partly filled, its last tile ragged) and an LM-head panel of two to
+    eight pieces, requested ahead and staged once for both rounds; 17, 33, 48, 64 and 18 rows: both sides of whole
+    sixteens, where the panel's layout and its pieces change, and every number of column tiles from two on."""
+    shape = small_shape(dtype, hidden=hidden, n_heads=8, n_kv_heads=8, head_dim=128, ffn=704, vocab=33100)
+    w = inputs.make_weights(shape, 39)
+    for step, (batch, k) in enumerate(steps):
+        kv = tuple((29 * (b + 1) + 7 * step) % 150 for b in range(batch))
+        wl = Workload("pieces", shape, batch=batch, kv_len=kv, n_new=1, k=k, topk=4, seed=300 + step)
+        inp = inputs.make_step_inputs(wl, kv_len=kv, n_new=1, k=k)
+        print("rows", batch * (1 + k), flush=True)
+        d = _drafter(shape, w, max_batch=batch, max_new=1, max_positions=200, k_max=k)
+        res = run_gpu_step(d, inp, 1, k, 4)
+        print(compare_with_oracle(shape, res, oracle_step(shape, w, inp, 1, k, 4), inp, 1, k, 4), flush=True)
+        d.close()
+
+
 @pytest.mark.parametrize("dtype,nk", [("f32", None), ("bf16", None), ("bf16", "1")])
 def test_very_long_sequence_many_key_blocks(dtype, nk, monkeypatch):
     # 33000 keys = 258 attention blocks of 128 keys (the float32 kernels' size; the bf16 kernels' when forced):
