@@ -203,6 +203,59 @@ def test_lm_head_panels_of_several_pieces_and_rounds(dtype, hidden, steps):
         d.close()
 
 
+@pytest.mark.parametrize("replayed", [False, True])
+def test_lm_head_pieces_are_those_of_this_step(replayed):
+    """The LM head's later pieces come through the L2, which must not hold an earlier step's: twelve steps of other inputs,
+    queued without a pause (or one captured step replayed), on one context whose weights fit the caches; every output
+    bit for bit as from a context of its own."""
+    import torch
+    shape = small_shape("bf16", hidden=1024, n_heads=8, n_kv_heads=8, head_dim=128, ffn=704, vocab=2000)
+    w = inputs.make_weights(shape, 41)
+    wl = Workload("queued", shape, batch=8, kv_len=(3, 40, 0, 77, 12, 5, 64, 31), n_new=1, k=5, topk=4, seed=42)
+    inp = inputs.make_step_inputs(wl)
+    rng = np.random.default_rng(43)
+    xs = [B.to_device((rng.standard_normal(inp["x"].shape).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16), "bf16") for _ in range(12)]
+    kc, vc = B.to_device(inp["k_cache"], "bf16"), B.to_device(inp["v_cache"], "bf16")
+
+    def outputs(d):
+        return d.alloc_outputs(8, 1, 5, 4, logits=True)
+
+    def args(d, x, out):
+        return d.make_args(x, kc, vc, inp["kv_offsets"], inp["kv_len"], 1, 5, 4, out)
+
+    alone = []
+    for x in xs:
+        d = _drafter(shape, w, max_batch=8, max_new=1, max_positions=100, k_max=5)
+        out = outputs(d)
+        d.step(args(d, x, out))
+        torch.cuda.synchronize()
+        alone.append(out)
+        d.close()
+    d = _drafter(shape, w, max_batch=8, max_new=1, max_positions=100, k_max=5)
+    outs = [outputs(d) for _ in xs]
+    if replayed:
+        x, out = xs[0].clone(), outputs(d)
+        a = args(d, x, out)
+        d.step(a)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            d.step(a, stream=torch.cuda.current_stream())
+        for xi, oi in zip(xs, outs):
+            x.copy_(xi)
+            graph.replay()
+            for n in oi:
+                oi[n].copy_(out[n])
+    else:
+        for a in [args(d, x, out) for x, out in zip(xs, outs)]:
+            d.step(a)
+    torch.cuda.synchronize()
+    for i, (got, want) in enumerate(zip(outs, alone)):
+        for n in want:
+            assert torch.equal(got[n], want[n]), (i, n)
+    d.close()
+
+
 @pytest.mark.parametrize("dtype,nk", [("f32", None), ("bf16", None), ("bf16", "1")])
 def test_very_long_sequence_many_key_blocks(dtype, nk, monkeypatch):
     # 33000 keys = 258 attention blocks of 128 keys (the float32 kernels' size; the bf16 kernels' when forced):
