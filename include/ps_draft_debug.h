@@ -48,7 +48,8 @@ PS_API int ps_draft_debug_step_plan(const ps_draft_config* config, int batch, co
 
 /*
  * Host only.  How ps_group_attention would launch a call (pointers are not looked at; its errors otherwise): out[8] =
- * {kernel (0: float32, 1: bf16 with 16-row tiles, 2: bf16 with blocks of 128 rows), workgroups of the attention in x, y
+ * {kernel (0: float32 with blocks of 64 rows, 1: bf16 with 16-row tiles, 2: bf16 with blocks of 128 rows, 3: float32 with
+ * blocks of 32 rows, 4: the same, short calls), workgroups of the attention in x, y
  * and z, threads of one, workgroups of the keys' rotation in x and y, threads of one}.
  */
 struct ps_group_attn_args;

@@ -19,7 +19,7 @@ constexpr int GA_THREADS = 256, GA_WAVES = GA_THREADS / 64;
 constexpr float GA_LAZY = 8.f;
 // A launch may have 2^32 - 1 work items in x at most: workgroups beyond GA_GRID_X go on in y (blockIdx.y is 0 but in huge calls)
 constexpr unsigned GA_GRID_X = 1u << 22;
-constexpr long long GA_MAX_WG = 0x7FFFFFFF;                // the kernels number their workgroups in 31 bits
+constexpr long long GA_MAX_WG = 0x7FFFFFFF;                // the kernels number their workgroups in 31 bits (the float32 ones in 32)
 
 // Wide accesses to the caller's q, k, v and out, which are only promised to be aligned to 4 bytes: the types say so, and the
 // compiler emits the same 16-byte instructions (global memory takes them at any multiple of 4).
@@ -197,65 +197,70 @@ __device__ __attribute__((noinline)) void ga_rows_alone(ga_args_t args, int seq,
 }
 
 // ------------------------------------------------------------------------------------------
-// float32 values.  A workgroup takes 64 consecutive layout rows, 16 per wavefront, with two wavefronts to every 16 rows
-// that share their keys; it walks the real tokens' keys 32 at a time, then the rows R0 - 16 .. R0 + 63, among which the
-// queries see their own groups' [MASK] rows, and of every 32 keys a wavefront takes 16.
+// float32 values.  A workgroup takes 16 QT consecutive layout rows, 16 per wavefront, with KH wavefronts to every 16 rows
+// that share their keys; it walks the real tokens' keys 16 KH at a time, then the rows R0 - 16 .. R0 + 16 QT - 1, among which the
+// queries see their own groups' [MASK] rows, and of every stage's keys a wavefront takes 16.
 //
 // All products are v_mfma_f32_16x16x4_f32 with the queries along the lanes (lane = query c + 16 kb): scores as S^T, a lane
 // holding keys 4 kb .. 4 kb + 3 of its query, register i of which is the column operand of O^T = V^T P^T for the four keys
 // 4 kb + i; the row operand, column 4 m + e of those keys' values (m = the lane's c, e = 0 .. 3), are the four elements of one 16-byte
-// LDS read.  Maximum, sum and output stay with the four lanes of a query; the two wavefronts of 16 rows meet in LDS at the
-// end.  K and V rows are staged for all eight wavefronts, into two buffers that take turns.
+// LDS read.  Maximum, sum and output stay with the four lanes of a query; the wavefronts of 16 rows meet in LDS at the
+// end.  K and V rows are staged for all wavefronts, into two buffers that take turns.
 //
 // Large calls are bound by the float32 matrix rate (32 MFMAs of 32 cycles per 16 x 16 tile at head_dim 64): 4 x T 512, k 10, 16 / 4 heads
-// x 64 takes 300 us, 185 at that rate.  A small one is bound by the chain of its longest rows' stages: 2 x T 300, k 3, 8 heads x 64 has
-// 304 workgroups for 512 places and the matrix cores 17 % busy.  Before, P.V was FMA work against probabilities broadcast from
-// LDS, a workgroup took one tile of whole groups and every wavefront fetched its own operands: whole calls, the two above:
-// 724 -> 300 and 40.5 -> 27.0 us; T 1024, k 4, 32 heads x 128: 1047 -> 470 us.
+// x 64 takes 294 us, 185 at that rate.  A small one is bound by the chain of its longest rows' stages and by compute units that have
+// nothing left to do: 2 x T 300, k 3, 8 heads x 64 had 304 workgroups of 64 rows, the longest with 13 stages of 1.4 us.  So
+// - large calls, head_dim 64: 32 rows, two wavefronts each (QT, KH = 2, 2; with 4, 2 311 us), whose LDS four workgroups share a
+//   compute unit; head_dim 128: 64 rows (T 1024, k 4, 32 heads: 442 us, with 2, 2 515: two workgroups of half the size in the same LDS);
+// - small ones: 32 rows, four wavefronts each (2, 4): half the stages, where the places suffice.  us, 4, 2 / 2, 2 / 2, 4: 2 x T 300, k 3,
+//   8 heads x 64 27.9 / 26.2 / 23.1; T 100, k 3 (two) 14.8 / 11.7 / 11.2; T 300, k 3, 8 heads x 128 36.7 / 31.2 / 25.5; from 704 workgroups of 32
+//   rows on (8 heads x 64: T 700, k 3 48.0 / 40.6 / 37.5, T 512, k 5 41.6 / 34.3 / 35.3), x 128 from 400 on (2 x T 300 46.2 / 42.0 / 46.8), not.
+// Before 16x16x4 tiles, P.V was FMA work against probabilities broadcast from LDS: 724 and 40.5 us for the first two.
 // ------------------------------------------------------------------------------------------
-constexpr int GF_THREADS = 512, GF_ROWS = 64;
+constexpr int GF_ROWS = 64;
 
-template <int D>
-__global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaParams P) {   // four wavefronts per SIMD: two workgroups
-    constexpr int STEPS = D / 16, NV = D / 64;              // 64-byte steps of a row; 16-byte pieces of a row per thread and lane
-    constexpr int KSTR = 4 * D + 16, VSTR = 4 * D, KBUF = 32 * KSTR, BUF = KBUF + 32 * VSTR;
+template <int D, int QT, int KH>
+__device__ __forceinline__ void ga_attn_f32(const GaParams& P) {
+    constexpr int THREADS = 64 * QT * KH, ROWS = 16 * QT, KEYS = 16 * KH, TPR = THREADS / KEYS;   // keys of a stage, threads that stage a row
+    constexpr int STEPS = D / 16, NV = D / 64, NS = D / 4 / TPR;   // 64-byte steps of a row; its 16-byte pieces per lane of 16, per thread that stages it
+    constexpr int KSTR = 4 * D + 16, VSTR = 4 * D, KBUF = KEYS * KSTR, BUF = KBUF + KEYS * VSTR;
     constexpr int QAREA = 16 * D * 4;                       // 16 query rows as MFMA operands; later one wavefront's output on its way to the other
-    constexpr int OFF_ML = 4 * QAREA;                       // [4][64 lanes] (maximum, sum)
-    static_assert(OFF_ML + 4 * 64 * 8 <= 2 * BUF, "query and merge areas fit the buffers");
+    constexpr int OFF_ML = QT * (KH - 1) * QAREA;           // [KH - 1][QT][64 lanes] (maximum, sum)
+    static_assert(QT * QAREA <= 2 * BUF && OFF_ML + QT * (KH - 1) * 64 * 8 <= 2 * BUF, "query and merge areas fit the buffers");
     __shared__ __attribute__((aligned(16))) char smem[2 * BUF];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 15, kb = lane >> 4, qt = wave & 3, kh = wave >> 2;   // query tile, half of the keys
+    const int c = lane & 15, kb = lane >> 4, qt = wave % QT, kh = wave / QT;   // query tile, half of the keys
     const int K1 = P.k + 1;
     auto group_of = [&](int row) __attribute__((always_inline)) { return P.k > 0 ? (int)__umulhi((unsigned)row, P.k1_magic) : row; };
     const unsigned wg = blockIdx.y * GA_GRID_X + blockIdx.x;
-    const int blk = (P.rows + GF_ROWS - 1) / GF_ROWS - 1 - (int)(wg / (unsigned)P.nq);   // the rows with the most keys start first
+    const int blk = (P.rows + ROWS - 1) / ROWS - 1 - (int)(wg / (unsigned)P.nq);   // the rows with the most keys start first
     if (blk < 0) return;                                    // (beyond the last, in a launch of several rows of workgroups)
     const int h = wg % (unsigned)P.nq, seq = blockIdx.z, hk = h / (P.nq / P.nkv);
-    const int R0 = GF_ROWS * blk, r0 = R0 + 16 * qt;
+    const int R0 = ROWS * blk, r0 = R0 + 16 * qt;
     const bool active = r0 < P.rows;
-    const int r_last = min(R0 + GF_ROWS, P.rows) - 1, g_last_wg = group_of(r_last);
-    const int n_real = g_last_wg / 32 + 1, n_stages = n_real + (P.k > 0 ? (r_last - R0 + 16) / 32 + 1 : 0);
+    const int r_last = min(R0 + ROWS, P.rows) - 1, g_last_wg = group_of(r_last);
+    const int n_real = g_last_wg / KEYS + 1, n_stages = n_real + (P.k > 0 ? (r_last - R0 + 16) / KEYS + 1 : 0);
     const int wg0 = group_of(min(r0, r_last)), wg1 = group_of(min(r0 + 15, r_last));   // the tile's first and last group
     const int qrow = min(r0 + c, r_last), qg = group_of(qrow);   // this lane's query (beyond the end: the last, repeated)
 
-    // ---- staging: 16 threads per row
-    const int skey = tid >> 4, sp = tid & 15;
+    // ---- staging
+    const int skey = tid / TPR, sp = tid % TPR;
     const size_t rs = (size_t)P.nkv * D * 4, head_off = (((size_t)seq * P.rows) * P.nkv + hk) * D * 4 + sp * 16;
     const char* kbase = (const char*)P.k_rot + head_off;
     const char* vbase = (const char*)P.v + head_off;
-    struct Stage { uint4 k[NV], v[NV]; };
+    struct Stage { uint4 k[NS], v[NS]; };
     auto stage_load = [&](int t, Stage& x) __attribute__((always_inline)) {
-        const int row = t < n_real ? min(32 * t + skey, g_last_wg) * K1 : min(max(R0 - 16 + 32 * (t - n_real) + skey, 0), r_last);
+        const int row = t < n_real ? min(KEYS * t + skey, g_last_wg) * K1 : min(max(R0 - 16 + KEYS * (t - n_real) + skey, 0), r_last);
         const size_t off = (size_t)(unsigned)row * rs;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) { x.k[i] = ld16(kbase + off + 256 * i); x.v[i] = ld16_q(vbase + off + 256 * i); }
+        for (int i = 0; i < NS; ++i) { x.k[i] = ld16(kbase + off + 16 * TPR * i); x.v[i] = ld16_q(vbase + off + 16 * TPR * i); }
     };
     auto stage_store = [&](int t, const Stage& x) __attribute__((always_inline)) {
         char* b = smem + (t & 1) * BUF;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            *reinterpret_cast<uint4*>(b + skey * KSTR + sp * 16 + 256 * i) = x.k[i];
-            *reinterpret_cast<uint4*>(b + KBUF + skey * VSTR + sp * 16 + 256 * i) = x.v[i];
+        for (int i = 0; i < NS; ++i) {
+            *reinterpret_cast<uint4*>(b + skey * KSTR + sp * 16 + 16 * TPR * i) = x.k[i];
+            *reinterpret_cast<uint4*>(b + KBUF + skey * VSTR + sp * 16 + 16 * TPR * i) = x.v[i];
         }
     };
     Stage st, st1;
@@ -266,8 +271,9 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
     {
         const char* qsrc = (const char*)P.q + ((size_t)seq * P.rows * P.nq + h) * D * 4;
 #pragma unroll
-        for (int i = 0; i < GF_ROWS * (D / 8) / GF_THREADS; ++i) {
-            const int x = tid + GF_THREADS * i, r = x / (D / 8), g4 = x % (D / 8);
+        for (int i = 0; i < (ROWS * (D / 8) + THREADS - 1) / THREADS; ++i) {
+            const int x = tid + THREADS * i, r = x / (D / 8), g4 = x % (D / 8);
+            if (ROWS * (D / 8) % THREADS != 0 && x >= ROWS * (D / 8)) break;
             const int row = min(R0 + r, r_last), pos = row - group_of(row) * P.k;                // group + slot
             const char* qr = qsrc + (size_t)row * P.nq * D * 4 + 16 * g4;
             const f32x4 a = load4_q<float>(qr), b = load4_q<float>(qr + 2 * D);
@@ -306,7 +312,7 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
         // this wavefront's 16 keys: first token / layout row; of the own rows the 16 of the tile itself and, where its first
         // row is not the first of its group, the 16 before
         const bool real = t < n_real;
-        const int unit = 2 * (real ? t : t - n_real) + kh, first = 16 * unit + (real ? 0 : R0 - 16);
+        const int unit = KH * (real ? t : t - n_real) + kh, first = 16 * unit + (real ? 0 : R0 - 16);
         const bool busy = active & (real ? first <= wg1 : (unit == qt + 1) | ((unit == qt) & (wg0 * K1 != r0)));
         if (busy) {
             const char* kt = smem + (t & 1) * BUF + 16 * kh * KSTR + c * KSTR + kb * 16;
@@ -350,20 +356,36 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
         __syncthreads();
     }
 
-    // ---- the two wavefronts of a tile meet; the first writes the rows
+    // ---- the wavefronts of a tile meet; the first writes the rows
     l_run = quad_rows_sum(l_run);
-    if (kh == 1) {
-        *reinterpret_cast<float2*>(smem + OFF_ML + (qt * 64 + lane) * 8) = make_float2(m_run, l_run);
+    if (kh > 0) {
+        const int area = (kh - 1) * QT + qt;
+        *reinterpret_cast<float2*>(smem + OFF_ML + (area * 64 + lane) * 8) = make_float2(m_run, l_run);
 #pragma unroll
-        for (int j = 0; j < D / 16; ++j) *reinterpret_cast<f32x4*>(smem + qt * QAREA + (j * 64 + lane) * 16) = o[j];
+        for (int j = 0; j < D / 16; ++j) *reinterpret_cast<f32x4*>(smem + area * QAREA + (j * 64 + lane) * 16) = o[j];
     }
     __syncthreads();
     if (kh == 0 && active) {
-        const float2 ml = *reinterpret_cast<const float2*>(smem + OFF_ML + (qt * 64 + lane) * 8);
-        const float M = fmaxf(m_run, ml.x);                 // (-inf only if no visible score is finite)
-        const float f0 = __builtin_amdgcn_exp2f(m_run - M), f1 = __builtin_amdgcn_exp2f(ml.x - M), den = l_run * f0 + ml.y * f1;
+        float2 ml[KH - 1];
+        float M = m_run;                                    // (-inf only if no visible score is finite)
 #pragma unroll
-        for (int j = 0; j < D / 16; ++j) o[j] = (o[j] * f0 + *reinterpret_cast<const f32x4*>(smem + qt * QAREA + (j * 64 + lane) * 16) * f1) / den;
+        for (int i = 0; i < KH - 1; ++i) {
+            ml[i] = *reinterpret_cast<const float2*>(smem + OFF_ML + ((i * QT + qt) * 64 + lane) * 8);
+            M = fmaxf(M, ml[i].x);
+        }
+        const float f0 = __builtin_amdgcn_exp2f(m_run - M);
+        float den = l_run * f0;
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) o[j] *= f0;
+#pragma unroll
+        for (int i = 0; i < KH - 1; ++i) {
+            const float f = __builtin_amdgcn_exp2f(ml[i].x - M);
+            den += ml[i].y * f;
+#pragma unroll
+            for (int j = 0; j < D / 16; ++j) o[j] += *reinterpret_cast<const f32x4*>(smem + (i * QT + qt) * QAREA + (j * 64 + lane) * 16) * f;
+        }
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) o[j] = o[j] / den;
         float z = 0.f;
 #pragma unroll
         for (int j = 0; j < D / 16; ++j) z = abs_max3(abs_max3(z, o[j][0], o[j][1]), o[j][2], o[j][3]);
@@ -378,6 +400,16 @@ __global__ void __launch_bounds__(GF_THREADS, 4) ga_attn_f32_kernel(const GaPara
         const unsigned alone = (unsigned)(b | b >> 16 | b >> 32 | b >> 48) & 0xFFFFu;
         if (alone) ga_rows_alone<float, D>(ga_args(), seq, h, r0, alone, lane);
     }
+}
+
+constexpr int GF_QT(int head_dim) { return head_dim == 64 ? 2 : 4; }
+template <int D>
+__global__ void __launch_bounds__(128 * GF_QT(D), 4) ga_attn_f32_kernel(const GaParams P) {   // four wavefronts per SIMD
+    ga_attn_f32<D, GF_QT(D), 2>(P);
+}
+template <int D>
+__global__ void __launch_bounds__(512, D == 64 ? 4 : 2) ga_attn_f32_short_kernel(const GaParams P) {
+    ga_attn_f32<D, 2, 4>(P);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1125,10 +1157,11 @@ GaLayout layout(const ps_group_attn_args* a) {
 }
 
 // How a call is launched: the attention's kernel with its grid, and the rotation's
-enum { GA_F32 = 0, GA_TILES = 1, GA_WIDE = 2 };
+enum { GA_F32 = 0, GA_TILES = 1, GA_WIDE = 2, GA_F32_32 = 3, GA_F32_SHORT = 4 };   // (GA_F32_32: ga_attn_f32_kernel with blocks of 32 rows)
 struct GaLaunch {
     int kernel;
-    dim3 rope, attn;      // (256 threads each; GA_F32's attention: GF_THREADS)
+    int threads;          // of the attention's workgroups (the rotation's: 256)
+    dim3 rope, attn;
 };
 dim3 grid_xy(long long workgroups, int z) {
     const unsigned x = (unsigned)min(workgroups, (long long)GA_GRID_X);
@@ -1136,6 +1169,7 @@ dim3 grid_xy(long long workgroups, int z) {
 }
 GaLaunch plan(const GaParams& P, int dtype, int head_dim) {
     GaLaunch L;
+    L.threads = GA_THREADS;
     if (dtype == PS_BF16) {
         // The wide kernel, except where the real tokens' keys are a single stage and the groups' own rows are most of the work:
         // there the 16-row kernel, whose workgroups are half as long, is the faster one as long as
@@ -1152,8 +1186,12 @@ GaLaunch plan(const GaParams& P, int dtype, int head_dim) {
         L.kernel = blocks > GA_MAX_WG || tiles ? GA_TILES : GA_WIDE;
         L.attn = L.kernel == GA_WIDE ? grid_xy(blocks, 1) : dim3((P.ntiles + GA_WAVES - 1) / GA_WAVES, P.nq, P.seqs);
     } else {
-        const long long blocks = (long long)((P.rows + GF_ROWS - 1) / GF_ROWS) * P.nq;
-        L.kernel = GA_F32;
+        // (both sides of the line stand at ga_attn_f32)
+        const bool is_short = (long long)((P.rows + 31) / 32) * P.nq * P.seqs <= (head_dim == 64 ? 704 : 400);
+        const int rows = is_short ? 32 : 16 * GF_QT(head_dim);
+        const long long blocks = (long long)((P.rows + rows - 1) / rows) * P.nq;
+        L.kernel = is_short ? GA_F32_SHORT : rows == 32 ? GA_F32_32 : GA_F32;
+        L.threads = is_short ? 512 : 128 * GF_QT(head_dim);
         L.attn = grid_xy(blocks, P.seqs);
     }
     // the rotation: a workgroup per position; where positions are few, several (of at most one item per thread each) share one's rows
@@ -1174,7 +1212,8 @@ int launch(const GaParams& P, const GaLaunch& L, hipStream_t s) {
         }
     } else {
         hipLaunchKernelGGL((ga_rope_kernel<WT, D, true>), L.rope, dim3(256), 0, s, P);
-        hipLaunchKernelGGL((ga_attn_f32_kernel<D>), L.attn, dim3(GF_THREADS), 0, s, P);
+        if (L.kernel == GA_F32_SHORT) hipLaunchKernelGGL((ga_attn_f32_short_kernel<D>), L.attn, dim3(L.threads), 0, s, P);
+        else hipLaunchKernelGGL((ga_attn_f32_kernel<D>), L.attn, dim3(L.threads), 0, s, P);
     }
     return hipGetLastError() == hipSuccess ? PS_OK : PS_ERR_DEVICE;
 }
@@ -1220,7 +1259,7 @@ extern "C" int ps_train_debug_launch(const ps_group_attn_args* a, unsigned* out)
     if (st != PS_OK) return st;
     if (!out) return PS_ERR_NULL;
     const GaLaunch G = plan(shape(a), a->dtype, a->head_dim);
-    const unsigned v[8] = {(unsigned)G.kernel, G.attn.x, G.attn.y, G.attn.z, (unsigned)(G.kernel == GA_F32 ? GF_THREADS : GA_THREADS), G.rope.x, G.rope.y, 256u};
+    const unsigned v[8] = {(unsigned)G.kernel, G.attn.x, G.attn.y, G.attn.z, (unsigned)G.threads, G.rope.x, G.rope.y, 256u};
     for (int i = 0; i < 8; ++i) out[i] = v[i];
     return PS_OK;
 }

@@ -93,6 +93,14 @@ def test_float32_blocks_of_64_rows_at_their_edges(seqs, T, k, nq, nkv, d):
     _case(seqs, T, k, nq, nkv, d, "f32", 200 + T + k)
 
 
+@pytest.mark.parametrize("seqs,T,k,nq,nkv,d", [
+    (1, 32, 0, 1, 1, 64), (1, 33, 0, 2, 1, 64), (1, 64, 0, 1, 1, 128), (2, 65, 0, 1, 1, 64),   # short calls: exactly 1, 2 and 3 blocks of 32 rows; 1 and 2 stages of 64 keys
+    (1, 9, 7, 2, 2, 64), (1, 5, 15, 2, 1, 128), (1, 1, 2, 1, 1, 64),                            # own rows of several stages; a wavefront without keys
+    (5, 150, 3, 8, 8, 64), (4, 100, 3, 8, 4, 128)])                                             # just beyond the short calls: 760 and 416 blocks
+def test_float32_blocks_of_32_rows_and_the_line_to_longer_calls(seqs, T, k, nq, nkv, d):
+    _case(seqs, T, k, nq, nkv, d, "f32", 300 + T + k)
+
+
 @pytest.mark.parametrize("dtype,k,d", [("bf16", 0, 128), ("bf16", 0, 64), ("bf16", 3, 128), ("f32", 0, 64)])
 def test_scores_that_overflow_before_a_row_sees_a_finite_one(dtype, k, d):
     """The first 32 real tokens' keys lie opposite to every query and so far out that their scores are -inf in float32

@@ -84,6 +84,19 @@ def test_launches_stay_within_the_limits_of_a_launch(lib):
     assert DBG.ps_train_debug_launch(TR.make_args(0, 64, 4, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_SHAPE
 
 
+def test_which_float32_calls_are_short(lib):
+    """Both sides of the line: 704 workgroups of 32 rows (head_dim 64), 400 (128); blocks of 32 rows cover the rows."""
+    from paper_2410_05589_amd import debug as DBG
+    for d, want, calls in ((64, 4, [(1, 1, 0, 1), (1, 700, 3, 8), (11, 256, 0, 8)]), (64, 3, [(1, 705, 3, 8), (11, 257, 0, 8)]),
+                           (128, 4, [(1, 400, 3, 8), (1, 12800, 0, 1)]), (128, 0, [(1, 401, 3, 8), (1, 12801, 0, 1)])):
+        for seqs, T, k, nq in calls:
+            st, g = DBG.ps_train_debug_launch(TR.make_args(seqs, T, k, nq, nq, d, "f32", 10000.0))
+            assert st == B.PS_OK and g["kernel"] == want, (d, seqs, T, k, nq, g)
+            x, y, z = g["grid"]
+            assert z == seqs and x * y == -(-T * (k + 1) // (64 if want == 0 else 32)) * nq, (d, seqs, T, k, nq, g)
+            assert g["threads"] == {4: 512, 3: 256, 0: 512}[want]
+
+
 def test_which_calls_take_the_16_row_kernel(lib):
     """Both sides of every limit of the rule: T 32, k 4, group sizes that divide 32, 256 workgroups, 8192 key rows."""
     from paper_2410_05589_amd import debug as DBG
