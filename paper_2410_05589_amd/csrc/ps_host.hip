@@ -424,9 +424,8 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
         s_log = 0;
         while (s_log < 3 && (2 << s_log) <= override_[0] && (2 << s_log) <= NG && (2 << s_log) <= nwg) ++s_log;
     }
-    for (; s_log >= 0; --s_log) {
-        const int S = 1 << s_log, Gs = nwg >> s_log;
-        const int min_slice = NG / S, max_slice = (NG + S - 1) / S;   // groups per slice
+    // the most wavefronts that share a tile, by the score
+    auto most_shared = [&](int S, int Gs, int min_slice) {
         int best_log = 0;
         double best = -1e9;
         for (int lg = 0; lg <= PS_WAVES_LOG; ++lg) {
@@ -442,6 +441,28 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
             best_log = 0;
             while ((2 << best_log) <= override_[1] && best_log < PS_WAVES_LOG && (2 << best_log) <= min_slice) ++best_log;
         }
+        return best_log;
+    };
+    // What is supported does not depend on the layout and the cut chosen below: some plan's panel has to fit row by row beside
+    // the reduction area
+    bool supported = false;
+    for (int sl = s_log; sl >= 0 && !supported; --sl) {
+        const int S = 1 << sl, min_slice = NG / S, max_slice = (NG + S - 1) / S;
+        for (int lg = most_shared(S, nwg >> sl, min_slice); lg >= 0 && !supported; --lg) {
+            const int kw = 1 << lg, SL = PS_WAVES >> lg, rounds = (T + (nwg >> sl) * SL - 1) / ((nwg >> sl) * SL);
+            const int beside = lds_limit - panel_offset_host(mt, true) - (ph == PH_LMHEAD ? rounds * SL * rows * 64 : 0) - 256;
+            int np = 1;
+            while (np <= max_slice && (beside <= 0 || arrays * panel_part_host(rows, false, (max_slice + np - 1) / np * PS_U) > beside)) ++np;
+            if (np > max_slice) continue;
+            const int pg = (max_slice + np - 1) / np, n = (max_slice + pg - 1) / pg;
+            supported = (min_slice + pg - 1) / pg == n && pg >= kw && min_slice - (n - 1) * pg >= kw;
+        }
+    }
+    if (!supported) return false;
+    for (; s_log >= 0; --s_log) {
+        const int S = 1 << s_log, Gs = nwg >> s_log;
+        const int min_slice = NG / S, max_slice = (NG + S - 1) / S;   // groups per slice
+        int best_log = most_shared(S, Gs, min_slice);
         for (; best_log >= 0; --best_log) {
             const int kw = 1 << best_log, SL = PS_WAVES >> best_log;
             const int per_round = Gs * SL;
