@@ -47,6 +47,12 @@ PS_API int ps_draft_debug_step_plan(const ps_draft_config* config, int batch, co
                              int n_cu, int lds_limit, int* out);
 
 /*
+ * Host only.  How the LM head's row merge finds the topk largest of the keys in `lists` workgroups' sorted lists of topk: by a
+ * lower bound from groups of lists (log2 of the lists of a group), or by merging them head by head (-1).
+ */
+PS_API int ps_draft_debug_merge_groups(int lists, int topk);
+
+/*
  * Host only.  How ps_group_attention would launch a call (pointers are not looked at; its errors otherwise): out[8] =
  * {kernel (0: float32 with blocks of 64 rows, 1: bf16 with 16-row tiles, 2: bf16 with blocks of 128 rows, 3: float32 with
  * blocks of 32 rows, 4: the same, short calls), workgroups of the attention in x, y

@@ -408,17 +408,20 @@ __device__ __forceinline__ bool grp_head(u64 key, unsigned& top) {
 }
 // Selecting by a lower bound.  Where the keys are in groups and v is the k-th largest of the groups' largest logits (mapped to
 // unsigned, see make_key), k keys have logits of at least v, so the k largest keys are among those that have: a few more
-// than k (32 groups, k = 8: about ten), whose order is found by counting.  Merging k times costs a chain of k wavefront-wide
-// reductions, 0.25 us each.  top[0 .. 31]: the groups' largest (0: no group), the same LDS words for every lane.
-__device__ __forceinline__ unsigned kth_largest_of_32(const unsigned* top, int k) {
-    const int lane = threadIdx.x & 31;
-    const unsigned mine = top[lane];
+// than k (see ps_merge_groups_log), whose order is found by counting.  Merging k times costs a chain of k wavefront-wide
+// reductions, 0.25 us each.  top[0 .. 31] (wide: 63): the groups' largest (0: no group), the same LDS words for every wavefront.
+__device__ __forceinline__ unsigned kth_largest(const unsigned* top, bool wide, int k) {
+    const unsigned mine = top[threadIdx.x & (wide ? 63 : 31)];
     int ge = 0;
+    auto count = [&](const unsigned* t) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 32; i += 4) {
-        const uint4 o = *reinterpret_cast<const uint4*>(top + i);
-        ge += (o.x >= mine) + (o.y >= mine) + (o.z >= mine) + (o.w >= mine);
-    }
+        for (int i = 0; i < 32; i += 4) {
+            const uint4 o = *reinterpret_cast<const uint4*>(t + i);
+            ge += (o.x >= mine) + (o.y >= mine) + (o.z >= mine) + (o.w >= mine);
+        }
+    };
+    count(top);
+    if (__builtin_expect(wide, 0)) count(top + 32);   // (0.4 us of a step)
     return wave_max_u32(ge >= k ? mine : 0u);   // (the largest value that k groups reach; 0 if there are fewer)
 }
 
@@ -2638,7 +2641,7 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
 // ------------------------------------------------------------------------------------------
 // LM-head merge of one output row by one workgroup.  Thread p fetches workgroup p's statistics
 // of the row (max, sum of exponentials, its sorted top-k keys) in one round of loads; the few keys that a
-// lower bound leaves (kth_largest_of_32) are put in order by wavefront 0.
+// lower bound leaves (kth_largest) are put in order by wavefront 0.
 // sk: LDS scratch of PS_MERGE_BYTES.
 // ------------------------------------------------------------------------------------------
 #define PS_MAX_TOPK 32
@@ -2691,11 +2694,12 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
     // published anything, so now that all statistics of the row are here the flag tells; requested here,
     // looked at when the outputs are written.
     const unsigned gave_up = ld_agent_u32(P.error_flag);
-    // Lists of 5 to 16 keys: the keys that a lower bound leaves, put in order by counting (see kth_largest_of_32); others,
-    // and where that leaves too many (a great many equal logits), merged head by head: by wavefront, then the wavefronts'.
-    // Whole steps, merged / selected: H 512, topk 8 40.6 / 39.1 us, topk 16 50.2 / 46.5; H 256, topk 4 36.2 / 36.4
-    constexpr int MAX_CAND = 64, SEL = 16;
-    const bool select = topk > 4 && topk <= SEL;
+    // The keys that a lower bound leaves, put in order by counting (see kth_largest); where there are too few lists for
+    // that (ps_merge_groups_log) or too many keys are left (a great many equal logits), merged head by head: by
+    // wavefront, then the wavefronts'.
+    constexpr int MAX_CAND = PS_MERGE_CANDIDATES, SEL = PS_MERGE_SELECT_MAX;
+    const int gs_log = ps_merge_groups_log(nparts, topk);  // log2 of the lists of a group
+    const bool select = gs_log >= 0, wide = select && ((nparts - 1) >> gs_log) >= 32;   // (more than 32 groups)
     auto merge_lists = [&]() __attribute__((always_inline)) {
         for (int t = 0; t < topk; ++t) {
             unsigned top;
@@ -2713,8 +2717,8 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
         }
     };
     // this wavefront's share of the log-sum-exp; the largest logit of every group of lists
-    unsigned* const s_top = reinterpret_cast<unsigned*>(scratch + 1024);   // [32]
-    unsigned* const s_n = s_top + 32;                                       // candidates so far
+    unsigned* const s_top = reinterpret_cast<unsigned*>(scratch + 1024);   // [64]
+    unsigned* const s_n = s_top + 64;                                       // candidates so far
     const float wmax = wave_max(pmax);
     if (lane == 0) sf[wave] = wmax;
     if (P.sample_ids) {
@@ -2722,15 +2726,15 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
         if (lane == 0) sg[wave] = wg_best;
     }
     if (select) {
-        const int gs_log = nparts <= 32 ? 0 : nparts <= 128 ? 2 : nparts <= 256 ? 3 : 4;   // lists per group: at most 32 groups
         unsigned g = (unsigned)(keys[0] >> 32);
 #define PS_C(CTRL) { const unsigned o = dpp_u32<CTRL>(0u, g); g = o > g ? o : g; }
-        if (gs_log > 0) { PS_C(0xB1) PS_C(0x4E) }
+        if (gs_log > 0) PS_C(0xB1)
+        if (gs_log > 1) PS_C(0x4E)
         if (gs_log > 2) PS_C(0x141)
         if (gs_log > 3) PS_C(0x140)
 #undef PS_C
         if (mine && (tid & ((1 << gs_log) - 1)) == 0) s_top[tid >> gs_log] = g;
-        if (tid < 32 && (tid << gs_log) >= nparts) s_top[tid] = 0;
+        if (tid < 64 && (tid << gs_log) >= nparts) s_top[tid] = 0;
         if (tid == 0) *s_n = 0;
     } else {
         merge_lists();
@@ -2745,7 +2749,7 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
     if (lane == 0) sf[PS_WAVES + wave] = wsum;
     if (select) {
         // the keys that may be among the topk largest, in no order (a thread's are the first of its list)
-        const unsigned bound = max(kth_largest_of_32(s_top, topk), 1u);
+        const unsigned bound = max(kth_largest(s_top, wide, topk), 1u);
         int n = 0;
         bool more = true;
 #pragma unroll

@@ -740,6 +740,9 @@ extern "C" int ps_draft_debug_step_plan(const ps_draft_config* c, int batch, con
     return PS_OK;
 }
 
+// see ps_draft_debug.h
+extern "C" int ps_draft_debug_merge_groups(int lists, int topk) { return ps_merge_groups_log(lists, topk); }
+
 extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, void* stream) {
     if (!ctx || !a) return PS_ERR_NULL;
     const ps_draft_config& c = ctx->cfg;

@@ -50,6 +50,26 @@ constexpr int ps_attn2_lds_bytes(int d) {
 }
 #define PS_ATTN2_NK_LOG_MAX 4   // at most 16 groups of 16 keys per wavefront and block: blocks of up to 2048 cache keys
 
+// How the LM head's row merge (lm_merge_row in ps_device.h) finds the topk largest keys in `lists` sorted lists of topk (the
+// workgroups' shares of the vocabulary): by a lower bound from groups of lists - the result is log2 of the lists of a group - or,
+// -1, by merging head by head.  Up to four keys the merge is as fast.  A bound from few more groups than topk is a small logit
+// and leaves more keys than the 64 that are put in order; such a row pays for the merge, too.  Rows of normally distributed
+// logits that do:
+//   a list per group: 12 % with 16 lists and topk 16, 1.2 % with 17; 3 % with 13 and topk 13, 0.8 % with 12 and topk 12: so many lists;
+//   several: 20 % with 16 groups and topk 16, 14 % with 17, 0.2 % with 20; 0.15 % with 17 and topk 14: so topk + 4 groups, of up to 32 if
+//   those are enough, else of up to 64 (whose bound costs 0.4 us).
+// us, mean over eight inputs, merged / selected by this rule: H 256, five rows, topk 16: V 272 43.5 / 38.6, V 528 43.7 / 38.2, V 1024 44.1 / 38.7,
+// V 1040 43.8 / 38.4; H 512, V 2064, topk 16 46.9 / 39.1, 20 rows 57.8 / 49.0, topk 8 42.1 / 36.9; 7B shape, topk 8 141.7 / 138.6.
+#define PS_MERGE_SELECT_MAX 16
+#define PS_MERGE_CANDIDATES 64
+__host__ __device__ inline int ps_merge_groups_log(int lists, int topk) {
+    if (topk <= 4 || topk > PS_MERGE_SELECT_MAX) return -1;
+    if (lists < topk + (topk > 12) && lists * topk > PS_MERGE_CANDIDATES) return -1;
+    const int log = lists <= 32 ? 0 : lists <= 64 ? 1 : lists <= 128 ? 2 : lists <= 256 ? 3 : 4;
+    return log > 0 && ((lists - 1) >> log) + 1 < topk + 4 ? log - 1 : log;
+}
+static_assert(PS_WG_THREADS <= 512, "at most 32 groups of 16 lists, a list per thread");
+
 // The five GEMM phases of the step, and the input projection of the feature-fusion input mode (a kernel of
 // its own in front of the step, built from the same engine)
 enum { PH_QKV = 0, PH_OPROJ = 1, PH_GATEUP = 2, PH_DOWN = 3, PH_LMHEAD = 4, PH_FC = 5, PH_COUNT = 6 };

@@ -7,7 +7,7 @@ from . import binding as B
 PS_PLAN_FIELDS = 12
 PLAN_FIELD_NAMES = ("T", "Kt", "K", "rows", "kw_log", "s_log", "Gs", "per_round", "rounds", "piece_groups",
                     "npieces", "lds_bytes")
-EXPORTED_SYMBOLS = ("ps_draft_debug_plan", "ps_draft_debug_attn_plan", "ps_draft_debug_step_plan", "ps_draft_debug_spin_limit", "ps_draft_debug_timeline",
+EXPORTED_SYMBOLS = ("ps_draft_debug_plan", "ps_draft_debug_attn_plan", "ps_draft_debug_step_plan", "ps_draft_debug_merge_groups", "ps_draft_debug_spin_limit", "ps_draft_debug_timeline",
                     "ps_train_debug_launch", "ps_verify_debug_exchange", "ps_measure_stream_read", "ps_measure_copy")
 
 _ready = False
@@ -25,6 +25,8 @@ def _lib():
         lib.ps_draft_debug_step_plan.restype = ctypes.c_int
         lib.ps_draft_debug_step_plan.argtypes = [ctypes.POINTER(B.ps_draft_config), ctypes.c_int, ctypes.POINTER(ctypes.c_int32)] + \
             [ctypes.c_int] * 5 + [ctypes.POINTER(ctypes.c_int)]
+        lib.ps_draft_debug_merge_groups.restype = ctypes.c_int
+        lib.ps_draft_debug_merge_groups.argtypes = [ctypes.c_int, ctypes.c_int]
         lib.ps_draft_debug_spin_limit.restype = ctypes.c_int
         lib.ps_draft_debug_spin_limit.argtypes = [ctypes.c_void_p, ctypes.c_int]
         lib.ps_draft_debug_timeline.restype = ctypes.c_int
@@ -64,6 +66,10 @@ def ps_draft_debug_step_plan(config, kv_len, n_new, k, all_rows, n_cu, lds_limit
     st = _lib().ps_draft_debug_step_plan(ctypes.byref(config), len(kv_len), ln, n_new, k, all_rows, n_cu, lds_limit, out)
     plans = [dict(zip(PLAN_FIELD_NAMES, out[1 + ph * PS_PLAN_FIELDS:1 + (ph + 1) * PS_PLAN_FIELDS])) for ph in range(5)]
     return st, out[0], plans, dict(zip(("keys", "units", "blocks", "merge_items", "workgroups", "sep"), out[1 + 5 * PS_PLAN_FIELDS:]))
+
+
+def ps_draft_debug_merge_groups(lists, topk):
+    return _lib().ps_draft_debug_merge_groups(lists, topk)
 
 
 def ps_train_debug_launch(args):

@@ -202,3 +202,22 @@ def test_equal_logits_are_listed_in_order_of_their_ids(vocab, batch, topk):
             assert res["logits"][b, r][order[0]] == res["logits"][b, r][order[1]]
             np.testing.assert_array_equal(res["top_ids"][b, r], order)
             np.testing.assert_allclose(res["top_p"][b, r], res["probs"][b, r][order], rtol=1e-5)
+
+
+@pytest.mark.parametrize("lists,topk", [
+    (6, 10), (7, 10), (12, 12), (13, 13), (14, 13), (16, 16), (17, 16), (32, 16), (33, 5), (33, 16), (64, 16), (65, 16), (68, 13), (128, 12), (129, 12), (129, 16), (160, 8), (160, 16)])
+def test_rows_are_merged_by_selection_or_head_by_head(lists, topk):
+    """Both sides of the limits of the rule by which the row merge selects or merges and groups its lists (64 keys in all; as many lists
+    as keys, one more from 13 on; 32, 64 and 128 lists; four groups more than keys); the last list holds three entries: ids are the
+    order of the step's own logits."""
+    vocab = 16 * lists - 13
+    print("lists", lists, "topk", topk, flush=True)
+    shape = dataclasses.replace(WORKLOADS["c0"].shape, vocab=vocab)
+    w = inputs.make_weights(shape, 6)
+    d = B.Drafter(shape, w, max_batch=6, max_new=1, max_positions=20 + 5, max_topk=topk, k_max=4)
+    wl = Workload("merge", shape, batch=6, kv_len=(20,) * 6, n_new=1, k=4, topk=topk, seed=7)
+    res = run_gpu_step(d, inputs.make_step_inputs(wl), 1, 4, topk)
+    d.close()
+    order = np.argsort(-res["logits"], axis=-1, kind="stable")[..., :topk]
+    np.testing.assert_array_equal(res["top_ids"], order)
+    np.testing.assert_allclose(res["top_p"], np.take_along_axis(res["probs"], order, axis=-1), rtol=1e-5)

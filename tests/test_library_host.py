@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 from paper_2410_05589_amd import binding as B
@@ -360,3 +361,29 @@ def test_step_plans_over_a_sweep_of_small_shapes(lib):
             if dtype == "f32" and n < n_cu:
                 assert attn["units"] <= n or -(-attn["units"] // n) <= -(-attn["units"] // n_cu), tag
     assert min(chosen.values()) > 100, chosen
+
+
+def _keys_left(g, lists, topk, per_list, log):
+    """Keys that the lower bound of lm_merge_row leaves, on a row of normally distributed logits: the topk-th largest of the
+    groups' largest (all keys of the lists if there are fewer groups)."""
+    x = np.sort(g.standard_normal((lists, per_list)), axis=1)[:, ::-1][:, :topk]
+    top = np.sort([x[i:i + (1 << log), 0].max() for i in range(0, lists, 1 << log)])[::-1]
+    return int((x >= top[topk - 1]).sum()) if len(top) >= topk else x.size
+
+
+def test_the_row_merge_selects_only_where_the_bound_leaves_few_keys(lib):
+    """A row whose bound leaves more than 64 keys pays for the selection and the merge: at most 1.2 % of rows of normally distributed
+    logits by the counts that the rule was made from, so (five standard deviations) at most 14 of 400, on both sides of every
+    limit of the number of lists; at most 64 groups; and rows are selected wherever there are more lists than keys."""
+    g = np.random.default_rng(17)
+    for topk in range(1, 33):
+        for lists in (1, 4, 5, 7, 8, 10, 11, 12, 13, 14, 16, 17, 18, 20, 31, 32, 33, 38, 39, 40, 50, 64, 65, 68, 72, 80, 128, 129, 137, 150, 160, 256, 257, 304, 512):
+            log = DBG.ps_draft_debug_merge_groups(lists, topk)
+            if not 5 <= topk <= 16:
+                assert log == -1, (lists, topk, log)
+            if log < 0:
+                assert topk < 5 or topk > 16 or lists <= topk, (lists, topk, log)
+                continue
+            assert -(-lists // (1 << log)) <= 64, (lists, log)
+            many = sum(_keys_left(g, lists, topk, 16, log) > 64 for _ in range(400 if topk >= 12 else 20))
+            assert many <= 14, (lists, topk, log, many)
