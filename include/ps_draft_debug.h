@@ -21,9 +21,10 @@ extern "C" {
  * five GEMM phases over n_cu workgroups with lds_limit bytes of LDS each
  * (persistent-kernel mode; a step may take fewer workgroups than there are compute units, see
  * ps_draft_debug_step_plan): per phase PS_PLAN_FIELDS ints {T, Kt, K, rows, kw_log, s_log, Gs,
- * per_round, rounds, piece_groups, npieces, lds_bytes} into out[5 * PS_PLAN_FIELDS].
+ * per_round, rounds, piece_groups, npieces, lds_bytes, panel_off, units, rs, g2_log, ahead, by_piece} into
+ * out[5 * PS_PLAN_FIELDS].
  */
-#define PS_PLAN_FIELDS 12
+#define PS_PLAN_FIELDS 18
 PS_API int ps_draft_debug_plan(const ps_draft_config* config, int batch, int n_new, int k, int all_rows, int n_cu,
                         int lds_limit, int* out);
 

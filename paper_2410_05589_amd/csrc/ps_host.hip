@@ -393,6 +393,7 @@ static long long panel_part_host(int rows, bool units, int panel_steps) {
     return units ? (long long)panel_steps * 4 * ((rows + 15) / 16 * 256) : (long long)rows * panel_row_stride_host(panel_steps);
 }
 // where a panel starts in LDS: see PS_LDS_RED in ps_device.h (shared: several wavefronts share a tile)
+static_assert((PS_LDS_BASE + 2304) % 256 == 0, "PanelAddr exchanges address bits below 256");
 static int panel_offset_host(int mt, bool shared) { return PS_LDS_BASE + 2304 + (shared ? PS_WAVES * mt * 1024 : 0); }
 
 // Cuts one GEMM phase: T tiles x Kt steps (K elements) over nwg workgroups of PS_WAVES wavefronts.
@@ -527,7 +528,7 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
 
 static void plan_fields(const PhaseDesc& d, int* out) {
     const int v[PS_PLAN_FIELDS] = {d.T, d.Kt, d.K, d.rows, d.kw_log, d.s_log, d.Gs, d.per_round, d.rounds,
-                                   d.piece_groups, d.npieces, d.lds_bytes};
+                                   d.piece_groups, d.npieces, d.lds_bytes, d.panel_off, d.units, d.rs, d.g2_log, d.ahead, d.by_piece};
     for (int i = 0; i < PS_PLAN_FIELDS; ++i) out[i] = v[i];
 }
 

@@ -4,9 +4,9 @@ import ctypes
 
 from . import binding as B
 
-PS_PLAN_FIELDS = 12
+PS_PLAN_FIELDS = 18
 PLAN_FIELD_NAMES = ("T", "Kt", "K", "rows", "kw_log", "s_log", "Gs", "per_round", "rounds", "piece_groups",
-                    "npieces", "lds_bytes")
+                    "npieces", "lds_bytes", "panel_off", "units", "rs", "g2_log", "ahead", "by_piece")
 EXPORTED_SYMBOLS = ("ps_draft_debug_plan", "ps_draft_debug_attn_plan", "ps_draft_debug_step_plan", "ps_draft_debug_merge_groups", "ps_draft_debug_spin_limit", "ps_draft_debug_timeline",
                     "ps_train_debug_launch", "ps_verify_debug_exchange", "ps_measure_stream_read", "ps_measure_copy")
 

@@ -202,6 +202,21 @@ def _check_plan(cfg, plans, batch, n_new, k, n_cu, lds):
         assert d["lds_bytes"] <= lds, tag
         arrays = 2 if cfg.dtype == B.PS_BF16 else 1
         assert d["lds_bytes"] >= d["rows"] * arrays * pg * PS_U * 64, tag   # the piece of the panel fits
+        # the panel: behind what every phase keeps at the start of LDS and, where wavefronts share a tile, their partial sums; in units
+        # at multiples of 256 bytes (their addresses are exchanged below that), and the tiles' logits behind it
+        mt = -(-batch * (n_new + k) // 16)
+        assert d["panel_off"] >= 1024 + 2304 + (PS_WAVES * mt * 1024 if KW > 1 else 0), tag
+        if d["units"]:
+            assert d["rows"] > 16 and d["panel_off"] % 256 == 0 and d["rs"] % 256 == 0 and d["rs"] >= -(-d["rows"] // 16) * 256, tag
+        else:
+            assert d["rs"] >= pg * PS_U * 64, tag
+        part = pg * PS_U * 4 * d["rs"] if d["units"] else d["rows"] * d["rs"]
+        logits = d["rounds"] * (PS_WAVES // KW) * d["rows"] * 64 if ph == 4 else 0
+        assert d["panel_off"] + arrays * part + logits <= d["lds_bytes"], tag
+        assert 6 <= d["g2_log"] <= 9, tag                        # whole wavefronts of the 512 threads along a row
+        if d["ahead"]:                                           # a thread's share of a piece: one group of at most 8 rows
+            assert ph == 4 and npc > 1 and pg * PS_U * 4 <= 1 << d["g2_log"] and d["rows"] <= (512 >> d["g2_log"]) * 8, tag
+        assert d["by_piece"] == (ph == 4 and npc > 1 and d["rounds"] > 1 and KW == 1), tag   # (sums wait where one wavefront's logits go)
 
 
 def test_phase_plans_of_the_five_workloads(lib):
@@ -263,6 +278,7 @@ def test_phase_plans_over_a_sweep_of_shapes_and_devices(lib):
     import random
     rnd = random.Random(7)
     checked = 0
+    seen = {"units": 0, "ahead": 0, "by_piece": 0, "ahead, not by piece": 0}
     for _ in range(400):
         dtype = rnd.choice(["bf16", "f32"])
         mul = 32 if dtype == "bf16" else 16
@@ -286,7 +302,11 @@ def test_phase_plans_over_a_sweep_of_shapes_and_devices(lib):
             if st == B.PS_OK:
                 _check_plan(cfg, plans, batch, n_new, k, n_cu, lds)
                 checked += 1
-    assert checked > 500
+                lm = plans[4]
+                for n in ("units", "ahead", "by_piece"):
+                    seen[n] += lm[n]
+                seen["ahead, not by piece"] += lm["ahead"] and not lm["by_piece"]
+    assert checked > 500 and min(seen.values()) > 20, (checked, seen)
 
 
 def _weight_bytes(cfg):
