@@ -444,6 +444,19 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
         }
         return best_log;
     };
+    // groups of a piece where the panel is cut into the fewest pieces that fit into `budget` bytes (0: none do)
+    auto fewest_pieces = [&](bool units, int max_slice, int budget) {
+        for (int np = 1; np <= max_slice; ++np) {
+            const int pg = (max_slice + np - 1) / np;
+            if (arrays * panel_part_host(rows, units, pg * PS_U) <= budget) return pg;
+        }
+        return 0;
+    };
+    // every slice must have the same number of pieces, each of at least kw groups (the streaming loop relies on it)
+    auto in_step = [](int pg, int min_slice, int max_slice, int kw) {
+        const int n = (max_slice + pg - 1) / pg;
+        return (min_slice + pg - 1) / pg == n && pg >= kw && min_slice - (n - 1) * pg >= kw;
+    };
     // What is supported does not depend on the layout and the cut chosen below: some plan's panel has to fit row by row beside
     // the reduction area
     bool supported = false;
@@ -451,12 +464,8 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
         const int S = 1 << sl, min_slice = NG / S, max_slice = (NG + S - 1) / S;
         for (int lg = most_shared(S, nwg >> sl, min_slice); lg >= 0 && !supported; --lg) {
             const int kw = 1 << lg, SL = PS_WAVES >> lg, rounds = (T + (nwg >> sl) * SL - 1) / ((nwg >> sl) * SL);
-            const int beside = lds_limit - panel_offset_host(mt, true) - (ph == PH_LMHEAD ? rounds * SL * rows * 64 : 0) - 256;
-            int np = 1;
-            while (np <= max_slice && (beside <= 0 || arrays * panel_part_host(rows, false, (max_slice + np - 1) / np * PS_U) > beside)) ++np;
-            if (np > max_slice) continue;
-            const int pg = (max_slice + np - 1) / np, n = (max_slice + pg - 1) / pg;
-            supported = (min_slice + pg - 1) / pg == n && pg >= kw && min_slice - (n - 1) * pg >= kw;
+            const int pg = fewest_pieces(false, max_slice, lds_limit - panel_offset_host(mt, true) - (ph == PH_LMHEAD ? rounds * SL * rows * 64 : 0) - 256);
+            supported = pg > 0 && in_step(pg, min_slice, max_slice, kw);
         }
     }
     if (!supported) return false;
@@ -472,29 +481,26 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
             const int fixed = panel_off + (ph == PH_LMHEAD ? rounds * SL * rows * 64 : 0);
             const int budget = lds_limit - fixed - 256;
             if (budget <= 0) continue;
-            // Fewest pieces whose panel fits; every slice must have the same number of pieces, each of
-            // at least kw groups (the streaming loop relies on it).  The LM head's pieces after the first are requested
-            // ahead if a thread's share of one is a single group of at most 8 rows (see request_piece): rather more
-            // pieces than none requested ahead
+            // Fewest pieces whose panel fits.  The LM head's pieces after the first are requested ahead if a thread's share of one
+            // is a single group of at most 8 rows (see request_piece): rather more pieces than none requested ahead.  us, more pieces /
+            // fewest: 7B shape, 18 rows 181.1 / 181.2 (4 / 2 pieces), 21 rows 182.8 / 187.1 (4 / 3), 36 rows 207 / 222 (8 / 6); 13B shape, 9 rows
+            // 206.3 / 209.2 (3 / 2), 18 rows 231.8 / 234.8 (5 / 3), 27 rows 244.6 / 252.4 (5 / 4), 42 rows 290 / 304 (10 / 7); 8B shape, V 128256, 18 rows 300 / 304 (4 / 3)
             struct Cut { int pg, npieces, g2_log; bool ahead; };
             auto cut = [&](bool units, Cut* x) {
-                int np = 1;
-                while (np <= max_slice && arrays * panel_part_host(rows, units, (max_slice + np - 1) / np * PS_U) > budget) ++np;
-                if (np > max_slice) return false;
+                const int pg0 = fewest_pieces(units, max_slice, budget);
+                if (pg0 == 0) return false;
                 auto make = [&](int pg) {
                     x->pg = pg;
                     x->npieces = (max_slice + pg - 1) / pg;
                     x->g2_log = 6;
                     while ((1 << x->g2_log) < pg * PS_U * 4 && (1 << x->g2_log) < PS_WG_THREADS) ++x->g2_log;
                     x->ahead = ph == PH_LMHEAD && x->npieces > 1 && pg * PS_U * 4 <= (1 << x->g2_log) && rows <= (PS_WG_THREADS >> x->g2_log) * 8;
-                    const int last = min_slice - (x->npieces - 1) * pg;   // smallest last piece over the slices
-                    return (min_slice + pg - 1) / pg == x->npieces && pg >= kw && last >= kw;
+                    return in_step(pg, min_slice, max_slice, kw);
                 };
-                const int pg = (max_slice + np - 1) / np;
-                if (ph == PH_LMHEAD && np > 1)
-                    for (int n = np; n <= max_slice; ++n)
-                        if (make((max_slice + n - 1) / n) && x->ahead) return true;
-                return make(pg);
+                if (ph == PH_LMHEAD && pg0 < max_slice)
+                    for (int np = (max_slice + pg0 - 1) / pg0; np <= max_slice; ++np)
+                        if (make((max_slice + np - 1) / np) && x->ahead) return true;
+                return make(pg0);
             };
             // Panel layout: in units from 17 rows on (see PanelAddr), unless the whole sixteens of rows that this takes make
             // more pieces.  us, units / rows, 7B shape: 48 rows 253 / 262, 27 rows 203.6 / 204.0, 42 rows 226.5 / 229.1; 8B shape with
