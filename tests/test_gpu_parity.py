@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 from paper_2410_05589_amd import binding as B
+from paper_2410_05589_amd import debug as DBG
 from paper_2410_05589_amd import inputs
 from paper_2410_05589_amd.configs import WORKLOADS, DrafterShape, Workload, small_shape
 from tests.gpu_util import run_gpu_step, compare_with_oracle, oracle_step
@@ -185,31 +186,67 @@ def test_maximum_rows_and_topk():
     _run_case(wl, all_rows=True, topk=1, label="64 rows, all decoded, top-1")
 
 
-@pytest.mark.parametrize("dtype,hidden,steps", [("bf16", 2048, ((17, 0), (11, 2), (8, 5), (8, 6), (9, 1))), ("f32", 1024, ((11, 2), (8, 7)))])
-def test_lm_head_panels_of_several_pieces_and_rounds(dtype, hidden, steps):
-    """A vocabulary of two rounds of tiles (the last partly filled, its last tile ragged) and an LM-head panel of two to
-    eight pieces, requested ahead and staged once for both rounds; 17, 33, 48, 56 (float32: 64) and 18 rows: both sides of whole
-    sixteens, where the panel's layout and its pieces change, and every number of column tiles from two on."""
-    shape = small_shape(dtype, hidden=hidden, n_heads=8, n_kv_heads=8, head_dim=128, ffn=704, vocab=33100)
-    w = inputs.make_weights(shape, 39)
+def _lm_plan(shape, batch, k, n_new=1):
+    """The plan of the LM head for such a step on this device."""
+    import torch
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    cfg = B.make_config(shape, max_batch=batch, max_new=n_new, max_positions=200, max_topk=8, k_max=max(k, 1))
+    st, _, plans, _ = DBG.ps_draft_debug_step_plan(cfg, [100] * batch, n_new, k, 0, n_cu, 160 * 1024)
+    assert st == B.PS_OK
+    return plans[4]
+
+
+def _lm_steps(shape, w, steps, seed):
+    """Steps of `batch` sequences with k [MASK] slots, each on a context of its own, against the oracle."""
     for step, (batch, k) in enumerate(steps):
         kv = tuple((29 * (b + 1) + 7 * step) % 150 for b in range(batch))
-        wl = Workload("pieces", shape, batch=batch, kv_len=kv, n_new=1, k=k, topk=4, seed=300 + step)
+        wl = Workload("pieces", shape, batch=batch, kv_len=kv, n_new=1, k=k, topk=4, seed=seed + step)
         inp = inputs.make_step_inputs(wl, kv_len=kv, n_new=1, k=k)
-        print("rows", batch * (1 + k), flush=True)
+        print("rows", batch * (1 + k), _lm_plan(shape, batch, k), flush=True)
         d = _drafter(shape, w, max_batch=batch, max_new=1, max_positions=200, k_max=k)
         res = run_gpu_step(d, inp, 1, k, 4)
         print(compare_with_oracle(shape, res, oracle_step(shape, w, inp, 1, k, 4), inp, 1, k, 4), flush=True)
         d.close()
 
 
-@pytest.mark.parametrize("replayed", [False, True])
-def test_lm_head_pieces_are_those_of_this_step(replayed):
+@pytest.mark.parametrize("dtype,hidden,steps", [("bf16", 2048, ((17, 0), (11, 2), (8, 5), (8, 6), (9, 1))), ("f32", 1024, ((11, 2), (8, 7)))])
+def test_lm_head_panels_of_several_pieces_and_rounds(dtype, hidden, steps):
+    """A vocabulary of three rounds of tiles that two wavefronts share (56 rows: of two rounds of tiles of their own), the last partly
+    filled, its last tile ragged, and an LM-head panel of two to eight pieces, all requested ahead and (but with 56 rows) staged again
+    for every round; 17, 33, 48, 56 (float32: 33 and 64) and 18 rows: both sides of whole sixteens, where the panel's layout and
+    its pieces change, and every number of column tiles from two on."""
+    shape = small_shape(dtype, hidden=hidden, n_heads=8, n_kv_heads=8, head_dim=128, ffn=704, vocab=33100)
+    for batch, k in steps:
+        p, own = _lm_plan(shape, batch, k), batch * (1 + k) == 56
+        assert p["ahead"] and p["npieces"] > 1 and (p["kw_log"], p["rounds"], p["by_piece"]) == ((0, 2, 1) if own else (1, 3, 0)), p
+    _lm_steps(shape, inputs.make_weights(shape, 39), steps, 300)
+
+
+@pytest.mark.parametrize("dtype,hidden,vocab,rounds,steps", [
+    ("bf16", 2048, 70005, 3, ((9, 1, 4, 1), (10, 2, 3, 1), (11, 2, 2, 1), (8, 5, 1, 1))),   # 18, 30 (last piece shorter), 33, 48 rows
+    ("bf16", 2048, 99990, 4, ((8, 1, 4, 0), (9, 1, 4, 0), (11, 2, 2, 0))),                  # 16, 18, 33 rows, panel row by row
+    ("f32", 1024, 70005, 3, ((8, 6, 2, 1),)),                                               # 56 rows
+    ("f32", 1024, 99990, 4, ((10, 2, 4, 1), (11, 2, 2, 1), (8, 5, 2, 1)))])                 # 30, 33, 48 rows
+def test_lm_head_piece_by_piece_over_several_rounds(dtype, hidden, vocab, rounds, steps):
+    """The LM head's panel staged once for three and four rounds of tiles, the sums waiting in the place of their logits: the last round
+    partly filled (280 and 106 of 2048 tiles, most wavefronts without one), its last tile ragged; pieces of one to four groups
+    (batch, k, groups, layout in units), one to four column tiles of rows, both layouts."""
+    shape = small_shape(dtype, hidden=hidden, n_heads=8, n_kv_heads=8, head_dim=128, ffn=704, vocab=vocab)
+    for batch, k, groups, units in steps:
+        p = _lm_plan(shape, batch, k)
+        assert p["by_piece"] and p["ahead"] and (p["rounds"], p["piece_groups"], p["units"]) == (rounds, groups, units), p
+    _lm_steps(shape, inputs.make_weights(shape, 40), [(batch, k) for batch, k, _, _ in steps], 320)
+
+
+@pytest.mark.parametrize("captured", [0, 1, 3])
+def test_lm_head_pieces_are_those_of_this_step(captured):
     """The LM head's later pieces come through the L2, which must not hold an earlier step's: twelve steps of other inputs,
-    queued without a pause (or one captured step replayed), on one context whose weights fit the caches; every output
-    bit for bit as from a context of its own."""
+    queued without a pause (or one captured step replayed, or three steps captured as neighbours of one graph), on one context
+    whose weights fit the caches; every output bit for bit as from a context of its own."""
     import torch
     shape = small_shape("bf16", hidden=1024, n_heads=8, n_kv_heads=8, head_dim=128, ffn=704, vocab=2000)
+    p = _lm_plan(shape, 8, 5)
+    assert p["npieces"] > 1 and p["ahead"], p
     w = inputs.make_weights(shape, 41)
     wl = Workload("queued", shape, batch=8, kv_len=(3, 40, 0, 77, 12, 5, 64, 31), n_new=1, k=5, topk=4, seed=42)
     inp = inputs.make_step_inputs(wl)
@@ -233,19 +270,22 @@ def test_lm_head_pieces_are_those_of_this_step(replayed):
         d.close()
     d = _drafter(shape, w, max_batch=8, max_new=1, max_positions=100, k_max=5)
     outs = [outputs(d) for _ in xs]
-    if replayed:
-        x, out = xs[0].clone(), outputs(d)
-        a = args(d, x, out)
-        d.step(a)
+    if captured:
+        nodes = [(x.clone(), outputs(d)) for x in xs[:captured]]
+        calls = [args(d, x, out) for x, out in nodes]
+        d.step(calls[0])
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
-            d.step(a, stream=torch.cuda.current_stream())
-        for xi, oi in zip(xs, outs):
-            x.copy_(xi)
+            for a in calls:
+                d.step(a, stream=torch.cuda.current_stream())
+        for i in range(0, len(xs), captured):
+            for (x, _), xi in zip(nodes, xs[i:]):
+                x.copy_(xi)
             graph.replay()
-            for n in oi:
-                oi[n].copy_(out[n])
+            for (_, out), oi in zip(nodes, outs[i:]):
+                for n in oi:
+                    oi[n].copy_(out[n])
     else:
         for a in [args(d, x, out) for x, out in zip(xs, outs)]:
             d.step(a)
