@@ -9,6 +9,8 @@
 // the key tiles; scores are MFMA tiles (the keys' rows are the row operand, the query rows the column operand).  bf16
 // values: ga_attn_wide_kernel (and, for the smallest calls, ga_attn_bf16_kernel); float32 values: ga_attn_f32_kernel.
 // Each describes its own scheme.
+#include <algorithm>
+
 #include "ps_device.h"
 #include "ps_train.h"
 #include "ps_draft_debug.h"
@@ -1164,7 +1166,7 @@ struct GaLaunch {
     dim3 rope, attn;
 };
 dim3 grid_xy(long long workgroups, int z) {
-    const unsigned x = (unsigned)min(workgroups, (long long)GA_GRID_X);
+    const unsigned x = (unsigned)std::min(workgroups, (long long)GA_GRID_X);   // (HIP's own host min is that of ints)
     return dim3(x, (unsigned)((workgroups + x - 1) / x), z);
 }
 GaLaunch plan(const GaParams& P, int dtype, int head_dim) {
@@ -1196,7 +1198,7 @@ GaLaunch plan(const GaParams& P, int dtype, int head_dim) {
     }
     // the rotation: a workgroup per position; where positions are few, several (of at most one item per thread each) share one's rows
     const long long items = (long long)P.seqs * P.nkv * (head_dim / 8) * (L.kernel == GA_WIDE ? 1 : P.k + 1);
-    L.rope = dim3(P.T + P.k, (unsigned)max(1LL, min((items + 255) / 256, 2048LL / (P.T + P.k))));
+    L.rope = dim3(P.T + P.k, (unsigned)std::max(1LL, std::min((items + 255) / 256, 2048LL / (P.T + P.k))));
     return L;
 }
 

@@ -61,12 +61,13 @@ def test_launches_stay_within_the_limits_of_a_launch(lib):
     """Work items of a launch in x are at most 2^32 - 1 and workgroups in y and z at most 65535 each, whatever the
     sizes that the entry point takes; and the attention's workgroups cover all rows of all heads and sequences."""
     from paper_2410_05589_amd import debug as DBG
-    rows_of = {0: 64, 2: 128}
+    rows_of, seen = {0: 64, 2: 128, 3: 32, 4: 32}, set()     # (1, the bf16 tiles of whole groups, counts otherwise)
     for dtype, seqs, T, k, nq, nkv, d in [
             ("bf16", 1, 2048, 4, 32, 32, 128), ("bf16", 4096, 1, 0, 4096, 1, 64), ("bf16", 4097, 1, 0, 4096, 1, 64),
             ("bf16", 65535, 1, 0, 8192, 1, 64), ("bf16", 1, (1 << 20) - 15, 15, 128, 8, 128), ("bf16", 65535, 4, 3, 640, 1, 128),
             ("f32", 2, 300, 3, 8, 8, 64), ("f32", 1, 1024, 15, 32768, 1, 64), ("f32", 1, (1 << 20) - 15, 15, 32, 8, 128),
-            ("f32", 65535, 1, 0, 65535, 1, 64), ("f32", 3, 1 << 19, 0, 1024, 1, 64)]:
+            ("f32", 65535, 1, 0, 65535, 1, 64), ("f32", 3, 1 << 19, 0, 1024, 1, 64),
+            ("f32", 1, (1 << 20) - 15, 15, 8190, 1, 64), ("f32", 1, (1 << 20) - 15, 15, 8190, 1, 128)]:
         a = TR.make_args(seqs, T, k, nq, nkv, d, dtype, 10000.0)
         st, g = DBG.ps_train_debug_launch(a)
         tag = (dtype, seqs, T, k, nq, g)
@@ -75,10 +76,12 @@ def test_launches_stay_within_the_limits_of_a_launch(lib):
             assert x * threads < 1 << 32 and 1 <= y <= 65535 and 1 <= z <= 65535, tag
         assert g["rope_grid"][0] == T + k, tag
         if g["kernel"] in rows_of:
-            blocks = -(-T * (k + 1) // rows_of[g["kernel"]]) * nq * (1 if g["kernel"] == 0 else seqs)
+            blocks = -(-T * (k + 1) // rows_of[g["kernel"]]) * nq * (seqs if dtype == "bf16" else 1)
             x, y, z = g["grid"]
-            assert blocks <= x * y < blocks + x and z == (seqs if g["kernel"] == 0 else 1), tag
-    huge = TR.make_args(1, 1 << 19, 15, 32768, 1, 64, "f32", 10000.0)           # 2^32 blocks of 64 rows
+            assert blocks <= x * y < blocks + x and blocks < 1 << 32 and z == (1 if dtype == "bf16" else seqs), tag
+        seen.add(g["kernel"])
+    assert seen >= set(rows_of), seen
+    huge = TR.make_args(1, 1 << 19, 15, 32768, 1, 64, "f32", 10000.0)           # 2^33 blocks of 32 rows
     assert DBG.ps_train_debug_launch(huge)[0] == B.PS_ERR_UNSUPPORTED and TR.ps_group_attention_workspace_bytes(huge) == 0
     assert DBG.ps_train_debug_launch(TR.make_args(1, 64, 16, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_UNSUPPORTED
     assert DBG.ps_train_debug_launch(TR.make_args(0, 64, 4, 8, 8, 64, "bf16", 10000.0))[0] == B.PS_ERR_SHAPE
