@@ -9,10 +9,20 @@ import pytest
 
 from oracle import group_attention as ga
 from paper_2410_05589_amd import binding as B
+from paper_2410_05589_amd import debug as DBG
 from paper_2410_05589_amd import inputs
 from paper_2410_05589_amd import train as TR
 
 pytestmark = pytest.mark.gpu
+
+# The kernels as ps_train_debug_launch numbers them: float32 with 64 rows x 2 wavefronts per 16 (head_dim 128), bf16 tiles of 16
+# rows, bf16 blocks of 128 rows, float32 with 32 rows x 2 (head_dim 64), float32 with 32 rows x 4 (short calls)
+F32_64, TILES, WIDE, F32_32, F32_SHORT = range(5)
+
+
+def check_kernel(want, seqs, T, k, nq, nkv, d, dtype):
+    st, g = DBG.ps_train_debug_launch(TR.make_args(seqs, T, k, nq, nkv, d, dtype, 10000.0))
+    assert st == B.PS_OK and g["kernel"] == want, g
 
 
 def run_gpu(inp, seqs, T, k, nq, nkv, d, dtype, base=10000.0):
@@ -30,7 +40,9 @@ def run_gpu(inp, seqs, T, k, nq, nkv, d, dtype, base=10000.0):
     return out.cpu().numpy()
 
 
-def _case(seqs, T, k, nq, nkv, d, dtype, seed, base=10000.0):
+def _case(seqs, T, k, nq, nkv, d, dtype, seed, base=10000.0, kernel=None):
+    if kernel is not None:
+        check_kernel(kernel, seqs, T, k, nq, nkv, d, dtype)
     print("case seqs", seqs, "T", T, "k", k, "heads", nq, nkv, "d", d, dtype, flush=True)
     inp = inputs.make_group_attention_inputs(seed, seqs, T, k, nq, nkv, d, dtype)
     got = run_gpu(inp, seqs, T, k, nq, nkv, d, dtype, base)
@@ -59,7 +71,7 @@ def test_longer_sequence_and_other_rope_base_bf16():
 
 def test_longer_sequences_with_other_group_sizes():
     """Several tiles of keys per wavefront (tiles every query sees entirely, the masked last ones, the own [MASK] rows), several
-    blocks of rows, with 8, 16 and 2 rows per group in the wide bf16 kernel and 4 in the float32 one."""
+    blocks of rows, with 8, 16 and 2 rows per group in the wide bf16 kernel and 4 in the float32 one of short calls."""
     _case(1, 200, 7, 4, 4, 128, "bf16", 8)
     _case(1, 130, 15, 2, 1, 128, "bf16", 9)
     _case(2, 150, 1, 4, 2, 64, "bf16", 10)
@@ -86,28 +98,39 @@ def test_tiles_of_16_rows_at_their_edges(seqs, T, k, nq, nkv, d):
 
 
 @pytest.mark.parametrize("seqs,T,k,nq,nkv,d", [
-    (1, 64, 0, 2, 1, 64), (1, 65, 0, 1, 1, 128),                  # k = 0: exactly 1 and 2 blocks of 64 rows; 2 and 3 stages of 32 keys
+    (1, 64, 0, 2, 1, 64), (1, 65, 0, 1, 1, 128),                  # k = 0: exactly 2 blocks of 32 rows and one more row; 1 and 2 stages of 64 keys
     (1, 33, 1, 2, 2, 64), (2, 43, 2, 3, 1, 64),                   # blocks that start inside a group; a query tile without rows
-    (1, 13, 4, 2, 2, 128), (1, 40, 10, 2, 1, 64), (3, 17, 15, 2, 2, 64)])
-def test_float32_blocks_of_64_rows_at_their_edges(seqs, T, k, nq, nkv, d):
-    _case(seqs, T, k, nq, nkv, d, "f32", 200 + T + k)
+    (1, 13, 4, 2, 2, 128), (1, 40, 10, 2, 1, 64), (3, 17, 15, 2, 2, 64),
+    (1, 32, 0, 1, 1, 64), (1, 33, 0, 2, 1, 64), (1, 64, 0, 1, 1, 128), (2, 65, 0, 1, 1, 64),   # exactly 1, 2 and 3 blocks of 32 rows
+    (1, 9, 7, 2, 2, 64), (1, 5, 15, 2, 1, 128), (1, 1, 2, 1, 1, 64),                            # own rows of several stages; a wavefront without keys
+    (1, 88, 7, 32, 8, 64), (1, 100, 7, 16, 16, 128)])                                           # the longest short calls: 704 and 400 blocks
+def test_float32_short_calls_at_their_edges(seqs, T, k, nq, nkv, d):
+    _case(seqs, T, k, nq, nkv, d, "f32", 200 + T + k, kernel=F32_SHORT)
 
 
 @pytest.mark.parametrize("seqs,T,k,nq,nkv,d", [
-    (1, 32, 0, 1, 1, 64), (1, 33, 0, 2, 1, 64), (1, 64, 0, 1, 1, 128), (2, 65, 0, 1, 1, 64),   # short calls: exactly 1, 2 and 3 blocks of 32 rows; 1 and 2 stages of 64 keys
-    (1, 9, 7, 2, 2, 64), (1, 5, 15, 2, 1, 128), (1, 1, 2, 1, 1, 64),                            # own rows of several stages; a wavefront without keys
-    (5, 150, 3, 8, 8, 64), (4, 100, 3, 8, 4, 128)])                                             # just beyond the short calls: 760 and 416 blocks
-def test_float32_blocks_of_32_rows_and_the_line_to_longer_calls(seqs, T, k, nq, nkv, d):
-    _case(seqs, T, k, nq, nkv, d, "f32", 300 + T + k)
+    (8, 64, 0, 46, 23, 64), (8, 65, 0, 30, 30, 64),               # k = 0: exactly 2 blocks of 32 rows, and one more row; 2 and 3 stages of 32 keys
+    (12, 33, 1, 20, 4, 64), (10, 43, 2, 15, 5, 64),               # blocks that start inside a group; a query tile without rows
+    (8, 13, 4, 32, 8, 64), (6, 40, 10, 9, 3, 64), (8, 17, 15, 10, 10, 64), (24, 1, 2, 30, 1, 64), (5, 5, 15, 50, 25, 64),
+    (5, 150, 3, 8, 8, 64),
+    (7, 64, 0, 30, 15, 128), (7, 65, 0, 20, 20, 128), (7, 129, 0, 12, 3, 128),   # blocks of 64 rows: exactly 1, one more row, exactly 2 and one more
+    (7, 33, 1, 20, 4, 128), (6, 43, 2, 15, 5, 128), (5, 13, 4, 28, 7, 128), (4, 40, 10, 9, 3, 128), (5, 17, 15, 10, 10, 128),
+    (16, 1, 2, 26, 1, 128), (4, 5, 15, 40, 20, 128), (4, 100, 3, 8, 4, 128)])
+def test_float32_longer_calls_at_their_edges(seqs, T, k, nq, nkv, d):
+    """Calls beyond the short ones (704 workgroups of 32 rows, head_dim 128: 400): 32 rows with two wavefronts per 16, 64 rows for head_dim 128."""
+    _case(seqs, T, k, nq, nkv, d, "f32", 300 + T + k, kernel=F32_32 if d == 64 else F32_64)
 
 
-@pytest.mark.parametrize("dtype,k,d", [("bf16", 0, 128), ("bf16", 0, 64), ("bf16", 3, 128), ("f32", 0, 64)])
-def test_scores_that_overflow_before_a_row_sees_a_finite_one(dtype, k, d):
+@pytest.mark.parametrize("dtype,k,nq,d,kernel", [
+    ("bf16", 0, 2, 128, WIDE), ("bf16", 0, 2, 64, WIDE), ("bf16", 3, 2, 128, WIDE), ("f32", 0, 2, 64, F32_SHORT), ("f32", 3, 2, 128, F32_SHORT),
+    ("f32", 0, 240, 64, F32_32), ("f32", 3, 80, 64, F32_32), ("f32", 0, 140, 128, F32_64), ("f32", 3, 46, 128, F32_64)])
+def test_scores_that_overflow_before_a_row_sees_a_finite_one(dtype, k, nq, d, kernel):
     """The first 32 real tokens' keys lie opposite to every query and so far out that their scores are -inf in float32
     (q.k = -1e40; in the pair of dimensions that the rotation turns least); from token 32 on all keys are ordinary.  Rows
     that see an ordinary real token have a finite result, the oracle's (float64: the first 32 weigh exp(-1e39) = 0)."""
-    T, nq = 70, 2
-    print("case overflowing scores", dtype, "k", k, "d", d, flush=True)
+    T = 70
+    print("case overflowing scores", dtype, "k", k, "heads", nq, "d", d, flush=True)
+    check_kernel(kernel, 1, T, k, nq, nq, d, dtype)
     inp = inputs.make_group_attention_inputs(31 + k, 1, T, k, nq, nq, d, dtype)
     from oracle.ps_oracle import round_to_storage, widen
     q, kk = widen(inp["q"], dtype), widen(inp["k"], dtype)
@@ -126,16 +149,19 @@ def test_scores_that_overflow_before_a_row_sees_a_finite_one(dtype, k, d):
     assert np.abs(got[rows] - want[rows]).max() <= (2e-3 if dtype == "bf16" else 2e-5) * np.abs(want[rows]).max()
 
 
-@pytest.mark.parametrize("dtype,T,k,nq,nkv,d", [
-    ("bf16", 70, 4, 2, 1, 128), ("bf16", 70, 4, 2, 2, 64), ("bf16", 150, 0, 2, 2, 128), ("bf16", 40, 15, 2, 2, 64),
-    ("f32", 70, 4, 2, 1, 64), ("f32", 90, 0, 2, 2, 128), ("f32", 20, 15, 2, 2, 64),
-    ("bf16", 20, 5, 2, 2, 128), ("bf16", 32, 14, 2, 2, 64),                      # (16-row tiles)
-    ("bf16", 32, 15, 2, 2, 64)])
-def test_values_that_a_row_may_not_see_do_not_reach_it(dtype, T, k, nq, nkv, d):
+@pytest.mark.parametrize("dtype,T,k,nq,nkv,d,kernel", [
+    ("bf16", 70, 4, 2, 1, 128, WIDE), ("bf16", 70, 4, 2, 2, 64, WIDE), ("bf16", 150, 0, 2, 2, 128, WIDE), ("bf16", 40, 15, 2, 2, 64, WIDE),
+    ("f32", 70, 4, 2, 1, 64, F32_SHORT), ("f32", 90, 0, 2, 2, 128, F32_SHORT), ("f32", 20, 15, 2, 2, 64, F32_SHORT),
+    ("f32", 70, 4, 66, 11, 64, F32_32), ("f32", 90, 0, 236, 59, 64, F32_32), ("f32", 20, 15, 72, 72, 64, F32_32),
+    ("f32", 70, 4, 38, 19, 128, F32_64), ("f32", 90, 0, 134, 67, 128, F32_64), ("f32", 20, 15, 42, 42, 128, F32_64),
+    ("bf16", 20, 5, 2, 2, 128, TILES), ("bf16", 32, 14, 2, 2, 64, TILES),
+    ("bf16", 32, 15, 2, 2, 64, WIDE)])
+def test_values_that_a_row_may_not_see_do_not_reach_it(dtype, T, k, nq, nkv, d, kernel):
     """Value rows that hold Inf and NaN: two [MASK] tokens' and one real token's.  Rows that see none of them have the
     oracle's result (their own keys and values only), the others are not finite."""
     from oracle.ps_oracle import widen
-    print("case non-finite values", dtype, "T", T, "k", k, "d", d, flush=True)
+    print("case non-finite values", dtype, "T", T, "k", k, "heads", nq, nkv, "d", d, flush=True)
+    check_kernel(kernel, 1, T, k, nq, nkv, d, dtype)
     inp = inputs.make_group_attention_inputs(61 + T + k, 1, T, k, nq, nkv, d, dtype)
     want = ga.group_attention(inp["q"][0], inp["k"][0], inp["v"][0], T, k, 10000.0, dtype)
     K1 = k + 1
@@ -156,11 +182,14 @@ def test_values_that_a_row_may_not_see_do_not_reach_it(dtype, T, k, nq, nkv, d):
     assert np.abs(got[~sees] - want[~sees]).max() <= (2e-3 if dtype == "bf16" else 2e-5) * np.abs(want).max()
 
 
-@pytest.mark.parametrize("dtype,T,k,nq,nkv,d", [("bf16", 90, 4, 4, 2, 128), ("bf16", 70, 0, 2, 2, 64), ("bf16", 20, 5, 2, 2, 128), ("f32", 50, 3, 4, 2, 64)])
-def test_tensors_that_are_aligned_to_four_bytes_only(dtype, T, k, nq, nkv, d):
+@pytest.mark.parametrize("dtype,T,k,nq,nkv,d,kernel", [
+    ("bf16", 90, 4, 4, 2, 128, WIDE), ("bf16", 70, 0, 2, 2, 64, WIDE), ("bf16", 20, 5, 2, 2, 128, TILES), ("f32", 50, 3, 4, 2, 64, F32_SHORT),
+    ("f32", 40, 2, 6, 3, 128, F32_SHORT), ("f32", 50, 3, 104, 52, 64, F32_32), ("f32", 50, 3, 60, 30, 128, F32_64)])
+def test_tensors_that_are_aligned_to_four_bytes_only(dtype, T, k, nq, nkv, d, kernel):
     """q, k, v and out at 4, 8 and 12 bytes from a 16-byte boundary: the outputs of the same call with aligned ones."""
     import torch
-    print("case alignment", dtype, "T", T, "k", k, "d", d, flush=True)
+    print("case alignment", dtype, "T", T, "k", k, "heads", nq, nkv, "d", d, flush=True)
+    check_kernel(kernel, 1, T, k, nq, nkv, d, dtype)
     inp = inputs.make_group_attention_inputs(91, 1, T, k, nq, nkv, d, dtype)
     want = run_gpu(inp, 1, T, k, nq, nkv, d, dtype)
     esz = 2 if dtype == "bf16" else 4
