@@ -483,9 +483,9 @@ def verify_walk_report(torch, with_oracle, vocab=32000, k=5, calls=200):
     workload's drafter: 61 nodes (fan-out 4, 2, 2, 1, 1 over the k+1 = 6 draft rows) for k = 5, 46 nodes
     (fan-out 3, 2, 1, ...) for k = 8; the workload's vocabulary; one sequence; a target that agrees with the
     drafter's next row to 70 %.  Latency per call from HIP
-    events over `calls` back-to-back calls; bytes = what the walk has to read when P stays on chip (first
-    rejection at a node: the target's row and the draft row; further ones: the draft row; the final draw: the
-    target's row if P is still that row), counted on the oracle's walk of the same inputs."""
+    events over `calls` back-to-back calls; bytes = what the walk has to read when P and the draft row of a node
+    stay on chip (first rejection at a node: the target's row and the draft row; further ones: nothing; the final
+    draw: the target's row if P is still that row), counted on the oracle's walk of the same inputs."""
     from paper_2410_05589_amd import inputs
     from paper_2410_05589_amd import verify as VF
     dev = torch.device("cuda:0")
@@ -545,8 +545,7 @@ def verify_walk_report(torch, with_oracle, vocab=32000, k=5, calls=200):
         c0 = time.perf_counter()
         ref = vw.acceptance_walk(parent, tok, inp["q"][0], inp["p"][0], inp["r"][0])
         cpu_s = time.perf_counter() - c0
-        nbytes = vocab * (8 * ref["rejected_from_row"] + 4 * ref["rejected_from_residual"]
-                          + (4 if ref["final_from_row"] else 0))
+        nbytes = vocab * (8 * ref["rejected_from_row"] + (4 if ref["final_from_row"] else 0))
         gbs = nbytes / (walk_us * 1e-6) / 1e9
         rep.update({"agrees_with_oracle": bool(out_tokens.cpu().numpy()[0, :len(ref["tokens"])].tolist() == ref["tokens"]),
                     "rejections": ref["rejected_from_row"] + ref["rejected_from_residual"],

@@ -440,7 +440,8 @@ __global__ void __launch_bounds__(WALK_THREADS) verify_walk_kernel(const WalkPar
 // rows of every node where a child was rejected (one compute unit takes 2 us for 256 KB), a sum over the workgroup per
 // rejection.  Trees of 61 nodes, tokens and walk, among others of their kind: one sequence of V 32000 27.9 -> 13.5 us, eight of
 // V 128256 37.3 -> 18.3 us, against this kernel with the drafter's row read again for every sibling, P(x) through LDS
-// and a pass over all slabs for the draw (and, V 128256, both rows read again for every rejection and the draw).
+// and a pass over all slabs for the draw (and, V 128256, both rows read again for every rejection and the draw).  Those are inputs
+// that come again at once; in turn with more inputs than the caches hold 25.3 -> 14.9 and 38.3 -> 20.0 us.
 constexpr int REG_SLABS = 8, REG_SLABS_MULTI = 4, REG_SLAB = 4 * WALK_THREADS;   // (entries a workgroup holds per slab of all its wavefronts)
 template <int SLABS, bool MULTI>
 __global__ void __launch_bounds__(WALK_THREADS) verify_walk_reg_kernel(const WalkParams Wp) {
