@@ -413,15 +413,14 @@ __device__ __forceinline__ bool grp_head(u64 key, unsigned& top) {
 __device__ __forceinline__ unsigned kth_largest(const unsigned* top, bool wide, int k) {
     const unsigned mine = top[threadIdx.x & (wide ? 63 : 31)];
     int ge = 0;
-    auto count = [&](const unsigned* t) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int h = 0; h <= (wide ? 32 : 0); h += 32) {   // (wide: 0.4 us of a step)
 #pragma unroll
         for (int i = 0; i < 32; i += 4) {
-            const uint4 o = *reinterpret_cast<const uint4*>(t + i);
+            const uint4 o = *reinterpret_cast<const uint4*>(top + h + i);
             ge += (o.x >= mine) + (o.y >= mine) + (o.z >= mine) + (o.w >= mine);
         }
-    };
-    count(top);
-    if (__builtin_expect(wide, 0)) count(top + 32);   // (0.4 us of a step)
+    }
     return wave_max_u32(ge >= k ? mine : 0u);   // (the largest value that k groups reach; 0 if there are fewer)
 }
 
@@ -2698,8 +2697,9 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
     // that (ps_merge_groups_log) or too many keys are left (a great many equal logits), merged head by head: by
     // wavefront, then the wavefronts'.
     constexpr int MAX_CAND = PS_MERGE_CANDIDATES, SEL = PS_MERGE_SELECT_MAX;
-    const int gs_log = ps_merge_groups_log(nparts, topk);  // log2 of the lists of a group
-    const bool select = gs_log >= 0, wide = select && ((nparts - 1) >> gs_log) >= 32;   // (more than 32 groups)
+    // (the host evaluates the rule: worked out here it cost steps of 17 to 32 rows 0.6 %; the bounds on topk are for the compiler)
+    const int gs_log = P.merge_log;                        // log2 of the lists of a group
+    const bool select = gs_log >= 0 && topk > 4 && topk <= SEL;
     auto merge_lists = [&]() __attribute__((always_inline)) {
         for (int t = 0; t < topk; ++t) {
             unsigned top;
@@ -2749,7 +2749,7 @@ __device__ __forceinline__ void lm_merge_row(const StepParams& P, int m, int wav
     if (lane == 0) sf[PS_WAVES + wave] = wsum;
     if (select) {
         // the keys that may be among the topk largest, in no order (a thread's are the first of its list)
-        const unsigned bound = max(kth_largest(s_top, wide, topk), 1u);
+        const unsigned bound = max(kth_largest(s_top, P.merge_wide, topk), 1u);
         int n = 0;
         bool more = true;
 #pragma unroll

@@ -845,6 +845,9 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
         P.ph[ph].frag = (float*)(ctx->act_base + ctx->off_frag[ph]);
         P.ph[ph].ssq_frag = (float*)(ctx->act_base + ctx->off_ssqf[ph]);
     }
+    const int lists = P.ph[PH_LMHEAD].T < nwg ? P.ph[PH_LMHEAD].T : nwg;   // workgroups that have vocabulary tiles
+    P.merge_log = ps_merge_groups_log(lists, P.topk);
+    P.merge_wide = P.merge_log >= 0 && ((lists - 1) >> P.merge_log) >= 32;
     P.attn_items = sp.attn.items; P.attn_single = sp.attn.single; P.attn_sep = sp.attn.sep; P.attn_tail = sp.attn.tail; P.attn_nk = sp.attn.nk;
     P.attn_merge_items = sp.attn.merge_items; P.attn_nwg = sp.attn.nwg;
     if (attn2) {

@@ -58,11 +58,11 @@ constexpr int ps_attn2_lds_bytes(int d) {
 //   a list per group: 12 % with 16 lists and topk 16, 1.2 % with 17; 3 % with 13 and topk 13, 0.8 % with 12 and topk 12: so many lists;
 //   several: 20 % with 16 groups and topk 16, 14 % with 17, 0.2 % with 20; 0.15 % with 17 and topk 14: so topk + 4 groups, of up to 32 if
 //   those are enough, else of up to 64 (whose bound costs 0.4 us).
-// us, mean over eight inputs, merged / selected by this rule: H 256, five rows, topk 16: V 272 43.5 / 38.6, V 528 43.7 / 38.2, V 1024 44.1 / 38.7,
-// V 1040 43.8 / 38.4; H 512, V 2064, topk 16 46.9 / 39.1, 20 rows 57.8 / 49.0, topk 8 42.1 / 36.9; 7B shape, topk 8 141.7 / 138.6.
+// us, mean over eight inputs, merged / selected by this rule: H 256, five rows, topk 16: V 272 43.5 / 38.6, V 528 43.7 / 38.6, V 1024 44.1 / 38.7,
+// V 1040 43.8 / 38.6; H 512, V 2064, topk 16 46.9 / 39.0, 20 rows 57.8 / 49.2, topk 8 42.1 / 36.9; 7B shape, topk 8 141.7 / 138.8.
 #define PS_MERGE_SELECT_MAX 16
 #define PS_MERGE_CANDIDATES 64
-__host__ __device__ inline int ps_merge_groups_log(int lists, int topk) {
+inline int ps_merge_groups_log(int lists, int topk) {
     if (topk <= 4 || topk > PS_MERGE_SELECT_MAX) return -1;
     if (lists < topk + (topk > 12) && lists * topk > PS_MERGE_CANDIDATES) return -1;
     const int log = lists <= 32 ? 0 : lists <= 64 ? 1 : lists <= 128 ? 2 : lists <= 256 ? 3 : 4;
@@ -126,6 +126,7 @@ struct StepParams {
     // shape
     int H, nq, nkv, d, F, V, QD, KVD;
     int B, n_new, k, M, Mtot, R, Rtot, all_rows, topk;
+    int merge_log, merge_wide;   // the row merge: see ps_merge_groups_log; 1 if that makes more than 32 groups
     int spin_limit;    // polls after which a wait for exchanged data is given up (see spin_again)
     int final_norm, max_positions;
     float eps, inv_sqrt_d;
