@@ -7,7 +7,8 @@
 // The attention kernels walk (a) the real tokens of groups up to the queries' own and (b) the rows of the queries'
 // own groups, whose [MASK] tokens they see: no key tile that the mask hides entirely is touched.  Online softmax over
 // the key tiles; scores are MFMA tiles (the keys' rows are the row operand, the query rows the column operand).  bf16
-// values: ga_attn_wide_kernel (and, for the smallest calls, ga_attn_bf16_kernel); float32 values: ga_attn_f32_kernel.
+// values: ga_attn_wide_kernel (and, for the smallest calls, ga_attn_bf16_kernel); float32 values: ga_attn_f32_kernel (and, for
+// short calls, ga_attn_f32_short_kernel).
 // Each describes its own scheme.
 #include <algorithm>
 
