@@ -51,8 +51,39 @@ struct GaParams {
     float* out;
     float2* table;      // [T + k][d / 2]
     void* k_rot;        // rotated keys, storage type: [seqs][rows][nkv][d], or real tokens only as [seqs][nkv][T][d]
-    double log_base;
+    double log2_base;
 };
+
+// 2^x: Taylor's series of e^(f ln 2), |f| <= 1/2, to the 13th power (the next is 4e-18)
+__device__ __forceinline__ double ga_exp2(double x) {
+    const double n = rint(x), y = (x - n) * 0.69314718055994530942;
+    double p = 1.0 / 6227020800.0;
+    constexpr double c[13] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
+                              1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600};
+#pragma unroll
+    for (int i = 12; i >= 0; --i) p = fma(p, y, c[i]);
+    return ldexp(p, (int)n);
+}
+// cosine and sine of a >= 0: the multiple of pi / 2 taken off in two parts (the first product is exact inside its fma, the second
+// part is below 1e-9), Taylor's series on [-pi / 4, pi / 4] to r^16 and r^17 (what follows is below 2e-18).  Angles beyond
+// 2^22 (a base below 1) are the library's business
+__device__ __forceinline__ float2 ga_cos_sin(double a) {
+    if (!(a <= 4194304.0)) return make_float2((float)cos(a), (float)sin(a));
+    const double n = rint(a * 0.63661977236758134308);
+    const double r = fma(-n, 6.123233995736766036e-17, fma(-n, 1.5707963267948965580, a)), z = r * r;
+    constexpr double cc[9] = {1.0, -1.0 / 2, 1.0 / 24, -1.0 / 720, 1.0 / 40320, -1.0 / 3628800, 1.0 / 479001600, -1.0 / 87178291200.0, 1.0 / 20922789888000.0};
+    constexpr double sc[9] = {1.0, -1.0 / 6, 1.0 / 120, -1.0 / 5040, 1.0 / 362880, -1.0 / 39916800, 1.0 / 6227020800.0, -1.0 / 1307674368000.0, 1.0 / 355687428096000.0};
+    double c = cc[8], s = sc[8];
+#pragma unroll
+    for (int i = 7; i >= 0; --i) {
+        c = fma(c, z, cc[i]);
+        s = fma(s, z, sc[i]);
+    }
+    const float fc = (float)c, fs = (float)(s * r);
+    const int q = (int)n;                                   // quarter turns
+    const float x = q & 1 ? fs : fc, y = q & 1 ? fc : fs;
+    return make_float2((q + 1) & 2 ? -x : x, q & 2 ? -y : y);
+}
 
 // Rotary table and keys in one launch.  A workgroup takes one position, works out its cosines and sines (double precision,
 // once for all heads, sequences and slots) and rotates the key rows that stand there, rounded as the inference path caches
@@ -60,29 +91,40 @@ struct GaParams {
 // slot) stands at group + slot).  Otherwise the real tokens' rows only, to k_rot as [seq][kv head][token][D]: a [MASK] key is
 // seen by its own group only, and ga_attn_wide_kernel rotates those while it stages them.  (A table kernel and a kernel over
 // all rows that reads the table back: about 30 us at T 2048, k 4, 32 heads x 128; the real tokens only, as here: 9.8 us.)
+// What bounds it where positions are few is the chain of one workgroup: its first key rows are requested before the table is
+// worked out, and the table takes some 45 double operations per pair, where the library's exp, cos and sin took most of the
+// kernel's time (whole calls, us: 2 x T 300, k 3, 8 heads x 64, float32 22.9 -> 22.4, 3 x T 120, k 2 16.9 -> 16.5, 2 x T 200, k 5,
+// 16 / 4 heads x 64, bf16 15.5 -> 15.3).  As exact: of 3.2 million entries (bases 2 .. 10^6, positions up to 2^20) 60 are not
+// the correctly rounded floats, 63 with the library's.
 template <typename WT, int D, bool ALL>
 __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
     constexpr int ESZ = Traits<WT>::ESZ, Q4 = D / 8;       // groups of 4 pairs per head
     __shared__ float2 cs[D / 2];
     const int pos = blockIdx.x, tid = threadIdx.x;
-    if (tid < D / 2) {
-        const double a = (double)pos * exp(-2.0 * tid / D * P.log_base);
-        const float2 t = make_float2((float)cos(a), (float)sin(a));
-        cs[tid] = t;
-        if (blockIdx.y == 0) P.table[(size_t)pos * (D / 2) + tid] = t;
-    }
-    __syncthreads();
     const int s0 = max(0, pos - P.T + 1), slots = ALL ? min(pos, P.k) - s0 + 1 : pos < P.T;   // slots s0 .. at this position
     const long long n = (long long)slots * P.seqs * P.nkv * Q4;
-    for (long long x = (long long)blockIdx.y * 256 + tid; x < n; x += (long long)gridDim.y * 256) {
-        const int g4 = (int)(x % Q4);
+    const int g4 = tid % Q4;                                // (256 and the grid's stride are multiples of Q4)
+    size_t to = 0;
+    f32x4 a, b;
+    auto request = [&](long long x) __attribute__((always_inline)) {
         const unsigned y = (unsigned)(x / Q4), z = y / P.nkv, head = y - z * P.nkv;   // y = (slot * seqs + seq) * nkv + head
         const unsigned slot = z / P.seqs, seq = z - slot * P.seqs;
         const int sl = ALL ? s0 + (int)slot : 0;
         const size_t row = (size_t)seq * P.rows + (size_t)(pos - sl) * (P.k + 1) + sl;
         const size_t from = ((row * P.nkv + head) * D + 4 * g4) * ESZ;
-        const size_t to = ALL ? from : ((((size_t)seq * P.nkv + head) * P.T + pos) * D + 4 * g4) * ESZ;
-        const f32x4 a = load4_q<WT>((const char*)P.k_ + from), b = load4_q<WT>((const char*)P.k_ + from + D / 2 * ESZ);
+        to = ALL ? from : ((((size_t)seq * P.nkv + head) * P.T + pos) * D + 4 * g4) * ESZ;
+        a = load4_q<WT>((const char*)P.k_ + from);
+        b = load4_q<WT>((const char*)P.k_ + from + D / 2 * ESZ);
+    };
+    long long x = (long long)blockIdx.y * 256 + tid;
+    if (x < n) request(x);                                  // (on its way while the table is worked out)
+    if (tid < D / 2) {
+        const float2 t = ga_cos_sin((double)pos * ga_exp2(-2.0 * tid / D * P.log2_base));
+        cs[tid] = t;
+        if (blockIdx.y == 0) P.table[(size_t)pos * (D / 2) + tid] = t;
+    }
+    __syncthreads();
+    while (x < n) {
         f32x4 ra, rb;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -92,6 +134,8 @@ __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
         }
         store4<WT>((char*)P.k_rot + to, ra);
         store4<WT>((char*)P.k_rot + to + D / 2 * ESZ, rb);
+        x += (long long)gridDim.y * 256;
+        if (x < n) request(x);
     }
 }
 
@@ -1230,7 +1274,7 @@ GaParams shape(const ps_group_attn_args* a) {
     P.k1_magic = (unsigned)((0x100000000ull + a->k) / (unsigned)(a->k + 1));
     P.ntiles = (a->tokens + P.gpt - 1) / P.gpt;
     P.inv_sqrt_d = (float)(1.0 / sqrt((double)a->head_dim));
-    P.log_base = log((double)a->rope_base);
+    P.log2_base = log2((double)a->rope_base);
     return P;
 }
 

@@ -69,6 +69,14 @@ def test_longer_sequence_and_other_rope_base_bf16():
     _case(1, 300, 4, 8, 2, 128, "bf16", 7, base=500000.0)
 
 
+@pytest.mark.parametrize("base", [2.0, 1.0, 2.0 ** -24])
+def test_rotary_bases_that_reach_large_angles(base):
+    """base 2: every pair turns many times; 1: all alike; 2^-24: angles up to 1.6e9, beyond the range that the table's own cosine and
+    sine reduce.  The call takes the base as float32, so these are numbers that it holds exactly (1e-7 is not: half a unit in its last
+    place turns an angle of 1e9 by 30); an angle of 1.6e9 is then known to 1.6e9 * 2^-52 = 4e-7 on either side."""
+    _case(1, 150, 3, 2, 1, 64, "f32", 12, base=base)
+
+
 def test_longer_sequences_with_other_group_sizes():
     """Several tiles of keys per wavefront (tiles every query sees entirely, the masked last ones, the own [MASK] rows), several
     blocks of rows, with 8, 16 and 2 rows per group in the wide bf16 kernel and 4 in the float32 one of short calls."""
