@@ -777,22 +777,27 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
 //
 // K and V rows are staged once per workgroup, row by row, into two LDS buffers that take turns (registers requested a
 // tile ahead); V is transposed by the LDS unit on the way out (ds_read_b64_tr_b16: 16 lanes get 4 keys of one column each).
-// The scores of tile t + 1 are worked out beside the exponentials of tile t, so every wavefront has matrix and vector work
-// to offer at any time; two workgroups per compute unit (256 registers) are what the query and output registers allow.
+// The scores of tile t + 1 are worked out beside the exponentials of tile t, and its maxima, the stages' stores and the next
+// requests beside P.V of tile t, so every wavefront has matrix and vector work to offer at any time; the last tile works out no
+// further scores, and tiles that every query sees entirely have a loop without masks.  (With maxima and stores in front of the
+// tile's first MFMA, one loop for all tiles and scores one tile too far: 1.3 .. 3.5 % slower, T 60 15.3 -> 14.8, T 500 (two) 56.4
+// -> 54.8, T 1300, k 0 50.0 -> 48.4 us.)  Two workgroups per compute unit (256 registers) are what the query and output registers allow.
 // Everything that a workgroup reads for the first time (table, query rows, own rows, first tiles) is requested at once.  The query
 // rows are read and the output rows are written once, past the caches (non-temporal): the L2 is left to the heads' keys and
 // values (3.7 % of a T 2048, k 4 call, 4.5 % of 4 x T 1024, k 8, 9 % of T 203; the own rows read that way, too: 1 % slower, the next
 // workgroup reads 16 of them again).
 //
-// A tile is 32 MFMAs of 32 cycles per wavefront and about as much vector work: at T 2048, k 4 the matrix cores are busy 52 % of the
-// kernel's time and the vector ALU 47 % (4 x T 1024, k 8: 48 and 50 %), at 1.9 GHz; the two wavefronts of a SIMD cover each other's
-// waits only in part, and a workgroup's start (its rows come from memory) and its own rows have few MFMAs to show.  At T 203 that is
+// A tile is 32 MFMAs of 32 cycles per wavefront and about as much vector work: at T 2048, k 4 the matrix cores are busy 54 % of the
+// kernel's time, at 1.9 GHz or less: large calls are bound by power (all inputs zero, the same instructions: 278 us where random
+// values took 384 on that card, 573 for 768 at 4 x T 1024, k 8; and a quarter of the vector instructions less changed nothing).  A
+// workgroup's start (its rows come from memory) and its own rows have few MFMAs to show.  At T 203 that is
 // most of the time (matrix cores 12 %).  All 256 registers are in use and none is spilled: eight spilled ones cost 1 .. 4 %.
 // Whole calls among others of their kind, against the 16-row kernel and its three launches: T 2048, k 4, 32 heads x 128: 503 -> 347 us
 // (496 TFLOP/s of visible pairs, every product twice); 4 x T 1024, k 8, 32 / 8 heads: 1501 -> 717 us; T 203, k 5, 40 heads: 40.9 -> 25.0 us.
 // Tried: no scores ahead (other wavefront alone fills the gaps): 5 % slower; own rows as further tiles of the loop, rotated
 // between the barriers: 4 % (T 2048) and 12 % (4 x 1024, k 8) slower; raised wavefront priority in the matrix part, two
-// accumulators for the scores, four K operands requested ahead: no change.
+// accumulators for the scores, four K operands requested ahead: no change; the low parts by v_dot2c_f32_bf16 (no shift or mask per
+// value) 0.6 .. 5.5 % slower; MFMAs and vector instructions in a given alternation (sched_group_barrier) 2 .. 12 % slower.
 // ------------------------------------------------------------------------------------------
 constexpr int GW_ROWS = 32 * GA_WAVES;                     // query rows of a workgroup
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -1014,12 +1019,14 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     };
     // the reference follows the maximum only when that has moved up by more than GA_LAZY (in units of ln 2): sums and outputs
     // are relative to the same reference, so the quotient is the same, and most tiles need no rescaling
-    auto follow = [&](const f32x16& x) __attribute__((always_inline)) {
+    auto highest = [&](const f32x16& x) __attribute__((always_inline)) {
         float mt = x[0];
 #pragma unroll
         for (int i = 1; i < 16; ++i) mt = fmaxf(mt, x[i]);
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
-        mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+        return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    };
+    auto follow = [&](float mt) __attribute__((always_inline)) {
         const bool moved = mt > m_run + GA_LAZY;            // (also the first finite scores of a row)
         if (__any(moved)) {
             const float m_new = moved ? mt : m_run;
@@ -1103,7 +1110,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
             const char* kt = smem + (first - R0 + 16) * (2 * D);
             f32x16 x = scores([&](int st) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, ld16(kt + (kro ^ (st << 5)))); });
             mask(x, qg * K1 + 1 - first - 4 * half, (before ? min(qrow, r0 - 1) : qrow) - first - 4 * half);
-            follow(x);
+            follow(highest(x));
             accumulate(x, m_run, [&](int j, int m2) __attribute__((always_inline)) {
                 return transposed(kt + OFF_OV + m2 * 16 * 2 * D + (vro ^ (j << 6)), 8 * 2 * D);
             });
@@ -1125,18 +1132,39 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     f32x16 s = stage_scores(0);
     __syncthreads();
     const int real_end = active ? wg1 / 32 + 1 : 0, whole_end = (wg0 + 1) / 32;   // tiles this wavefront's queries see some of, all of
-    for (int t = 0; t < n_real; ++t) {
+    auto visible = [&](int t, f32x16& x) __attribute__((always_inline)) { mask(x, 0, qg - 32 * t - 4 * half); };
+    auto stage = [&](int t) __attribute__((always_inline)) {
         store_k(t, kst);                                    // (tile t + 2's, into the buffer of tile t, whose scores are known)
         store_v(t + 1, vst);
         load_k(t + 3, kst);
         load_v(t + 2, vst);
-        if (t < real_end) {
-            if (t >= whole_end) mask(s, 0, qg - 32 * t - 4 * half);
-            follow(s);
-            const f32x16 sn = stage_scores(t + 1);
-            accumulate(s, m_run, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
+    };
+    auto values = [&](int t) __attribute__((always_inline)) {
+        accumulate(s, m_run, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
+    };
+    int t = 0;
+    if (real_end > 0) {
+        if (whole_end == 0) visible(0, s);
+        follow(highest(s));
+        auto step = [&](auto masked) __attribute__((always_inline)) {
+            stage(t);
+            f32x16 sn = stage_scores(t + 1);
+            values(t);
+            if constexpr (masked) visible(t + 1, sn);
+            const float mt = highest(sn);
             s = sn;
-        }
+            follow(mt);
+            __syncthreads();
+        };
+        for (; t + 1 < min(whole_end, real_end); ++t) step(std::false_type{});
+        for (; t + 1 < real_end; ++t) step(std::true_type{});
+        stage(t);
+        values(t);
+        __syncthreads();
+        ++t;
+    }
+    for (; t < n_real; ++t) {
+        stage(t);
         __syncthreads();
     }
 
