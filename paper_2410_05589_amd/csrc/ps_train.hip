@@ -43,10 +43,22 @@ template <typename WT> __device__ __forceinline__ f32x4 load4_q(const void* p) {
 }
 __device__ __forceinline__ void stg_stream16_q(float* p, f32x4 v) { __builtin_nontemporal_store((f32x4_q)v, reinterpret_cast<f32x4_q*>(p)); }
 
+// Division of numbers below 2^31 by one that the host knows: n / d = (n * mul) >> shift
+struct GaDiv {
+    unsigned mul, shift;
+    __device__ __forceinline__ unsigned operator()(unsigned n) const { return (unsigned)((u64)n * mul >> shift); }
+};
+GaDiv ga_div(unsigned d) {
+    unsigned s = 0;
+    while ((1ull << s) < d) ++s;
+    return GaDiv{(unsigned)(((1ull << (31 + s)) + d - 1) / d), 31 + s};   // (mul * d exceeds 2^(31 + s) by less than d <= 2^s)
+}
 struct GaParams {
     int seqs, T, k, nq, nkv, rows, gpt, ntiles;   // gpt: groups per query tile
     unsigned k1_magic;    // ceil(2^32 / (k + 1)): a row's group is the upper half of the product (rows < 2^28; k > 0)
     float inv_sqrt_d;
+    GaDiv by_heads, by_slots, by_nkv;   // nq * seqs, nkv * seqs, nkv
+    int group;            // query heads per kv head
     const void *q, *k_, *v;
     float* out;
     float2* table;      // [T + k][d / 2]
@@ -782,7 +794,11 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
 // further scores, and tiles that every query sees entirely have a loop without masks.  (With maxima and stores in front of the
 // tile's first MFMA, one loop for all tiles and scores one tile too far: 1.3 .. 3.5 % slower, T 60 15.3 -> 14.8, T 500 (two) 56.4
 // -> 54.8, T 1300, k 0 50.0 -> 48.4 us.)  Two workgroups per compute unit (256 registers) are what the query and output registers allow.
-// Everything that a workgroup reads for the first time (table, query rows, own rows, first tiles) is requested at once.  The query
+// Everything that a workgroup reads for the first time (table, query rows, own rows, first tiles) is requested at once.  Its start
+// took 17 .. 20 thousand clocks of a workgroup's 25 (T 60), 40 (T 203), 74 (T 700) thousand: so query rows pass through LDS once, as
+// they are, and are rotated and split as operands (three passes before: high parts, low parts), the own rows' two tiles share their maximum
+// and the second multiplies the 16 keys that count, and no index is divided for.  Whole calls, us: T 60, k 4, 32 heads 14.8 -> 13.7; T 203 24.6 ->
+// 23.3; T 700, k 2, 40 heads 58.3 -> 57.2; 4 x T 1024, k 8 725 -> 702.  The output rows in one pass through LDS instead of two: 0 (head_dim 64: slower).  The query
 // rows are read and the output rows are written once, past the caches (non-temporal): the L2 is left to the heads' keys and
 // values (3.7 % of a T 2048, k 4 call, 4.5 % of 4 x T 1024, k 8, 9 % of T 203; the own rows read that way, too: 1 % slower, the next
 // workgroup reads 16 of them again).
@@ -792,8 +808,8 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
 // values took 384 on that card, 573 for 768 at 4 x T 1024, k 8; and a quarter of the vector instructions less changed nothing).  A
 // workgroup's start (its rows come from memory) and its own rows have few MFMAs to show.  At T 203 that is
 // most of the time (matrix cores 12 %).  All 256 registers are in use and none is spilled: eight spilled ones cost 1 .. 4 %.
-// Whole calls among others of their kind, against the 16-row kernel and its three launches: T 2048, k 4, 32 heads x 128: 503 -> 347 us
-// (496 TFLOP/s of visible pairs, every product twice); 4 x T 1024, k 8, 32 / 8 heads: 1501 -> 717 us; T 203, k 5, 40 heads: 40.9 -> 25.0 us.
+// Whole calls among others of their kind, against the 16-row kernel and its three launches: T 2048, k 4, 32 heads x 128: 503 -> 339 us
+// (507 TFLOP/s of visible pairs, every product twice); 4 x T 1024, k 8, 32 / 8 heads: 1501 -> 700 us; T 203, k 5, 40 heads: 40.9 -> 23.3 us.
 // Tried: no scores ahead (other wavefront alone fills the gaps): 5 % slower; own rows as further tiles of the loop, rotated
 // between the barriers: 4 % (T 2048) and 12 % (4 x 1024, k 8) slower; raised wavefront priority in the matrix part, two
 // accumulators for the scores, four K operands requested ahead: no change; the low parts by v_dot2c_f32_bf16 (no shift or mask per
@@ -826,12 +842,13 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     constexpr int NP = D / 64;                              // pieces of a row per thread, 8 threads per row
     constexpr int KSTR = 2 * D + 16, VSTR = 2 * D + 64, KBUF = 32 * KSTR, VBUF = 32 * VSTR, OFF_V = 2 * KBUF;
     // before them: the query rows on their way into registers (from 0), the rows' part of the rotary table
-    constexpr int OFF_T = GA_WAVES * 32 * KSTR, TROW = D / 2 * 8, TROWS = 66;   // positions of GW_ROWS rows: at most (GW_ROWS - 2) / K1 + 1 + K1, K1 = 2 .. 16
+    constexpr int OFF_T = GA_WAVES * 32 * KSTR, TROW = D / 2 * 8 + 16, TROWS = 66;   // positions of GW_ROWS rows: at most (GW_ROWS - 2) / K1 + 1 + K1, K1 = 2 .. 16
     // ... then the own rows: layout rows R0 - 16 .. R0 + 127, K and V
     constexpr int OROWS = GW_ROWS + 16, OFF_OV = OROWS * 2 * D;
     constexpr int OCOLS = D == 128 ? 64 : 32;               // output columns that pass through LDS at a time
     constexpr int SMEM = 2 * OFF_OV > OFF_T + TROWS * TROW ? 2 * OFF_OV : OFF_T + TROWS * TROW;
-    static_assert(OFF_V + 2 * VBUF <= SMEM && GA_WAVES * 32 * OCOLS * 4 <= SMEM && 2 * SMEM <= 160 * 1024, "");
+    constexpr int TAREA = SMEM / GA_WAVES & ~15;            // k = 0: the wavefront's part of the table
+    static_assert(32 * TROW <= TAREA && OFF_V + 2 * VBUF <= SMEM && GA_WAVES * 32 * OCOLS * 4 <= SMEM && 2 * SMEM <= 160 * 1024, "");
     __shared__ __attribute__((aligned(16))) char smem[SMEM];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, half = lane >> 5;
@@ -840,10 +857,10 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     // heads, so that (kv heads x sequences a multiple of 8) a kv head's rows are read through one L2
     const unsigned slots = (unsigned)P.nkv * P.seqs, heads = (unsigned)P.nq * P.seqs;
     const unsigned wg = blockIdx.y * GA_GRID_X + blockIdx.x;
-    const int blk = (P.rows + GW_ROWS - 1) / GW_ROWS - 1 - (int)(wg / heads);
+    const unsigned wb = P.by_heads(wg), hs = wg - wb * heads, hb = P.by_slots(hs), sl = hs - hb * slots;
+    const int blk = (P.rows + GW_ROWS - 1) / GW_ROWS - 1 - (int)wb;
     if (blk < 0) return;                                    // (beyond the last, in a launch of several rows of workgroups)
-    const unsigned hs = wg % heads, sl = hs % slots;
-    const int seq = sl / P.nkv, hk = sl % P.nkv, h = hk * (P.nq / P.nkv) + hs / slots;
+    const int seq = P.by_nkv(sl), hk = sl - seq * P.nkv, h = hk * P.group + hb;
     const int R0 = GW_ROWS * blk, r0 = R0 + 32 * wave;
     const bool active = r0 < P.rows;
     auto group_of = [&](int row) __attribute__((always_inline)) { return P.k > 0 ? (int)__umulhi((unsigned)row, P.k1_magic) : row; };
@@ -857,10 +874,10 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     const char* vraw = (const char*)P.v + ((size_t)seq * P.rows * P.nkv + hk) * D * 2;
 
     // ---- requests: the rows' part of the rotary table, the query rows, the own rows, the first tiles
-    constexpr int TU = (TROWS * TROW / 16 + GA_THREADS - 1) / GA_THREADS, TU1 = 4;   // 16-byte units per thread; the first 4 do for K1 >= 5
+    constexpr int TPC = D / 4, TU = (TROWS * TPC + GA_THREADS - 1) / GA_THREADS, TU1 = 4;   // 16-byte units per thread; the first 4 do for K1 >= 5
     u32x4 tv[TU1];
     const u32x4* const tab_src = reinterpret_cast<const u32x4*>(P.table + (size_t)gB0 * (D / 2));
-    const int tab_n = (g_last_wg - gB0 + K1) * (TROW / 16);   // positions of the rows of groups gB0 .. g_last_wg
+    const int tab_n = (g_last_wg - gB0 + K1) * TPC;   // positions of the rows of groups gB0 .. g_last_wg
     if (P.k > 0) {
 #pragma unroll
         for (int i = 0; i < TU1; ++i) tv[i] = tab_src[min(tid + GA_THREADS * i, tab_n - 1)];
@@ -911,6 +928,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
 #pragma unroll
         for (int i = 0; i < NP; ++i) *reinterpret_cast<uint4*>(smem + OFF_V + (t & 1) * VBUF + skey * VSTR + sj * 16 + i * 128) = x[i];
     };
+    auto table_unit = [&](int u) __attribute__((always_inline)) { return reinterpret_cast<u32x4*>(smem + OFF_T + u / TPC * TROW + u % TPC * 16); };
     uint4 k0[NP], k1[NP], v0[NP], kst[NP], vst[NP];
     load_k(0, k0);
     load_k(1, k1);
@@ -919,13 +937,13 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     load_v(1, vst);
     if (P.k > 0) {
 #pragma unroll
-        for (int i = 0; i < TU1; ++i) reinterpret_cast<u32x4*>(smem + OFF_T)[min(tid + GA_THREADS * i, tab_n - 1)] = tv[i];
+        for (int i = 0; i < TU1; ++i) *table_unit(min(tid + GA_THREADS * i, tab_n - 1)) = tv[i];
         if (tab_n > TU1 * GA_THREADS) {                     // (two or three rows per group: more positions)
             u32x4 tw[TU - TU1];
 #pragma unroll
             for (int i = TU1; i < TU; ++i) tw[i - TU1] = tab_src[min(tid + GA_THREADS * i, tab_n - 1)];
 #pragma unroll
-            for (int i = TU1; i < TU; ++i) reinterpret_cast<u32x4*>(smem + OFF_T)[min(tid + GA_THREADS * i, tab_n - 1)] = tw[i - TU1];
+            for (int i = TU1; i < TU; ++i) *table_unit(min(tid + GA_THREADS * i, tab_n - 1)) = tw[i - TU1];
         }
         __syncthreads();
     }
@@ -950,41 +968,53 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         return reinterpret_cast<const float4*>(smem + OFF_T + max(pos - gB0, 0) * TROW) + pj * 4;
     };
 
-    // ---- the query rows, rotated in float32, scaled by log2(e) / sqrt(d), split: high parts, then low parts by way of LDS
-    // into registers (lane (c, half): bytes [32 t + 16 half, +16) of row c at step t)
+    // ---- the query rows by way of LDS into registers, as operands (lane (c, half): bytes [32 t + 16 half, +16) of row c at step
+    // t, so both pieces of a pair), rotated in float32, scaled by log2(e) / sqrt(d), split into high and low parts
     bf16x8 qh[STEPS], ql[STEPS];
     {
         char* const sQ = smem + wave * (32 * KSTR);
         const float qscale = P.inv_sqrt_d * 1.4426950408889634f;
-        uint4 la[QI], lb[QI];
-#pragma unroll
-        for (int i = 0; i < QI; ++i) {
-            const int rr = QPI * i + lane / PAIRS, pos = position(min(r0 + rr, r_last));
-            float ra[8], rb[8];
-            if (P.k > 0) rotate(qa[i], qb[i], table_lds(pos), qscale, ra, rb);
-            else rotate(qa[i], qb[i], reinterpret_cast<const float4*>(P.table + (size_t)pos * (D / 2)) + pj * 4, qscale, ra, rb);
-            unsigned hi[4];
-            *reinterpret_cast<bf16x8*>(sQ + rr * KSTR + pj * 16) = split_hi(ra, hi);
-            la[i] = __builtin_bit_cast(uint4, split_lo(ra, hi));
-            *reinterpret_cast<bf16x8*>(sQ + rr * KSTR + (pj + PAIRS) * 16) = split_hi(rb, hi);
-            lb[i] = __builtin_bit_cast(uint4, split_lo(rb, hi));
-        }
-        lds_sync_wave();
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int t = 0; t < STEPS; ++t) qh[t] = __builtin_bit_cast(bf16x8, ld16(sQ + c * KSTR + 32 * t + 16 * half));
-        lds_sync_wave();
-        __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int i = 0; i < QI; ++i) {
             const int rr = QPI * i + lane / PAIRS;
-            *reinterpret_cast<uint4*>(sQ + rr * KSTR + pj * 16) = la[i];
-            *reinterpret_cast<uint4*>(sQ + rr * KSTR + (pj + PAIRS) * 16) = lb[i];
+            *reinterpret_cast<uint4*>(sQ + rr * KSTR + pj * 16) = qa[i];
+            *reinterpret_cast<uint4*>(sQ + rr * KSTR + (pj + PAIRS) * 16) = qb[i];
         }
+        uint4 xa[STEPS / 2], xb[STEPS / 2];
         lds_sync_wave();
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int t = 0; t < STEPS; ++t) ql[t] = __builtin_bit_cast(bf16x8, ld16(sQ + c * KSTR + 32 * t + 16 * half));
+        for (int t = 0; t < STEPS / 2; ++t) {
+            xa[t] = ld16(sQ + c * KSTR + 32 * t + 16 * half);
+            xb[t] = ld16(sQ + c * KSTR + D + 32 * t + 16 * half);
+        }
+        const char* tab = smem + OFF_T + (position(qrow) - gB0) * TROW;
+        if (P.k == 0) {                                     // (as many positions as rows: each wavefront's in its own area)
+            char* const sT = smem + wave * TAREA;
+            const int tq_last = r_last - w_first;
+            u32x4 tq[TPC / 2];
+#pragma unroll
+            for (int i = 0; i < TPC / 2; ++i) {
+                const int u = lane + 64 * i;
+                tq[i] = reinterpret_cast<const u32x4*>(P.table)[(size_t)(unsigned)(w_first + min(u / TPC, tq_last)) * TPC + u % TPC];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < TPC / 2; ++i) *reinterpret_cast<u32x4*>(sT + (lane + 64 * i) / TPC * TROW + (lane + 64 * i) % TPC * 16) = tq[i];
+            lds_sync_wave();
+            __builtin_amdgcn_wave_barrier();
+            tab = sT + min(c, tq_last) * TROW;
+        }
+#pragma unroll
+        for (int t = 0; t < STEPS / 2; ++t) {
+            float ra[8], rb[8];
+            rotate(xa[t], xb[t], reinterpret_cast<const float4*>(tab) + (2 * t + half) * 4, qscale, ra, rb);
+            unsigned hi[4];
+            qh[t] = split_hi(ra, hi);
+            ql[t] = split_lo(ra, hi);
+            qh[t + STEPS / 2] = split_hi(rb, hi);
+            ql[t + STEPS / 2] = split_lo(rb, hi);
+        }
     }
 
     // of this lane's query: the reference of the exponentials (both halves agree) and the half's sum.  The reference starts at
@@ -1019,10 +1049,9 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
     };
     // the reference follows the maximum only when that has moved up by more than GA_LAZY (in units of ln 2): sums and outputs
     // are relative to the same reference, so the quotient is the same, and most tiles need no rescaling
-    auto highest = [&](const f32x16& x) __attribute__((always_inline)) {
-        float mt = x[0];
+    auto highest = [&](const f32x16& x, float mt) __attribute__((always_inline)) {   // of the query's scores, and mt
 #pragma unroll
-        for (int i = 1; i < 16; ++i) mt = fmaxf(mt, x[i]);
+        for (int i = 0; i < 16; ++i) mt = fmaxf(mt, x[i]);
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
         return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     };
@@ -1038,11 +1067,12 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         }
     };
     // exponentials against m, P.V: vf(j, m) = V^T as operand, columns 32 j + c, keys 16 m + 4 half + 0..3 and 16 m + 8 + 4 half + 0..3
-    auto accumulate = [&](const f32x16& x, float m, auto vf) __attribute__((always_inline)) {
+    // (of the tile's first 16 keys or of all 32)
+    auto accumulate = [&](const f32x16& x, float m, auto halves, auto vf) __attribute__((always_inline)) {
         float pr[2][8];
         float l0 = 0.f, l1 = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < 8 * halves; ++i) {
             const float e = __builtin_amdgcn_exp2f(x[i] - m);
             pr[i / 8][i % 8] = e;
             if (i & 1) l1 += e; else l0 += e;
@@ -1050,7 +1080,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         l_run += l0 + l1;
         bf16x8 ph[2], pl[2];
 #pragma unroll
-        for (int m2 = 0; m2 < 2; ++m2) {
+        for (int m2 = 0; m2 < halves; ++m2) {
             unsigned hi8[4];
             ph[m2] = split_hi(pr[m2], hi8);
             pl[m2] = split_lo(pr[m2], hi8);
@@ -1058,7 +1088,7 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
 #pragma unroll
         for (int j = 0; j < NJ; j += 2)
 #pragma unroll
-            for (int m2 = 0; m2 < 2; ++m2) {
+            for (int m2 = 0; m2 < halves; ++m2) {
                 const bf16x8 va = vf(j, m2), vb = vf(j + 1, m2);
                 o[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, ph[m2], o[j], 0, 0, 0);
                 o[j + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb, ph[m2], o[j + 1], 0, 0, 0);
@@ -1103,17 +1133,30 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         __syncthreads();
         const int kro = c * (2 * D) + ((half ^ (D == 128 ? c & 15 : (c >> 1) & 7)) << 4);
         const int vro = (4 * half + vkey) * (2 * D) + ((vhi ^ (D == 128 ? vkey << 1 : vkey & 2)) << 5) + (lane & 3) * 8;
-#pragma unroll 1
-        for (int before = 0; before < 2; ++before) {
-            if (!active || (before && wg0 * K1 == r0)) continue;
-            const int first = before ? r0 - 16 : r0;        // layout row of the tile's first key
-            const char* kt = smem + (first - R0 + 16) * (2 * D);
-            f32x16 x = scores([&](int st) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, ld16(kt + (kro ^ (st << 5)))); });
-            mask(x, qg * K1 + 1 - first - 4 * half, (before ? min(qrow, r0 - 1) : qrow) - first - 4 * half);
-            follow(highest(x));
-            accumulate(x, m_run, [&](int j, int m2) __attribute__((always_inline)) {
-                return transposed(kt + OFF_OV + m2 * 16 * 2 * D + (vro ^ (j << 6)), 8 * 2 * D);
-            });
+        if (active) {
+            // both tiles' scores, one reference, then the values: of the tile before, the 16 keys that are not the own tile's, too
+            auto own_scores = [&](int first, int last, f32x16& x) __attribute__((always_inline)) {   // first: layout row of the tile's first key
+                const char* kt = smem + (first - R0 + 16) * (2 * D);
+                x = scores([&](int st) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, ld16(kt + (kro ^ (st << 5)))); });
+                mask(x, qg * K1 + 1 - first - 4 * half, last - first - 4 * half);
+            };
+            auto own_values = [&](int first, int j, int m2) __attribute__((always_inline)) {
+                return transposed(smem + (first - R0 + 16) * (2 * D) + OFF_OV + m2 * 16 * 2 * D + (vro ^ (j << 6)), 8 * 2 * D);
+            };
+            f32x16 x;
+            own_scores(r0, qrow, x);
+            if (wg0 * K1 != r0) {
+                f32x16 y;
+                own_scores(r0 - 16, min(qrow, r0 - 1), y);
+                float mt = y[0];
+#pragma unroll
+                for (int i = 1; i < 8; ++i) mt = fmaxf(mt, y[i]);
+                follow(highest(x, mt));
+                accumulate(y, m_run, std::integral_constant<int, 1>{}, [&](int j, int m2) __attribute__((always_inline)) { return own_values(r0 - 16, j, m2); });
+            } else {
+                follow(highest(x, x[0]));
+            }
+            accumulate(x, m_run, std::integral_constant<int, 2>{}, [&](int j, int m2) __attribute__((always_inline)) { return own_values(r0, j, m2); });
         }
     }
     __syncthreads();                                        // the stages' buffers are free
@@ -1140,18 +1183,18 @@ __global__ void __launch_bounds__(GA_THREADS, 2) ga_attn_wide_kernel(const GaPar
         load_v(t + 2, vst);
     };
     auto values = [&](int t) __attribute__((always_inline)) {
-        accumulate(s, m_run, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
+        accumulate(s, m_run, std::integral_constant<int, 2>{}, [&](int j, int m2) __attribute__((always_inline)) { return transposed(smem + (t & 1) * VBUF + vr + j * 64 + m2 * 16 * VSTR, 8 * VSTR); });
     };
     int t = 0;
     if (real_end > 0) {
         if (whole_end == 0) visible(0, s);
-        follow(highest(s));
+        follow(highest(s, s[0]));
         auto step = [&](auto masked) __attribute__((always_inline)) {
             stage(t);
             f32x16 sn = stage_scores(t + 1);
             values(t);
             if constexpr (masked) visible(t + 1, sn);
-            const float mt = highest(sn);
+            const float mt = highest(sn, sn[0]);
             s = sn;
             follow(mt);
             __syncthreads();
@@ -1301,6 +1344,10 @@ GaParams shape(const ps_group_attn_args* a) {
     P.gpt = 16 / (a->k + 1);
     P.k1_magic = (unsigned)((0x100000000ull + a->k) / (unsigned)(a->k + 1));
     P.ntiles = (a->tokens + P.gpt - 1) / P.gpt;
+    P.by_heads = ga_div(P.nq * P.seqs);
+    P.by_slots = ga_div(P.nkv * P.seqs);
+    P.by_nkv = ga_div(P.nkv);
+    P.group = P.nq / P.nkv;
     P.inv_sqrt_d = (float)(1.0 / sqrt((double)a->head_dim));
     P.log2_base = log2((double)a->rope_base);
     return P;
