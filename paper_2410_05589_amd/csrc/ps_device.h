@@ -249,6 +249,15 @@ __device__ __forceinline__ void sx_reset_stale(const StepParams& P, int wg, int 
                 coh_st16(alt, e * 4, sent);
         }
     }
+    if (rows_prev > (unsigned)P.Mtot && P.final_norm) {      // the final rows' partial sums of squares (see epilogue_down)
+        const rsrc_t alt = make_rsrc(reinterpret_cast<const char*>(P.y2_ss) + (1u - par) * P.act_bytes);
+        const unsigned oct_units = (unsigned)P.H / 16u * 8u;
+        for (unsigned oct = (unsigned)P.Mtot >> 3; 8u * oct < rows_prev; ++oct)
+            for (unsigned x = wg * PS_WG_THREADS + threadIdx.x; x < oct_units; x += nwg * PS_WG_THREADS) {
+                const unsigned row = 8u * oct + (x & 7u);
+                if (row >= (unsigned)P.Mtot && row < rows_prev) coh_st4(alt, (oct * oct_units + x) * 4, PS_SENT);
+            }
+    }
     for (int ph = 0; ph < PH_COUNT; ++ph) {
         if (!P.ph[ph].frag) continue;
         const unsigned fp = __builtin_amdgcn_readfirstlane(ld_agent_u32(prev + 1 + ph)), fc = P.foot[1 + ph];
@@ -551,9 +560,10 @@ __device__ __forceinline__ const char* weight_row_ptr(const StepParams& P, int t
 
 // Panel row r of the LM head is a decoding row: the last real row and the k mask rows of each
 // sequence (or all rows).
-__device__ __forceinline__ int lm_src_row(const StepParams& P, int r) {
-    const int b = P.R == 1 ? r : (int)__umulhi((unsigned)r, P.r_magic), jj = r - b * P.R;
-    return b * P.M + (P.all_rows ? jj : (P.n_new - 1 + jj));
+// row m of the step as a row of the LM head's panel, or -1
+__device__ __forceinline__ int lm_row(const StepParams& P, int m) {
+    const int b = row_seq(P, m), i = m - b * P.M, jj = P.all_rows ? i : i - (P.n_new - 1);
+    return jj < 0 ? -1 : b * P.R + jj;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -694,6 +704,48 @@ __device__ __forceinline__ const char* first_stream(const StepParams& P, int ph,
     return stream_ptr(D, tau, lo, min(D.piece_groups, hi - lo), wave & ((1 << D.kw_log) - 1), a0, n);
 }
 
+// Maximum / sum over the four lanes (c, 0 .. 3) that share a query row c, returned to all four: two row swaps
+// (v_permlane32_swap exchanges the upper half of one register with the lower half of another, v_permlane16_swap
+// the odd 16-lane rows of one with the even rows of another; fed the same value twice they yield the value of
+// lane ^ 32 resp. lane ^ 16 beside the lane's own)
+__device__ __forceinline__ float quad_rows_max(float v) {
+    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quad_rows_sum(float v) {
+    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+// two floats -> two bf16 (round to nearest even) in one dword, first value in the low half
+__device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
+    const f32x2_t v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2_t));
+}
+
+// Rows that are exchanged as panels hold them: the producer, which has each element once, converts, not the consumers, which
+// have them all (bf16: 8 elements are 16 bytes of high parts, then 16 of low parts, in the place of their 32 bytes of float32).
+// v: four consecutive elements, the first at a multiple of 4; the lane 16 further on holds the next four in even sixteens of lanes, the
+// four before in odd ones.  Returns the 16 bytes that belong where the lane's four float32 would: even sixteens high parts, odd ones low.
+template <typename WT> __device__ __forceinline__ u32x4 panel_words(f32x4 v) {
+    if constexpr (!Traits<WT>::BF) {
+        return __builtin_bit_cast(u32x4, v);
+    } else {
+        const unsigned h0 = pack_bf16x2(v[0], v[1]), h1 = pack_bf16x2(v[2], v[3]);
+        const unsigned l0 = pack_bf16x2(v[0] - __uint_as_float(h0 << 16), v[1] - __uint_as_float(h0 & 0xFFFF0000u));
+        const unsigned l1 = pack_bf16x2(v[2] - __uint_as_float(h1 << 16), v[3] - __uint_as_float(h1 & 0xFFFF0000u));
+        const auto a = __builtin_amdgcn_permlane16_swap(h0, l0, false, false), b = __builtin_amdgcn_permlane16_swap(h1, l1, false, false);
+        // (two NaNs may look like "not written yet")
+        return u32x4{min(a[0], PS_SENT - 1), min(b[0], PS_SENT - 1), min(a[1], PS_SENT - 1), min(b[1], PS_SENT - 1)};
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // epilogues: lane (c = lane % 16, q = lane / 16) holds, for column tile mt, the outputs of
 // activation row m = 16 (mt0 + mt) + c and tile rows 4q .. 4q+3
@@ -793,19 +845,35 @@ __device__ __forceinline__ void epilogue_gateup(const StepParams& P, int tau, in
     }
 }
 
+// The LM head's panel rows leave here as the panel holds them: times the final norm's gain, converted (panel_words), in the
+// order of the LM head's rows, and beside them the sums of squares of a row's 16 elements of this tile: y2_ss[row / 8][tile][row % 8].
+// Every workgroup of the LM head needs the whole panel; with multiplication, squares and conversion there it took, us: 7B shape,
+// LM head of 6 / 20 / 48 / 60 rows 144.6 -> 143.5, 191.8 -> 187.6, 244.7 -> 237.8, 278.7 -> 259.8; V 128256, 9 / 36 rows 273.8 -> 273.0,
+// 332.8 -> 328.6.
 template <typename WT, int MT>
 __device__ __forceinline__ void epilogue_down(const StepParams& P, int tau, int lane, f32x4 (&acc)[MT], int mt0 = 0) {
     const int c = lane & 15, q = lane >> 4;
     const int n = 16 * tau + 4 * q;
     const rsrc_t ry = make_rsrc(act_ptr(P, P.y_buf));
-    const SxBuf ry2 = sx_buf(P, P.y2_buf);
+    const SxBuf ry2 = sx_buf(P, P.y2_buf), rss = sx_buf(P, P.y2_ss);
+    const u32x4 sent = {PS_SENT, PS_SENT, PS_SENT, PS_SENT};
+    f32x4 gain = {1.f, 1.f, 1.f, 1.f};
+    if (P.final_norm) gain = load4<WT>((const char*)P.g_final + (size_t)n * Traits<WT>::ESZ);
+    const int oct_units = P.H / 16 * 8;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const int m = 16 * (mt0 + mt) + c;
+        const int m = 16 * (mt0 + mt) + c, mc = min(m, P.Mtot - 1);
+        const f32x4 o = sx_wait4(P, ry, (unsigned)(mc * P.H + n)) + acc[mt];
+        const u32x4 w = panel_words<WT>(o * gain);
+        const float ss = quad_rows_sum((o[0] * o[0] + o[1] * o[1]) + (o[2] * o[2] + o[3] * o[3]));
         if (m >= P.Mtot) continue;
-        const unsigned idx = (unsigned)((size_t)m * P.H + n);
-        const f32x4 o = sx_wait4(P, ry, idx) + acc[mt];
-        sx_st4(ry2, idx, o);
+        const int r = lm_row(P, m);
+        if (r >= 0) coh_st16(ry2.cur, (unsigned)(r * P.H + n) * 4, w);
+        coh_st16(ry2.alt, (unsigned)(m * P.H + n) * 4, sent);
+        if (P.final_norm && q == 0) {
+            if (r >= 0) coh_st4(rss.cur, (unsigned)((r >> 3) * oct_units + 8 * tau + (r & 7)) * 4, __float_as_uint(ss));
+            coh_st4(rss.alt, (unsigned)((m >> 3) * oct_units + 8 * tau + (m & 7)) * 4, PS_SENT);
+        }
         if (P.hidden_out) *reinterpret_cast<f32x4*>(P.hidden_out + (size_t)m * P.H + n) = o;
     }
 }
@@ -847,14 +915,6 @@ __host__ __device__ inline int panel_row_stride(int panel_steps) {
 #define PS_LDS_ZERO (PS_LDS_BASE + 2048)    // 64 zero bytes: B operand of unused MFMA columns
 #define PS_LDS_RED (PS_LDS_BASE + 2304)     // [wavefronts][MT][64 lanes] f32x4: partial sums of wavefronts sharing a tile (if any do)
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-// two floats -> two bf16 (round to nearest even) in one dword, first value in the low half
-__device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
-    const f32x2_t v = {a, b};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2_t));
-}
-
 // Sums over the wavefront of eight registers: two rounds of swaps that halve the registers (every lane keeps the half it
 // goes on with), then row sums.  Lane l gets the sums of v[2 (l / 16)] and v[2 (l / 16) + 1].
 __device__ __forceinline__ float2 wave_sum8(const float (&v)[8]) {
@@ -874,25 +934,62 @@ __device__ __forceinline__ float2 wave_sum8(const float (&v)[8]) {
 
 // A thread's 16-byte groups gi of rows rb, rb + nrt, ... of the panel, as they came from memory, into LDS (see stage_piece;
 // whole: the piece lies inside K).  With many rows this is what a workgroup does longest between two streams, so the
-// checks, the zeros beyond K and the reductions of the sums of squares are kept off the elements: 48 rows, eight pieces of
-// the LM head's panel: a reduction per row took 9 us of a 270 us step.
+// checks, the zeros beyond K and the reductions of the sums of squares are kept off the elements (with 48 rows and the eight pieces of
+// an LM-head panel that was still converted here, a reduction per row took 9 us of a 270 us step).
 constexpr int PS_RB = 8;                             // rows per thread requested before any is used
+// (SPLIT phases: the rows come as the panel holds them, ss are partial sums of squares, see ss_offset)
+template <int PH> constexpr bool SPLIT = PH == PH_LMHEAD;
 template <typename WT, int MT, int PH>
 __device__ __forceinline__ void place_rows(const StepParams& P, const PhaseDesc& D, int wave, char* smem, char* s_pa, char* s_pb, int gi,
                                            bool gvalid, bool live, bool whole, int rb, const u32x4 (&raw)[PS_RB][Traits<WT>::GE / 4],
-                                           const float (&gn)[Traits<WT>::GE], bool fresh_ssq, bool want_ssq) {
+                                           const float (&gn)[Traits<WT>::GE], u32x4 ss4, bool fresh_ssq, bool want_ssq) {
     constexpr bool BF = Traits<WT>::BF;
     constexpr int GE = Traits<WT>::GE, NL = GE / 4;
     constexpr bool from_x = PH == PH_QKV || PH == PH_FC;
     const int lane = threadIdx.x & 63;
     float* s_ssq = reinterpret_cast<float*>(smem + PS_LDS_SSQ);
     const int nrt = PS_WG_THREADS >> D.g2_log, wsub = wave & (((1 << D.g2_log) >> 6) - 1), rows = D.rows, RS = D.rs;
-    const bool norm = PH == PH_QKV || PH == PH_GATEUP || (PH == PH_LMHEAD && D.norm != 0);
+    const bool norm = PH == PH_QKV || PH == PH_GATEUP || (PH == PH_LMHEAD && D.norm != 0);   // (of a SPLIT phase only the sums of squares)
     // is row r of the QKV panel an fp32 row (the input projection's output)?
     auto fused_row = [&](int r) __attribute__((always_inline)) {
         return PH == PH_QKV && P.in_mode == PS_IN_FUSED && r - row_seq(P, r) * P.M < P.n_new;
     };
+    auto panel_at = [&](int r) __attribute__((always_inline)) {
+        return MT >= PS_UNITS_MT && D.units ? gi * RS + ((r ^ (gi & 15)) << 4) : r * RS + gi * 16;
+    };
     float ss[PS_RB];
+    if constexpr (SPLIT<PH>) {
+#pragma unroll
+        for (int i = 0; i < PS_RB; ++i) {
+            const int r = rb + nrt * i;
+            if (r >= rows || !gvalid) continue;
+#pragma unroll
+            for (int h = 0; h < NL; ++h) {
+                uint4 x = make_uint4(raw[i][h][0], raw[i][h][1], raw[i][h][2], raw[i][h][3]);
+                if (!whole) {
+                    x.x = live ? x.x : 0u; x.y = live ? x.y : 0u; x.z = live ? x.z : 0u; x.w = live ? x.w : 0u;
+                }
+                *reinterpret_cast<uint4*>((h == 0 ? s_pa : s_pb) + panel_at(r)) = x;
+            }
+        }
+        if (norm && want_ssq) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ss[e] = gi & 1 ? 0.f : __uint_as_float(ss4[e]);
+                ss[4 + e] = gi & 1 ? __uint_as_float(ss4[e]) : 0.f;
+            }
+            const float2 t = wave_sum8(ss);
+            if ((lane & 15) < 2) {
+                const int rsub = (wave << 6) >> D.g2_log, rr = rb - rsub + 8 * rsub + 2 * (lane >> 4) + (lane & 1);
+                if (rr < rows) {
+                    float* s = s_ssq + rr * 8 + wsub;
+                    const float x = lane & 1 ? t.y : t.x;
+                    *s = fresh_ssq ? x : *s + x;
+                }
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < PS_RB; ++i) {
         const int r = rb + nrt * i;
@@ -926,7 +1023,7 @@ __device__ __forceinline__ void place_rows(const StepParams& P, const PhaseDesc&
             ss[i] = gvalid ? ss[i] : 0.f;            // (a thread without a group of its own repeats another's)
         }
         if (gvalid) {
-            const int at = MT >= PS_UNITS_MT && D.units ? gi * RS + ((r ^ (gi & 15)) << 4) : r * RS + gi * 16;
+            const int at = panel_at(r);
             if constexpr (BF) {
                 uint4 ph4, pl4;
                 unsigned* hp = &ph4.x;
@@ -970,6 +1067,22 @@ __device__ __forceinline__ bool sx_ok_rows(const u32x4 (&raw)[PS_RB][NL]) {
     return top != PS_SENT;
 }
 
+// The partial sums of squares that go with a thread's groups gi of rows rb, rb + nrt, ... (rb = first + rsub, nrt rows of 8): a
+// thread's unit of 16 bytes are those of elements [16 (kk / 16), + 16) of rows first + 8 rsub + 4 (gi & 1) + 0 .. 3, so the nrt threads that
+// share a group's place have the rows of all; the lanes of the third and later groups of a tile (float32) have none.
+__device__ __forceinline__ unsigned ss_offset(const PhaseDesc& D, int rb, int rsub, int kkc, int gi) {
+    const int oct = min(((rb - rsub) >> 3) + rsub, (D.rows - 1) >> 3);
+    return (unsigned)(oct * (D.K >> 4) * 8 + (kkc >> 4) * 8 + 4 * (gi & 1)) * 4;
+}
+// ... without those of rows that the step does not have
+template <typename WT> __device__ __forceinline__ u32x4 ss_own(const PhaseDesc& D, u32x4 x, int rb, int rsub, int gi, bool live) {
+    const int row = rb - rsub + 8 * rsub + 4 * (gi & 1);
+    const bool mine = live && D.norm != 0 && (Traits<WT>::BF || (gi & 2) == 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = mine && row + e < D.rows ? x[e] : 0u;
+    return x;
+}
+
 // Stages steps [a_step, a_step + nsteps) of the activation panel.  The 16-byte groups of a row
 // lie along 2^g2_log threads, the remaining threads take different rows; every thread requests
 // its group of RB rows before it uses any of them (one memory round trip per RB rows), and
@@ -1007,11 +1120,13 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
         const bool live = gvalid && kk < K;          // beyond K the packed weights are zero: so is the panel
         const int kkc = kk < K ? kk : 0;
         float gn[GE];
-        if (norm) unpack_group<WT>(ld16((const char*)D.gain + (size_t)kkc * ESZ), gn);
+        if (norm && !SPLIT<PH>) unpack_group<WT>(ld16((const char*)D.gain + (size_t)kkc * ESZ), gn);
         for (int rb = rsub; rb < rows; rb += nrt * RB) {
-            u32x4 raw[RB][NL];
+            u32x4 raw[RB][NL], ss4 = {0u, 0u, 0u, 0u};
             int spins = 0;
             for (;;) {
+                if constexpr (SPLIT<PH>)
+                    ss4 = coh_ld16(make_rsrc(act_ptr(P, P.y2_ss)), ss_offset(D, rb, rsub, kkc, gi));
 #pragma unroll
                 for (int i = 0; i < RB; ++i) {
                     const int r = min(rb + nrt * i, rows - 1);   // clamped: every load is unconditional
@@ -1038,27 +1153,27 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
                             ? __builtin_amdgcn_raw_buffer_load_b128(rs, kkc * ESZ, r * P.H * ESZ, 0)
                             : __builtin_amdgcn_raw_buffer_load_b128(rmask, (kkc - P.H) * ESZ, tok * P.H * ESZ, 0);
                     } else {
-                        const int srow = PH == PH_LMHEAD ? lm_src_row(P, r) : r;
 #pragma unroll
                         for (int h = 0; h < NL; ++h)
-                            raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kkc + 4 * h) * 4, srow * ld * 4, PS_SC1);
+                            raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kkc + 4 * h) * 4, r * ld * 4, PS_SC1);
                     }
                 }
                 if (from_x) break;
-                if (__all(sx_ok_rows<NL>(raw)) || !spin_again(P, spins)) break;   // produced earlier in this step: wait for it
+                if constexpr (SPLIT<PH>) ss4 = ss_own<WT>(D, ss4, rb, rsub, gi, live);
+                if (__all(sx_ok_rows<NL>(raw) && sx_ok(ss4)) || !spin_again(P, spins)) break;   // produced earlier in this step: wait for it
                 // Not all there yet: until this thread's columns of one row are, only those are asked for (a tile's rows
                 // are stored together).  Everybody asking for whole panels again and again is traffic that the
                 // producers' own accesses queue behind: 1 .. 2.5 % of a step of the small shapes (H 256 and 512, where most
                 // workgroups only wait), nothing of the large ones'.  These polls count towards the same limit as the panel's
                 if (!from_x) {
-                    const int r0 = min(rb, rows - 1), srow = PH == PH_LMHEAD ? lm_src_row(P, r0) : r0;
+                    const int r0 = min(rb, rows - 1);
                     for (;;) {
-                        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, kkc * 4, srow * ld * 4, PS_SC1);
+                        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, kkc * 4, r0 * ld * 4, PS_SC1);
                         if (__all(sx_ok(x)) || !spin_again(P, spins)) break;
                     }
                 }
             }
-            place_rows<WT, MT, PH>(P, D, wave, smem, s_pa, s_pb, gi, gvalid, live, (a_step + nsteps) * KSTEP <= K, rb, raw, gn, first_piece && gc == 0, want_ssq);
+            place_rows<WT, MT, PH>(P, D, wave, smem, s_pa, s_pb, gi, gvalid, live, (a_step + nsteps) * KSTEP <= K, rb, raw, gn, ss4, first_piece && gc == 0, want_ssq);
         }
     }
 }
@@ -1069,61 +1184,52 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
 // kernel before left in memory - "not written yet" - or something newer, so the check for that pattern, when the
 // piece is placed, still tells; what was read too early is read again past the L2.
 template <typename WT> struct PieceAhead {
-    u32x4 raw[PS_RB][Traits<WT>::GE / 4];
-    uint4 gain;
+    u32x4 raw[PS_RB][Traits<WT>::GE / 4], ss;
     // no instruction: what the registers held is not needed any more (the compiler cannot see that a piece is placed only
     // where one was requested, and would keep the last one's registers through the streaming loop)
     __device__ __forceinline__ void forget() {
-        u32x4 g;
-        asm volatile("" : "=v"(g));
-        gain = make_uint4(g[0], g[1], g[2], g[3]);
+        asm volatile("" : "=v"(ss));
 #pragma unroll
         for (int i = 0; i < PS_RB; ++i)
 #pragma unroll
             for (int h = 0; h < Traits<WT>::GE / 4; ++h) asm volatile("" : "=v"(raw[i][h]));
     }
 };
-template <typename WT>
+template <typename WT, int AUX = 0>
 __device__ __forceinline__ void request_piece(const StepParams& P, const PhaseDesc& D, int wave, int a_step, int nsteps, PieceAhead<WT>& x) {
-    constexpr int KSTEP = Traits<WT>::KSTEP, GE = Traits<WT>::GE, ESZ = Traits<WT>::ESZ, NL = GE / 4;
+    constexpr int KSTEP = Traits<WT>::KSTEP, GE = Traits<WT>::GE, NL = GE / 4;
     const int rsub = (wave << 6) >> D.g2_log, nrt = PS_WG_THREADS >> D.g2_log;
     const int gi = min((int)threadIdx.x & ((1 << D.g2_log) - 1), nsteps * 4 - 1);
     const int kk = a_step * KSTEP + gi * GE, kkc = kk < D.K ? kk : 0;
     const rsrc_t rs = make_rsrc(act_ptr(P, D.src));
-    x.gain = ld16(D.norm ? (const char*)D.gain + (size_t)kkc * ESZ : (const char*)P.ph[PH_LMHEAD].wpack);
+    x.ss = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(act_ptr(P, P.y2_ss)), ss_offset(D, rsub, rsub, kkc, gi), 0, AUX);
 #pragma unroll
     for (int i = 0; i < PS_RB; ++i) {
-        const int srow = lm_src_row(P, min(rsub + nrt * i, D.rows - 1));   // clamped: every load is unconditional
+        const int off = min(rsub + nrt * i, D.rows - 1) * D.src_ld * 4;   // clamped: every load is unconditional
 #pragma unroll
-        for (int h = 0; h < NL; ++h) x.raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kkc + 4 * h) * 4, srow * D.src_ld * 4, 0);
+        for (int h = 0; h < NL; ++h) x.raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kkc + 4 * h) * 4, off, AUX);
     }
 }
 template <typename WT, int MT>
 __device__ __forceinline__ void place_piece(const StepParams& P, const PhaseDesc& D, int wave, char* smem, char* s_pa, char* s_pb, int a_step,
                                             int nsteps, PieceAhead<WT>& x, bool want_ssq) {
     constexpr int KSTEP = Traits<WT>::KSTEP, GE = Traits<WT>::GE, NL = GE / 4;
-    const int rsub = (wave << 6) >> D.g2_log, nrt = PS_WG_THREADS >> D.g2_log;
+    const int rsub = (wave << 6) >> D.g2_log;
     const int gi = (int)threadIdx.x & ((1 << D.g2_log) - 1);
     const bool gvalid = gi < nsteps * 4;
-    const int kk = a_step * KSTEP + (gvalid ? gi : nsteps * 4 - 1) * GE, kkc = kk < D.K ? kk : 0;
-    float gn[GE];
-    unpack_group<WT>(x.gain, gn);
+    const int gic = gvalid ? gi : nsteps * 4 - 1, kk = a_step * KSTEP + gic * GE;
+    const bool live = gvalid && kk < D.K;
     auto all_there = [&]() __attribute__((always_inline)) {
-        return __all(sx_ok_rows<NL>(x.raw));
+        return __all(sx_ok_rows<NL>(x.raw) && sx_ok(ss_own<WT>(D, x.ss, rsub, rsub, gi, live)));
     };
     if (!all_there()) {
-        const rsrc_t rs = make_rsrc(act_ptr(P, D.src));
         int spins = 0;
         do {
-#pragma unroll
-            for (int i = 0; i < PS_RB; ++i) {
-                const int srow = lm_src_row(P, min(rsub + nrt * i, D.rows - 1));
-#pragma unroll
-                for (int h = 0; h < NL; ++h) x.raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rs, (kkc + 4 * h) * 4, srow * D.src_ld * 4, PS_SC1);
-            }
+            request_piece<WT, PS_SC1>(P, D, wave, a_step, nsteps, x);
         } while (!all_there() && spin_again(P, spins));
     }
-    place_rows<WT, MT, PH_LMHEAD>(P, D, wave, smem, s_pa, s_pb, gi, gvalid, gvalid && kk < D.K, (a_step + nsteps) * KSTEP <= D.K, rsub, x.raw, gn, false, want_ssq);
+    const float none[GE] = {};
+    place_rows<WT, MT, PH_LMHEAD>(P, D, wave, smem, s_pa, s_pb, gi, gvalid, live, (a_step + nsteps) * KSTEP <= D.K, rsub, x.raw, none, ss_own<WT>(D, x.ss, rsub, rsub, gi, live), false, want_ssq);
 }
 
 // Softmax statistics and top-k of the logits a workgroup holds in LDS (s_lm[local tile][row][16]) for its
@@ -2324,23 +2430,6 @@ __device__ __forceinline__ AttnItem attn_decode2(const StepParams& P, int item, 
     }
     it.b = b; it.nch = nch; it.hk = rem / nch; it.ch = rem - it.hk * nch; it.L = kvlen_u(b);
     return it;
-}
-
-// Maximum / sum over the four lanes (c, 0 .. 3) that share a query row c, returned to all four: two row swaps
-// (v_permlane32_swap exchanges the upper half of one register with the lower half of another, v_permlane16_swap
-// the odd 16-lane rows of one with the even rows of another; fed the same value twice they yield the value of
-// lane ^ 32 resp. lane ^ 16 beside the lane's own)
-__device__ __forceinline__ float quad_rows_max(float v) {
-    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float quad_rows_sum(float v) {
-    auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // K rows (MFMA operand) and value rows of one group of 16 keys, as they come from memory

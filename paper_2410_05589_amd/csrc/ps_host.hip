@@ -44,7 +44,7 @@ struct ps_draft_ctx {
     size_t exch_begin, exch_end;      // workspace range of the tagged exchange buffers (cleared at init)
     char* act_base;                   // two copies of the activation buffers, act_bytes each
     size_t act_bytes;
-    size_t off_q, off_o, off_y, off_u, off_y2, off_kvnew, off_x;   // offsets inside one copy
+    size_t off_q, off_o, off_y, off_u, off_y2, off_kvnew, off_x, off_y2ss;   // offsets inside one copy
     int spin_limit;                   // polls before a kernel gives up a wait (PS_SPIN_LIMIT; tests of that path: less)
     char* wpack[PH_COUNT];
     int* counters;
@@ -93,7 +93,7 @@ struct WsLayout {
     size_t wpack[PH_COUNT];
     size_t rope, q_buf, o_buf, y_buf, u_buf, y2_buf, kvnew, attn_acc, attn_ml, counters, lm_part, logits_ws, total;
     size_t exch_begin, exch_end;
-    size_t act_base, act_bytes, off_q, off_o, off_y, off_u, off_y2, off_kvnew, off_x, off_frag[PH_COUNT], off_ssqf[PH_COUNT];
+    size_t act_base, act_bytes, off_q, off_o, off_y, off_u, off_y2, off_kvnew, off_x, off_y2ss, off_frag[PH_COUNT], off_ssqf[PH_COUNT];
     int n_counters;
     bool fits32;   // the kernels address every exchange buffer with 32-bit byte offsets
 };
@@ -148,6 +148,7 @@ static WsLayout ws_layout(const ps_draft_config* c) {
             const bool sliced = ph != PH_LMHEAD;
             L.off_frag[ph] = sub(sliced ? (size_t)PS_S_MAX * T[ph] * mt_max * 1024 : 256);
         }
+        L.off_y2ss = sub((rows + 7) / 8 * 8 * (size_t)(c->hidden / 16) * 4);
         L.act_bytes = a;
         L.act_base = take(2 * a);
     }
@@ -163,7 +164,7 @@ static WsLayout ws_layout(const ps_draft_config* c) {
     L.logits_ws = take(rows * c->vocab * 4);
     L.total = off;
     const size_t lim = 0xFFFFFFF0ull;
-    L.fits32 = L.act_bytes <= lim && L.lm_part - L.attn_acc <= lim && L.exch_end - L.lm_part <= lim;
+    L.fits32 = L.off_y2ss <= lim && L.lm_part - L.attn_acc <= lim && L.exch_end - L.lm_part <= lim;
     return L;
 }
 static_assert(PS_CTR_WORDS * 4 <= 256, "counters");
@@ -271,7 +272,7 @@ extern "C" int ps_draft_init(ps_draft_ctx** out, const ps_draft_config* config, 
     ctx->rope = (float2*)(base + L.rope);
     ctx->act_base = base + L.act_base; ctx->act_bytes = L.act_bytes;
     ctx->off_q = L.off_q; ctx->off_o = L.off_o; ctx->off_y = L.off_y; ctx->off_u = L.off_u;
-    ctx->off_y2 = L.off_y2; ctx->off_kvnew = L.off_kvnew; ctx->off_x = L.off_x;
+    ctx->off_y2 = L.off_y2; ctx->off_y2ss = L.off_y2ss; ctx->off_kvnew = L.off_kvnew; ctx->off_x = L.off_x;
     for (int ph = 0; ph < PH_COUNT; ++ph) { ctx->off_frag[ph] = L.off_frag[ph]; ctx->off_ssqf[ph] = L.off_ssqf[ph]; }
     ctx->spin_limit = PS_SPIN_LIMIT;
     ctx->attn_acc = (float*)(base + L.attn_acc);
@@ -820,7 +821,7 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
     char* const act0 = ctx->act_base;
     P.act_bytes = (long long)ctx->act_bytes;
     P.q_buf = (float*)(act0 + ctx->off_q); P.o_buf = (float*)(act0 + ctx->off_o); P.y_buf = (float*)(act0 + ctx->off_y);
-    P.u_buf = (float*)(act0 + ctx->off_u); P.y2_buf = (float*)(act0 + ctx->off_y2); P.kvnew = (float*)(act0 + ctx->off_kvnew);
+    P.u_buf = (float*)(act0 + ctx->off_u); P.y2_buf = (float*)(act0 + ctx->off_y2); P.y2_ss = (float*)(act0 + ctx->off_y2ss); P.kvnew = (float*)(act0 + ctx->off_kvnew);
     P.x_buf = (c.flags & PS_FLAG_INPUT_FC) ? (float*)(act0 + ctx->off_x) : nullptr;
     P.spin_limit = ctx->spin_limit;
     P.foot_mem = (unsigned*)ctx->counters + PS_CTR_FOOT;

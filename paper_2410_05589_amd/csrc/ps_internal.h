@@ -154,7 +154,8 @@ struct StepParams {
     const float2* rope; // [max_positions][d/2] (cos, sin)
     // Activations between phases: plain fp32, 0xFFFFFFFF = not written yet.  Two copies alternate; the
     // pointers are those of copy 0, step n uses copy n & 1.
-    float *q_buf, *o_buf, *y_buf, *u_buf, *y2_buf;   // [Mtot][QD], [Mtot][QD], [Mtot][H], [Mtot][F], [Mtot][H]
+    float *q_buf, *o_buf, *y_buf, *u_buf, *y2_buf;   // [Mtot][QD], [Mtot][QD], [Mtot][H], [Mtot][F], [Mtot][H] (y2: the LM head's panel, see epilogue_down)
+    float* y2_ss;      // [Mtot / 8][H / 16][8] partial sums of squares of its rows
     float* kvnew;      // [Mtot][2][KVD] this step's K and V rows as stored in the cache
     long long act_bytes;   // distance between the two copies
     unsigned *step_ctr, *done_ctr;   // steps completed so far; tickets of the running kernel (see step_begin)

@@ -178,6 +178,23 @@ def test_steps_with_fewer_and_with_all_workgroups_take_turns(dtype, hidden, ffn)
     d.close()
 
 
+@pytest.mark.parametrize("dtype,hidden,all_rows", [("bf16", 544, False), ("bf16", 512, True), ("f32", 272, False)])
+def test_lm_head_rows_in_eights_that_are_not_full(dtype, hidden, all_rows):
+    """The sums of squares of the LM head's rows are exchanged in eights of rows: last eights of one, seven and eight rows, fewer LM-head
+    rows than rows of the step, contraction lengths that end inside a group, larger and smaller steps in turn on one context."""
+    shape = small_shape(dtype, hidden=hidden, n_heads=4, n_kv_heads=4, head_dim=64, ffn=704, vocab=2069)
+    w = inputs.make_weights(shape, 43)
+    d = _drafter(shape, w, max_batch=9, max_new=4, max_positions=200, k_max=7)
+    for step, (batch, n_new, k) in enumerate(((1, 1, 0), (9, 2, 5), (1, 1, 7), (3, 4, 2), (1, 1, 6), (9, 1, 6), (2, 3, 7), (8, 1, 2), (1, 4, 0))):
+        kv = tuple((37 * (b + 1) + 11 * step) % 150 for b in range(batch))
+        wl = Workload("eights", shape, batch=batch, kv_len=kv, n_new=n_new, k=k, topk=4, seed=400 + step)
+        inp = inputs.make_step_inputs(wl, kv_len=kv, n_new=n_new, k=k)
+        res = run_gpu_step(d, inp, n_new, k, 4, all_rows=all_rows)
+        ref = oracle_step(shape, w, inp, n_new, k, 4, all_rows=all_rows)
+        print("step", step, (batch, n_new, k), compare_with_oracle(shape, res, ref, inp, n_new, k, 4), flush=True)
+    d.close()
+
+
 def test_maximum_rows_and_topk():
     # 8 sequences x 8 rows = 64 activation rows (the most the library takes), top-32, all rows decoded
     shape = small_shape("bf16", hidden=512, n_heads=8, n_kv_heads=4, head_dim=64, ffn=1376, vocab=3000)
