@@ -645,17 +645,22 @@ __device__ __forceinline__ void preload_weights(uint4 (&wb)[PS_U], const char* b
 // loads of the last group start the wavefront's next stream, so when this returns wb holds the
 // head of that stream.  Every load is unconditional and only the oldest is waited for.
 // (consume_group: PS_U of the steps, A at the first of them; `last`: no step follows)
+// The first barrier keeps the reads of step t + 1 in front of the products of step t; the compiler puts them behind, where the next
+// step waits for them at once.  us: 7B shape, 60 rows 265.6 -> 259.0, H 512, 36 rows 58.4 -> 57.9, float32 H 256 37.1 -> 36.6, fewer rows of
+// the large shapes +-0.3; bf16 with one column tile 144.3 -> 144.8: not there.  (The LM head's 60 rows gain most of it from the registers
+// that the last steps' own code below frees.)
 template <typename WT, int MT>
 __device__ __forceinline__ void consume_group(uint4 (&wb)[PS_U], const char* refill, bool last, int lane16, const PanelAddr<MT>& A,
                                               BRegs<WT, MT>& bc, f32x4 (&acc)[MT]) {
     BRegs<WT, MT> bn;
 #pragma unroll
     for (int u = 0; u < PS_U; ++u) {
-        mma_step<WT, MT>(wb[u], bc, acc);
-        wb[u] = ldg_stream16(refill + u * PS_WS + lane16);   // reuses the register just consumed
         int tb = u + 1;
         if (u == PS_U - 1 && last) tb = u;
         load_b<WT, MT>(bn, A, tb);
+        if constexpr (MT > 1 || !Traits<WT>::BF) __builtin_amdgcn_sched_barrier(0);
+        mma_step<WT, MT>(wb[u], bc, acc);
+        wb[u] = ldg_stream16(refill + u * PS_WS + lane16);   // reuses the register just consumed
         bc = bn;
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -1492,7 +1497,6 @@ __device__ __forceinline__ void gemm_phase(const StepParams& P, int wg, int wave
                 stamp(P, wg, SB + 1);
             }
         }
-        if constexpr (may_ahead) next_piece.forget();
         // the tile's sum so far: lane (c, kb) has rows 16 mt + c, tile rows 4 kb .. 4 kb + 3
         auto waiting_sum = [&](int mt) __attribute__((always_inline)) {
             return reinterpret_cast<f32x4*>(s_lm + ((size_t)(rd * SL + slot) * rows + min(16 * mt + c, rows - 1)) * 16 + 4 * kb);
@@ -1520,20 +1524,21 @@ __device__ __forceinline__ void gemm_phase(const StepParams& P, int wg, int wave
             }
             PanelAddr<MT> pa_t = pa;
             pa_t.advance(a0);
-            // (the last PS_U steps run straight on: there the compiler can count the weight loads in front of the piece's)
-            const int n_loop = ahead ? n - PS_U : n;
-            consume_weights<WT, MT>(wb, wp, n_loop, ahead ? wp + (size_t)n_loop * PS_WS : next_wp, lane16, pa_t, acc);
             if constexpr (may_ahead) {
-                if (ahead) {
-                    request_piece<WT>(P, D, wave, g_next * PS_U, min(D.piece_groups, sg_hi - g_next) * PS_U, next_piece);
-                    BRegs<WT, MT> bc;
-                    load_b<WT, MT>(bc, pa_t, 0);
-                    consume_group<WT, MT>(wb, next_wp, true, lane16, pa_t, bc, acc);
-                }
+                // (the last PS_U steps run straight on: there the compiler can count the weight loads in front of the piece's)
+                consume_weights<WT, MT>(wb, wp, n - PS_U, wp + (size_t)(n - PS_U) * PS_WS, lane16, pa_t, acc);
+                if (ahead) request_piece<WT>(P, D, wave, g_next * PS_U, min(D.piece_groups, sg_hi - g_next) * PS_U, next_piece);
+                else next_piece.forget();
+                BRegs<WT, MT> bc;
+                load_b<WT, MT>(bc, pa_t, 0);
+                consume_group<WT, MT>(wb, next_wp, true, lane16, pa_t, bc, acc);
+            } else {
+                consume_weights<WT, MT>(wb, wp, n, next_wp, lane16, pa_t, acc);
             }
             streamed = true;
         } else if constexpr (may_ahead) {
             if (ahead) request_piece<WT>(P, D, wave, g_next * PS_U, min(D.piece_groups, sg_hi - g_next) * PS_U, next_piece);
+            else next_piece.forget();
         }
         if (pc + 1 < D.npieces) {                    // the tile goes on with another piece
             if (by_piece && valid) {
