@@ -417,7 +417,7 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
     memset(d, 0, sizeof(*d));
     // Slices pay for the two narrow projections (few tiles, long K: measured), and for any phase but
     // the LM head whose activation panel does not fit in LDS as a whole (many rows): a workgroup
-    // that needs only 1/S of the panel stages it in far fewer pieces.
+    // that needs only 1/S of the panel stages it in far fewer pieces (but see below).
     int s_log = 0;
     const bool whole_fits = arrays * panel_part_host(rows, false, ktp) <= lds_limit - panel_offset_host(mt, true) - 256;
     if (ph == PH_OPROJ || ph == PH_DOWN || ph == PH_FC || (ph != PH_LMHEAD && !whole_fits))
@@ -470,10 +470,42 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
         }
     }
     if (!supported) return false;
+    // Fewer slices with up to two column tiles of rows: the slices' parts of the tiles, written past the L2, read again and their places in the other
+    // copy reset, are S KiB per tile and column tile, more than the weights' sixteenth part.  us, 8 slices / so (7B, 13B, 8B shape):
+    //   gate/up, one column tile, panel in two pieces, one round of tiles: no slices.  9 rows 13B 230.1 / 217.6; 12 rows 159.7 / 152.4, 204.4 / 194.1,
+    //     277.5 / 270.6 (two slices that fit as a whole: 154.4, 197.3, 272.0); 16 rows 160.8 / 154.4 (155.2)
+    //   else gate/up as few as fit as a whole: 18 rows, two 175.6 / 170.9 (four 172.7), 24 rows, four 179.9 / 177.0 (two, in pieces 181.7), 32 rows,
+    //     four 182.4 / 176.7 (186.2); 36 rows, four 209.5 / 211.6: not with three column tiles
+    //   QKV four that fit as a whole: 11 rows 155.4 / 154.8, 18 rows 175.6 / 172.4 (two 174.0), 24 rows 179.9 / 176.8 (180.4), 13B 9 rows 228.5 / 225.2
+    //     (228.6; none, in pieces 6 us more than four)
+    //   bf16, output projection four: 6 rows 144.3 / 144.2, 188.9 / 187.2, 261.5 / 260.7, 12 rows 153.0 / 151.3, 197.3 / 195.2, 32 rows 172.0 / 169.7, but 36 rows
+    //     207.5 / 210.4, 294 / 304
+    //   bf16, down projection with at most eight rows four: 3 rows 142.1 / 140.8, 6 rows 144.3 / 143.1, 188.9 / 188.9, 261.5 / 260.4, but 9 rows 151.2 / 151.7
+    //   (float32, H 1024, both: 6 rows 53.0 / 53.9, 12 rows 57.1 / 57.6)
+    bool tile_each = false;           // a tile to a wavefront
+    if (mt <= 2 && override_[0] <= 0) {
+        auto fits = [&](int groups, bool shared) {
+            const int budget = lds_limit - panel_offset_host(mt, shared) - 256;
+            return arrays * panel_part_host(rows, false, groups * PS_U) <= budget || (rows > 16 && arrays * panel_part_host(rows, true, groups * PS_U) <= budget);
+        };
+        auto groups = [&](int sl) { return (NG + (1 << sl) - 1) >> sl; };
+        if (ph == PH_GATEUP && s_log > 0 && mt == 1 && T <= nwg * PS_WAVES && fits((NG + 1) / 2, false)) {
+            s_log = 0;
+            tile_each = true;
+        } else if (ph == PH_GATEUP || ph == PH_QKV) {
+            for (int sl = ph == PH_GATEUP ? 1 : 2; sl < s_log && !tile_each; ++sl)
+                if (fits(groups(sl), false)) {
+                    s_log = sl;
+                    tile_each = true;
+                }
+        } else if (bf && s_log > 2 && (ph == PH_OPROJ || (ph == PH_DOWN && rows <= 8)) && fits(groups(2), true)) {
+            s_log = 2;
+        }
+    }
     for (; s_log >= 0; --s_log) {
         const int S = 1 << s_log, Gs = nwg >> s_log;
         const int min_slice = NG / S, max_slice = (NG + S - 1) / S;   // groups per slice
-        int best_log = most_shared(S, Gs, min_slice);
+        int best_log = tile_each && override_[1] <= 0 ? 0 : most_shared(S, Gs, min_slice);
         for (; best_log >= 0; --best_log) {
             const int kw = 1 << best_log, SL = PS_WAVES >> best_log;
             const int per_round = Gs * SL;

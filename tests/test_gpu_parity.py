@@ -203,6 +203,25 @@ def test_maximum_rows_and_topk():
     _run_case(wl, all_rows=True, topk=1, label="64 rows, all decoded, top-1")
 
 
+@pytest.mark.parametrize("batch,n_new,k,slices", [
+    (1, 1, 5, (1, 4, 1, 4)),      # rows, panels whole: 6, the down projection's limit at 8 / 9
+    (1, 3, 5, (1, 4, 1, 4)), (1, 4, 5, (1, 4, 1, 8)),
+    (2, 1, 5, (4, 4, 1, 8)),      # 12, 16: gate/up's panel in two pieces, no slices
+    (2, 1, 7, (4, 4, 1, 8)),
+    (3, 1, 5, (4, 4, 2, 8)),      # 18, 19 ... 24, 32: two column tiles; gate/up's slices as few as fit as a whole
+    (4, 1, 5, (4, 4, 4, 8)), (4, 1, 7, (4, 4, 4, 8)),
+    (3, 4, 7, (8, 8, 8, 8))])     # 33: three column tiles
+def test_slices_of_the_contraction_by_rows(batch, n_new, k, slices):
+    """The K-slices that the plan chooses (QKV, output projection, gate/up, down projection), on both sides of its lines."""
+    import torch
+    shape = small_shape("bf16", hidden=4096, n_heads=16, n_kv_heads=4, head_dim=128, ffn=2816, vocab=2069)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    cfg = B.make_config(shape, max_batch=batch, max_new=n_new, max_positions=200, max_topk=8, k_max=k)
+    st, _, plans, _ = DBG.ps_draft_debug_step_plan(cfg, [100] * batch, n_new, k, 0, n_cu, 160 * 1024)
+    assert st == B.PS_OK and tuple(1 << p["s_log"] for p in plans[:4]) == slices, plans
+    _run_case(Workload("slices", shape, batch=batch, kv_len=tuple(31 * (b + 1) for b in range(batch)), n_new=n_new, k=k, topk=4, seed=47))
+
+
 def _lm_plan(shape, batch, k, n_new=1):
     """The plan of the LM head for such a step on this device."""
     import torch
