@@ -2400,7 +2400,10 @@ __device__ __forceinline__ void attn_phase(const StepParams& P, int wg, int nwg,
 // too: the score tile leaves the matrix core with a lane holding four consecutive keys of one query row,
 // which is the 16-row operand layout of v_mfma_f32_16x16x16_bf16 (P, split into high and low parts); the
 // other operand needs four consecutive keys of one value column per lane, so a wavefront passes its 16 value
-// rows through LDS with the two rows of a key pair interleaved (one dword = the same column of two keys).
+// rows through LDS, which transposes them on the way out (ds_read_b64_tr_b16: sixteen lanes get four keys of a column each).  Rows
+// interleaved in pairs on the way in (32 v_perm_b32 of the 237 vector instructions per 32 keys; 197 so) and value requests of 32-byte
+// pieces of 8 rows, us: 7B shape, batch 1 142.8 -> 141.8, 18 rows 165.9 -> 164.5, batch 8 248.2 -> 247.5, 60 rows 262.8 -> 261.0, 8B, batch 1
+// 270.6 -> 269.7, batch 3 291.2 -> 289.0, H 512 57.9 -> 56.8.
 // The host picks the block size so that the units fill the compute units once; a sequence that is a single
 // block hands its rows straight to the output projection, else (max, sum, output) per block go to memory
 // and attn_merge puts them together.
@@ -2412,11 +2415,11 @@ __device__ __forceinline__ void lds_sync_wave() { asm volatile("s_waitcnt lgkmcn
 
 template <int D> struct Attn2Cfg {
     static constexpr int G = 2;                                          // groups of 16 keys a wavefront works on at a time
-    static constexpr int VSTR = D + 8;                                   // dwords between key pairs of the staged values (no bank conflicts)
+    static constexpr int VSTR = 2 * D + 16;                              // bytes between the staged value rows (no bank conflicts)
     static constexpr int OSTR = D + 4;                                   // floats between rows of a wavefront's output
     static constexpr int OFF_Q = PS_LDS_BASE;                            // 16 query rows as MFMA operands (hi, lo)
-    static constexpr int OFF_V = OFF_Q + 16 * D * 4;                     // [waves][G][8 key pairs][VSTR] dwords
-    static constexpr int OFF_A = OFF_V + PS_WAVES * G * 8 * VSTR * 4;    // [waves][16] rescale factors of the running output
+    static constexpr int OFF_V = OFF_Q + 16 * D * 4;                     // [waves][G][16 keys][VSTR]
+    static constexpr int OFF_A = OFF_V + PS_WAVES * G * 16 * VSTR;       // [waves][16] rescale factors of the running output
     static constexpr int OFF_ML = OFF_A + PS_WAVES * 16 * 4;             // [waves][16][2] final (max, sum); attn_merge: sM, sL
     static constexpr int OFF_O = OFF_ML + PS_WAVES * 16 * 2 * 4;         // [waves][16][OSTR] final outputs; attn_merge: weights
     static constexpr int LDS = OFF_O + PS_WAVES * 16 * OSTR * 4;
@@ -2438,7 +2441,7 @@ __device__ __forceinline__ AttnItem attn_decode2(const StepParams& P, int item, 
 }
 
 // K rows (MFMA operand) and value rows of one group of 16 keys, as they come from memory
-template <int STEPS> struct KvRegs { uint4 k[STEPS]; uint4 va[2], vb[2]; };
+template <int STEPS> struct KvRegs { uint4 k[STEPS], v[STEPS]; };
 
 template <typename WT, int D>
 __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg, int wave, char* smem) {
@@ -2457,15 +2460,15 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
     const int ch_log = P.attn_ch_log, CH = 1 << ch_log, npass = P.attn_npass;
     const float scale2 = P.inv_sqrt_d * LOG2E;     // scores are kept in units of ln 2: exponentials are v_exp_f32
     char* sQ = smem + C::OFF_Q;
-    unsigned* sV = reinterpret_cast<unsigned*>(smem + C::OFF_V) + wave * G * 8 * VSTR;
+    char* sV = smem + C::OFF_V + wave * G * 16 * VSTR;
     float* sA = reinterpret_cast<float*>(smem + C::OFF_A) + wave * 16;
     float* sML = reinterpret_cast<float*>(smem + C::OFF_ML);
     float* sO = reinterpret_cast<float*>(smem + C::OFF_O);
     const rsrc_t racc = make_rsrc(P.attn_acc), rml = make_rsrc(P.attn_ml), rn = make_rsrc(act_ptr(P, P.kvnew));
     const SxBuf ro = sx_buf(P, P.o_buf);
     const unsigned seq = ps_seq();
-    const int vm = min(lane / CBN, 7), vcb = lane % CBN;   // this lane's key pair and column block of the value rows
-    const bool vlive = lane / CBN < 8;
+    constexpr int VL = D / 8, VK = 64 / VL;         // lanes along a value row, rows per request
+    const int vkey = lane / VL, vp = lane % VL;     // this lane's row of a request and its 16 bytes
 
     // work units and merge items: the host's counts, unless the lengths are device data (then it only knew upper bounds)
     int n_units = P.attn_units, n_merge = P.attn_merge_items;
@@ -2492,7 +2495,7 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
         stamp(P, wg, 44);
 
         // K rows of cache keys key0 .. key0 + 15 as the MFMA operand (lane (c, kb): bytes [64 t + 16 kb, +16) of key
-        // c) and the value rows (lane (vm, vcb): columns [16 vcb, +16) of keys 2 vm and 2 vm + 1); keys beyond the
+        // c) and the value rows (lane (vkey, vp): columns [8 vp, +8) of keys vkey, vkey + VK, ...); keys beyond the
         // block are clamped (masked later)
         auto load_cache = [&](int s, Kv& r) __attribute__((always_inline)) {
             const int key0 = k_lo + 16 * s, k_last = max(k_hi - 1, 0);
@@ -2500,21 +2503,16 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
             const char* krow = (const char*)P.kc + ((cache_row0 + (size_t)kp * P.nkv) * D) * 2 + kb * 16;
 #pragma unroll
             for (int t = 0; t < STEPS; ++t) r.k[t] = ld16(krow + t * 64);
-            const int pa = min(key0 + 2 * vm, k_last), pb = min(key0 + 2 * vm + 1, k_last);
-            const char* pa_ = (const char*)P.vc + ((cache_row0 + (size_t)pa * P.nkv) * D) * 2 + vcb * 32;
-            const char* pb_ = (const char*)P.vc + ((cache_row0 + (size_t)pb * P.nkv) * D) * 2 + vcb * 32;
-            r.va[0] = ld16(pa_); r.va[1] = ld16(pa_ + 16);
-            r.vb[0] = ld16(pb_); r.vb[1] = ld16(pb_ + 16);
+#pragma unroll
+            for (int t = 0; t < STEPS; ++t)
+                r.v[t] = ld16((const char*)P.vc + ((cache_row0 + (size_t)min(key0 + VK * t + vkey, k_last) * P.nkv) * D) * 2 + vp * 16);
         };
         // the same for rows 16 ts .. 16 ts + 15 of this step: from the exchange buffer, once the QKV phase has
         // published them (fp32, exactly representable in bf16: they were rounded when they went to the cache)
         auto load_tail = [&](int ts, Kv& r) __attribute__((always_inline)) {
             const int jk = min(16 * ts + c, P.M - 1);
-            const int ja = min(16 * ts + 2 * vm, P.M - 1), jb = min(16 * ts + 2 * vm + 1, P.M - 1);
             const unsigned kbase = (unsigned)(((size_t)(it.b * P.M + jk) * 2) * P.KVD + it.hk * D + kb * 8);
-            const unsigned abase = (unsigned)(((size_t)(it.b * P.M + ja) * 2 + 1) * P.KVD + it.hk * D + vcb * 16);
-            const unsigned bbase = (unsigned)(((size_t)(it.b * P.M + jb) * 2 + 1) * P.KVD + it.hk * D + vcb * 16);
-            u32x4 kx[STEPS][2], ax[4], bx[4];
+            u32x4 kx[STEPS][2], vx[STEPS][2];
             int spins = 0;
             for (;;) {
 #pragma unroll
@@ -2522,12 +2520,16 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
 #pragma unroll
                     for (int h = 0; h < 2; ++h) kx[t][h] = coh_ld16(rn, (kbase + 32 * t + 4 * h) * 4);
 #pragma unroll
-                for (int h = 0; h < 4; ++h) { ax[h] = coh_ld16(rn, (abase + 4 * h) * 4); bx[h] = coh_ld16(rn, (bbase + 4 * h) * 4); }
+                for (int t = 0; t < STEPS; ++t) {
+                    const int jv = min(16 * ts + VK * t + vkey, P.M - 1);
+                    const unsigned vbase = (unsigned)(((size_t)(it.b * P.M + jv) * 2 + 1) * P.KVD + it.hk * D + vp * 8);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) vx[t][h] = coh_ld16(rn, (vbase + 4 * h) * 4);
+                }
                 unsigned bad = 0;   // all loads first, then all checks: no wait between the loads
 #pragma unroll
-                for (int t = 0; t < STEPS; ++t) bad |= (unsigned)!sx_ok(kx[t][0]) | (unsigned)!sx_ok(kx[t][1]);
-#pragma unroll
-                for (int h = 0; h < 4; ++h) bad |= (unsigned)!sx_ok(ax[h]) | (unsigned)!sx_ok(bx[h]);
+                for (int t = 0; t < STEPS; ++t)
+                    bad |= (unsigned)!sx_ok(kx[t][0]) | (unsigned)!sx_ok(kx[t][1]) | (unsigned)!sx_ok(vx[t][0]) | (unsigned)!sx_ok(vx[t][1]);
                 if (__all(!bad) || !spin_again(P, spins)) break;
             }
             auto pk = [](u32x4 lo, u32x4 hi) __attribute__((always_inline)) {
@@ -2535,9 +2537,10 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
                                   pack_bf16x2(__uint_as_float(hi[0]), __uint_as_float(hi[1])), pack_bf16x2(__uint_as_float(hi[2]), __uint_as_float(hi[3])));
             };
 #pragma unroll
-            for (int t = 0; t < STEPS; ++t) r.k[t] = pk(kx[t][0], kx[t][1]);
-            r.va[0] = pk(ax[0], ax[1]); r.va[1] = pk(ax[2], ax[3]);
-            r.vb[0] = pk(bx[0], bx[1]); r.vb[1] = pk(bx[2], bx[3]);
+            for (int t = 0; t < STEPS; ++t) {
+                r.k[t] = pk(kx[t][0], kx[t][1]);
+                r.v[t] = pk(vx[t][0], vx[t][1]);
+            }
         };
 
         // A wavefront works on G = 2 groups at a time (groups s and s + 8 of the block), and the K and V rows of the
@@ -2606,22 +2609,11 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
             l_run = l_run * alpha + ls;
             m_run = m_new;
             if (kb == 0) sA[c] = alpha;
-            // the value rows into LDS, the two keys of a pair interleaved column by column
-            if (vlive) {
+            // the value rows into LDS
 #pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    unsigned ov[16];
+            for (int g = 0; g < NG; ++g)
 #pragma unroll
-                    for (int w = 0; w < 8; ++w) {
-                        const unsigned a2 = w < 4 ? (&r[g].va[0].x)[w] : (&r[g].va[1].x)[w - 4], b2 = w < 4 ? (&r[g].vb[0].x)[w] : (&r[g].vb[1].x)[w - 4];
-                        ov[2 * w] = __builtin_amdgcn_perm(b2, a2, 0x05040100u);       // (low half of a2, low half of b2)
-                        ov[2 * w + 1] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);   // (high half of a2, high half of b2)
-                    }
-                    uint4* dst = reinterpret_cast<uint4*>(sV + (g * 8 + vm) * VSTR + 16 * vcb);
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) dst[w] = make_uint4(ov[4 * w], ov[4 * w + 1], ov[4 * w + 2], ov[4 * w + 3]);
-                }
-            }
+                for (int t = 0; t < STEPS; ++t) *reinterpret_cast<u32x4*>(sV + (16 * g + VK * t + vkey) * VSTR + 16 * vp) = __builtin_bit_cast(u32x4, r[g].v[t]);
             lds_sync_wave();                                         // written and read by this wavefront only
             __builtin_amdgcn_wave_barrier();
             // rescale the running output (rows 4 kb .. 4 kb + 3) unless no row's maximum moved
@@ -2638,6 +2630,10 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
                 pl2[g][0] = pack_bf16x2(pr[g][0] - __uint_as_float(ph2[g][0] << 16), pr[g][1] - __uint_as_float(ph2[g][0] & 0xFFFF0000u));
                 pl2[g][1] = pack_bf16x2(pr[g][2] - __uint_as_float(ph2[g][1] << 16), pr[g][3] - __uint_as_float(ph2[g][1] & 0xFFFF0000u));
             }
+            // (column 16 j + c of keys 4 kb .. 4 kb + 3: sixteen lanes read 4 rows x 32 bytes and get a column of the four each)
+            typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+            const char* vt = sV + (4 * kb + (c >> 2)) * VSTR + (c & 3) * 8;
+            auto column = [&](int g, int j) __attribute__((always_inline)) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + 16 * g * VSTR + 32 * j)); };
             if constexpr (NG == 2) {
                 // two groups = 32 keys: one v_mfma_f32_16x16x32_bf16 per part and column block; its contraction index
                 // 8 kb + e is key 4 kb + e of the first group (e < 4) or key 4 kb + e - 4 of the second
@@ -2645,8 +2641,7 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
                 const bf16x8 pb = __builtin_bit_cast(bf16x8, make_uint4(pl2[0][0], pl2[0][1], pl2[1][0], pl2[1][1]));
 #pragma unroll
                 for (int j = 0; j < CBN; ++j) {
-                    const bf16x8 vv = __builtin_bit_cast(bf16x8, make_uint4(sV[(2 * kb) * VSTR + 16 * j + c], sV[(2 * kb + 1) * VSTR + 16 * j + c],
-                                                                            sV[(8 + 2 * kb) * VSTR + 16 * j + c], sV[(8 + 2 * kb + 1) * VSTR + 16 * j + c]));
+                    const bf16x8 vv = __builtin_bit_cast(bf16x8, __builtin_shufflevector(column(0, j), column(1, j), 0, 1, 2, 3, 4, 5, 6, 7));
                     const f32x4 t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, vv, oacc[j], 0, 0, 0);
                     oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pb, vv, t, 0, 0, 0);
                 }
@@ -2656,9 +2651,7 @@ __device__ __forceinline__ void attn_phase2(const StepParams& P, int wg, int nwg
                     const s16x4 ph_ = __builtin_bit_cast(s16x4, make_uint2(ph2[g][0], ph2[g][1])), pl_ = __builtin_bit_cast(s16x4, make_uint2(pl2[g][0], pl2[g][1]));
 #pragma unroll
                     for (int j = 0; j < CBN; ++j) {
-                        // values of keys 4 kb .. 4 kb + 3, column 16 j + c: the key pairs 2 kb and 2 kb + 1
-                        const unsigned w0 = sV[(g * 8 + 2 * kb) * VSTR + 16 * j + c], w1 = sV[(g * 8 + 2 * kb + 1) * VSTR + 16 * j + c];
-                        const s16x4 vv = __builtin_bit_cast(s16x4, make_uint2(w0, w1));
+                        const s16x4 vv = column(g, j);
                         const f32x4 t = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ph_, vv, oacc[j], 0, 0, 0);
                         oacc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pl_, vv, t, 0, 0, 0);
                     }
