@@ -482,6 +482,19 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
     //     207.5 / 210.4, 294 / 304
     //   bf16, down projection with at most eight rows four: 3 rows 142.1 / 140.8, 6 rows 144.3 / 143.1, 188.9 / 188.9, 261.5 / 260.4, but 9 rows 151.2 / 151.7
     //   (float32, H 1024, both: 6 rows 53.0 / 53.9, 12 rows 57.1 / 57.6)
+    // These shapes have tiles for most wavefronts.  Fewer slices of few tiles leave wavefronts without a stream, and a workgroup stages more of the
+    // panel for the same streams, so there have to be enough of them, one wavefront to a tile.  us, 8 slices / fewer, share of the wavefronts that stream:
+    //   gate/up, bf16, more than 5/8 in the first round.  No slices: H 8192, F 1024, 6 rows 0.06 118.0 / 130.0; H 7168, F 2048, 6 rows 0.12 111.4 / 119.5;
+    //     H 4096, F 4096, 12 rows 0.25 98.1 / 101.0 (four slices, 1.0: 96.7); H 4096, F 10496, 16 rows 0.64 110.8 / 106.5.  Two: H 4096, F 2816, 18 rows 0.34
+    //     92.9 / 94.3; H 4096, F 4096, 18 rows 0.5 112.1 / 113.1 (four 110.5); H 2048, F 5632, 18 rows 0.69 78.8 / 75.7.  Four: H 8192, F 1024, 18 rows 0.25
+    //     150.6 / 154.3; H 8192, F 2048, 18 rows 0.5 122.0 / 123.2; H 4096, F 2816, 24 rows 0.69 93.9 / 93.1
+    //   float32 both phases, 3/4 and no round that is mostly empty: H 3072, F 1024, 18 rows 0.12 113.4 / 123.4; H 2816, F 4352, 24 rows 0.53 in two rounds 109.3 /
+    //     111.8; H 4096, F 5632, 18 rows 0.69 140.0 / 143.8; H 3328, F 6144, 16 rows 0.75 116.0 / 113.4
+    //   QKV, bf16, more than a quarter with K up to 4096 and 24 rows: H 4096, 18 rows 0.19 109.9 / 110.7, 24 rows 0.19 110.9 / 112.0; H 2048, 18 rows 0.31 76.6 / 75.7,
+    //     0.5 81.0 / 78.3; else more than 3/4: H 7680, 18 rows 0.38 199.9 / 201.8, H 5376, 18 rows 0.62 121.9 / 123.3, H 5888, 24 rows 0.75 133.7 / 134.5, H 3584,
+    //     32 rows 0.38 108.3 / 109.3, H 6400, 16 rows 1.25 115.7 / 114.2
+    //   output and down projection: where eight slices are single groups not four that two wavefronts share again: H 2048 (K 2048), 18 rows 74.4 / 75.7,
+    //     24 rows 75.1 / 76.0, 32 rows 76.8 / 78.1; K 3072, 18 rows 100.7 / 99.4
     bool tile_each = false;           // a tile to a wavefront
     if (mt <= 2 && override_[0] <= 0) {
         auto fits = [&](int groups, bool shared) {
@@ -489,16 +502,23 @@ static bool make_desc(PhaseDesc* d, int ph, int T, int Kt, int K, int rows, int 
             return arrays * panel_part_host(rows, false, groups * PS_U) <= budget || (rows > 16 && arrays * panel_part_host(rows, true, groups * PS_U) <= budget);
         };
         auto groups = [&](int sl) { return (NG + (1 << sl) - 1) >> sl; };
-        if (ph == PH_GATEUP && s_log > 0 && mt == 1 && T <= nwg * PS_WAVES && fits((NG + 1) / 2, false)) {
+        const long long slots = (long long)nwg * PS_WAVES;
+        auto enough = [&](int sl) {
+            const long long streams = (long long)T << sl, rounds = (streams + slots - 1) / slots;
+            if (!bf) return streams * 4 >= slots * rounds * 3;
+            return ph == PH_QKV ? streams * 4 > slots * (NG > 16 || rows > 24 ? 3 : 1) : streams * 8 > slots * 5;
+        };
+        if (ph == PH_GATEUP && s_log > 0 && mt == 1 && T <= slots && enough(0) && fits((NG + 1) / 2, false)) {
             s_log = 0;
             tile_each = true;
         } else if (ph == PH_GATEUP || ph == PH_QKV) {
             for (int sl = ph == PH_GATEUP ? 1 : 2; sl < s_log && !tile_each; ++sl)
-                if (fits(groups(sl), false)) {
+                if (enough(sl) && fits(groups(sl), false)) {
                     s_log = sl;
                     tile_each = true;
                 }
-        } else if (bf && s_log > 2 && (ph == PH_OPROJ || (ph == PH_DOWN && rows <= 8)) && fits(groups(2), true)) {
+        } else if (bf && s_log > 2 && (ph == PH_OPROJ || (ph == PH_DOWN && rows <= 8)) && fits(groups(2), true) &&
+                   (NG > 8 || most_shared(4, nwg >> 2, NG >> 2) == 0)) {
             s_log = 2;
         }
     }

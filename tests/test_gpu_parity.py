@@ -203,18 +203,18 @@ def test_maximum_rows_and_topk():
     _run_case(wl, all_rows=True, topk=1, label="64 rows, all decoded, top-1")
 
 
-@pytest.mark.parametrize("batch,n_new,k,slices", [
-    (1, 1, 5, (1, 4, 1, 4)),      # rows, panels whole: 6, the down projection's limit at 8 / 9
-    (1, 3, 5, (1, 4, 1, 4)), (1, 4, 5, (1, 4, 1, 8)),
-    (2, 1, 5, (4, 4, 1, 8)),      # 12, 16: gate/up's panel in two pieces, no slices
-    (2, 1, 7, (4, 4, 1, 8)),
-    (3, 1, 5, (4, 4, 2, 8)),      # 18, 19 ... 24, 32: two column tiles; gate/up's slices as few as fit as a whole
-    (4, 1, 5, (4, 4, 4, 8)), (4, 1, 7, (4, 4, 4, 8)),
-    (3, 4, 7, (8, 8, 8, 8))])     # 33: three column tiles
-def test_slices_of_the_contraction_by_rows(batch, n_new, k, slices):
+@pytest.mark.parametrize("batch,n_new,k,ffn,slices", [
+    (1, 1, 5, 2816, (1, 4, 1, 4)),      # rows, panels whole: 6, the down projection's limit at 8 / 9
+    (1, 3, 5, 2816, (1, 4, 1, 4)), (1, 4, 5, 2816, (1, 4, 1, 8)),
+    (2, 1, 5, 10272, (4, 4, 1, 8)),     # 12, 16: gate/up's panel in two pieces, no slices, where tiles are many
+    (2, 1, 7, 10272, (4, 4, 1, 8)), (2, 1, 5, 2816, (4, 4, 4, 8)), (2, 1, 7, 2560, (4, 4, 8, 8)),
+    (3, 1, 5, 5152, (4, 4, 2, 8)),      # 18, 24, 32: two column tiles; gate/up's slices as few as fit as a whole and leave enough streams
+    (3, 1, 5, 2816, (4, 4, 4, 8)), (4, 1, 5, 2816, (4, 4, 4, 8)), (4, 1, 7, 2816, (8, 4, 4, 8)),
+    (11, 1, 2, 2816, (8, 8, 8, 8))])    # 33: three column tiles
+def test_slices_of_the_contraction_by_rows(batch, n_new, k, ffn, slices):
     """The K-slices that the plan chooses (QKV, output projection, gate/up, down projection), on both sides of its lines."""
     import torch
-    shape = small_shape("bf16", hidden=4096, n_heads=16, n_kv_heads=4, head_dim=128, ffn=2816, vocab=2069)
+    shape = small_shape("bf16", hidden=4096, n_heads=24, n_kv_heads=4, head_dim=128, ffn=ffn, vocab=2069)
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     cfg = B.make_config(shape, max_batch=batch, max_new=n_new, max_positions=200, max_topk=8, k_max=k)
     st, _, plans, _ = DBG.ps_draft_debug_step_plan(cfg, [100] * batch, n_new, k, 0, n_cu, 160 * 1024)

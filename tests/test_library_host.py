@@ -309,6 +309,38 @@ def test_phase_plans_over_a_sweep_of_shapes_and_devices(lib):
     assert checked > 500 and min(seen.values()) > 20, (checked, seen)
 
 
+# (dtype, hidden, ffn, heads, kv heads), (batch, n_new, k), phase, slices: both sides of every line of the rule on 256 compute units
+SLICES = [
+    ("bf16", 4096, 10240, 8, 8, (2, 1, 5), 2, 2), ("bf16", 4096, 10272, 8, 8, (2, 1, 5), 2, 1),      # gate/up: 5/8 of 2048 wavefronts, none, ...
+    ("bf16", 4096, 5120, 8, 8, (3, 1, 5), 2, 4), ("bf16", 4096, 5152, 8, 8, (3, 1, 5), 2, 2),        # ... two ...
+    ("bf16", 4096, 2560, 8, 8, (4, 1, 5), 2, 8), ("bf16", 4096, 2592, 8, 8, (4, 1, 5), 2, 4),        # ... and four slices
+    ("bf16", 8192, 1024, 8, 8, (1, 1, 5), 2, 8), ("bf16", 7168, 2048, 8, 8, (1, 1, 5), 2, 8),
+    ("f32", 4096, 6128, 8, 8, (3, 1, 5), 2, 8), ("f32", 4096, 6144, 8, 8, (3, 1, 5), 2, 2),          # 3/4, over all rounds
+    ("f32", 4096, 3056, 8, 8, (3, 1, 5), 2, 8), ("f32", 4096, 3072, 8, 8, (3, 1, 5), 2, 4), ("f32", 4096, 4352, 8, 8, (3, 1, 5), 2, 8),
+    ("f32", 4096, 2816, 32, 4, (3, 1, 5), 0, 8), ("f32", 4096, 2816, 32, 8, (3, 1, 5), 0, 4),
+    ("bf16", 4096, 2816, 8, 4, (3, 1, 5), 0, 8), ("bf16", 4096, 2816, 16, 2, (3, 1, 5), 0, 4),       # QKV: a quarter with K 4096, up to 24 rows
+    ("bf16", 4096, 2816, 16, 2, (4, 1, 5), 0, 4), ("bf16", 4096, 2816, 16, 2, (5, 1, 4), 0, 8),
+    ("bf16", 4352, 2816, 32, 8, (3, 1, 5), 0, 8), ("bf16", 4352, 2816, 32, 16, (3, 1, 5), 0, 4), ("bf16", 4096, 2816, 32, 8, (8, 1, 3), 0, 8),
+    ("bf16", 2048, 2816, 16, 16, (3, 1, 5), 1, 8), ("bf16", 4096, 2816, 16, 4, (3, 1, 5), 1, 8),     # output projection: K 2048, one tile a wavefront or not
+    ("bf16", 4352, 2816, 16, 4, (3, 1, 5), 1, 4), ("bf16", 2304, 2816, 18, 18, (3, 1, 5), 1, 4),
+    ("bf16", 2048, 2048, 16, 16, (1, 1, 5), 3, 8), ("bf16", 2048, 2304, 16, 16, (1, 1, 5), 3, 4), ("bf16", 4352, 2048, 16, 16, (1, 1, 5), 3, 4)]
+
+
+@pytest.mark.parametrize("shape,step,phase,slices", [(s[:5], s[5], s[6], s[7]) for s in SLICES])
+def test_fewer_slices_only_where_enough_wavefronts_stream(lib, shape, step, phase, slices):
+    """With fewer K-slices a wavefront takes a whole tile: where there are few tiles, eight slices stream wider."""
+    dtype, hidden, ffn, heads, kv = shape
+    batch, n_new, k = step
+    cfg = B.make_config(small_shape(dtype, hidden=hidden, n_heads=heads, n_kv_heads=kv, head_dim=128, ffn=ffn, vocab=2069), max_batch=batch,
+                        max_new=n_new, max_positions=512, max_topk=8, k_max=k)
+    st, plans = _plan(lib, cfg, batch, n_new, k)
+    assert st == B.PS_OK
+    _check_plan(cfg, plans, batch, n_new, k, 256, 160 * 1024)
+    p = plans[phase]
+    streaming = p["T"] * (1 << p["s_log"] + p["kw_log"]) / (p["rounds"] * 256 * PS_WAVES)
+    assert 1 << p["s_log"] == slices and streaming >= 0.25, (p, streaming)
+
+
 def _weight_bytes(cfg):
     qd, esz = cfg.n_heads * cfg.head_dim, 2 if cfg.dtype == B.PS_BF16 else 4
     kv = cfg.n_kv_heads * cfg.head_dim
