@@ -1344,8 +1344,8 @@ GaParams shape(const ps_group_attn_args* a) {
     P.gpt = 16 / (a->k + 1);
     P.k1_magic = (unsigned)((0x100000000ull + a->k) / (unsigned)(a->k + 1));
     P.ntiles = (a->tokens + P.gpt - 1) / P.gpt;
-    P.by_heads = ga_div(P.nq * P.seqs);
-    P.by_slots = ga_div(P.nkv * P.seqs);
+    P.by_heads = ga_div((unsigned)P.nq * (unsigned)P.seqs);   // (up to 65535^2: beyond an int)
+    P.by_slots = ga_div((unsigned)P.nkv * (unsigned)P.seqs);
     P.by_nkv = ga_div(P.nkv);
     P.group = P.nq / P.nkv;
     P.inv_sqrt_d = (float)(1.0 / sqrt((double)a->head_dim));

@@ -2,6 +2,7 @@
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -110,3 +111,41 @@ def test_which_calls_take_the_16_row_kernel(lib):
             for d in (64, 128):
                 st, g = DBG.ps_train_debug_launch(TR.make_args(seqs, T, k, nq, nkv, d, "bf16", 10000.0))
                 assert st == B.PS_OK and g["kernel"] == want, (seqs, T, k, nq, nkv, g)
+
+
+def test_plans_of_the_largest_calls_do_not_overflow(tmp_path):
+    """The host code that plans a call, built with checks for signed overflow, on the most heads, sequences
+    and tokens that the entry points take."""
+    from paper_2410_05589_amd import build
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", build.CSRC]
+    obj, main, exe = (str(tmp_path / n) for n in ("train.o", "main.cpp", "main"))
+
+    def run(cmd):
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert res.returncode == 0, (cmd, res.stdout[-2000:])
+        return res.stdout
+    checks = [a for f in ("-fsanitize=signed-integer-overflow", "-fno-sanitize-recover=signed-integer-overflow") for a in ("-Xarch_host", f)]
+    run([build.hipcc_path(), "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17", *checks, *inc, "-c", "-o", obj,
+         os.path.join(build.CSRC, "ps_train.hip")])
+    image = re.search(r"U (__hip_fatbin\w*)", run(["nm", obj])).group(1)        # (no device code in this build)
+    calls = [(dt, 65535, 1, 0, 65535, nkv, 64) for dt in ("bf16", "f32") for nkv in (1, 65535)]
+    calls += [("bf16", 65535, (1 << 20) - 15, 15, 65534, 32767, 64), ("f32", 1, (1 << 20) - 15, 15, 8190, 1, 128)]
+    rows = ",".join("{%s, %d, %d, %d, %d, %d, %d}" % ("PS_BF16" if c[0] == "bf16" else "PS_F32", *c[1:]) for c in calls)
+    open(main, "w").write("""#include <cstdio>
+#include "ps_train.h"
+#include "ps_draft_debug.h"
+extern "C" { extern const char %s[4096] = {}; }
+int main() {
+    const int calls[][7] = {%s};
+    for (auto& c : calls) {
+        ps_group_attn_args a = {};
+        a.dtype = c[0]; a.seqs = c[1]; a.tokens = c[2]; a.k = c[3]; a.n_heads = c[4]; a.n_kv_heads = c[5]; a.head_dim = c[6]; a.rope_base = 10000.f;
+        unsigned out[8];
+        if (ps_train_debug_launch(&a, out) != PS_OK || ps_group_attention_workspace_bytes(&a) == 0) return printf("refused: %%d %%d\\n", a.seqs, a.n_heads), 3;
+    }
+    return 0;
+}
+""" % (image, rows))
+    run([build.hipcc_path(), "-x", "c++", "-std=c++17", *inc, "-c", "-o", main + ".o", main])
+    run([build.hipcc_path(), *checks[:2], "-o", exe, main + ".o", obj])
+    run([exe])
