@@ -558,9 +558,8 @@ __device__ __forceinline__ const char* weight_row_ptr(const StepParams& P, int t
     }
 }
 
-// Panel row r of the LM head is a decoding row: the last real row and the k mask rows of each
-// sequence (or all rows).
-// row m of the step as a row of the LM head's panel, or -1
+// Row m of the step as a row of the LM head's panel, or -1.  That panel's rows are the decoding rows: the last real row and
+// the k mask rows of each sequence (or all rows).
 __device__ __forceinline__ int lm_row(const StepParams& P, int m) {
     const int b = row_seq(P, m), i = m - b * P.M, jj = P.all_rows ? i : i - (P.n_new - 1);
     return jj < 0 ? -1 : b * P.R + jj;
@@ -639,11 +638,11 @@ __device__ __forceinline__ void preload_weights(uint4 (&wb)[PS_U], const char* b
     for (int u = 0; u < PS_U; ++u) wb[u] = ldg_stream16(base + u * PS_WS + lane16);
 }
 
-// Software pipeline over the n steps (a positive multiple of PS_U) of one weight stream: step t
-// multiplies the weights loaded PS_U steps earlier with the B operands read one step earlier,
+// Software pipeline over the n steps (a multiple of PS_U, 0 where the caller takes the last PS_U itself) of one weight
+// stream: step t multiplies the weights loaded PS_U steps earlier with the B operands read one step earlier,
 // then refills its register with step t + PS_U and reads the B operands of step t + 1.  The
 // loads of the last group start the wavefront's next stream, so when this returns wb holds the
-// head of that stream.  Every load is unconditional and only the oldest is waited for.
+// head of that stream (n = 0: as it did).  Every load is unconditional and only the oldest is waited for.
 // (consume_group: PS_U of the steps, A at the first of them; `last`: no step follows)
 // The first barrier keeps the reads of step t + 1 in front of the products of step t; the compiler puts them behind, where the next
 // step waits for them at once.  us: 7B shape, 60 rows 265.6 -> 259.0, H 512, 36 rows 58.4 -> 57.9, float32 H 256 37.1 -> 36.6, fewer rows of
@@ -874,7 +873,7 @@ __device__ __forceinline__ void epilogue_down(const StepParams& P, int tau, int 
         if (m >= P.Mtot) continue;
         const int r = lm_row(P, m);
         if (r >= 0) coh_st16(ry2.cur, (unsigned)(r * P.H + n) * 4, w);
-        coh_st16(ry2.alt, (unsigned)(m * P.H + n) * 4, sent);
+        coh_st16(ry2.alt, (unsigned)(m * P.H + n) * 4, sent);   // (every row: the step before may have decoded them all)
         if (P.final_norm && q == 0) {
             if (r >= 0) coh_st4(rss.cur, (unsigned)((r >> 3) * oct_units + 8 * tau + (r & 7)) * 4, __float_as_uint(ss));
             coh_st4(rss.alt, (unsigned)((m >> 3) * oct_units + 8 * tau + (m & 7)) * 4, PS_SENT);
@@ -954,11 +953,6 @@ __device__ __forceinline__ void place_rows(const StepParams& P, const PhaseDesc&
     const int lane = threadIdx.x & 63;
     float* s_ssq = reinterpret_cast<float*>(smem + PS_LDS_SSQ);
     const int nrt = PS_WG_THREADS >> D.g2_log, wsub = wave & (((1 << D.g2_log) >> 6) - 1), rows = D.rows, RS = D.rs;
-    const bool norm = PH == PH_QKV || PH == PH_GATEUP || (PH == PH_LMHEAD && D.norm != 0);   // (of a SPLIT phase only the sums of squares)
-    // is row r of the QKV panel an fp32 row (the input projection's output)?
-    auto fused_row = [&](int r) __attribute__((always_inline)) {
-        return PH == PH_QKV && P.in_mode == PS_IN_FUSED && r - row_seq(P, r) * P.M < P.n_new;
-    };
     auto panel_at = [&](int r) __attribute__((always_inline)) {
         return MT >= PS_UNITS_MT && D.units ? gi * RS + ((r ^ (gi & 15)) << 4) : r * RS + gi * 16;
     };
@@ -977,7 +971,7 @@ __device__ __forceinline__ void place_rows(const StepParams& P, const PhaseDesc&
                 *reinterpret_cast<uint4*>((h == 0 ? s_pa : s_pb) + panel_at(r)) = x;
             }
         }
-        if (norm && want_ssq) {
+        if (D.norm != 0 && want_ssq) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 ss[e] = gi & 1 ? 0.f : __uint_as_float(ss4[e]);
@@ -995,6 +989,11 @@ __device__ __forceinline__ void place_rows(const StepParams& P, const PhaseDesc&
         }
         return;
     }
+    constexpr bool norm = PH == PH_QKV || PH == PH_GATEUP;
+    // is row r of the QKV panel an fp32 row (the input projection's output)?
+    auto fused_row = [&](int r) __attribute__((always_inline)) {
+        return PH == PH_QKV && P.in_mode == PS_IN_FUSED && r - row_seq(P, r) * P.M < P.n_new;
+    };
 #pragma unroll
     for (int i = 0; i < PS_RB; ++i) {
         const int r = rb + nrt * i;
@@ -1093,7 +1092,8 @@ template <typename WT> __device__ __forceinline__ u32x4 ss_own(const PhaseDesc& 
 // its group of RB rows before it uses any of them (one memory round trip per RB rows), and
 // re-requests them until none holds the "not written" pattern.  The panel holds x (.) gain
 // (RMSNorm's 1/rms is applied in the epilogue); the sum of x^2 of row r over the groups a
-// wavefront saw goes to s_ssq[8 r + w] (w = the wavefront's index along the row).
+// wavefront saw goes to s_ssq[8 r + w] (w = the wavefront's index along the row).  Rows of a SPLIT phase
+// arrive like that, and are copied; their sums of squares are added up from the partial sums beside them.
 template <typename WT, int MT, int PH>
 __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc& D, int wave, char* smem,
                                             char* s_pa, char* s_pb, int a_step, int nsteps, bool first_piece,
@@ -1109,7 +1109,7 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
     // depends only on the row is scalar arithmetic
     const int gi0 = tid & (G2 - 1), rsub = (wave << 6) >> g2_log, nrt = PS_WG_THREADS >> g2_log;
     const int rows = D.rows, K = D.K, ld = D.src_ld;
-    const bool norm = PH == PH_QKV || PH == PH_GATEUP || (PH == PH_LMHEAD && D.norm != 0);
+    constexpr bool norm = PH == PH_QKV || PH == PH_GATEUP;
     const int in_mode = P.in_mode;
     // where the rows come from.  QKV: the real rows of Z by input mode (see StepParams), the [MASK] rows from
     // mask_emb; input projection: features (columns < H) and the tokens' embedding rows (columns >= H)
@@ -1125,7 +1125,7 @@ __device__ __forceinline__ void stage_piece(const StepParams& P, const PhaseDesc
         const bool live = gvalid && kk < K;          // beyond K the packed weights are zero: so is the panel
         const int kkc = kk < K ? kk : 0;
         float gn[GE];
-        if (norm && !SPLIT<PH>) unpack_group<WT>(ld16((const char*)D.gain + (size_t)kkc * ESZ), gn);
+        if (norm) unpack_group<WT>(ld16((const char*)D.gain + (size_t)kkc * ESZ), gn);
         for (int rb = rsub; rb < rows; rb += nrt * RB) {
             u32x4 raw[RB][NL], ss4 = {0u, 0u, 0u, 0u};
             int spins = 0;

@@ -886,7 +886,6 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
     }
     // how the step is cut up
     const bool attn2 = c.dtype == PS_BF16;                   // bf16 storage: attn_phase2 (ps_device.h)
-    P.r_magic = 0xFFFFFFFFu / (unsigned)P.R + 1u;
     StepPlan sp;
     const PlanLimits lim = {ctx->n_cu, ctx->lds_limit, ctx->fused != 0, ctx->plan_override, ctx->attn_sep_override, ctx->attn_nk_override};
     if (!plan_step(&c, a->kv_len, a->batch, a->n_new, a->k, a->out_rows, lim, &sp)) return PS_ERR_UNSUPPORTED;
@@ -911,7 +910,7 @@ extern "C" int ps_draft_step(ps_draft_ctx* ctx, const ps_draft_step_args* a, voi
     P.ph[PH_OPROJ].src = P.o_buf; P.ph[PH_OPROJ].src_ld = P.QD;
     P.ph[PH_GATEUP].norm = 1; P.ph[PH_GATEUP].gain = P.g_post; P.ph[PH_GATEUP].src = P.y_buf; P.ph[PH_GATEUP].src_ld = P.H;
     P.ph[PH_DOWN].src = P.u_buf; P.ph[PH_DOWN].src_ld = P.F;
-    P.ph[PH_LMHEAD].norm = P.final_norm; P.ph[PH_LMHEAD].gain = P.g_final; P.ph[PH_LMHEAD].src = P.y2_buf; P.ph[PH_LMHEAD].src_ld = P.H;
+    P.ph[PH_LMHEAD].norm = P.final_norm; P.ph[PH_LMHEAD].src = P.y2_buf; P.ph[PH_LMHEAD].src_ld = P.H;
     P.timeline = ctx->timeline;
     // what this step leaves in the sentinel-coded buffers of its copy (see sx_reset_stale in ps_device.h)
     P.foot[0] = (unsigned)P.Mtot;

@@ -192,7 +192,7 @@ struct StepParams {
     // of real rows.  The rows of the unused slots run through the step as zero rows that nobody sees: they are
     // no keys, get no cache rows, and the positions of the sequence's rows start at kv_len[b] behind them.
     int skip[PS_MAX_ROWS];
-    unsigned m_magic, r_magic;   // ceil(2^32 / M), ceil(2^32 / R): row -> sequence without a division
+    unsigned m_magic;            // ceil(2^32 / M): row -> sequence without a division
     int tph_log;                 // log2(head_dim / 16): QKV tile -> head
     PhaseDesc ph[PH_COUNT];
     unsigned long long* timeline; // debugging aid: per-workgroup time stamps, or NULL
