@@ -644,10 +644,11 @@ __device__ __forceinline__ void preload_weights(uint4 (&wb)[PS_U], const char* b
 // loads of the last group start the wavefront's next stream, so when this returns wb holds the
 // head of that stream (n = 0: as it did).  Every load is unconditional and only the oldest is waited for.
 // (consume_group: PS_U of the steps, A at the first of them; `last`: no step follows)
-// The first barrier keeps the reads of step t + 1 in front of the products of step t; the compiler puts them behind, where the next
-// step waits for them at once.  us: 7B shape, 60 rows 265.6 -> 259.0, H 512, 36 rows 58.4 -> 57.9, float32 H 256 37.1 -> 36.6, fewer rows of
-// the large shapes +-0.3; bf16 with one column tile 144.3 -> 144.8: not there.  (The LM head's 60 rows gain most of it from the registers
-// that the last steps' own code below frees.)
+// The first barrier (float32) keeps the reads of step t + 1 in front of the products of step t; the compiler puts them behind, where the
+// next step waits for them at once.  us, without / with it: float32 H 256, 5 rows 37.1 / 36.5, H 1024, 36 / 48 / 64 rows 91.4 / 90.9, 93.3 / 92.8, 106.1 /
+// 105.4, 21 rows 72.1 / 72.6.  bf16 gains nothing with up to three column tiles (7B shape, 21 / 36 / 48 rows 168.4 / 167.6, 207.8 / 207.6, 212.2 / 212.4,
+// 13B 32 / 42 / 48 rows 252.0 / 252.5, 305.1 / 304.0, 314.3 / 311.8, H 2048, 32 rows 99.1 / 100.5) and with four it spills seven registers: 54 rows 246.9 / 252.9
+// (13B 367.1 / 374.3, H 2048 140.5 / 143.2), 60 rows 262.6 / 266.7, 64 rows 259.0 / 260.7.
 template <typename WT, int MT>
 __device__ __forceinline__ void consume_group(uint4 (&wb)[PS_U], const char* refill, bool last, int lane16, const PanelAddr<MT>& A,
                                               BRegs<WT, MT>& bc, f32x4 (&acc)[MT]) {
@@ -657,7 +658,7 @@ __device__ __forceinline__ void consume_group(uint4 (&wb)[PS_U], const char* ref
         int tb = u + 1;
         if (u == PS_U - 1 && last) tb = u;
         load_b<WT, MT>(bn, A, tb);
-        if constexpr (MT > 1 || !Traits<WT>::BF) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!Traits<WT>::BF) __builtin_amdgcn_sched_barrier(0);
         mma_step<WT, MT>(wb[u], bc, acc);
         wb[u] = ldg_stream16(refill + u * PS_WS + lane16);   // reuses the register just consumed
         bc = bn;
