@@ -76,7 +76,7 @@ __device__ __forceinline__ double ga_exp2(double x) {
     for (int i = 12; i >= 0; --i) p = fma(p, y, c[i]);
     return ldexp(p, (int)n);
 }
-// cosine and sine of a >= 0: the multiple of pi / 2 taken off in two parts (the first product is exact inside its fma, the second
+// cosine and sine of a >= 0: the multiple of pi / 2 taken off in two parts (Cody and Waite's reduction; the first product is exact inside its fma, the second
 // part is below 1e-9), Taylor's series on [-pi / 4, pi / 4] to r^16 and r^17 (what follows is below 2e-18).  Angles beyond
 // 2^22 (a base below 1) are the library's business
 __device__ __forceinline__ float2 ga_cos_sin(double a) {
@@ -106,8 +106,8 @@ __device__ __forceinline__ float2 ga_cos_sin(double a) {
 // What bounds it where positions are few is the chain of one workgroup: its first key rows are requested before the table is
 // worked out, and the table takes some 45 double operations per pair, where the library's exp, cos and sin took most of the
 // kernel's time (whole calls, us: 2 x T 300, k 3, 8 heads x 64, float32 22.9 -> 22.4, 3 x T 120, k 2 16.9 -> 16.5, 2 x T 200, k 5,
-// 16 / 4 heads x 64, bf16 15.5 -> 15.3).  As exact: of 3.2 million entries (bases 2 .. 10^6, positions up to 2^20) 60 are not
-// the correctly rounded floats, 63 with the library's.
+// 16 / 4 heads x 64, bf16 15.5 -> 15.3).  As exact: of 4.75 million entries (bases 2 .. 10^6, positions up to 2^20) 1068 are not
+// the nearest floats, 1268 with the library's; none is further off than that by more than 1e-10, with either.
 template <typename WT, int D, bool ALL>
 __global__ void __launch_bounds__(256) ga_rope_kernel(const GaParams P) {
     constexpr int ESZ = Traits<WT>::ESZ, Q4 = D / 8;       // groups of 4 pairs per head

@@ -77,6 +77,68 @@ def test_rotary_bases_that_reach_large_angles(base):
     _case(1, 150, 3, 2, 1, 64, "f32", 12, base=base)
 
 
+@pytest.mark.parametrize("base", [2.0, 1.0, 2.0 ** -24])
+@pytest.mark.parametrize("T,k,d", [(150, 0, 128), (150, 0, 64), (97, 1, 64), (60, 8, 128)])
+def test_rotary_bases_that_reach_large_angles_in_the_wide_kernel(T, k, d, base):
+    """The same where the wide kernel takes a wavefront's (k = 0) or a workgroup's part of the table through LDS."""
+    _case(1, T, k, 2, 1, d, "bf16", 13, base=base, kernel=WIDE)
+
+
+@pytest.mark.parametrize("T,d,base", [(1 << 17, 64, 2.0), (1 << 17, 128, 10.0), (1 << 17, 128, 10000.0), (1 << 17, 64, 500000.0), (1 << 20, 64, 1000000.0)])
+def test_entries_of_the_rotary_table(T, d, base):
+    """The table (first in the workspace) against cosines and sines in extended precision: half a unit in the last place of the float
+    that is nearest, and what two units in the last place of the angle in double precision turn; and nearly all entries are that float."""
+    import torch
+    a = TR.make_args(1, T, 0, 1, 1, d, "bf16", base)
+    x = torch.zeros((T, 1, d), dtype=torch.bfloat16, device="cuda:0")
+    out = torch.empty((T, 1, d), dtype=torch.float32, device="cuda:0")
+    nbytes = TR.ps_group_attention_workspace_bytes(a)
+    ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device="cuda:0")
+    a.q = a.k_ = a.v = x.data_ptr()
+    a.out = out.data_ptr()
+    a.workspace, a.workspace_bytes = (ws.data_ptr() + 255) & ~255, nbytes
+    print("case table T", T, "d", d, "base", base, flush=True)
+    assert TR.ps_group_attention(a, torch.cuda.current_stream().cuda_stream) == B.PS_OK
+    torch.cuda.synchronize()
+    lo = a.workspace - ws.data_ptr()
+    tab = ws[lo:lo + T * d * 4].cpu().numpy().view(np.float32).reshape(T, d // 2, 2)
+    g = np.random.default_rng(5)
+    pos = np.unique(np.concatenate([np.arange(300), g.integers(0, T, 3000), np.arange(T - 100, T)]))
+    ld = np.longdouble
+    ang = pos.astype(ld)[:, None] * np.exp2(-ld(2) * np.arange(d // 2).astype(ld) / ld(d) * np.log2(ld(base)))[None, :]
+    want = np.stack([np.cos(ang), np.sin(ang)], axis=2)
+    near = want.astype(np.float32)
+    err = np.abs(tab[pos].astype(ld) - want)
+    assert (err <= np.spacing(np.abs(near)) / 2 + ang[:, :, None] * ld(2.0 ** -51) + ld(2.0 ** -53)).all(), float(err.max())
+    other = int((tab[pos] != near).sum())
+    print("    not the nearest float:", other, "of", near.size, "largest error", float(err.max()), flush=True)
+    assert other <= near.size // 1000
+
+
+@pytest.mark.parametrize("T,k,d", [(40, 14, 128), (45, 12, 64), (50, 8, 128), (50, 10, 64)])
+def test_own_keys_in_both_tiles_whose_scores_lie_far_apart(T, k, d):
+    """The wide kernel gives the own [MASK] keys of a wavefront's rows and of the 16 rows before one reference.  Keys 32 times as long: the
+    scores of a row spread over a hundred and more, and where the largest leads by 20 the output is its value row (what is left weighs
+    below T e^-20; a key that rounds the other way moves a score by less than 1), in whichever tile it stands."""
+    from oracle.ps_oracle import round_to_storage, widen
+    check_kernel(WIDE, 1, T, k, 8, 8, d, "bf16")
+    inp = inputs.make_group_attention_inputs(17, 1, T, k, 8, 8, d, "bf16")
+    inp["k"] = round_to_storage(32.0 * widen(inp["k"], "bf16"), "bf16")
+    print("case far apart T", T, "k", k, "d", d, flush=True)
+    got = run_gpu(inp, 1, T, k, 8, 8, d, "bf16")[0]
+    _, probs = ga.group_attention(inp["q"][0], inp["k"][0], inp["v"][0], T, k, 10000.0, "bf16", return_probs=True)
+    v = widen(inp["v"][0], "bf16")
+    order = np.sort(probs, axis=2)
+    won = probs.argmax(axis=2)
+    i, h = np.nonzero(order[:, :, -2] < np.exp(-20.0))
+    w = won[i, h]
+    own = (w % (k + 1) > 0)
+    before = own & (w // 32 < i // 32)
+    print("    rows:", len(i), "own key:", int(own.sum()), "in the tile before:", int(before.sum()), flush=True)
+    assert own.sum() >= 100 and before.sum() >= 10
+    assert np.abs(got[i, h] - v[w, h]).max() <= 1e-5 * np.abs(v).max()
+
+
 def test_longer_sequences_with_other_group_sizes():
     """Several tiles of keys per wavefront (tiles every query sees entirely, the masked last ones, the own [MASK] rows), several
     blocks of rows, with 8, 16 and 2 rows per group in the wide bf16 kernel and 4 in the float32 one of short calls."""
