@@ -803,11 +803,10 @@ __global__ void __launch_bounds__(GA_THREADS, 4) ga_attn_bf16_kernel(const GaPar
 // values (3.7 % of a T 2048, k 4 call, 4.5 % of 4 x T 1024, k 8, 9 % of T 203; the own rows read that way, too: 1 % slower, the next
 // workgroup reads 16 of them again).
 //
-// A tile is 32 MFMAs of 32 cycles per wavefront and about as much vector work: at T 2048, k 4 the matrix cores are busy 54 % of the
-// kernel's time, at 1.9 GHz or less: large calls are bound by power (all inputs zero, the same instructions: 278 us where random
-// values took 384 on that card, 573 for 768 at 4 x T 1024, k 8; and a quarter of the vector instructions less changed nothing).  A
-// workgroup's start (its rows come from memory) and its own rows have few MFMAs to show.  At T 203 that is
-// most of the time (matrix cores 12 %).  All 256 registers are in use and none is spilled: eight spilled ones cost 1 .. 4 %.
+// A tile is 32 MFMAs of 32 cycles per wavefront and about as much vector work: at T 2048, k 4 the matrix cores are busy 53 % of the
+// kernel's time and the vector ALU 47 %, at 1.9 GHz or less: large calls are bound by power (the same instructions on zeros: 259 us where random
+// values take 360 on that card, 545 for 735 at 4 x T 1024, k 8).  A workgroup's start (its rows come from memory) and its own rows have few
+// MFMAs to show.  At T 203 that is most of the time (matrix cores 11 %).  All 256 registers are in use and none is spilled: eight spilled ones cost 1 .. 4 %.
 // Whole calls among others of their kind, against the 16-row kernel and its three launches: T 2048, k 4, 32 heads x 128: 503 -> 339 us
 // (507 TFLOP/s of visible pairs, every product twice); 4 x T 1024, k 8, 32 / 8 heads: 1501 -> 700 us; T 203, k 5, 40 heads: 40.9 -> 23.3 us.
 // Tried: no scores ahead (other wavefront alone fills the gaps): 5 % slower; own rows as further tiles of the loop, rotated
