@@ -74,8 +74,8 @@ def test_streaming_loops_keep_seven_weight_loads_in_flight(asm):
 
 
 def test_no_flat_loads_and_few_spills_in_the_persistent_kernel(asm):
-    """Nothing spilled for up to three column tiles of rows; four (49 to 64 rows) spill a handful of values that live through
-    the step, none of them inside a streaming loop (see above)."""
+    """Nothing spilled for up to three column tiles of rows; four (49 to 64 rows) may spill a handful of values that live through
+    the step (at present none, see below), none of them inside a streaming loop (see above)."""
     assert "flat_load" not in asm
     meta = re.findall(r"\.name:\s+(\S+)\n(?:.*\n)*?\s+\.vgpr_spill_count:\s+(\d+)", asm)
     spills = {n: int(v) for n, v in meta}
